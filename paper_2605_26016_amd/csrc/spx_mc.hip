@@ -52,7 +52,7 @@ struct MCState {
     int C_fail = 0;  // why the search failed (a ColourResult)
     int ky = 0, kz = 0;
     int o[kMaxSub] = {0};
-    unsigned long long *d_acc = nullptr;  // accepted-move counter of the last call
+    unsigned long long *d_acc = nullptr;  // accepted-move counters of the last call (kAccSlots lines)
     double *d_part = nullptr;             // magnetisation block partials [kMagBlocks][3]
     int64_t *d_off = nullptr;             // linear index offset of every bond (interior sites)
     int rad[3] = {0, 0, 0};               // largest |delta| of the bonds along each axis
@@ -180,6 +180,23 @@ __device__ __forceinline__ int64_t xcd_block() {
     return k * q + (k < r ? k : r) + b / 8;
 }
 
+// Accepted moves of a launch.  One counter for the whole chip serialises the
+// waves' additions in one L2 channel (sc 200^3, one shell: 760 us a launch
+// against 120 us without a count), so each wave adds to one of kAccSlots
+// counters, each on a cache line of its own; k_mc_accepted adds them up.
+// Integer counts: the order of the additions does not matter.
+constexpr int kAccSlots = 1024;
+constexpr int kAccPitch = 16;  // 128-byte lines
+
+__device__ __forceinline__ void add_accepted(unsigned long long *__restrict__ acc, unsigned w) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) w += __shfl_down(w, off, 64);
+    if ((threadIdx.x & 63) == 0 && w) {
+        const unsigned wave = blockIdx.x * (kMcB / 64) + (threadIdx.x >> 6);
+        atomicAdd(acc + (size_t)(wave % kAccSlots) * kAccPitch, (unsigned long long)w);
+    }
+}
+
 // One colour of one sweep.  Thread t covers x-slot j = t % J of row (y, z, a)
 // = t / J, J = ceil(Lx / C): the row's sites of colour c are x = x0 + C j.
 // Bilinear field of an interior site (every neighbour inside the lattice):
@@ -265,13 +282,7 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
         S[N + i] = sn[1];
         S[2 * N + i] = sn[2];
     }
-    if (acc) {
-        // integer counts: the order of the atomic additions does not matter
-        unsigned int w = accepted;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) w += __shfl_down(w, off, 64);
-        if ((threadIdx.x & 63) == 0 && w) atomicAdd(acc, (unsigned long long)w);
-    }
+    if (acc) add_accepted(acc, accepted);
 }
 
 // The padded colour-major layout.  Row (y, z, a) holds C class blocks of Jp
@@ -470,15 +481,29 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
             }
         }
     }
-    if (acc) {
-        unsigned int w = accepted;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) w += __shfl_down(w, off, 64);
-        if ((threadIdx.x & 63) == 0 && w) atomicAdd(acc, (unsigned long long)w);
-    }
+    if (acc) add_accepted(acc, accepted);
 }
 
-__global__ void k_mc_zero(unsigned long long *acc) { *acc = 0ull; }
+__global__ __launch_bounds__(kMcB) void k_mc_zero(unsigned long long *acc) {
+    for (int k = threadIdx.x; k < kAccSlots; k += kMcB) acc[k * kAccPitch] = 0ull;
+}
+
+// The call's count: the slots' sum, or `known` where acc is NULL (heat-bath
+// accepts every draw, so nothing is counted on the device).
+__global__ __launch_bounds__(kMcB) void k_mc_accepted(const unsigned long long *__restrict__ acc,
+                                                      unsigned long long known, unsigned long long *__restrict__ out) {
+    __shared__ unsigned long long red[kMcB];
+    unsigned long long v = 0ull;
+    if (acc)
+        for (int k = threadIdx.x; k < kAccSlots; k += kMcB) v += acc[k * kAccPitch];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int h = kMcB / 2; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *out = acc ? red[0] : known;
+}
 
 // sum_i S_i: block partials (grid-stride, fixed order), then one block
 __global__ __launch_bounds__(kMcB) void k_mag_partial(const double *__restrict__ S, int64_t N,
@@ -622,7 +647,7 @@ spx_status mc_state(const HamView &v, MCState **out) {
         return SPX_OK;
     }
     MCState *m = new MCState();
-    if (hipMalloc((void **)&m->d_acc, sizeof(unsigned long long)) != hipSuccess ||
+    if (hipMalloc((void **)&m->d_acc, sizeof(unsigned long long) * kAccSlots * kAccPitch) != hipSuccess ||
         hipMalloc((void **)&m->d_part, sizeof(double) * 3 * kMagBlocks) != hipSuccess) {
         (void)hipGetLastError();
         mc_destroy(m);
@@ -817,8 +842,8 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
     col.kz = m->kz;
     for (int a = 0; a < kMaxSub; ++a) col.o[a] = m->o[a];
     const double beta = 1.0 / (kKB * p->temperature_K);
-    unsigned long long *acc = accepted ? m->d_acc : nullptr;
-    if (acc) k_mc_zero<<<1, 1, 0, st>>>(acc);
+    unsigned long long *acc = accepted && p->method == 1 ? m->d_acc : nullptr;
+    if (acc) k_mc_zero<<<1, kMcB, 0, st>>>(acc);
     const int64_t total = (int64_t)((v.grid.Lx + col.C - 1) / col.C) * v.grid.Ly * v.grid.Lz * v.grid.n_sub;
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + kMcB - 1) / kMcB, 65536));
     const bool iso = v.tab.iso != 0;
@@ -872,9 +897,9 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
         }
     }
     if (cm) k_mc_from_cm<<<ngrid, kMcB, 0, st>>>(m->d_cm, S, v.grid, cd);
+    if (accepted)
+        k_mc_accepted<<<1, kMcB, 0, st>>>(acc, (unsigned long long)v.grid.N * (unsigned long long)p->n_sweeps, accepted);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && accepted)
-        e = hipMemcpyAsync(accepted, m->d_acc, sizeof(unsigned long long), hipMemcpyDeviceToDevice, st);
     if (e != hipSuccess) return set_hip_error(e, "spx_mc_sweep");
     return SPX_OK;
 }

@@ -241,3 +241,22 @@ def test_binder_cumulant_crossing_at_the_heisenberg_critical_point():
     t_cross = lo + (hi - lo) * d[lo] / (d[lo] - d[hi])
     print(f"U4(16) - U4(8) crosses zero at T/Tc = {t_cross:.4f}", flush=True)
     assert abs(t_cross - 1.0) < 0.015
+
+
+@pytest.mark.parametrize("L", [(4, 4, 4), (64, 64, 66), (130, 98, 62)])
+@pytest.mark.parametrize("method", ["heat_bath", "metropolis"])
+def test_accepted_count_equals_changed_spins(L, method):
+    # one wave up to several times the counter slots; in one sweep a site's
+    # move was accepted exactly when its spin changed (a trial equal to the
+    # old spin in all 53 x 3 bits does not occur)
+    import torch
+    from paper_2605_26016_amd import spx
+    N = L[0] * L[1] * L[2]
+    h = spx.setup_hamiltonian(L, J_shell=(1.0,), field_prec="fp64")
+    S = to_dev(random_sphere(N, 31))
+    old = S.clone()
+    acc = torch.full((1,), 12345, dtype=torch.int64, device="cuda")
+    spx.mc_sweep(h, S, 12.0, seed=8, n_sweeps=1, method=method, accepted=acc)
+    assert int(acc.item()) == int((S != old).any(0).sum().item())
+    spx.mc_sweep(h, S, 12.0, seed=8, sweep0=1, n_sweeps=0, method=method, accepted=acc)
+    assert int(acc.item()) == 0
