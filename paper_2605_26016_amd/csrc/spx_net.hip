@@ -47,7 +47,6 @@ namespace {
 
 constexpr int kTXn = 8, kTYn = 8, kTZn = 4;  // output tile
 constexpr int kHX = kTXn + 2, kHY = kTYn + 2, kHZ = kTZn + 2;
-constexpr int kHalo = kHX * kHY * kHZ;
 constexpr int kNT = 256;
 
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
@@ -83,62 +82,191 @@ __device__ __forceinline__ NetTile tile_origin_at(const NetDims &d, int bx, int 
     t.pz = by / nbz;
     return t;
 }
-__device__ __forceinline__ NetTile tile_origin(const NetDims &d) {
-    return tile_origin_at(d, (int)blockIdx.x, (int)blockIdx.y);
+// ---------------------------------------------------------------- FP32 matrix-core form
+// Tiles of the FP32 layers: a box of bx x by x bz <= 256 sub-grid sites whose
+// one-cell halo holds at most kBoxHalo sites, chosen per layer on the host
+// (conv_box) for the fewest tiles.  An 8 x 8 x 4 box fills only 42% of its
+// sites on the 6^3 sub-grids of dilation 8 at 48^3 and 56% on the 12^3 of
+// dilation 4; 6 x 6 x 6 fills 84% of both.  Blocks are persistent over the
+// tiles (tile index = box, then phase, then image).
+constexpr int kBoxSites = 256, kBoxHalo = 640;
+constexpr int kConvBlocks = 512;  // two per CU: what the registers and LDS of either kernel admit
+
+struct NetBox {
+    int bx, by, bz;     // box
+    int nx, ny, nz;     // boxes per axis of one phase's sub-grid
+    int hx, hy, halo;   // halo row, rows per halo plane, halo sites
+    int px, py, pz;     // phases per axis, min(dil, L)
+    int vol;            // bx by bz
+    int64_t tiles;      // nx ny nz px py pz batch
+};
+
+struct BoxTile {
+    int x0, y0, z0;  // lattice coordinates of box site (0, 0, 0)
+    int image;
+};
+__device__ __forceinline__ BoxTile box_tile(const NetDims &d, const NetBox &b, int64_t t) {
+    // at most one tile per site: 32 bits hold an image's tiles
+    const uint32_t per_image = (uint32_t)b.nx * b.ny * b.nz * b.px * b.py * b.pz;
+    BoxTile o;
+    o.image = (int)(t / per_image);
+    uint32_t r = (uint32_t)(t - (int64_t)o.image * per_image);
+    const uint32_t px = r % (uint32_t)b.px;  // phases innermost: they share cache lines
+    r /= (uint32_t)b.px;
+    const uint32_t py = r % (uint32_t)b.py;
+    r /= (uint32_t)b.py;
+    const uint32_t ix = r % (uint32_t)b.nx;
+    r /= (uint32_t)b.nx;
+    const uint32_t iy = r % (uint32_t)b.ny;
+    r /= (uint32_t)b.ny;
+    const uint32_t iz = r % (uint32_t)b.nz;
+    const uint32_t pz = r / (uint32_t)b.nz;
+    o.x0 = (int)px + d.dil * b.bx * (int)ix;
+    o.y0 = (int)py + d.dil * b.by * (int)iy;
+    o.z0 = (int)pz + d.dil * b.bz * (int)iz;
+    return o;
 }
 
-// Stage CIN input channels of image blockIdx.z with a 1-cell zero halo (in
-// sub-grid cells: d sites in the lattice).
-template <int CIN, bool SILU_IN>
-__device__ __forceinline__ void stage_tile(const float *__restrict__ in, const NetDims &d, const NetTile &t,
-                                           float (*tile)[kHalo]) {
-    const float *src = in + (int64_t)blockIdx.z * CIN * d.P;
-    for (int idx = threadIdx.x; idx < CIN * kHalo; idx += kNT) {
-        const int ci = idx / kHalo, r = idx - ci * kHalo;
-        const int hx = r % kHX, hy = (r / kHX) % kHY, hz = r / (kHX * kHY);
-        const int gx = t.px + d.dil * (t.x0 + hx - 1), gy = t.py + d.dil * (t.y0 + hy - 1),
-                  gz = t.pz + d.dil * (t.z0 + hz - 1);
-        float v = 0.0f;
-        if (gx >= 0 && gy >= 0 && gz >= 0 && gx < d.Lx && gy < d.Ly && gz < d.Lz) {
-            v = src[ci * d.P + gx + (int64_t)d.Lx * (gy + (int64_t)d.Ly * gz)];
-            if (SILU_IN) v = silu(v);
-        }
-        tile[ci][r] = v;
+// First tile of this block when workgroups are dealt to the 8 XCDs in turn:
+// blocks of one XCD take consecutive tiles, so the halos that neighbouring
+// tiles share meet in one L2.
+__device__ __forceinline__ int64_t first_tile() {
+    const uint32_t T = gridDim.x, b = blockIdx.x, q = T / 8, r = T % 8, k = b % 8;
+    return (int64_t)(k * q + (k < r ? k : r) + b / 8);
+}
+
+// The halo sites that a thread stages, (x, y, z) packed by 10 bits, -1 past the end.
+constexpr int kSlots = (kBoxHalo + kNT - 1) / kNT;
+__device__ __forceinline__ void halo_slots(const NetBox &b, int slot[kSlots]) {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+        const int r = (int)threadIdx.x + q * kNT;
+        const int x = r % b.hx, yz = r / b.hx, y = yz % b.hy, z = yz / b.hy;
+        slot[q] = r < b.halo ? x | (y << 10) | (z << 20) : -1;
     }
 }
+// lattice index of a packed halo site of a tile, -1 outside the lattice
+__device__ __forceinline__ int64_t halo_site(const NetDims &d, const BoxTile &t, int slot) {
+    const int x = t.x0 + d.dil * ((slot & 1023) - 1), y = t.y0 + d.dil * (((slot >> 10) & 1023) - 1),
+              z = t.z0 + d.dil * ((slot >> 20) - 1);
+    const bool in = x >= 0 && y >= 0 && z >= 0 && x < d.Lx && y < d.Ly && z < d.Lz;
+    return in ? x + (int64_t)d.Lx * (y + (int64_t)d.Ly * z) : -1;
+}
+// box site s = threadIdx.x of a tile: its coordinates packed likewise (-1 past the box)
+__device__ __forceinline__ int box_slot(const NetBox &b, int s) {
+    const int x = s % b.bx, yz = s / b.bx, y = yz % b.by, z = yz / b.by;
+    return s < b.vol ? (x + 1) | ((y + 1) << 10) | ((z + 1) << 20) : -1;
+}
 
-// out[co] = bias[co] + sum_ci sum_k W[co][ci][k] a[ci](p + k - 1)   (bias may be NULL)
+// out[co] = bias[co] + sum_ci sum_k W[co][ci][k] a[ci](p + (k - 1) d)   (bias may be NULL)
 // MUL_GRAD: the result is multiplied by silu'(zmul) (input-gradient pass).
+//
+// Each wavefront takes 64 sites of the box as four groups of 16, all 16
+// output channels (COUT < 16: zero weights) and K = 27 CIN in steps of four:
+// v_mfma_f32_16x16x4_f32 with the sites as rows and W[co][kk], kk = 27 ci +
+// k, as columns.  That instruction adds its four products to the accumulator
+// one after another, each a fused multiply-add with FP32 rounding (checked
+// bit for bit against fmaf, subnormals included), and kk runs in the order of
+// the sum above, so a result is the same chain of FMAs, bit for bit, as one
+// thread per site doing them in turn on the vector ALU.  The weights of the
+// block stay in LDS and the 27 tap offsets of a lane in registers over all its
+// tiles; kk + 108 is the same tap four channels on.
+// Bound by the matrix cores' FP32 rate with the staging of the next block's
+// tile beside it: 16 -> 16 channels on 16 images of 48^3 (24.5 GFLOP) took
+// 908 us on the vector ALUs.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 template <int CIN, int COUT, bool SILU_IN, bool MUL_GRAD>
-__global__ __launch_bounds__(kNT) void k_conv(const float *__restrict__ in, const float *__restrict__ W,
-                                              const float *__restrict__ bias, const float *__restrict__ zmul,
-                                              float *__restrict__ out, NetDims d) {
-    __shared__ float tile[CIN][kHalo];
-    const NetTile tl = tile_origin(d);
-    stage_tile<CIN, SILU_IN>(in, d, tl, tile);
-    __syncthreads();
-    const int tx = threadIdx.x % kTXn, ty = (threadIdx.x / kTXn) % kTYn, tz = threadIdx.x / (kTXn * kTYn);
-    float acc[COUT];
-#pragma unroll
-    for (int co = 0; co < COUT; ++co) acc[co] = bias ? bias[co] : 0.0f;
-    for (int ci = 0; ci < CIN; ++ci) {
-#pragma unroll
-        for (int k = 0; k < 27; ++k) {
-            const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-            const float v = tile[ci][(tx + kx) + kHX * ((ty + ky) + kHY * (tz + kz))];
-#pragma unroll
-            for (int co = 0; co < COUT; ++co) acc[co] += W[(co * CIN + ci) * 27 + k] * v;
-        }
+__global__ __launch_bounds__(kNT, 2) void k_conv(const float *__restrict__ in, const float *__restrict__ W,
+                                                 const float *__restrict__ bias, const float *__restrict__ zmul,
+                                                 float *__restrict__ out, NetDims d, NetBox bx) {
+    constexpr int K = 27 * CIN, NS = (K + 3) / 4;
+    constexpr int kOt = kBoxSites + 4;      // floats per channel row of the output staging
+    constexpr int kTile = CIN * kBoxHalo > COUT * kOt ? CIN * kBoxHalo : COUT * kOt;
+    __shared__ __attribute__((aligned(16))) float tile[kTile + 1];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, row = lane & 15, quad = lane >> 4;
+    // weight fragments: lane l of step i reads W[co = l % 16][4 i + l / 16]
+    __shared__ float wl[NS * 64];
+    for (int q = t; q < NS * 64; q += kNT) {
+        const int co = q & 15, kk = 4 * (q >> 6) + ((q >> 4) & 3);
+        wl[q] = (co < COUT && kk < K) ? W[co * K + kk] : 0.0f;
     }
-    const int x = tl.px + d.dil * (tl.x0 + tx), y = tl.py + d.dil * (tl.y0 + ty), z = tl.pz + d.dil * (tl.z0 + tz);
-    if (x >= d.Lx || y >= d.Ly || z >= d.Lz) return;
-    const int64_t p = x + (int64_t)d.Lx * (y + (int64_t)d.Ly * z);
-    float *dst = out + (int64_t)blockIdx.z * COUT * d.P;
+    const float bco = (bias && row < COUT) ? bias[row] : 0.0f;
+    int off[27];
 #pragma unroll
-    for (int co = 0; co < COUT; ++co) {
-        float v = acc[co];
-        if (MUL_GRAD) v *= silu_grad(zmul[(int64_t)blockIdx.z * COUT * d.P + co * d.P + p]);
-        dst[co * d.P + p] = v;
+    for (int i = 0; i < 27; ++i) {
+        const int kk = 4 * i + quad, ci = kk / 27, k = kk - 27 * ci;
+        off[i] = ci * kBoxHalo + k % 3 + bx.hx * ((k / 3) % 3 + bx.hy * (k / 9));
+    }
+    int base[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int s = 16 * (4 * wave + m) + row;
+        const int q = s < bx.vol ? s : 0;
+        base[m] = q % bx.bx + bx.hx * ((q / bx.bx) % bx.by + bx.hy * (q / (bx.bx * bx.by)));
+    }
+    int slot[kSlots];
+    halo_slots(bx, slot);
+    const int own = box_slot(bx, t);
+    for (int64_t tl = first_tile(); tl < bx.tiles; tl += gridDim.x) {
+        const BoxTile o = box_tile(d, bx, tl);
+        const float *src = in + (int64_t)o.image * CIN * d.P;
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+            if (slot[q] < 0) continue;
+            const int64_t p = halo_site(d, o, slot[q]);
+            float v[CIN];
+#pragma unroll
+            for (int ci = 0; ci < CIN; ++ci) v[ci] = p >= 0 ? src[ci * d.P + p] : 0.0f;
+#pragma unroll
+            for (int ci = 0; ci < CIN; ++ci)
+                tile[ci * kBoxHalo + t + q * kNT] = SILU_IN ? (p >= 0 ? silu(v[ci]) : 0.0f) : v[ci];
+        }
+        if (K % 4 != 0 && t == 0) tile[kTile] = 0.0f;  // read by the lanes past K in the last step
+        __syncthreads();
+        f32x4 acc[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) acc[m] = f32x4{bco, bco, bco, bco};
+        auto step = [&](int i, int r, int ch) __attribute__((always_inline)) {
+            const float wv = wl[i * 64 + lane];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                int at = base[m] + off[r] + ch * kBoxHalo;
+                if (K % 4 != 0 && i == NS - 1) at = 4 * i + quad < K ? at : kTile;
+                acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(tile[at], wv, acc[m], 0, 0, 0);
+            }
+        };
+        // four channels are 27 steps; the loop over them stays rolled and its
+        // 108 tile addresses are made in it (held over the tiles they spill)
+#pragma unroll 1
+        for (int c4 = 0; c4 < NS / 27; ++c4) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) asm volatile("" : "+v"(base[m]));
+#pragma unroll
+            for (int r = 0; r < 27; ++r) step(27 * c4 + r, r, 4 * c4);
+        }
+#pragma unroll
+        for (int i = NS / 27 * 27; i < NS; ++i) step(i, i % 27, i / 27 * 4);
+        __syncthreads();  // every wavefront is done with the tile
+        // accumulator j of a lane: site 16 (4 wave + m) + 4 quad + j, channel row
+        if (row < COUT) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                *reinterpret_cast<f32x4 *>(tile + row * kOt + 16 * (4 * wave + m) + 4 * quad) = acc[m];
+        }
+        __syncthreads();
+        const int64_t p = own >= 0 ? halo_site(d, o, own) : -1;
+        if (p >= 0) {
+            float *dst = out + (int64_t)o.image * COUT * d.P + p;
+            const float *zm = MUL_GRAD ? zmul + (int64_t)o.image * COUT * d.P + p : nullptr;
+#pragma unroll
+            for (int co = 0; co < COUT; ++co) {
+                float v = tile[co * kOt + t];
+                if (MUL_GRAD) v *= silu_grad(zm[co * d.P]);
+                dst[co * d.P] = v;
+            }
+        }
+        __syncthreads();  // the next tile is staged over the outputs
     }
 }
 
@@ -150,65 +278,153 @@ __global__ void k_transpose_flip(const float *__restrict__ W, float *__restrict_
     Wt[i] = W[(co * cin + ci) * 27 + (26 - k)];
 }
 
-// Per-block weight/bias gradient partials:
-//   dW[co][ci][k] = sum_p g[co](p) a[ci](p + (k - 1) d),  db[co] = sum_p g[co](p)
-// over the block's output tile; partial[blk][COUT*CIN*27 + COUT].
-template <int CIN, int COUT, bool SILU_IN>
-__global__ __launch_bounds__(kNT) void k_conv_wgrad(const float *__restrict__ in, const float *__restrict__ g,
-                                                    double *__restrict__ partial, NetDims d) {
-    __shared__ float tile[CIN][kHalo];
-    __shared__ float gt[COUT][kTXn * kTYn * kTZn];
-    const NetTile tl = tile_origin(d);
-    stage_tile<CIN, SILU_IN>(in, d, tl, tile);
-    const float *gsrc = g + (int64_t)blockIdx.z * COUT * d.P;
-    for (int idx = threadIdx.x; idx < COUT * kNT; idx += kNT) {
-        const int co = idx / kNT, s = idx % kNT;
-        const int x = tl.px + d.dil * (tl.x0 + s % kTXn), y = tl.py + d.dil * (tl.y0 + (s / kTXn) % kTYn),
-                  z = tl.pz + d.dil * (tl.z0 + s / (kTXn * kTYn));
-        float v = 0.0f;
-        if (x < d.Lx && y < d.Ly && z < d.Lz) v = gsrc[co * d.P + x + (int64_t)d.Lx * (y + (int64_t)d.Ly * z)];
-        gt[co][s] = v;
+// Weight and bias gradients of a layer, one partial per block (and site half):
+//   dW[co][ci][k] = sum_p g[co](p) a[ci](p + (k - 1) d),  db[co] = sum_p g[co](p).
+// FP64 accumulation: the product of two floats is exact in double, so the
+// sums carry no FP32 rounding of their own.  v_mfma_f64_16x16x4_f64 contracts
+// four sites at a time: the 16 channels of one field (rows, the box alone)
+// against channel and tap of the other (columns, with halo), flattened so
+// that 10 channels fill 17 column tiles of 16 and 3 channels 6.
+//   SWAP = false: rows g, columns a (CC = cin); true (3 outputs): rows a,
+//   columns g (CC = cout), whose tap k is a's tap 26 - k.
+// The column tiles are dealt to 4 / WS wavefronts, the sites to WS groups of
+// them; the accumulators live in registers over all tiles of the block, so a
+// block writes one partial (before: one per tile, 6912 of 55 kB for a 16 ->
+// 16 layer of 16 images of 48^3, which one thread per weight then summed).
+// Bound by the FP64 matrix rate; the vector ALUs took 3792 us for that layer
+// and the sum 4054 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <int CC, bool SWAP, bool SILU_A, int WS>
+__global__ __launch_bounds__(kNT, 2) void k_conv_wgrad(const float *__restrict__ in, const float *__restrict__ g,
+                                                       double *__restrict__ partial, NetDims d, NetBox bx) {
+    constexpr int NC = 27 * CC, NT = (NC + 15) / 16, NWV = 4 / WS, NJ = (NT + NWV - 1) / NWV;
+    constexpr int PC = CC | 1, PR = 17;  // odd pitches: staging writes and fragment reads spread over the banks
+    constexpr int COUT = SWAP ? CC : 16, CIN = SWAP ? 16 : CC;
+    constexpr int nw = COUT * CIN * 27 + COUT;
+    __shared__ float hal[kBoxHalo * PC];
+    __shared__ float rows[kBoxSites * PR];
+    __shared__ int hb[kBoxSites];
+    __shared__ double red[kNT / 64][COUT];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, row = lane & 15, quad = lane >> 4;
+    const int wv = wave % NWV, ws = wave / NWV;
+    int coff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int n = 16 * (wv + NWV * j) + row;
+        const int k = n < NC ? n / CC : 0, c = n < NC ? n - CC * (n / CC) : 0;
+        coff[j] = PC * (k % 3 + bx.hx * ((k / 3) % 3 + bx.hy * (k / 9))) + c;
     }
-    __syncthreads();
-    const int nw = COUT * CIN * 27 + COUT;
-    const size_t blk = (size_t)blockIdx.z * gridDim.x * gridDim.y + (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    // FP64 accumulation: the product of two floats is exact in double, so the
-    // weight-gradient sums carry no FP32 rounding of their own (only that of
-    // the FP32 activations and back-propagated fields they multiply)
-    double *dst = partial + blk * nw;
-    const int t = threadIdx.x;
-    if (t < COUT * CIN) {
-        const int co = t / CIN, ci = t % CIN;
-        double acc[27];
+    {
+        const int q = t < bx.vol ? t : 0;
+        hb[t] = PC * (q % bx.bx + bx.hx * ((q / bx.bx) % bx.by + bx.hy * (q / (bx.bx * bx.by))));
+    }
+    int slot[kSlots];
+    halo_slots(bx, slot);
+    const int own = box_slot(bx, t);
+    f64x4 acc[NJ];
 #pragma unroll
-        for (int k = 0; k < 27; ++k) acc[k] = 0.0;
-        for (int s = 0; s < kNT; ++s) {
-            const double gv = (double)gt[co][s];
-            const int sx = s % kTXn, sy = (s / kTXn) % kTYn, sz = s / (kTXn * kTYn);
+    for (int j = 0; j < NJ; ++j) acc[j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double sb[COUT];
 #pragma unroll
-            for (int k = 0; k < 27; ++k) {
-                const int kx = k % 3, ky = (k / 3) % 3, kz = k / 9;
-                acc[k] = fma(gv, (double)tile[ci][(sx + kx) + kHX * ((sy + ky) + kHY * (sz + kz))], acc[k]);
+    for (int c = 0; c < COUT; ++c) sb[c] = 0.0;
+    const int groups = (bx.vol + 3) / 4;  // at most 64, a multiple of 4 WS
+    for (int64_t tl = first_tile(); tl < bx.tiles; tl += gridDim.x) {
+        const BoxTile o = box_tile(d, bx, tl);
+        const float *csrc = (SWAP ? g : in) + (int64_t)o.image * CC * d.P;
+        const float *rsrc = (SWAP ? in : g) + (int64_t)o.image * 16 * d.P;
+        __syncthreads();  // the previous tile's reads are done (and hb is written)
+#pragma unroll
+        for (int q = 0; q < kSlots; ++q) {
+            if (slot[q] < 0) continue;
+            const int64_t p = halo_site(d, o, slot[q]);
+            float v[CC];
+#pragma unroll
+            for (int c = 0; c < CC; ++c) v[c] = p >= 0 ? csrc[c * d.P + p] : 0.0f;
+#pragma unroll
+            for (int c = 0; c < CC; ++c)
+                hal[(t + q * kNT) * PC + c] = (!SWAP && SILU_A) ? (p >= 0 ? silu(v[c]) : 0.0f) : v[c];
+        }
+        {
+            const int64_t p = own >= 0 ? halo_site(d, o, own) : -1;
+            float v[16];
+#pragma unroll
+            for (int c = 0; c < 16; ++c) v[c] = p >= 0 ? rsrc[c * d.P + p] : 0.0f;
+#pragma unroll
+            for (int c = 0; c < 16; ++c)
+                rows[t * PR + c] = (SWAP && SILU_A) ? (p >= 0 ? silu(v[c]) : 0.0f) : v[c];
+            if constexpr (!SWAP) {
+#pragma unroll
+                for (int c = 0; c < COUT; ++c) sb[c] += (double)v[c];
+            } else if (p >= 0) {
+#pragma unroll
+                for (int c = 0; c < COUT; ++c) sb[c] += (double)csrc[c * d.P + p];
             }
         }
+        __syncthreads();
+        // four groups of four sites a turn (rows past the box are zero)
+        for (int q0 = ws; q0 < groups; q0 += 4 * WS) {
+            int h[4];
+            double a[4];
 #pragma unroll
-        for (int k = 0; k < 27; ++k) dst[(co * CIN + ci) * 27 + k] = acc[k];
+            for (int e = 0; e < 4; ++e) {
+                const int sq = 4 * (q0 + e * WS) + quad;
+                h[e] = hb[sq];
+                a[e] = (double)rows[sq * PR + row];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], (double)hal[h[e] + coff[j]], acc[j], 0, 0, 0);
+        }
     }
+    // accumulator i of a lane: row 4 i + quad, column lane % 16 of the tile
+    double *dst = partial + ((size_t)blockIdx.x * WS + ws) * nw;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int n = 16 * (wv + NWV * j) + row;
+        if (n >= NC) continue;
+        const int k = n / CC, c = n - CC * k;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = 4 * i + quad;
+            dst[SWAP ? (c * CIN + r) * 27 + 26 - k : (r * CIN + c) * 27 + k] = acc[j][i];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < COUT; ++c) {
+        const double v = wave_sum(sb[c]);
+        if (lane == 0) red[wave][c] = v;
+    }
+    __syncthreads();
     if (t < COUT) {
-        double sb = 0.0;
-        for (int s = 0; s < kNT; ++s) sb += (double)gt[t][s];
-        dst[COUT * CIN * 27 + t] = sb;
+        double v = 0.0;
+        for (int q = 0; q < kNT / 64; ++q) v += red[q][t];
+        double *db = partial + (size_t)blockIdx.x * WS * nw + COUT * CIN * 27 + t;
+        db[0] = v;
+        for (int q = 1; q < WS; ++q) db[(size_t)q * nw] = 0.0;
     }
 }
 
-// Fixed-order FP64 sum of n_blk partial vectors of length nw, rounded to
-// float once.
-__global__ void k_sum_partials(const double *__restrict__ partial, int n_blk, int nw, float *__restrict__ out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nw) return;
+// Fixed-order FP64 sum of n_part partial vectors of length nw, rounded to
+// float once: 32 weights per block, eight interleaved runs of partials each.
+constexpr int kSumW = 32;
+__global__ __launch_bounds__(kNT) void k_sum_partials(const double *__restrict__ partial, int n_part, int nw,
+                                                      float *__restrict__ out) {
+    __shared__ double red[kNT / kSumW][kSumW];
+    const int c = threadIdx.x % kSumW, r = threadIdx.x / kSumW, i = blockIdx.x * kSumW + c;
     double s = 0.0;
-    for (int b = 0; b < n_blk; ++b) s += partial[(size_t)b * nw + i];
-    out[i] = (float)s;
+    if (i < nw) {
+#pragma unroll 8
+        for (int b = r; b < n_part; b += kNT / kSumW) s += partial[(size_t)b * nw + i];
+    }
+    red[r][c] = s;
+    __syncthreads();
+    if (r == 0 && i < nw) {
+        for (int q = 1; q < kNT / kSumW; ++q) s += red[q][c];
+        out[i] = (float)s;
+    }
 }
 
 // Network input: channels (S_g, S_A, S_B, t) as FP32.
@@ -290,16 +506,24 @@ __global__ __launch_bounds__(kNT) void k_net_head(const float *__restrict__ u, c
     }
 }
 
-__global__ void k_loss_final(const double *__restrict__ part, int n, double scale, double *__restrict__ loss) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// The loss: a fixed-order sum of the block partials by one block.
+__global__ __launch_bounds__(kNT) void k_loss_final(const double *__restrict__ part, int n, double scale,
+                                                    double *__restrict__ loss) {
+    __shared__ double red[kNT / 64];
     double s = 0.0;
-    for (int i = 0; i < n; ++i) s += part[i];
-    *loss = s * scale;
+    for (int i = threadIdx.x; i < n; i += kNT) s += part[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double a = 0.0;
+        for (int q = 0; q < kNT / 64; ++q) a += red[q];
+        *loss = a * scale;
+    }
 }
 
 // ---------------------------------------------------------------- BF16 MFMA form
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kTapPairs = 14;  // 27 taps in pairs, the last padded
 
 // v_mfma_f32_16x16x32_bf16, one wavefront: lane l holds A[l % 16][8 (l / 16) + j]
@@ -638,6 +862,43 @@ dim3 conv_grid(const NetDims &d, int B) {
     return dim3((unsigned)(nbx * nby * d.dil * d.dil), (unsigned)(nbz * d.dil), (unsigned)B);
 }
 
+// The box of a layer's FP32 kernels: the fewest tiles, then the smallest
+// halo (what is staged per tile), then the longest rows.  Extents that split
+// the sub-grid evenly are enough: a longer box with as many boxes per axis
+// only pads.
+NetBox conv_box(const NetDims &d, int B) {
+    NetBox best{};
+    for (int nx = (d.Sx + kBoxSites - 1) / kBoxSites, x = 0; x != 1; nx = x == 1 ? nx : (d.Sx + x - 2) / (x - 1)) {
+        x = (d.Sx + nx - 1) / nx;
+        const int ycap = kBoxSites / x;
+        for (int ny = (d.Sy + ycap - 1) / ycap, y = 0; y != 1; ny = y == 1 ? ny : (d.Sy + y - 2) / (y - 1)) {
+            y = (d.Sy + ny - 1) / ny;
+            const int zcap = std::min(kBoxSites / (x * y), kBoxHalo / ((x + 2) * (y + 2)) - 2);
+            if (zcap < 1) continue;
+            NetBox b{};
+            b.bx = x;
+            b.by = y;
+            b.nx = nx;
+            b.ny = ny;
+            b.nz = (d.Sz + zcap - 1) / zcap;
+            b.bz = (d.Sz + b.nz - 1) / b.nz;
+            b.hx = x + 2;
+            b.hy = y + 2;
+            b.halo = b.hx * b.hy * (b.bz + 2);
+            b.vol = x * y * b.bz;
+            b.tiles = (int64_t)b.nx * b.ny * b.nz;
+            if (!best.vol || b.tiles < best.tiles || (b.tiles == best.tiles && b.halo < best.halo)) best = b;
+        }
+    }
+    best.px = std::min(d.dil, d.Lx);
+    best.py = std::min(d.dil, d.Ly);
+    best.pz = std::min(d.dil, d.Lz);
+    best.tiles *= (int64_t)best.px * best.py * best.pz * B;
+    return best;
+}
+
+unsigned conv_blocks(const NetBox &b) { return (unsigned)std::min<int64_t>(b.tiles, kConvBlocks); }
+
 // forward through the four layers as BF16 implicit GEMMs (inference), from
 // the input states to the FP32 pre-activation u = z[3]
 hipError_t net_forward_layers_mfma(NetWork &w, const float *params, const NetDims &d, const int dil[4], int B,
@@ -688,10 +949,11 @@ hipError_t net_forward_layers(NetWork &w, const float *params, const NetDims &d,
                   d3 = layer_dims(d, dil, 3);
     const float *W0 = params + layer_off(0), *W1 = params + layer_off(1);
     const float *W2 = params + layer_off(2), *W3 = params + layer_off(3);
-    k_conv<10, 16, false, false><<<conv_grid(d0, B), kNT, 0, st>>>(w.x, W0, W0 + 16 * 10 * 27, nullptr, w.z[0], d0);
-    k_conv<16, 16, true, false><<<conv_grid(d1, B), kNT, 0, st>>>(w.z[0], W1, W1 + 16 * 16 * 27, nullptr, w.z[1], d1);
-    k_conv<16, 16, true, false><<<conv_grid(d2, B), kNT, 0, st>>>(w.z[1], W2, W2 + 16 * 16 * 27, nullptr, w.z[2], d2);
-    k_conv<16, 3, true, false><<<conv_grid(d3, B), kNT, 0, st>>>(w.z[2], W3, W3 + 3 * 16 * 27, nullptr, w.z[3], d3);
+    const NetBox b0 = conv_box(d0, B), b1 = conv_box(d1, B), b2 = conv_box(d2, B), b3 = conv_box(d3, B);
+    k_conv<10, 16, false, false><<<conv_blocks(b0), kNT, 0, st>>>(w.x, W0, W0 + 16 * 10 * 27, nullptr, w.z[0], d0, b0);
+    k_conv<16, 16, true, false><<<conv_blocks(b1), kNT, 0, st>>>(w.z[0], W1, W1 + 16 * 16 * 27, nullptr, w.z[1], d1, b1);
+    k_conv<16, 16, true, false><<<conv_blocks(b2), kNT, 0, st>>>(w.z[1], W2, W2 + 16 * 16 * 27, nullptr, w.z[2], d2, b2);
+    k_conv<16, 3, true, false><<<conv_blocks(b3), kNT, 0, st>>>(w.z[2], W3, W3 + 3 * 16 * 27, nullptr, w.z[3], d3, b3);
     return hipGetLastError();
 }
 
@@ -811,13 +1073,13 @@ spx_status spx_net_backward(spx_net *net, const float *params, const int32_t *di
     NetWork &w = net->w;
     if ((s = net_reserve(w, d.P, batch, true)) != SPX_OK) return s;
     NetDims dl[4];
-    size_t max_blk = 0;
+    NetBox box[4];
+    size_t need = 0;  // doubles of the weight-gradient partials
     for (int l = 0; l < 4; ++l) {
         dl[l] = layer_dims(d, net->dil, l);
-        const dim3 g = conv_grid(dl[l], batch);
-        max_blk = std::max(max_blk, (size_t)g.x * g.y * g.z);
+        box[l] = conv_box(dl[l], batch);
+        need = std::max(need, (size_t)conv_blocks(box[l]) * (l == 3 ? 2 : 1) * (kC[l + 1] * kC[l] * 27 + kC[l + 1]));
     }
-    const size_t need = max_blk * (16 * 16 * 27 + 16);
     const dim3 pg((unsigned)((d.P + kNT - 1) / kNT), (unsigned)batch);
     const size_t nl = (size_t)pg.x * pg.y;
     if (need > w.part_cap) {
@@ -845,7 +1107,7 @@ spx_status spx_net_backward(spx_net *net, const float *params, const int32_t *di
     if (e != hipSuccess) return set_hip_error(e, "network backward (forward pass)");
     const double inv_count = 1.0 / ((double)d.P * batch);
     k_net_head<<<pg, kNT, 0, st>>>(w.z[3], Sg, Sstar, nullptr, w.g[3], w.lpart, d.P, inv_count);
-    if (loss) k_loss_final<<<1, 1, 0, st>>>(w.lpart, (int)nl, inv_count, loss);
+    if (loss) k_loss_final<<<1, kNT, 0, st>>>(w.lpart, (int)nl, inv_count, loss);
     // layer 4 (16 -> 3), 3 (16 -> 16), 2 (16 -> 16), 1 (10 -> 16)
     for (int l = 3; l >= 0; --l) {
         const int cin = kC[l], cout = kC[l + 1];
@@ -854,18 +1116,18 @@ spx_status spx_net_backward(spx_net *net, const float *params, const int32_t *di
         float *gl = grad + layer_off(l);
         const float *ain = l == 0 ? w.x : w.z[l - 1];
         const NetDims &d_l = dl[l];
-        const dim3 gr = conv_grid(d_l, batch);
-        const size_t n_blk = (size_t)gr.x * gr.y * gr.z;
-        if (l == 3) k_conv_wgrad<16, 3, true><<<gr, kNT, 0, st>>>(ain, w.g[3], w.part, d_l);
-        else if (l == 0) k_conv_wgrad<10, 16, false><<<gr, kNT, 0, st>>>(ain, w.g[0], w.part, d_l);
-        else k_conv_wgrad<16, 16, true><<<gr, kNT, 0, st>>>(ain, w.g[l], w.part, d_l);
-        k_sum_partials<<<(nw + 255) / 256, 256, 0, st>>>(w.part, (int)n_blk, nw, gl);
+        const NetBox &b_l = box[l];
+        const unsigned gr = conv_blocks(b_l);
+        if (l == 3) k_conv_wgrad<3, true, true, 2><<<gr, kNT, 0, st>>>(ain, w.g[3], w.part, d_l, b_l);
+        else if (l == 0) k_conv_wgrad<10, false, false, 1><<<gr, kNT, 0, st>>>(ain, w.g[0], w.part, d_l, b_l);
+        else k_conv_wgrad<16, false, true, 1><<<gr, kNT, 0, st>>>(ain, w.g[l], w.part, d_l, b_l);
+        k_sum_partials<<<(nw + kSumW - 1) / kSumW, kNT, 0, st>>>(w.part, (int)gr * (l == 3 ? 2 : 1), nw, gl);
         if (l > 0) {
             // g_{l-1} = silu'(z_{l-1}) * conv(g_l, W^T flipped)
             k_transpose_flip<<<(cin * cout * 27 + 255) / 256, 256, 0, st>>>(Wl, w.wt, cin, cout);
             // the transposed convolution of layer l has layer l's dilation
-            if (l == 3) k_conv<3, 16, false, true><<<gr, kNT, 0, st>>>(w.g[3], w.wt, nullptr, w.z[2], w.g[2], d_l);
-            else k_conv<16, 16, false, true><<<gr, kNT, 0, st>>>(w.g[l], w.wt, nullptr, w.z[l - 1], w.g[l - 1], d_l);
+            if (l == 3) k_conv<3, 16, false, true><<<gr, kNT, 0, st>>>(w.g[3], w.wt, nullptr, w.z[2], w.g[2], d_l, b_l);
+            else k_conv<16, 16, false, true><<<gr, kNT, 0, st>>>(w.g[l], w.wt, nullptr, w.z[l - 1], w.g[l - 1], d_l, b_l);
         }
         e = hipGetLastError();
         if (e != hipSuccess) return set_hip_error(e, "network backward");

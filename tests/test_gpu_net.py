@@ -162,6 +162,34 @@ def test_net_dilated_backward_matches_oracle():
     assert err <= 1e-5, err
 
 
+@pytest.mark.parametrize("L,dil", [((1, 1, 1), (1, 1, 1, 1)), ((8, 8, 4), (1, 1, 1, 1)), ((9, 9, 5), (1, 2, 4, 8)),
+                                   ((70, 33, 1), (3, 1, 2, 64)), ((1, 1, 90), (1, 1, 1, 1)),
+                                   ((25, 24, 23), (1, 2, 4, 8))],
+                         ids=["site", "one_box", "box_plus_one", "film", "chain", "many_boxes"])
+def test_net_backward_at_box_edges_matches_oracle(L, dil):
+    # the matrix-core layers run on boxes chosen from the sub-grid extents:
+    # boxes cut short on every axis, sub-grids of one site, phases that do not
+    # exist, more boxes than resident blocks; K padded (10 and 3 channels)
+    import torch
+    from paper_2605_26016_amd import spx
+    B = 2
+    p32 = init_params(7)
+    Sg, SA, SB, Ss, t = batch_case(L, B, 60)
+    net = spx.Net(dilation=dil)
+    n = spx.net_nparams()
+    grad = torch.zeros(n, dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    spx.net_backward(net, to_dev(p32), L, B, to_dev(Sg), to_dev(SA), to_dev(SB), to_dev(t), to_dev(Ss), grad, loss)
+    ref, lref = np.zeros(n), 0.0
+    for b in range(B):
+        lb, gb = oracle.net_backward(L, p32.astype(np.float64), oracle_x(Sg[b], SA[b], SB[b], t[b]), Sg[b], Ss[b],
+                                     dil=dil)
+        ref += gb / B
+        lref += lb / B
+    assert abs(loss.item() - lref) <= 1e-5 * lref
+    assert np.max(np.abs(grad.cpu().numpy() - ref)) <= 1e-5 * np.max(np.abs(ref))
+
+
 def test_net_dilation_is_validated():
     from paper_2605_26016_amd import spx
     net = spx.Net()
