@@ -117,7 +117,8 @@ typedef struct {
  * stencil_engine: 0 auto, 1 gather kernel (any bond table), 2 z-marching LDS
  * engine (bond tables that match a built-in shell shape: simple cubic shells
  * 1, 1-3, 1-4; bcc shells 1-5).  zchunk: z planes per block of the z-march
- * engine (0 = default 8).  heun_field (z-march engine; the gather engine
+ * engine (0: every kernel takes the even split that fills the chip with the
+ * fewest repeated planes, unless the autotuner picks one).  heun_field (z-march engine; the gather engine
  * always recomputes): 0 auto (3, or the autotuner's choice), 1 the
  * corrector recomputes the field of S^n, 2 the predictor stores the FP32
  * bilinear field of S^n for the corrector (FP32 field_prec only; results
@@ -139,7 +140,7 @@ typedef struct {
  * shells 1, any tensor, or shells 1-3 isotropic; no dipolar term; results
  * equal to 3 up to the summation order of the bilinear sums).  heun_field 8
  * on any other Hamiltonian fails with SPX_ERR_UNSUPPORTED; heun_field 0
- * selects 8 where it applies (z chunk 64 unless zchunk is given), else 3. */
+ * selects 8 where it applies, else 3. */
 typedef struct {
     int32_t field_prec;        /* spx_precision */
     int32_t backend;
@@ -282,7 +283,7 @@ typedef struct {
     int64_t workspace_bytes;   /* library-owned device memory */
     int32_t stencil_engine;    /* 1 gather, 2 z-march */
     int32_t shape;             /* z-march shell shape id, -1 if none */
-    int32_t zchunk;
+    int32_t zchunk;            /* as requested or tuned; a nominal 8 (heun_field 8: 64) when each kernel takes its own */
     int32_t heun_field;        /* 1 recompute, 2 stored FP32 field, 3 stored stage and noise, 4 as 3 + noise pre-pass, 5 split, 6 split predictor, 7 stored stage, noise drawn again, 8 fused single pass */
     int32_t tuned;             /* 1 if the autotuner chose zchunk / heun_field */
     double tuned_step_us;      /* its timing of one Heun step (microseconds) */

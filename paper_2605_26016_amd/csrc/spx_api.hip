@@ -540,7 +540,10 @@ spx_status spx_setup_hamiltonian(const spx_lattice_desc *lat, const spx_model_de
             return fail(SPX_ERR_UNSUPPORTED, "the bond table matches no z-march shell shape");
         }
         h->engine = (have && engine_req != 1) ? 2 : 1;
-        if (have && zchunk_req > 0) h->zp.zch = zchunk_req;
+        if (have && zchunk_req > 0) {
+            h->zp.zch = zchunk_req;
+            h->zp.zauto = 0;
+        }
         if (have) h->zp.frows = rows_req;
         h->heun_field = 1;
         // the fused step needs a single-sublattice shape of range one cell and
@@ -834,7 +837,10 @@ static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z,
             std::fclose(f);
             if (hit && !((chf == 2 || chf == 5 || chf == 6) && h->field_prec != SPX_FP32) &&
                 !(chf == kHeunFused && !h->fusable)) {
-                if (tune_z) h->zp.zch = cz;
+                if (tune_z) {
+                    h->zp.zch = cz;
+                    h->zp.zauto = 0;
+                }
                 if (tune_field) h->heun_field = chf;
                 if (tune_rows && h->heun_field == kHeunFused && chf == kHeunFused && crows != 0) h->zp.frows = crows;
                 h->tune_us = cus;
@@ -900,6 +906,7 @@ static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z,
         for (int rows : rowlist(hf))
         for (int z : zlist(hf)) {
             h->zp.zch = z;
+            h->zp.zauto = 0;
             h->zp.frows = rows;
             h->heun_field = hf;
             spx_status r = SPX_OK;
@@ -1034,9 +1041,9 @@ spx_status spx_energy(spx_ham *h, const double *S, double *E, double *terms, voi
     const void *bil = nullptr;
     hipError_t e = hipSuccess;
     if (h->engine == 2 && h->zp.valid &&
-        (size_t)4 * ((size_t)zmarch_tiles(h->zp, h->grid) + kEnergyL2) <= energy_partial_doubles(h->grid)) {
+        (size_t)4 * ((size_t)zmarch_energy_tiles(h->zp, h->grid) + kEnergyL2) <= energy_partial_doubles(h->grid)) {
         e = zmarch_energy(h->zp, h->grid, h->onsite, S, bdip, h->d_partial, st);
-        if (e == hipSuccess) e = launch_energy_reduce(h->d_partial, zmarch_tiles(h->zp, h->grid), E, terms, st);
+        if (e == hipSuccess) e = launch_energy_reduce(h->d_partial, zmarch_energy_tiles(h->zp, h->grid), E, terms, st);
         if (e != hipSuccess) return hip_fail(e, "spx_energy (z-march)");
         return SPX_OK;
     }

@@ -67,11 +67,24 @@ struct ZPlan {
     int iso = 1;
     int nw = 0;
     int zch = 8;    // z planes per block
+    int zauto = 0;  // 1: each launch takes its chunk from zchunk_rule instead
     int txw = 64;   // tile width in x (GNEB passes: 64, 32 or 16; others 64)
     int frows = 0;  // rows (wavefronts) per block of the fused Heun step, 0: 16 for FP32 NN, else 8
     double wd[9 * kMaxShapeBonds];
     float wf[9 * kMaxShapeBonds];
 };
+// z planes per block of a march over Lz planes by `columns` tiles (images
+// included): the even split with the least (rounds of resident blocks) x
+// (planes a block marches).  slots: blocks resident on the chip; extra: planes
+// a chunk marches besides its own (shared with its neighbours, pipeline
+// fill); most: the longest chunk; max_tiles: no split into more tiles (unless
+// the fewest already are).  A short chunk fills the chip, a long one repeats
+// fewer planes, and the last round should be full: with a fixed 64 planes sc
+// 32^3 ran on 6 blocks (46 us a fused FP64 step, 8.5 with 1 plane), sc 100^3
+// on 32 (226 us, 41 with 8 planes), and sc 512^3 left the last round of 256
+// blocks 41% full (2951 us, 2813 with 171 planes).
+int zchunk_rule(int64_t columns, int Lz, int slots, int extra, int most, int64_t max_tiles);
+int device_cus();
 bool zmarch_plan(int prec, int n_sub, const int *bond_a, const int *bond_b, const int *bond_d,
                  const double *bond_J, int n_bonds, bool iso, ZPlan &zp);
 hipError_t zmarch_field(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, const float *bdip,
@@ -81,7 +94,7 @@ hipError_t zmarch_predict(const ZPlan &zp, const Grid &g, const Onsite &os, cons
                           double *estore, const double *eload, hipStream_t st);
 hipError_t zmarch_noise(const HeunConst &hc, uint64_t step, int64_t N, double *eta, hipStream_t st);
 // Energy terms of S in the z-march epilogue: one quadruple (bilinear, Zeeman,
-// anisotropy, dipolar) per tile into partial[zmarch_tiles()][4], fixed order.
+// anisotropy, dipolar) per tile into partial[zmarch_energy_tiles()][4], fixed order.
 hipError_t zmarch_energy(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, const float *bdip,
                          double *partial, hipStream_t st);
 // split Heun mode: FP32 bilinear field pass + elementwise FP64 stages
@@ -98,9 +111,10 @@ hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, co
                             const double *V, const double *Up, const double *Fp, double *Sh, double *Yh,
                             const double *state, int done_idx, int cand_idx, int method, double *partial,
                             hipStream_t st);
-// Tiles of one image (x tiles x y tiles x z chunks) of the z-march engine.
-int zmarch_tiles(const ZPlan &zp, const Grid &g);
-// The same for the GNEB passes (256-thread blocks, tile width zp.txw), and
+// Tiles (x tiles x y tiles x z chunks) of the energy and minimiser passes.
+int zmarch_energy_tiles(const ZPlan &zp, const Grid &g);
+int zmarch_min_tiles(const ZPlan &zp, const Grid &g);
+// The same for one image of the GNEB passes (256-thread blocks, tile width zp.txw), and
 // the width those passes should use on a lattice.
 int zmarch_gneb_tiles(const ZPlan &zp, const Grid &g);
 int zmarch_gneb_width(const ZPlan &zp, const Grid &g);

@@ -367,6 +367,11 @@ hipError_t launch_fused_kind(const ZPlan &zp, const FArgs &a0, const FConst &fc,
     FArgs a = a0;
     a.nbx = (a.Lx + kFXI - 1) / kFXI;
     a.nby = (a.Ly + NW - 3) / (NW - 2);
+    // one block per CU: what the LDS and registers of 16 FP32 rows or 8 FP64
+    // rows admit; a second block of 8 FP32 rows adds little to a kernel bound
+    // by its vector work (sc 100^3, three shells: 58 us as 238 blocks, 67 as
+    // 442).  Four planes are marched besides the chunk's own.
+    if (zp.zauto) a.zch = zchunk_rule((int64_t)a.nbx * a.nby, a.Lz, device_cus(), 4, a.Lz, INT64_MAX);
     const int nzc = (a.Lz + a.zch - 1) / a.zch;
     const int64_t ntile = (int64_t)a.nbx * a.nby * nzc;
     if (ntile > 0x7fffffff) return hipErrorInvalidValue;

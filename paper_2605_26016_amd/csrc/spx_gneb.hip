@@ -896,7 +896,10 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         // the batched z-march field pass needs an FP64 plan of the table
         gi.Bbil = nullptr;
         g->zplan.push_back(v.zp64 ? *v.zp64 : ZPlan{});
-        if (v.zp64) g->zplan.back().zch = 16;
+        if (v.zp64) {
+            g->zplan.back().zch = 16;
+            g->zplan.back().zauto = 0;
+        }
         for (int n = 0; n < n_img[k]; ++n) {
             imgs.push_back(make_int2(k, n));
             for (int b = 0; b < gi.items_per_img; ++b) items.push_back(GItem{k, n, b * kGB, 0});

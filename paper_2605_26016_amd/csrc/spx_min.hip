@@ -457,10 +457,9 @@ spx_status spx_min_create(spx_ham *h, const spx_min_params *p, void *stream, spx
     if (v.zp64 && !v.dip && !v.pl) {
         m->fused = true;
         m->zp = *v.zp64;
-        m->zp.zch = 16;
         m->g = v.grid;
         m->os = v.onsite;
-        m->ntile = zmarch_tiles(m->zp, v.grid);
+        m->ntile = zmarch_min_tiles(m->zp, v.grid);
     }
     const size_t n3 = (size_t)3 * a.N;
     auto alloc = [&](double **ptr, size_t count) -> bool {

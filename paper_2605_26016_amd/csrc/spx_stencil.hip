@@ -22,6 +22,7 @@
 // for the thread's sites (the predictor across its sublattice sites phase by
 // phase, the correctors site by site), with the corrector's stored stage
 // fetched one plane ahead.
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -1241,6 +1242,8 @@ __global__ __launch_bounds__(256) void k_heun_post(int64_t M, int64_t N, Onsite 
     out[2 * N + i] = p[2];
 }
 
+}  // namespace
+
 // Compute units of the current device (queried once per process).
 int device_cus() {
     static int n = 0;
@@ -1254,63 +1257,134 @@ int device_cus() {
     return n;
 }
 
+int zchunk_rule(int64_t columns, int Lz, int slots, int extra, int most, int64_t max_tiles) {
+    if (slots < 1) slots = 256;
+    int best = 0;
+    double cost = 0.0;
+    // every distinct even split: n chunks of ceil(Lz / n) planes
+    for (int n = (Lz + most - 1) / most, z = 0; z != 1; n = z == 1 ? n : (Lz + z - 2) / (z - 1)) {
+        z = (Lz + n - 1) / n;
+        const int64_t tiles = columns * ((Lz + z - 1) / z);
+        if (best && tiles > max_tiles) break;  // more chunks only add tiles
+        const double c = (double)((tiles + slots - 1) / slots) * (z + extra);
+        if (!best || c < cost) {
+            best = z;
+            cost = c;
+        }
+    }
+    return best;
+}
+
+namespace {
+
+// Resident blocks per CU of a kernel (queried once per instantiation).
 template <int KIND, typename T, bool ISO, int MODE, int TXW>
-hipError_t launch_tile(const ZPlan &zp, const ZArgs &a0, const Onsite &os, const HeunConst &hc, hipStream_t st) {
+int kernel_occupancy() {
+    static const int occ = [] {
+        int n = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_zmarch<KIND, T, ISO, MODE, TXW>,
+                                                                          zm_block(MODE, KIND), 0);
+        return e == hipSuccess && n > 0 ? n : 1;
+    }();
+    return occ;
+}
+
+// The chunk of a launch whose plan leaves it open (zp.zauto); at most 64
+// planes, where the shared planes are under 5% and longer marches let
+// neighbouring tiles drift apart in L2 (sc 512^3 field: 1045 us at 64, 1082
+// at 256).  Two resident blocks per CU at most are counted: a third shares
+// the same bandwidth.
+template <int KIND, typename T, bool ISO, int MODE, int TXW>
+int chunk_of(const ZPlan &zp, const Grid &g, int nimg) {
+    if (!zp.zauto) return zp.zch;
+    constexpr int rows = zm_block(MODE, KIND) / TXW * kYB;
+    const int64_t columns = (int64_t)((g.Lx + TXW - 1) / TXW) * ((g.Ly + rows - 1) / rows) * nimg;
+    const int occ = std::min(kernel_occupancy<KIND, T, ISO, MODE, TXW>(), 2);
+    constexpr int D = make_shape(KIND).dzhi - make_shape(KIND).dzlo + 1;
+    // the energy's tiles fit its partial buffer (one quadruple per 256 sites)
+    const int64_t most = MODE == ZM_ENERGY ? energy_partial_count(g) : INT64_MAX;
+    return zchunk_rule(columns, g.Lz, device_cus() * occ, D, 64, most);
+}
+
+template <int KIND, typename T, bool ISO, int MODE, int TXW>
+hipError_t launch_tile(const ZPlan &zp, const Grid &grid, ZArgs a, const Onsite &os, const HeunConst &hc,
+                       hipStream_t st) {
     constexpr int NB = make_shape(KIND).nb;
     constexpr int NW = ISO ? make_shape(KIND).nshell : 9 * NB;
     constexpr int kBlock = zm_block(MODE, KIND), kRows = kBlock / TXW * kYB;
+    a.zch = chunk_of<KIND, T, ISO, MODE, TXW>(zp, grid, a.nimg);
+    a.nzc = (a.Lz + a.zch - 1) / a.zch;
     ZWeights<T, NW> W;
     for (int k = 0; k < NW; ++k) W.w[k] = (T)(sizeof(T) == 4 ? (double)zp.wf[k] : zp.wd[k]);
-    const int64_t ntile = (int64_t)((a0.Lx + TXW - 1) / TXW) * ((a0.Ly + kRows - 1) / kRows) * a0.nzc * a0.nimg;
+    const int64_t ntile = (int64_t)((a.Lx + TXW - 1) / TXW) * ((a.Ly + kRows - 1) / kRows) * a.nzc * a.nimg;
     if (ntile > 0x7fffffff) return hipErrorInvalidValue;
     // a grid whose tiles are all resident at once (two blocks per CU) gets
     // the XCD-contiguous tile order: the x/y halo rows shared by concurrent
     // neighbouring tiles are then fetched into one L2 once (measured: the
     // bcc 128^3 bilinear pass fetches 2.25x fewer bytes).  Larger grids keep
     // the round-robin order, which measured faster there.
-    ZArgs a = a0;
     const int ncu = device_cus();
-    a.xcd = (a0.imgfast || (ncu > 0 && ntile <= 2 * (int64_t)ncu)) ? 1 : 0;
+    a.xcd = (a.imgfast || (ncu > 0 && ntile <= 2 * (int64_t)ncu)) ? 1 : 0;
     k_zmarch<KIND, T, ISO, MODE, TXW><<<(unsigned)ntile, kBlock, 0, st>>>(a, os, hc, W);
     return hipGetLastError();
 }
 
-template <int KIND, typename T, bool ISO, int MODE>
-hipError_t launch_kind(const ZPlan &zp, const ZArgs &a, const Onsite &os, const HeunConst &hc, hipStream_t st) {
+// What launch_any dispatches to: a launch, or the chunk that launch takes.
+struct ZLaunch {
+    const ZArgs &a;
+    const Onsite &os;
+    const HeunConst &hc;
+    hipStream_t st;
+    template <int KIND, typename T, bool ISO, int MODE, int TXW>
+    hipError_t run(const ZPlan &zp, const Grid &g) const {
+        return launch_tile<KIND, T, ISO, MODE, TXW>(zp, g, a, os, hc, st);
+    }
+};
+struct ZChunkQuery {
+    int *zch;
+    template <int KIND, typename T, bool ISO, int MODE, int TXW>
+    hipError_t run(const ZPlan &zp, const Grid &g) const {
+        *zch = chunk_of<KIND, T, ISO, MODE, TXW>(zp, g, 1);
+        return hipSuccess;
+    }
+};
+
+template <int KIND, typename T, bool ISO, int MODE, typename F>
+hipError_t launch_kind(const ZPlan &zp, const Grid &g, const F &f) {
     if constexpr (zm_gneb(MODE)) {
-        if (zp.txw == 32) return launch_tile<KIND, T, ISO, MODE, 32>(zp, a, os, hc, st);
-        if (zp.txw == 16) return launch_tile<KIND, T, ISO, MODE, 16>(zp, a, os, hc, st);
+        if (zp.txw == 32) return f.template run<KIND, T, ISO, MODE, 32>(zp, g);
+        if (zp.txw == 16) return f.template run<KIND, T, ISO, MODE, 16>(zp, g);
     }
     if (zp.txw != kTX) return hipErrorInvalidValue;
-    return launch_tile<KIND, T, ISO, MODE, kTX>(zp, a, os, hc, st);
+    return f.template run<KIND, T, ISO, MODE, kTX>(zp, g);
 }
 
-template <typename T, bool ISO, int MODE>
-hipError_t launch_mode(const ZPlan &zp, const ZArgs &a, const Onsite &os, const HeunConst &hc, hipStream_t st) {
+template <typename T, bool ISO, int MODE, typename F>
+hipError_t launch_mode(const ZPlan &zp, const Grid &g, const F &f) {
     switch (zp.kind) {
-    case SHAPE_SC_NN: return launch_kind<SHAPE_SC_NN, T, ISO, MODE>(zp, a, os, hc, st);
+    case SHAPE_SC_NN: return launch_kind<SHAPE_SC_NN, T, ISO, MODE>(zp, g, f);
     case SHAPE_SC_3SH:
-        if constexpr (ISO) return launch_kind<SHAPE_SC_3SH, T, ISO, MODE>(zp, a, os, hc, st);
+        if constexpr (ISO) return launch_kind<SHAPE_SC_3SH, T, ISO, MODE>(zp, g, f);
         break;
     case SHAPE_SC_4SH:
-        if constexpr (ISO) return launch_kind<SHAPE_SC_4SH, T, ISO, MODE>(zp, a, os, hc, st);
+        if constexpr (ISO) return launch_kind<SHAPE_SC_4SH, T, ISO, MODE>(zp, g, f);
         break;
     case SHAPE_BCC_5SH:
-        if constexpr (ISO && sizeof(T) == 4) return launch_kind<SHAPE_BCC_5SH, T, ISO, MODE>(zp, a, os, hc, st);
+        if constexpr (ISO && sizeof(T) == 4) return launch_kind<SHAPE_BCC_5SH, T, ISO, MODE>(zp, g, f);
         break;
     default: break;
     }
     return hipErrorInvalidValue;
 }
 
-template <int MODE>
-hipError_t launch_any(const ZPlan &zp, const ZArgs &a, const Onsite &os, const HeunConst &hc, hipStream_t st) {
+template <int MODE, typename F>
+hipError_t launch_any(const ZPlan &zp, const Grid &g, const F &f) {
     if (zp.prec == 0) {
-        if (zp.iso) return launch_mode<double, true, MODE>(zp, a, os, hc, st);
-        return launch_mode<double, false, MODE>(zp, a, os, hc, st);
+        if (zp.iso) return launch_mode<double, true, MODE>(zp, g, f);
+        return launch_mode<double, false, MODE>(zp, g, f);
     }
-    if (zp.iso) return launch_mode<float, true, MODE>(zp, a, os, hc, st);
-    return launch_mode<float, false, MODE>(zp, a, os, hc, st);
+    if (zp.iso) return launch_mode<float, true, MODE>(zp, g, f);
+    return launch_mode<float, false, MODE>(zp, g, f);
 }
 
 ZArgs make_args(const ZPlan &zp, const Grid &g) {
@@ -1321,8 +1395,6 @@ ZArgs make_args(const ZPlan &zp, const Grid &g) {
     for (int k = 0; k < 3; ++k) a.per[k] = g.per[k];
     a.M = g.M;
     a.N = g.N;
-    a.zch = zp.zch;
-    a.nzc = (g.Lz + zp.zch - 1) / zp.zch;
     a.nimg = 1;
     return a;
 }
@@ -1383,6 +1455,7 @@ bool zmarch_plan(int prec, int n_sub, const int *bond_a, const int *bond_b, cons
             zp.wf[k] = (float)w[k];
         }
         zp.zch = 8;
+        zp.zauto = 1;
         zp.valid = true;
         return true;
     }
@@ -1396,7 +1469,7 @@ hipError_t zmarch_field(const ZPlan &zp, const Grid &g, const Onsite &os, const 
     a.bout = b;
     a.bdip0 = bdip;
     HeunConst hc{};
-    return launch_any<ZM_FIELD>(zp, a, os, hc, st);
+    return launch_any<ZM_FIELD>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t zmarch_energy(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, const float *bdip,
@@ -1406,7 +1479,7 @@ hipError_t zmarch_energy(const ZPlan &zp, const Grid &g, const Onsite &os, const
     a.bdip0 = bdip;
     a.gpart = partial;
     HeunConst hc{};
-    return launch_any<ZM_ENERGY>(zp, a, os, hc, st);
+    return launch_any<ZM_ENERGY>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t zmarch_bil(const ZPlan &zp, const Grid &g, const double *S, float *bil, hipStream_t st) {
@@ -1416,7 +1489,7 @@ hipError_t zmarch_bil(const ZPlan &zp, const Grid &g, const double *S, float *bi
     a.bout = bil;
     Onsite os{};
     HeunConst hc{};
-    return launch_any<ZM_BIL>(zp, a, os, hc, st);
+    return launch_any<ZM_BIL>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, double *F,
@@ -1438,11 +1511,24 @@ hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, co
     a.mmethod = method;
     a.mcand_idx = cand_idx;
     HeunConst hc{};
-    if (zp.iso) return launch_mode<double, true, ZM_MIN_FORCE>(zp, a, os, hc, st);
-    return launch_mode<double, false, ZM_MIN_FORCE>(zp, a, os, hc, st);
+    if (zp.iso) return launch_mode<double, true, ZM_MIN_FORCE>(zp, g, ZLaunch{a, os, hc, st});
+    return launch_mode<double, false, ZM_MIN_FORCE>(zp, g, ZLaunch{a, os, hc, st});
 }
 
-int zmarch_tiles(const ZPlan &zp, const Grid &g) { return zm_tiles(g, zp.zch, kThreads, kTX); }
+int zmarch_energy_tiles(const ZPlan &zp, const Grid &g) {
+    int zch = zp.zch;
+    (void)launch_any<ZM_ENERGY>(zp, g, ZChunkQuery{&zch});
+    return zm_tiles(g, zch, kThreads, kTX);
+}
+
+int zmarch_min_tiles(const ZPlan &zp, const Grid &g) {
+    int zch = zp.zch;
+    if (zp.prec == 0) {
+        if (zp.iso) (void)launch_mode<double, true, ZM_MIN_FORCE>(zp, g, ZChunkQuery{&zch});
+        else (void)launch_mode<double, false, ZM_MIN_FORCE>(zp, g, ZChunkQuery{&zch});
+    }
+    return zm_tiles(g, zch, kThreads, kTX);
+}
 
 int zmarch_gneb_tiles(const ZPlan &zp, const Grid &g) {
     return zm_tiles(g, zp.zch, zm_block(ZM_GNEB_A2, zp.kind), zp.txw);
@@ -1491,11 +1577,11 @@ hipError_t zmarch_gneb_pass(int pass, const ZPlan &zp, const Grid &g, const Onsi
     a.imgfast = 1;
     HeunConst hc{};
     if (pass == 0) {
-        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zp, a, os, hc, st);
-        return launch_mode<double, false, ZM_GNEB_A2>(zp, a, os, hc, st);
+        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zp, g, ZLaunch{a, os, hc, st});
+        return launch_mode<double, false, ZM_GNEB_A2>(zp, g, ZLaunch{a, os, hc, st});
     }
-    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zp, a, os, hc, st);
-    return launch_mode<double, false, ZM_GNEB_C2>(zp, a, os, hc, st);
+    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zp, g, ZLaunch{a, os, hc, st});
+    return launch_mode<double, false, ZM_GNEB_C2>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t zmarch_bil_images(const ZPlan &zp, const Grid &g, int n_img, const double *S0, const double *S0alt,
@@ -1511,7 +1597,7 @@ hipError_t zmarch_bil_images(const ZPlan &zp, const Grid &g, int n_img, const do
     a.bout = bil;
     Onsite os{};
     HeunConst hc{};
-    return launch_any<ZM_BIL>(zp, a, os, hc, st);
+    return launch_any<ZM_BIL>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t heun_split_pre(const Grid &g, const Onsite &os, const HeunConst &hc, uint64_t step, const double *S,
@@ -1546,7 +1632,7 @@ hipError_t zmarch_predict(const ZPlan &zp, const Grid &g, const Onsite &os, cons
     a.pstore = pstore;
     a.estore = estore;
     a.step = step;
-    return launch_any<ZM_PREDICT>(zp, a, os, hc, st);
+    return launch_any<ZM_PREDICT>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 hipError_t zmarch_correct(const ZPlan &zp, const Grid &g, const Onsite &os, const HeunConst &hc, uint64_t step,
@@ -1563,9 +1649,9 @@ hipError_t zmarch_correct(const ZPlan &zp, const Grid &g, const Onsite &os, cons
     a.pload = pload;
     a.eload = eload;
     a.step = step;
-    if (pload) return launch_any<ZM_CORRECT_P>(zp, a, os, hc, st);  // eload NULL: noise drawn again
-    if (bload) return launch_any<ZM_CORRECT_STORED>(zp, a, os, hc, st);
-    return launch_any<ZM_CORRECT>(zp, a, os, hc, st);
+    if (pload) return launch_any<ZM_CORRECT_P>(zp, g, ZLaunch{a, os, hc, st});  // eload NULL: noise drawn again
+    if (bload) return launch_any<ZM_CORRECT_STORED>(zp, g, ZLaunch{a, os, hc, st});
+    return launch_any<ZM_CORRECT>(zp, g, ZLaunch{a, os, hc, st});
 }
 
 }  // namespace spx

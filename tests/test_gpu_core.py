@@ -466,3 +466,31 @@ def test_autotuner_picks_candidate_and_caches(tmp_path):
     spx.llg_heun_step(h3, Sb, **kw)
     torch.cuda.synchronize()
     assert torch.equal(Sa, Sb)
+
+
+@pytest.mark.parametrize("L", [(1, 1, 1), (3, 5, 1), (130, 70, 2), (20, 9, 1500), (65, 33, 257)],
+                         ids=["site", "film", "two_planes", "bar", "ragged"])
+@pytest.mark.parametrize("shells", [1, 4])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_default_chunk_equals_a_given_one(L, shells, prec):
+    # each kernel splits z by its own rule when no chunk is given; a site's
+    # arithmetic does not depend on the split (field and Heun bit for bit), and
+    # the energy only sums other partials (1e-13 of its largest term)
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="c", L=L, periodic=(1, 0, 0), J_shell=(1.0, 0.188, -0.274, -0.161)[:shells], K=0.1,
+                 B=(0.0, 0.0, 1.0), field_prec=prec)
+    S0 = to_dev(random_sphere(w.N, 71))
+    out = []
+    for z in (0, 5):
+        h = gpu_hamiltonian(w, zchunk=z)
+        b = torch.zeros((3, w.N), dtype=torch.float64 if prec == "fp64" else torch.float32, device="cuda")
+        terms = torch.zeros(5, dtype=torch.float64, device="cuda")
+        S = S0.clone()
+        spx.eval_field(h, S, b)
+        spx.energy(h, S, terms[4:], terms)
+        spx.llg_heun_step(h, S, alpha=0.1, dt_fs=0.1, temperature_K=20.0, seed=3, n_steps=3)
+        out.append((b, S, terms))
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1], out[1][1])
+    assert float((out[0][2] - out[1][2]).abs().max()) <= 1e-13 * float(out[0][2].abs().max()) * max(1.0, w.N ** 0.5)
