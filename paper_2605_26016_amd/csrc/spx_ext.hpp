@@ -139,8 +139,16 @@ struct GnebPassArgs {
     int string;
     double *partial;
 };
-hipError_t zmarch_gneb_pass(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
-                            hipStream_t st);
+// Instances whose plans agree in shape, isotropy and tile width share a launch:
+// zmarch_gneb_entry fills one instance's entry of the pass (false: the plan
+// has no such pass) and says how many blocks it takes from block0 on (a
+// multiple of 8); zmarch_gneb_batch launches n entries (device memory and the
+// host's copy, ascending block0) with the blocks of all of them.
+size_t zmarch_gneb_entry_bytes();
+bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
+                       unsigned block0, void *entry, unsigned *blocks);
+hipError_t zmarch_gneb_batch(int pass, const ZPlan &zp, const void *entries, const void *host, int n, unsigned blocks,
+                             hipStream_t st);
 hipError_t zmarch_bil_images(const ZPlan &zp, const Grid &g, int n_img, const double *S0, const double *S0alt,
                              const double *sel, const double *skip, double *bil, hipStream_t st);
 hipError_t heun_split_pre(const Grid &g, const Onsite &os, const HeunConst &hc, uint64_t step, const double *S,

@@ -95,6 +95,8 @@ struct GItem {
     int inst, img, site0, pad;
 };
 
+// NT: threads of the block
+template <int NT = kGB>
 __device__ __forceinline__ double block_sum(double v, double *red) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     v = wave_sum(v);
@@ -103,20 +105,26 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
     __syncthreads();
     double t = 0.0;
     if (threadIdx.x == 0)
-        for (int k = 0; k < kGB / 64; ++k) t += red[k];
+        for (int k = 0; k < NT / 64; ++k) t += red[k];
     return t;  // valid in thread 0
 }
 
-__device__ __forceinline__ double block_max(double v, double *red) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
+    return v;
+}
+
+template <int NT = kGB>
+__device__ __forceinline__ double block_max(double v, double *red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    v = wave_max(v);
     __syncthreads();
     if (lane == 0) red[w] = v;
     __syncthreads();
     double t = 0.0;
     if (threadIdx.x == 0)
-        for (int k = 0; k < kGB / 64; ++k) t = fmax(t, red[k]);
+        for (int k = 0; k < NT / 64; ++k) t = fmax(t, red[k]);
     return t;
 }
 
@@ -296,15 +304,14 @@ __global__ __launch_bounds__(kGB) void k_gneb_reduce(const GInst *__restrict__ i
 }
 
 // climbing image and tangent weights (Henkelman-Jonsson improved tangent);
-// one block per instance, threads over the images
-__global__ __launch_bounds__(kGB) void k_gneb_scalars1(const GInst *__restrict__ inst) {
-    __shared__ double rv[kGB / 64];
-    __shared__ int ri[kGB / 64];
-    const GInst &G = inst[blockIdx.x];
-    if (G.st[ST_DONE] != 0.0) return;
+// one block of NT threads per instance, threads over the images
+template <int NT>
+__device__ __forceinline__ void scalars1(const GInst &G) {
+    __shared__ double rv[NT / 64];
+    __shared__ int ri[NT / 64];
     double *im = G.img;
     const int M = G.n_img;
-    for (int n = 1 + (int)threadIdx.x; n < M - 1; n += kGB) {
+    for (int n = 1 + (int)threadIdx.x; n < M - 1; n += NT) {
         double wp = 0.0, wm = 0.0;
         if (G.ci_mode != 3) {  // minimisation: no tangent, so no projection and no spring
             const double Ep = im[(n + 1) * IS_N + IS_E], Em = im[(n - 1) * IS_N + IS_E], E0 = im[n * IS_N + IS_E];
@@ -323,7 +330,7 @@ __global__ __launch_bounds__(kGB) void k_gneb_scalars1(const GInst *__restrict__
     int ci = -1;
     if (G.ci_mode == 2 || (G.ci_mode == 1 && G.st[ST_CION] != 0.0)) {
         double best = 0.0;
-        for (int n = 1 + (int)threadIdx.x; n < M - 1; n += kGB) {
+        for (int n = 1 + (int)threadIdx.x; n < M - 1; n += NT) {
             const double e = im[n * IS_N + IS_E];
             if (ci < 0 || e > best) { best = e; ci = n; }
         }
@@ -337,11 +344,17 @@ __global__ __launch_bounds__(kGB) void k_gneb_scalars1(const GInst *__restrict__
         if (lane == 0) { rv[w] = best; ri[w] = ci; }
         __syncthreads();
         if (threadIdx.x == 0) {
-            for (int q = 1; q < kGB / 64; ++q)
+            for (int q = 1; q < NT / 64; ++q)
                 if (ri[q] >= 0 && (ci < 0 || rv[q] > best || (rv[q] == best && ri[q] < ci))) { best = rv[q]; ci = ri[q]; }
         }
     }
     if (threadIdx.x == 0) G.st[ST_CI] = (double)ci;
+}
+
+__global__ __launch_bounds__(kGB) void k_gneb_scalars1(const GInst *__restrict__ inst) {
+    const GInst &G = inst[blockIdx.x];
+    if (G.st[ST_DONE] != 0.0) return;
+    scalars1<kGB>(G);
 }
 
 // tangent of image n at site t (projected on the tangent plane, unnormalised)
@@ -400,14 +413,13 @@ __global__ __launch_bounds__(kGB) void k_gneb_b(const GInst *__restrict__ inst, 
 // F_gneb = F + c_n tau^, c_n = -2 F.tau^ on the climbing image, else
 // -F.tau^ + k (d_n - d_{n-1});  v.F_gneb and F_gneb.F_gneb follow in closed form.
 // One block per instance, threads over the images, fixed-order block sums.
-__global__ __launch_bounds__(kGB) void k_gneb_scalars2(const GInst *__restrict__ inst) {
-    __shared__ double red[kGB / 64];
-    const GInst &G = inst[blockIdx.x];
-    if (G.st[ST_DONE] != 0.0) return;
+template <int NT>
+__device__ __forceinline__ void scalars2(const GInst &G) {
+    __shared__ double red[NT / 64];
     double *im = G.img;
     const int ci = (int)G.st[ST_CI];
     double P = 0.0, Q = 0.0;
-    for (int n = 1 + (int)threadIdx.x; n + 1 < G.n_img; n += kGB) {
+    for (int n = 1 + (int)threadIdx.x; n + 1 < G.n_img; n += NT) {
         double *r = im + n * IS_N;
         if (G.zt_per_img > 0) {
             // two-pass instance: tau = w+ a + w- b
@@ -429,9 +441,48 @@ __global__ __launch_bounds__(kGB) void k_gneb_scalars2(const GInst *__restrict__
         P += r[IS_VF] + c * vt;
         Q += r[IS_FF] + 2.0 * c * ft + c * c;
     }
-    const double Ps = block_sum(P, red);
-    const double Qs = block_sum(Q, red);
+    const double Ps = block_sum<NT>(P, red);
+    const double Qs = block_sum<NT>(Q, red);
     if (threadIdx.x == 0) G.st[ST_PROJ] = (G.ci_mode != MODE_STRING && Ps > 0.0 && Qs > 0.0) ? Ps / Qs : 0.0;
+}
+
+__global__ __launch_bounds__(kGB) void k_gneb_scalars2(const GInst *__restrict__ inst) {
+    const GInst &G = inst[blockIdx.x];
+    if (G.st[ST_DONE] != 0.0) return;
+    scalars2<kGB>(G);
+}
+
+// Per-image sums of the projection pass, then both scalar steps, of a batch
+// of small two-pass instances: one block per instance, a wavefront per image.
+// One launch instead of three where the tiles are few (kFoldTiles): between
+// the passes of a batch of films the launches themselves were the time.
+constexpr int kFoldB = 1024;
+constexpr int kFoldTiles = 2048;  // images x tiles per image of an instance
+__global__ __launch_bounds__(kFoldB) void k_gneb_mid(const GInst *__restrict__ inst,
+                                                     const double *__restrict__ partial) {
+    const GInst &G = inst[blockIdx.x];
+    if (G.st[ST_DONE] != 0.0) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int n = wave; n < G.n_img; n += kFoldB / 64) {
+        const double *p = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS;
+        double v[kPassA2Values];
+#pragma unroll
+        for (int q = 0; q < kPassA2Values; ++q) v[q] = 0.0;
+        for (int k = lane; k < G.zt_per_img; k += 64)
+#pragma unroll
+            for (int q = 0; q < kPassA2Values; ++q) v[q] += p[(size_t)k * kPS + q];
+#pragma unroll
+        for (int q = 0; q < kPassA2Values; ++q) {
+            const double t = wave_sum(v[q]);
+            if (lane == 0) G.img[n * IS_N + IS_E + q] = t;
+        }
+    }
+    __threadfence_block();
+    __syncthreads();
+    scalars1<kFoldB>(G);
+    __threadfence_block();
+    __syncthreads();
+    scalars2<kFoldB>(G);
 }
 
 // ---------------------------------------------------------------- pass C
@@ -495,23 +546,44 @@ __global__ __launch_bounds__(kGB) void k_gneb_c(const GInst *__restrict__ inst, 
     }
 }
 
-// max |F_gneb| per instance (from the per-image maxima), climbing-image
-// switch, convergence, buffer flip
+// max |F_gneb| per instance (mx, in thread 0), climbing-image switch,
+// convergence, buffer flip
+__device__ __forceinline__ void finish_instance(const GInst &G, double mx) {
+    if (threadIdx.x != 0) return;
+    G.st[ST_MAXF] = mx;
+    G.st[ST_ITER] += 1.0;
+    G.st[ST_CUR] = 1.0 - G.st[ST_CUR];
+    const bool ci_ready = G.ci_mode != 1 || G.st[ST_CION] != 0.0;
+    if (G.ci_mode == 1 && G.st[ST_CION] == 0.0 && mx < G.ci_on_below) G.st[ST_CION] = 1.0;
+    if (G.tol > 0.0 && mx < G.tol && ci_ready) G.st[ST_DONE] = 1.0;
+}
+
 __global__ __launch_bounds__(kGB) void k_gneb_finish(const GInst *__restrict__ inst) {
     __shared__ double red[kGB / 64];
     const GInst &G = inst[blockIdx.x];
     if (G.st[ST_DONE] != 0.0) return;
     double m = 0.0;
     for (int n = 1 + (int)threadIdx.x; n + 1 < G.n_img; n += kGB) m = fmax(m, G.img[n * IS_N + IS_FM]);
-    const double mx = block_max(m, red);
-    if (threadIdx.x == 0) {
-        G.st[ST_MAXF] = mx;
-        G.st[ST_ITER] += 1.0;
-        G.st[ST_CUR] = 1.0 - G.st[ST_CUR];
-        const bool ci_ready = G.ci_mode != 1 || G.st[ST_CION] != 0.0;
-        if (G.ci_mode == 1 && G.st[ST_CION] == 0.0 && mx < G.ci_on_below) G.st[ST_CION] = 1.0;
-        if (G.tol > 0.0 && mx < G.tol && ci_ready) G.st[ST_DONE] = 1.0;
+    finish_instance(G, block_max(m, red));
+}
+
+// The same from the tiles' maxima (small two-pass instances, as k_gneb_mid).
+__global__ __launch_bounds__(kFoldB) void k_gneb_end(const GInst *__restrict__ inst,
+                                                     const double *__restrict__ partial) {
+    __shared__ double red[kFoldB / 64];
+    const GInst &G = inst[blockIdx.x];
+    if (G.st[ST_DONE] != 0.0) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double m = 0.0;
+    for (int n = 1 + wave; n + 1 < G.n_img; n += kFoldB / 64) {
+        const double *p = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS;
+        double t = 0.0;
+        for (int k = lane; k < G.zt_per_img; k += 64) t = fmax(t, p[(size_t)k * kPS]);
+        t = wave_max(t);
+        if (lane == 0) G.img[n * IS_N + IS_FM] = t;
+        m = fmax(m, t);
     }
+    finish_instance(G, block_max<kFoldB>(m, red));
 }
 
 // bring the state back to the caller's buffer Y[0] (after an odd number of flips)
@@ -698,8 +770,20 @@ struct spx_gneb {
     hipGraphExec_t graph = nullptr;
     hipStream_t cap_stream = nullptr;  // library-owned capture stream (the caller's may be the null stream)
     int use_graph = 1;
-    // Parallel branches of the captured iteration: one stream per instance,
-    // a fork event and per-instance join events for each of the two passes.
+    // Two-pass instances of one kernel (shape, isotropy, tile width) share its
+    // launches: entry tables of the two passes on the device.
+    struct Group {
+        ZPlan zp;
+        std::vector<int> inst;
+        void *entries[2] = {nullptr, nullptr};
+        std::vector<char> host[2];  // the host's copies
+        unsigned blocks[2] = {0, 0};
+    };
+    std::vector<Group> groups;
+    std::vector<int> field_inst;  // item-path instances with a batched field pass
+    bool fold = false;            // k_gneb_mid / k_gneb_end serve every instance
+    // Parallel branches of the captured iteration: one stream per group (and
+    // item-path field pass), a fork event and join events per pass.
     std::vector<hipStream_t> side;
     hipEvent_t fork_ev[2] = {nullptr, nullptr};
     std::vector<hipEvent_t> join_ev[2];
@@ -773,65 +857,99 @@ hipError_t enqueue_reparam(spx_gneb *g, int gate, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Enqueue one GNEB iteration (all instances) on stream st.
-GnebPassArgs pass_args(const spx_gneb *g, int k);
-
-// Enqueue one z-march pass of every instance that has one: in turn on st,
-// or, while g->branch is set (capture), each instance on its own stream
-// between a fork from st and a join back into it, so that the graph runs
-// the instances' passes side by side and the small lattices' blocks fill
-// the chip beside the large one's.  The instances share no buffer.
-constexpr int kMaxBranches = 8;
-template <typename F>
-hipError_t per_instance(spx_gneb *g, int pass, hipStream_t st, F launch) {
-    if (!g->branch) {
-        for (int k = 0; k < g->n_inst; ++k) {
-            const hipError_t e = launch(k, st);
+// The entries of every group, for the instances' present parameters.
+// Synchronises st.
+hipError_t upload_groups(spx_gneb *g, hipStream_t st) {
+    const size_t eb = zmarch_gneb_entry_bytes();
+    for (spx_gneb::Group &gr : g->groups)
+        for (int pass = 0; pass < 2; ++pass) {
+            std::vector<char> &tab = gr.host[pass];
+            tab.resize(eb * gr.inst.size());
+            unsigned at = 0;
+            for (size_t q = 0; q < gr.inst.size(); ++q) {
+                const int k = gr.inst[q];
+                unsigned blocks = 0;
+                if (!zmarch_gneb_entry(pass, g->zplan[k], g->hinst[k].g, g->hos[k], pass_args(g, k), at,
+                                       tab.data() + eb * q, &blocks))
+                    return hipErrorInvalidValue;
+                at += blocks;
+            }
+            gr.blocks[pass] = at;
+            hipError_t e = hipMemcpyAsync(gr.entries[pass], tab.data(), tab.size(), hipMemcpyHostToDevice, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
             if (e != hipSuccess) return e;
         }
-        return hipSuccess;
+    return hipSuccess;
+}
+
+// Enqueue one z-march pass of every unit (group, or item-path field pass):
+// in turn on st, or, while g->branch is set (capture), each on its own stream
+// between a fork from st and a join back into it, so that the graph runs them
+// side by side and the small lattices' blocks fill the chip beside the large
+// one's.  The instances share no buffer.
+constexpr int kMaxBranches = 8;
+int pass_units(const spx_gneb *g, int pass) {
+    return (int)g->groups.size() + (pass == 0 ? (int)g->field_inst.size() : 0);
+}
+hipError_t enqueue_pass(spx_gneb *g, int pass, hipStream_t st) {
+    auto launch = [&](int u, hipStream_t s) {
+        const int ng = (int)g->groups.size();
+        if (u < ng) {
+            const spx_gneb::Group &gr = g->groups[u];
+            return zmarch_gneb_batch(pass, gr.zp, gr.entries[pass], gr.host[pass].data(), (int)gr.inst.size(),
+                                     gr.blocks[pass], s);
+        }
+        const int k = g->field_inst[u - ng];
+        const GInst &G = g->hinst[k];
+        return zmarch_bil_images(g->zplan[k], G.g, G.n_img, G.Y[0], G.Y[1], G.st + ST_CUR, G.st + ST_DONE,
+                                 (double *)G.Bbil, s);
+    };
+    const int n = pass_units(g, pass);
+    hipError_t e = hipSuccess;
+    if (!g->branch || n < 2) {
+        for (int u = 0; u < n && e == hipSuccess; ++u) e = launch(u, st);
+        return e;
     }
-    hipError_t e = hipEventRecord(g->fork_ev[pass], st);
-    for (int k = 0; k < g->n_inst && e == hipSuccess; ++k) {
-        e = hipStreamWaitEvent(g->side[k], g->fork_ev[pass], 0);
-        if (e == hipSuccess) e = launch(k, g->side[k]);
-        if (e == hipSuccess) e = hipEventRecord(g->join_ev[pass][k], g->side[k]);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, g->join_ev[pass][k], 0);
+    e = hipEventRecord(g->fork_ev[pass], st);
+    for (int u = 0; u < n && e == hipSuccess; ++u) {
+        e = hipStreamWaitEvent(g->side[u], g->fork_ev[pass], 0);
+        if (e == hipSuccess) e = launch(u, g->side[u]);
+        if (e == hipSuccess) e = hipEventRecord(g->join_ev[pass][u], g->side[u]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, g->join_ev[pass][u], 0);
     }
     return e;
 }
 
+// Enqueue one GNEB iteration (all instances) on stream st.
 hipError_t enqueue_iteration(spx_gneb *g, hipStream_t st) {
     const unsigned gi = grid_for(g->n_items);
     bool any_items = false;  // an instance that runs the item passes
     for (const GInst &G : g->hinst) any_items = any_items || G.zt_per_img == 0;
-    hipError_t e0 = per_instance(g, 0, st, [&](int k, hipStream_t s) {
-        const GInst &G = g->hinst[k];
-        if (G.zt_per_img > 0) return zmarch_gneb_pass(0, g->zplan[k], G.g, g->hos[k], pass_args(g, k), s);
-        if (G.Bbil)
-            return zmarch_bil_images(g->zplan[k], G.g, G.n_img, G.Y[0], G.Y[1], G.st + ST_CUR, G.st + ST_DONE,
-                                     (double *)G.Bbil, s);
-        return hipSuccess;
-    });
+    hipError_t e0 = enqueue_pass(g, 0, st);
     if (e0 != hipSuccess) return e0;
-    if (any_items) k_gneb_a<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
-    k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 2, kPassA2Values, IS_E, 0, GATE_ITER,
-                                             0, 0);
-    k_gneb_scalars1<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
-    if (any_items) {
-        k_gneb_b<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
-        k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 5, 0, IS_VF, 1, GATE_ITER, 0, 0);
+    if (g->fold) {
+        k_gneb_mid<<<g->n_inst, kFoldB, 0, st>>>(g->d_inst, g->d_partial);
+    } else {
+        if (any_items) k_gneb_a<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
+        k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 2, kPassA2Values, IS_E, 0,
+                                                 GATE_ITER, 0, 0);
+        k_gneb_scalars1<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
+        if (any_items) {
+            k_gneb_b<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
+            k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 5, 0, IS_VF, 1, GATE_ITER, 0,
+                                                     0);
+        }
+        k_gneb_scalars2<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
+        if (any_items) k_gneb_c<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
     }
-    k_gneb_scalars2<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
-    if (any_items) k_gneb_c<<<gi, kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items, g->d_partial);
-    hipError_t e1 = per_instance(g, 1, st, [&](int k, hipStream_t s) {
-        const GInst &G = g->hinst[k];
-        if (G.zt_per_img == 0) return hipSuccess;
-        return zmarch_gneb_pass(1, g->zplan[k], G.g, g->hos[k], pass_args(g, k), s);
-    });
+    hipError_t e1 = enqueue_pass(g, 1, st);
     if (e1 != hipSuccess) return e1;
-    k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 1, 1, IS_FM, 1, GATE_ITER, 1, 0);
-    k_gneb_finish<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
+    if (g->fold) {
+        k_gneb_end<<<g->n_inst, kFoldB, 0, st>>>(g->d_inst, g->d_partial);
+    } else {
+        k_gneb_reduce<<<g->n_imgs, kGB, 0, st>>>(g->d_inst, g->d_imgs, g->d_partial, 1, 1, IS_FM, 1, GATE_ITER, 1, 0);
+        k_gneb_finish<<<g->n_inst, kGB, 0, st>>>(g->d_inst);
+    }
     bool any_string = false;
     for (const GInst &G : g->hinst) any_string = any_string || G.ci_mode == MODE_STRING;
     if (any_string) {
@@ -941,6 +1059,28 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
                 break;
         }
     }
+    g->fold = true;
+    for (int k = 0; k < n_inst && s == SPX_OK; ++k) {
+        const GInst &gi = g->hinst[k];
+        g->fold = g->fold && gi.zt_per_img > 0 && (int64_t)gi.n_img * gi.zt_per_img <= kFoldTiles;
+        if (gi.zt_per_img == 0) {
+            if (gi.Bbil) g->field_inst.push_back(k);
+            continue;
+        }
+        const ZPlan &zp = g->zplan[k];
+        size_t q = 0;
+        while (q < g->groups.size() && (g->groups[q].zp.kind != zp.kind || g->groups[q].zp.iso != zp.iso ||
+                                        g->groups[q].zp.txw != zp.txw))
+            ++q;
+        if (q == g->groups.size()) {
+            g->groups.emplace_back();
+            g->groups[q].zp = zp;
+        }
+        g->groups[q].inst.push_back(k);
+    }
+    for (spx_gneb::Group &gr : g->groups)
+        for (int pass = 0; pass < 2 && s == SPX_OK; ++pass)
+            s = gneb_alloc(g, &gr.entries[pass], zmarch_gneb_entry_bytes() * gr.inst.size(), "GNEB pass tables");
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_inst, sizeof(GInst) * n_inst, "GNEB instances");
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_items, sizeof(GItem) * items.size(), "GNEB items");
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_imgs, sizeof(int2) * imgs.size(), "GNEB image list");
@@ -980,6 +1120,7 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         e = hipMemcpyAsync(gi.Y[1], gi.Y[0], bytes, hipMemcpyDeviceToDevice, st);
         if (e == hipSuccess) e = hipMemsetAsync(gi.V, 0, bytes, st);
     }
+    if (e == hipSuccess) e = upload_groups(g, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) {
         gneb_free(g);
@@ -1046,13 +1187,14 @@ spx_status spx_gneb_step(spx_gneb *g, int32_t n_iter, void *stream) {
         // launched on whatever stream the caller passes.  Capture failure
         // (graphs unsupported) leaves direct launches in place.
         if (!g->cap_stream) e = hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking);
-        // with two to kMaxBranches instances, their passes become parallel
-        // branches (streams and events of default priority, made once)
-        const bool branches = g->n_inst > 1 && g->n_inst <= kMaxBranches;
+        // two to kMaxBranches units of a pass become parallel branches
+        // (streams and events of default priority, made once)
+        const int units = pass_units(g, 0);
+        const bool branches = units > 1 && units <= kMaxBranches;
         if (e == hipSuccess && branches && g->side.empty()) {
-            g->side.assign(g->n_inst, nullptr);
-            for (int p = 0; p < 2; ++p) g->join_ev[p].assign(g->n_inst, nullptr);
-            for (int k = 0; k < g->n_inst && e == hipSuccess; ++k) {
+            g->side.assign(units, nullptr);
+            for (int p = 0; p < 2; ++p) g->join_ev[p].assign(units, nullptr);
+            for (int k = 0; k < units && e == hipSuccess; ++k) {
                 e = hipStreamCreateWithFlags(&g->side[k], hipStreamNonBlocking);
                 for (int p = 0; p < 2 && e == hipSuccess; ++p)
                     e = hipEventCreateWithFlags(&g->join_ev[p][k], hipEventDisableTiming);
@@ -1173,6 +1315,7 @@ spx_status spx_gneb_set_params(spx_gneb *g, const spx_gneb_params *p, void *stre
         const GInst &gi = g->hinst[k];
         e = hipMemsetAsync(gi.V, 0, sizeof(double) * 3 * gi.g.N * gi.n_img, st);
     }
+    if (e == hipSuccess) e = upload_groups(g, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return set_hip_error(e, "spx_gneb_set_params");
     return SPX_OK;

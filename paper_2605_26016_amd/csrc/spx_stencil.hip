@@ -23,6 +23,7 @@
 // phase, the correctors site by site), with the corrector's stored stage
 // fetched one plane ahead.
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 #include <vector>
 
@@ -94,6 +95,8 @@ int zm_tiles(const Grid &g, int zch, int block, int txw) {
     const int rows = block / txw * kYB;
     return ((g.Lx + txw - 1) / txw) * ((g.Ly + rows - 1) / rows) * ((g.Lz + zch - 1) / zch);
 }
+
+constexpr int kMaxTensorBonds = 6;  // tensor couplings exist on the nearest-neighbour shape only
 
 template <typename T, int NW>
 struct ZWeights {
@@ -183,9 +186,17 @@ __device__ __forceinline__ int zwrap(int c, int L, int per, bool &ok) {
     return c < 0 ? c + L : c;
 }
 
+// Couplings of a shape: one per shell (isotropic) or one tensor per bond.
+template <int KIND, bool ISO>
+constexpr int zm_weights() {
+    return ISO ? make_shape(KIND).nshell : 9 * make_shape(KIND).nb;
+}
+
+// The march of one block: block `tile` of the launch's ntile tiles.
 template <int KIND, typename T, bool ISO, int MODE, int TXW>
-__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite os, HeunConst hc,
-                                                           ZWeights<T, ISO ? make_shape(KIND).nshell : 9 * make_shape(KIND).nb> W) {
+__device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, const HeunConst &hc,
+                                             const ZWeights<T, zm_weights<KIND, ISO>()> &W, unsigned tile,
+                                             unsigned ntile) {
     // block size and tile shape of this instantiation (they shadow the
     // engine-wide defaults): TXW lanes along x, the other threads along y
     constexpr int kThreads = zm_block(MODE, KIND);
@@ -213,8 +224,6 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite
     // contiguous XCD order they run together on one XCD, and the neighbouring
     // images that each block reads besides its own come from that L2.
     const unsigned nbx = (unsigned)((g.Lx + kTX - 1) / kTX), nby = (unsigned)((g.Ly + kTYE - 1) / kTYE);
-    const unsigned ntile = gridDim.x;
-    unsigned tile = blockIdx.x;
     if (g.xcd && (ntile & 7u) == 0) tile = (tile & 7u) * (ntile >> 3) + (tile >> 3);
     unsigned stile;  // spatial tile of the image: x tile + nbx (y tile + nby z chunk)
     int img;
@@ -415,6 +424,10 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite
 #pragma unroll
                 for (int c = 0; c < 3; ++c) own[DZHI][k][c] = pre[P][k][0][c];
         }
+    };
+    auto plane_inside = [&](int q) __attribute__((always_inline)) {
+        const int z = zs + DZLO + q;
+        return g.per[2] || (z >= 0 && z < g.Lz);
     };
     auto fetch_plane = [&](int q, auto ps) __attribute__((always_inline)) {
         constexpr int P = decltype(ps)::value;
@@ -920,7 +933,11 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite
                     }
                 }
             });
-        } else {
+        } else if (!zm_gneb(MODE) || plane_inside(q)) {
+        // (an input plane beyond an open face holds zeros and adds nothing: a
+        // film is one plane between two of them, and its tensors are most of
+        // the GNEB passes' arithmetic; the isotropic sums are too few for the
+        // branch, which held back the fetches around it: 96^3 809 against 799 us)
         static_for<NB>([&](auto kc) __attribute__((always_inline)) {
             constexpr int kb = decltype(kc)::value;
             constexpr ZBond bd = ShapeC<KIND>::t.bonds[kb];
@@ -1114,25 +1131,33 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite
     if constexpr (MODE == ZM_GNEB_A2 || MODE == ZM_GNEB_C2) {
         // fixed-order block sums (A2: energy, squared distance and the nine
         // image sums) or maximum (C2: max |F_gneb|), one set per tile
-        constexpr int NV = MODE == ZM_GNEB_A2 ? 11 : 1;
-        __shared__ double gred[NV][kThreads / 64];
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            double v = MODE == ZM_GNEB_C2 ? sqrt(gX[0]) : gacc[k * kThreads + threadIdx.x];
-            if constexpr (MODE == ZM_GNEB_C2) {
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
-            } else {
-                v = wave_sum(v);
-            }
-            if ((threadIdx.x & 63) == 0) gred[k][threadIdx.x >> 6] = v;
-        }
-        __syncthreads();
-        if (threadIdx.x < NV) {
+        double *const set = g.gpart + ((size_t)g.gitem0 + (size_t)gimg * g.gipi + stile) * 11;
+        if constexpr (MODE == ZM_GNEB_A2) {
+            // kThreads / 16 threads sum sixteen LDS entries of a value each,
+            // then four or five lane steps: eleven whole-wavefront sums by
+            // lane steps cost a block of one plane as much as its sites
+            constexpr int R = kThreads / 16;
+            __syncthreads();  // every thread's column is final
+            const int k = threadIdx.x / R, sub = threadIdx.x % R;
             double t = 0.0;
-            for (int w = 0; w < kThreads / 64; ++w)
-                t = MODE == ZM_GNEB_C2 ? fmax(t, gred[threadIdx.x][w]) : t + gred[threadIdx.x][w];
-            g.gpart[((size_t)g.gitem0 + (size_t)gimg * g.gipi + stile) * 11 + threadIdx.x] = t;
+            if (k < 11)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) t += gacc[k * kThreads + j * R + sub];
+#pragma unroll
+            for (int off = R / 2; off > 0; off >>= 1) t += __shfl_down(t, off, R);
+            if (k < 11 && sub == 0) set[k] = t;
+        } else {
+            __shared__ double gred[kThreads / 64];
+            double v = sqrt(gX[0]);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
+            if ((threadIdx.x & 63) == 0) gred[threadIdx.x >> 6] = v;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                double t = 0.0;
+                for (int w = 0; w < kThreads / 64; ++w) t = fmax(t, gred[w]);
+                set[0] = t;
+            }
         }
     }
     if constexpr (MODE == ZM_ENERGY) {
@@ -1150,6 +1175,43 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite
             g.gpart[(size_t)tile * 4 + threadIdx.x] = t;
         }
     }
+}
+
+template <int KIND, typename T, bool ISO, int MODE, int TXW>
+__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite os, HeunConst hc,
+                                                                 ZWeights<T, zm_weights<KIND, ISO>()> W) {
+    zmarch_block<KIND, T, ISO, MODE, TXW>(g, os, hc, W, blockIdx.x, gridDim.x);
+}
+
+// One instance of a batched GNEB pass: its arguments and the blocks
+// [block0, block0 + ntile) of the launch (block0 a multiple of 8, so that a
+// block's XCD is that of its local index).
+struct ZBatchEntry {
+    ZArgs a;
+    Onsite os;
+    double w[9 * kMaxTensorBonds];
+    unsigned block0, ntile;
+};
+
+// The GNEB passes of several instances in one launch.  The films of a
+// skyrmion batch are a few dozen to a few hundred blocks each; launched one
+// after another (twelve 48^2 .. 96^2 films of 32 images) a pass took 210 us.
+// The entries are read through the constant address space, so their fields
+// are scalar loads where they are used.  Those loads stay behind the march's
+// branches, where kernel arguments are read ahead of them (96^3 x 32 images
+// alone: 821 against 799 us), so an instance alone takes k_zmarch.
+template <int KIND, bool ISO, int MODE, int TXW>
+__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch_batch(const ZBatchEntry *tab, int n) {
+    using CEntry = const __attribute__((address_space(4))) ZBatchEntry;
+    CEntry *t = (CEntry *)(uintptr_t)tab;
+    int e = 0;
+    while (e + 1 < n && t[e + 1].block0 <= blockIdx.x) ++e;
+    const ZBatchEntry &en = *(const ZBatchEntry *)(t + e);
+    const unsigned b = blockIdx.x - en.block0, ntile = en.ntile;
+    if (b >= ntile) return;  // padding between instances
+    const HeunConst hc{};
+    zmarch_block<KIND, double, ISO, MODE, TXW>(
+        en.a, en.os, hc, *reinterpret_cast<const ZWeights<double, zm_weights<KIND, ISO>()> *>(en.w), b, ntile);
 }
 
 // Thermal noise of one Heun step for every site (Heun mode 4: generated by
@@ -1328,6 +1390,29 @@ hipError_t launch_tile(const ZPlan &zp, const Grid &grid, ZArgs a, const Onsite 
     k_zmarch<KIND, T, ISO, MODE, TXW><<<(unsigned)ntile, kBlock, 0, st>>>(a, os, hc, W);
     return hipGetLastError();
 }
+
+// The GNEB passes of a group of instances: n entries on the device, or the
+// host's copy of the only one.
+struct ZBatchLaunch {
+    const ZBatchEntry *tab;
+    const ZBatchEntry *only;
+    int n;
+    unsigned blocks;
+    hipStream_t st;
+    template <int KIND, typename T, bool ISO, int MODE, int TXW>
+    hipError_t run(const ZPlan &, const Grid &) const {
+        static_assert(zm_weights<KIND, ISO>() <= 9 * kMaxTensorBonds, "entry weights");
+        if (n == 1) {
+            ZWeights<double, zm_weights<KIND, ISO>()> W;
+            for (int k = 0; k < zm_weights<KIND, ISO>(); ++k) W.w[k] = only->w[k];
+            k_zmarch<KIND, double, ISO, MODE, TXW>
+                <<<only->ntile, zm_block(MODE, KIND), 0, st>>>(only->a, only->os, HeunConst{}, W);
+        } else {
+            k_zmarch_batch<KIND, ISO, MODE, TXW><<<blocks, zm_block(MODE, KIND), 0, st>>>(tab, n);
+        }
+        return hipGetLastError();
+    }
+};
 
 // What launch_any dispatches to: a launch, or the chunk that launch takes.
 struct ZLaunch {
@@ -1549,10 +1634,17 @@ int zmarch_gneb_width(const ZPlan &zp, const Grid &g) {
     return best;
 }
 
-hipError_t zmarch_gneb_pass(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
-                            hipStream_t st) {
-    if (zp.prec != 0 || ga.n_img < 3 || zmarch_gneb_tiles(zp, g) > ga.items_per_img) return hipErrorInvalidValue;
-    ZArgs a = make_args(zp, g);
+size_t zmarch_gneb_entry_bytes() { return sizeof(ZBatchEntry); }
+
+bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
+                       unsigned block0, void *entry, unsigned *blocks) {
+    if (zp.prec != 0 || ga.n_img < 3 || zmarch_gneb_tiles(zp, g) > ga.items_per_img) return false;
+    ZBatchEntry en;
+    std::memset(&en, 0, sizeof(en));
+    ZArgs &a = en.a;
+    a = make_args(zp, g);
+    a.zch = zp.zch;
+    a.nzc = (g.Lz + zp.zch - 1) / zp.zch;
     a.bstride = 3 * g.N;
     a.gntot = ga.n_img;
     // the second pass runs over the interior images only
@@ -1575,13 +1667,28 @@ hipError_t zmarch_gneb_pass(int pass, const ZPlan &zp, const Grid &g, const Onsi
     a.gitem0 = ga.item0;
     a.gipi = ga.items_per_img;
     a.imgfast = 1;
-    HeunConst hc{};
+    a.xcd = 1;
+    en.os = os;
+    for (int k = 0; k < zp.nw && k < 9 * kMaxTensorBonds; ++k) en.w[k] = zp.wd[k];
+    const int64_t ntile = (int64_t)zmarch_gneb_tiles(zp, g) * a.nimg;
+    if (ntile > 0x7fffffff || ntile + block0 > 0x7fffffff) return false;
+    en.block0 = block0;
+    en.ntile = (unsigned)ntile;
+    *blocks = ((unsigned)ntile + 7u) & ~7u;
+    std::memcpy(entry, &en, sizeof(en));
+    return true;
+}
+
+hipError_t zmarch_gneb_batch(int pass, const ZPlan &zp, const void *entries, const void *host, int n, unsigned blocks,
+                             hipStream_t st) {
+    const ZBatchLaunch l{(const ZBatchEntry *)entries, (const ZBatchEntry *)host, n, blocks, st};
+    const Grid g{};
     if (pass == 0) {
-        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zp, g, ZLaunch{a, os, hc, st});
-        return launch_mode<double, false, ZM_GNEB_A2>(zp, g, ZLaunch{a, os, hc, st});
+        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zp, g, l);
+        return launch_mode<double, false, ZM_GNEB_A2>(zp, g, l);
     }
-    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zp, g, ZLaunch{a, os, hc, st});
-    return launch_mode<double, false, ZM_GNEB_C2>(zp, g, ZLaunch{a, os, hc, st});
+    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zp, g, l);
+    return launch_mode<double, false, ZM_GNEB_C2>(zp, g, l);
 }
 
 hipError_t zmarch_bil_images(const ZPlan &zp, const Grid &g, int n_img, const double *S0, const double *S0alt,
