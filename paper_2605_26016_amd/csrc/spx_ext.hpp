@@ -118,6 +118,11 @@ int zmarch_min_tiles(const ZPlan &zp, const Grid &g);
 // the width those passes should use on a lattice.
 int zmarch_gneb_tiles(const ZPlan &zp, const Grid &g);
 int zmarch_gneb_width(const ZPlan &zp, const Grid &g);
+// Tiles per plane of an image, and the z planes per block of an instance in a
+// batch whose images' tiles per plane add up to batch_columns (at most
+// max_tiles tiles per image, if any split has so few).
+int64_t zmarch_gneb_columns(const ZPlan &zp, const Grid &g);
+int zmarch_gneb_chunk(const ZPlan &zp, const Grid &g, int64_t batch_columns, int64_t max_tiles);
 // The two passes of a GNEB iteration that stores no force (see spx_stencil.hip
 // ZM_GNEB_A2 / ZM_GNEB_C2), over the images of one instance.  pass 0: every
 // image, eleven partials per tile into partial[(item0 + n items_per_img +

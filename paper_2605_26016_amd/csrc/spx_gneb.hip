@@ -767,6 +767,7 @@ struct spx_gneb {
     std::vector<void *> owned;  // library allocations
     float *d_tvals = nullptr;   // reaction coordinates for the learned init
     int max_img = 0;
+    double *h_stats = nullptr;  // pinned: one instance's state and image statistics
     hipGraphExec_t graph = nullptr;
     hipStream_t cap_stream = nullptr;  // library-owned capture stream (the caller's may be the null stream)
     int use_graph = 1;
@@ -821,6 +822,8 @@ void gneb_free(spx_gneb *g) {
     }
     for (void *p : g->owned) (void)hipFree(p);
     g->owned.clear();
+    if (g->h_stats) (void)hipHostFree(g->h_stats);
+    g->h_stats = nullptr;
 }
 
 // Arguments of the two z-march passes of instance k.
@@ -1014,10 +1017,6 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         // the batched z-march field pass needs an FP64 plan of the table
         gi.Bbil = nullptr;
         g->zplan.push_back(v.zp64 ? *v.zp64 : ZPlan{});
-        if (v.zp64) {
-            g->zplan.back().zch = 16;
-            g->zplan.back().zauto = 0;
-        }
         for (int n = 0; n < n_img[k]; ++n) {
             imgs.push_back(make_int2(k, n));
             for (int b = 0; b < gi.items_per_img; ++b) items.push_back(GItem{k, n, b * kGB, 0});
@@ -1033,6 +1032,14 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
     g->n_items = (int)items.size();
     g->n_imgs = (int)imgs.size();
     spx_status s = SPX_OK;
+    // widths first: an instance's chunk follows from the whole batch's tiles
+    int64_t columns = 0;
+    for (int k = 0; k < n_inst; ++k) {
+        ZPlan &zp = g->zplan[k];
+        if (!zp.valid || zp.prec != 0) continue;
+        zp.txw = zmarch_gneb_width(zp, g->hinst[k].g);
+        columns += zmarch_gneb_columns(zp, g->hinst[k].g) * g->hinst[k].n_img;
+    }
     Onsite *d_os = nullptr;
     s = gneb_alloc(g, (void **)&d_os, sizeof(Onsite) * n_inst, "GNEB on-site tables");
     for (int k = 0; k < n_inst && s == SPX_OK; ++k) {
@@ -1042,13 +1049,19 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         gi.Y[0] = images[k];
         if ((s = gneb_alloc(g, (void **)&gi.Y[1], n3 * sizeof(double), "GNEB image buffer")) != SPX_OK) break;
         if ((s = gneb_alloc(g, (void **)&gi.V, n3 * sizeof(double), "GNEB velocities")) != SPX_OK) break;
-        if ((s = gneb_alloc(g, (void **)&gi.img, sizeof(double) * IS_N * gi.n_img, "GNEB image stats")) != SPX_OK) break;
-        if ((s = gneb_alloc(g, (void **)&gi.st, sizeof(double) * ST_N, "GNEB state")) != SPX_OK) break;
+        // state and image statistics in one run: read back by one copy
+        if ((s = gneb_alloc(g, (void **)&gi.st, sizeof(double) * (ST_N + IS_N * (size_t)gi.n_img),
+                            "GNEB state and image stats")) != SPX_OK)
+            break;
+        gi.img = gi.st + ST_N;
         if ((s = gneb_alloc(g, (void **)&gi.alpha, sizeof(double) * gi.n_img, "GNEB image spacing")) != SPX_OK) break;
         const ZPlan &zp = g->zplan[k];
         gi.zt_per_img = 0;
         gi.F = nullptr;
-        if (zp.valid && zp.prec == 0) g->zplan[k].txw = zmarch_gneb_width(zp, gi.g);
+        if (zp.valid && zp.prec == 0) {
+            g->zplan[k].zch = zmarch_gneb_chunk(zp, gi.g, columns, gi.items_per_img);
+            g->zplan[k].zauto = 0;
+        }
         if (zp.valid && zp.prec == 0 && zmarch_gneb_tiles(zp, gi.g) <= gi.items_per_img) {
             gi.zt_per_img = zmarch_gneb_tiles(zp, gi.g);  // the two z-march passes; no stored force
         } else {
@@ -1087,6 +1100,12 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
     if (s == SPX_OK)
         s = gneb_alloc(g, (void **)&g->d_partial, sizeof(double) * kPassA2Values * items.size(), "GNEB partials");
     for (int k = 0; k < n_inst; ++k) g->max_img = std::max(g->max_img, n_img[k]);
+    if (s == SPX_OK &&
+        hipHostMalloc((void **)&g->h_stats, sizeof(double) * (ST_N + IS_N * (size_t)g->max_img), 0) != hipSuccess) {
+        (void)hipGetLastError();
+        g->h_stats = nullptr;
+        s = set_error(SPX_ERR_OUT_OF_MEMORY, "hipHostMalloc failed for GNEB statistics");
+    }
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_tvals, sizeof(float) * g->max_img * n_inst, "GNEB t values");
     if (s != SPX_OK) {
         gneb_free(g);
@@ -1242,9 +1261,10 @@ spx_status spx_gneb_get_stats(spx_gneb *g, int32_t inst, double *E, double *dist
     if (inst < 0 || inst >= g->n_inst) return set_error(SPX_ERR_INVALID_ARG, "instance out of range");
     hipStream_t st = (hipStream_t)stream;
     const GInst &gi = g->hinst[inst];
-    std::vector<double> im(IS_N * gi.n_img), s(ST_N);
-    hipError_t e = hipMemcpyAsync(im.data(), gi.img, sizeof(double) * im.size(), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(s.data(), gi.st, sizeof(double) * ST_N, hipMemcpyDeviceToHost, st);
+    // one copy into pinned memory (two into pageable vectors took 80 us a call)
+    const double *s = g->h_stats, *im = g->h_stats + ST_N;
+    hipError_t e = hipMemcpyAsync(g->h_stats, gi.st, sizeof(double) * (ST_N + IS_N * (size_t)gi.n_img),
+                                  hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return set_hip_error(e, "spx_gneb_get_stats");
     for (int n = 0; n < gi.n_img; ++n) {
