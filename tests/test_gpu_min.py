@@ -96,3 +96,24 @@ def test_arguments_are_checked():
     w32 = Workload(name="b", L=(3, 3, 3), J_shell=(1.0,), field_prec="fp32")
     with pytest.raises(spx.SpxError):
         spx.min_create(gpu_hamiltonian(w32))
+
+
+@pytest.mark.parametrize("history", [1, 2, 4, 5, 6, 8, 9])
+def test_lbfgs_histories_match_the_oracle(history):
+    # each size of the scalar recursion, exactly full and not, and the vector
+    # recursion beyond it (9); a lattice of more sites than one block, with
+    # tails; the history is full from iteration `history` + 1 on
+    from paper_2605_26016_amd import spx
+    w = Workload(name="f", L=(21, 10, 7), periodic=(1, 0, 1), J_shell=(1.0,), K=0.3, B=(0.5, 0.0, 1.0),
+                 field_prec="fp64")
+    S0 = random_sphere(w.N, 19)
+    S = to_dev(S0)
+    mn = spx.min_create(gpu_hamiltonian(w), method="lbfgs", dt=0.05, history=history, max_step=0.3)
+    st = oracle.MinState(w.N, "lbfgs", "exp", max_step=0.3, hist=history, dt=0.05)
+    ref = S0.copy()
+    m = oracle_model(w)
+    for it in range(13):
+        oracle.min_iterate(m, ref, st)
+        spx.min_step(mn, S, 1)
+        err = float(np.max(np.abs(S.cpu().numpy() - ref)))
+        assert err <= 1e-9, (it, err)
