@@ -19,7 +19,7 @@
 //            newest to oldest then back, one fused pass (axpy of the previous
 //            step + dot of the next) per stored pair
 //   update   step u (per method), tangent projection, length cap, retraction;
-//            keeps u and F for the next iteration
+//            keeps u (F stays where it is) for the next iteration
 //   finish   iteration count, convergence flag (max |F| < tol_force)
 #include <algorithm>
 #include <cmath>
@@ -40,8 +40,11 @@ constexpr int kGramBlocks = 512;
 constexpr int kNP = 6;  // partials per block: max|F|, v.F, F.F, s.s, s.y, y.y
 
 // device scalars
-enum { MS_ITER = 0, MS_NP, MS_NEWEST, MS_DONE, MS_MAXF, MS_PROJ, MS_ALPHA, MS_GAMMA, MS_CAND, MS_RED, MS_N = 16 };
+enum { MS_ITER = 0, MS_NP, MS_NEWEST, MS_DONE, MS_MAXF, MS_PROJ, MS_ALPHA, MS_GAMMA, MS_CAND, MS_RED, MS_VC, MS_N = 16 };
 
+// F and Fp change places every iteration, so the previous force needs no copy.
+// Velocity projection keeps no velocity either: v = MS_VC F of the iteration
+// before, so v.F is MS_VC Fp.F.
 struct MinArgs {
     int64_t N;
     int method, retraction, hist;
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(kMinB) void k_min_force(MinArgs a, const double *__
         ff += f2;
         if (a.method == 0) {
             double v[3];
-            ld3(a.V, N, i, v);
+            ld3(a.Fp, N, i, v);
             vf += v[0] * f[0] + v[1] * f[1] + v[2] * f[2];
         } else if (pair) {
             double sv[3], yv[3];
@@ -165,7 +168,7 @@ __global__ __launch_bounds__(kMinB) void k_min_scalars(MinArgs a) {
         for (int k = 1; k < kNP; ++k) v[k] += p[k];
     }
     const double mf = blk_max(v[0], red);
-    const double vf = blk_sum(v[1], red);
+    const double vf = a.st[MS_VC] * blk_sum(v[1], red);
     const double ff = blk_sum(v[2], red);
     const double ss = blk_sum(v[3], red);
     const double sy = blk_sum(v[4], red);
@@ -473,7 +476,6 @@ __global__ __launch_bounds__(kMinB) void k_min_update(MinArgs a, double *__restr
         } else if (a.method == 0) {
             for (int c = 0; c < 3; ++c) {
                 const double v = proj * f[c] + (a.dt / a.mass) * f[c];
-                a.V[c * N + i] = v;
                 u[c] = a.dt * v;
             }
         } else if (a.method == 1) {
@@ -512,11 +514,9 @@ __global__ __launch_bounds__(kMinB) void k_min_update(MinArgs a, double *__restr
             for (int c = 0; c < 3; ++c) o[c] = s[c] + u[c];
             normalise3(o);
         }
-        for (int c = 0; c < 3; ++c) {
-            S[c * N + i] = o[c];
-            a.Up[c * N + i] = u[c];
-            a.Fp[c * N + i] = f[c];
-        }
+        for (int c = 0; c < 3; ++c) S[c * N + i] = o[c];
+        if (a.method == 1 || a.method == 2)
+            for (int c = 0; c < 3; ++c) a.Up[c * N + i] = u[c];
     }
 }
 
@@ -524,6 +524,7 @@ __global__ void k_min_finish(MinArgs a) {
     double *st = a.st;
     if (st[MS_DONE] != 0.0) return;
     st[MS_ITER] += 1.0;
+    st[MS_VC] = st[MS_PROJ] + a.dt / a.mass;
     // candidate slot of the next pair: after the newest (ring of hist + 1)
     st[MS_CAND] = st[MS_NP] == 0.0 ? 0.0 : (double)(((int)st[MS_NEWEST] + 1) % (a.hist + 1));
     if (a.tol > 0.0 && st[MS_MAXF] < a.tol) st[MS_DONE] = 1.0;
@@ -551,6 +552,7 @@ struct spx_min {
     Grid g{};
     Onsite os{};
     int ntile = 0;
+    bool flip = false;  // F and Fp have changed places
 };
 
 namespace {
@@ -563,7 +565,7 @@ void min_free(spx_min *m) {
 hipError_t min_zero_state(spx_min *m, hipStream_t st) {
     const MinArgs &a = m->a;
     const int64_t n3 = 3 * a.N;
-    double *blocks[] = {a.V, a.W, a.Fp, a.Up, a.q};
+    double *blocks[] = {a.V, a.W, a.F, a.Fp, a.Up, a.q};
     for (double *p : blocks) k_min_zero<<<1024, 256, 0, st>>>(p, n3);
     k_min_zero<<<1024, 256, 0, st>>>(a.Sh, n3 * (a.hist + 1));
     k_min_zero<<<1024, 256, 0, st>>>(a.Yh, n3 * (a.hist + 1));
@@ -662,11 +664,13 @@ spx_status spx_min_step(spx_min *m, double *S, int32_t n_iter, void *stream) {
     if (!handle_alive(m)) return set_error(SPX_ERR_BAD_HANDLE, "invalid spx_min handle");
     if (!S || n_iter < 0) return set_error(SPX_ERR_INVALID_ARG, "S is NULL or n_iter < 0");
     hipStream_t st = (hipStream_t)stream;
-    const MinArgs &a = m->a;
-    const unsigned nb = (unsigned)a.nb;
     for (int it = 0; it < n_iter; ++it) {
+        MinArgs a = m->a;
+        if (m->flip) std::swap(a.F, a.Fp);
+        m->flip = !m->flip;
+        const unsigned nb = (unsigned)a.nb;
         if (m->fused) {
-            hipError_t e = zmarch_min_force(m->zp, m->g, m->os, S, a.F, a.V, a.Up, a.Fp, a.Sh, a.Yh, a.st, MS_DONE,
+            hipError_t e = zmarch_min_force(m->zp, m->g, m->os, S, a.F, a.Fp, a.Up, a.Fp, a.Sh, a.Yh, a.st, MS_DONE,
                                             MS_CAND, a.method, a.part, st);
             if (e != hipSuccess) return set_hip_error(e, "spx_min_step: force pass");
             MinArgs af = a;
