@@ -8,21 +8,27 @@
 // built once in FP64 (scaled by mu^2 and by the 1/(Px Py Pz) of the
 // unnormalised inverse).  Per evaluation the three spin components go through
 // a pruned FP32 transform pipeline that never touches the zero padding:
-//   x: R2C (hipFFT, rows of length Px) on the Ly x Lz occupied rows only;
+//   x: R2C of rows of length Px on the Ly x Lz occupied rows only;
 //   y: column FFT of length Py reading the Ly occupied rows (the rest are
 //      zero by construction), on the Lz occupied planes only;
 //   z: column FFT of length Pz reading the Lz occupied planes;
 // then the 3x3 spectral product, and the inverse transforms in reverse order
 // keeping only the outputs inside the lattice (z < Lz, then y < Ly, then the
 // C2R rows and x < Lx).  Linear (aperiodic) convolution = open boundaries.
-// The column FFTs: for P = 512 a register radix-8 kernel (three passes, two
-// LDS exchanges, 8 columns per block); for other P an LDS radix-2 kernel (a
-// block stages P rows x W adjacent columns, bit-reverses on load, runs log2 P
-// in-place butterfly stages).  Both write only the rows that are kept.
+// Padded extents of 64 to 1024 points: register kernels of radix 8 (two to
+// four passes, LDS exchanges between), x rows in pairs as one complex
+// transform, and z transform, product and inverse in one pass.  Others: hipFFT
+// for the x rows and an LDS radix-2 kernel for the columns (a block stages P
+// rows x W adjacent columns, bit-reverses on load, runs log2 P in-place
+// butterfly stages), z, product and inverse z as three passes.  Both write
+// only the rows that are kept.  The register kernels are bound by HBM; at 256
+// points (sc 100^3) the radix-2 ones took 84 - 100 us a column pass, 100 us
+// for the product and 71 us for the x rows with hipFFT.
 #include <hipfft/hipfft.h>
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "spx_ext.hpp"
@@ -38,10 +44,10 @@ struct DipolarPlan {
     float *R = nullptr;    // [3][Lz][Ly][Px] real rows (padded spins in, field rows out)
     float2 *X = nullptr;   // [3][Lz][Ly][H] after the x transform
     float2 *Y = nullptr;   // [3][Lz][Py][H] after the y transform
-    float2 *Z = nullptr;   // [3][Pz][Py][H] full spectrum (Pz != 512; 512 uses the fused z pass)
+    float2 *Z = nullptr;   // [3][Pz][Py][H] full spectrum (not with the fused z pass)
     float *kern = nullptr; // [6][Pz][Py][H] real dipole spectrum xx, xy, xz, yy, yz, zz
-    // Pz = 512: the spectrum in the fused z pass's order instead,
-    // [column group][kz < nkz][6][16 columns] (nkz = 257 with z parity, else 512)
+    // own z transform: the spectrum in the fused z pass's order instead,
+    // [column group][kz < nkz][6][columns] (nkz = Pz / 2 + 1 with z parity, else Pz)
     float *kernb = nullptr;
     int nkz = 0;
     // the third cell vector is along z and the first two have no z part: the
@@ -50,7 +56,7 @@ struct DipolarPlan {
     // kz <= Pz / 2 (half the spectrum traffic)
     bool zsym = false;
     float2 *tw_y = nullptr, *tw_z = nullptr;  // exp(-2 pi i k / P), k < P
-    float2 *tw_x = nullptr;                    // Px = 512: the x rows run in k_xfft512_*
+    float2 *tw_x = nullptr;                    // own x transform (k_xfft_fwd, k_xfft_inv)
     hipfftHandle fwd = 0, inv = 0;
     bool fwd_ok = false, inv_ok = false;
 };
@@ -213,17 +219,34 @@ __global__ __launch_bounds__(kColThreads) void k_colfft(const float2 *__restrict
     }
 }
 
-// ---- 512-point column FFT in registers (512 = 8 x 8 x 8) -----------------
-// 64 threads per column, each holding 8 values; three radix-8 passes in
-// registers with two exchanges through LDS.  With n = 64 a + b and
-// k = c + 8 (g + 8 h), b = 8 e + f:
-//   y_b[c]    = W512^{b c} sum_a x[64 a + b] W8^{a c}
-//   z_cf[g]   = W64^{f g}  sum_e y_{8e+f}[c] W8^{e g}
-//   X[c+8g+64h] =          sum_f z_cf[g] W8^{f h}.
-constexpr int kW512Log = 4;
-constexpr int kW512 = 1 << kW512Log;   // columns per block
-constexpr int kT512 = 64 * kW512;      // threads per block
-constexpr int kPitch = kW512 + 1;      // LDS float2 per position (one pad against bank conflicts)
+// ---- N-point FFTs in registers, N = 64 .. 1024 ----------------------------
+// Stockham's autosort form (T. G. Stockham, 1966): N / 8 threads per column
+// with 8 values each, passes of radix 8 and a last one of radix N / 8^k, the
+// values exchanged through LDS in between.  With Ns the product of the radices
+// done, butterfly j of a pass of radix R takes x[j + r N / R] W^(r (j mod Ns)),
+// W = exp(-2 pi i / (Ns R)), and puts its results at (j div Ns) Ns R + j mod
+// Ns + r Ns.  Thread t has butterflies t + k N / 8, k < 8 / R, so it always
+// reads rows t + m N / 8 (m = k + r 8 / R) and, after the last pass, holds
+// rows t + m N / 8 in natural order: what the inverse starts from.
+constexpr bool fft_own(int P) { return P >= 64 && P <= 1024; }
+// Columns (y, z): a block takes W adjacent columns, consecutive lanes on
+// consecutive columns, and exchanges through LDS rows of W values with block
+// barriers.  W is 16 (128-byte row segments), 8 for 1024 points (threads) and
+// in the fused z pass from 256 points on, so that two blocks share a CU.
+// Rows (x): consecutive lanes on consecutive points, so up to 512 points a
+// pair of rows is part of one wavefront and needs no barrier (1024 points: two
+// wavefronts, barriers).  The same for the columns, staged through LDS to and
+// from their wavefronts, was slower (sc 256^3: y 390 against 335 us, the z pass
+// 1116 against 835), as were persistent z blocks that load ahead (971).  At sc
+// 100^3 (256 points) the passes take 15 + 25 + 89 + 24 + 13 us.
+constexpr int fft_w(int N) { return N <= 512 ? 16 : 8; }
+constexpr int fft_zw(int N) { return N <= 128 ? 16 : 8; }
+constexpr int fft_xw(int N) { return N <= 256 ? 16 : 8; }  // row pairs per block
+// position p of an exchange: one row (value) skipped after every eight, so
+// that the steps of 1 and of 8 between the rows that half a wavefront touches
+// both fall on different banks
+__device__ __forceinline__ int fft_pos(int p) { return p + (p >> 3); }
+constexpr int fft_lds(int N, int W) { return N / 8 * 9 * W; }
 
 template <bool INV>
 __device__ __forceinline__ float2 cmulw(float2 x, float2 w) {
@@ -232,17 +255,24 @@ __device__ __forceinline__ float2 cmulw(float2 x, float2 w) {
     return make_float2(x.x * w.x - x.y * w.y, x.x * w.y + x.y * w.x);
 }
 
-// in-place 8-point DFT, natural order in and out
-template <bool INV>
+// In-place 8-point DFT, natural order in and out.  HIN: v[4..7] are zero on
+// entry (and not read); HOUT: only v[0..3] are wanted.
+template <bool INV, bool HIN = false, bool HOUT = false>
 __device__ __forceinline__ void dft8(float2 v[8]) {
     const float h = 0.70710678118654752f;
     // two 4-point DFTs of the even and odd samples
     float2 E[4], O[4];
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
-        const float2 a0 = v[part], a1 = v[part + 2], a2 = v[part + 4], a3 = v[part + 6];
-        const float2 s02 = make_float2(a0.x + a2.x, a0.y + a2.y), d02 = make_float2(a0.x - a2.x, a0.y - a2.y);
-        const float2 s13 = make_float2(a1.x + a3.x, a1.y + a3.y), d13 = make_float2(a1.x - a3.x, a1.y - a3.y);
+        const float2 a0 = v[part], a1 = v[part + 2];
+        float2 s02 = a0, d02 = a0, s13 = a1, d13 = a1;
+        if constexpr (!HIN) {
+            const float2 a2 = v[part + 4], a3 = v[part + 6];
+            s02 = make_float2(a0.x + a2.x, a0.y + a2.y);
+            d02 = make_float2(a0.x - a2.x, a0.y - a2.y);
+            s13 = make_float2(a1.x + a3.x, a1.y + a3.y);
+            d13 = make_float2(a1.x - a3.x, a1.y - a3.y);
+        }
         // W4 d13: -i d13 forward, +i d13 inverse
         const float2 wd = INV ? make_float2(-d13.y, d13.x) : make_float2(d13.y, -d13.x);
         float2 *T = part ? O : E;
@@ -261,229 +291,239 @@ __device__ __forceinline__ void dft8(float2 v[8]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         v[k] = make_float2(E[k].x + t[k].x, E[k].y + t[k].y);
-        v[k + 4] = make_float2(E[k].x - t[k].x, E[k].y - t[k].y);
+        if constexpr (!HOUT) v[k + 4] = make_float2(E[k].x - t[k].x, E[k].y - t[k].y);
     }
 }
 
-// 512-point FFT of one column held by 64 threads: on entry v[a] = x[64 a + qin]
-// (qin = the column position this thread loaded), on exit v[h] = X[c + 8 g + 64 h]
-// with c = q / 8, g = q % 8.  lds holds 512 x kPitch float2; w = column slot.
-template <bool INV>
-__device__ __forceinline__ void fft512(float2 v[8], float2 *lds, int qin, int q, int w,
-                                       const float2 *__restrict__ tw) {
-    dft8<INV>(v);
-    __syncthreads();  // the previous user of lds has finished reading it
+// radix-R DFTs of the sets {v[k + (8 / R) r], r < R}, k < 8 / R
+// (HOUT: v[4..7] are not wanted; the compiler drops what only they need)
+template <int R, bool INV, bool HOUT>
+__device__ __forceinline__ void dft_sets(float2 v[8]) {
+    if constexpr (R == 8) {
+        dft8<INV, false, HOUT>(v);
+    } else if constexpr (R == 4) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) lds[(c * 64 + qin) * kPitch + w] = c ? cmulw<INV>(v[c], tw[(qin * c) & 511]) : v[c];
-    __syncthreads();
-    const int c2 = q >> 3, f = q & 7;
+        for (int k = 0; k < 2; ++k) {
+            const float2 a0 = v[k], a1 = v[k + 2], a2 = v[k + 4], a3 = v[k + 6];
+            const float2 s02 = make_float2(a0.x + a2.x, a0.y + a2.y), d02 = make_float2(a0.x - a2.x, a0.y - a2.y);
+            const float2 s13 = make_float2(a1.x + a3.x, a1.y + a3.y), d13 = make_float2(a1.x - a3.x, a1.y - a3.y);
+            const float2 wd = INV ? make_float2(-d13.y, d13.x) : make_float2(d13.y, -d13.x);
+            v[k] = make_float2(s02.x + s13.x, s02.y + s13.y);
+            v[k + 2] = make_float2(d02.x + wd.x, d02.y + wd.y);
+            v[k + 4] = make_float2(s02.x - s13.x, s02.y - s13.y);
+            v[k + 6] = make_float2(d02.x - wd.x, d02.y - wd.y);
+        }
+    } else {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = lds[(c2 * 64 + 8 * e + f) * kPitch + w];
-    dft8<INV>(v);
-    __syncthreads();
-#pragma unroll
-    for (int g = 0; g < 8; ++g) lds[(c2 * 64 + 8 * g + f) * kPitch + w] = cmulw<INV>(v[g], tw[(8 * f * g) & 511]);
-    __syncthreads();
-#pragma unroll
-    for (int ff = 0; ff < 8; ++ff) v[ff] = lds[(c2 * 64 + 8 * f + ff) * kPitch + w];
-    dft8<INV>(v);
-}
-
-// The same transform with its two exchanges in two LDS buffers (A, then B):
-// each exchange is write, barrier, read, and a buffer is written again only
-// after the barrier that followed its last read, so two barriers per
-// transform suffice (against four with one buffer).
-template <bool INV>
-__device__ __forceinline__ void fft512_2buf(float2 v[8], float2 *ldsA, float2 *ldsB, int qin, int q, int w,
-                                            const float2 *__restrict__ tw) {
-    dft8<INV>(v);
-#pragma unroll
-    for (int c = 0; c < 8; ++c) ldsA[(c * 64 + qin) * kPitch + w] = c ? cmulw<INV>(v[c], tw[(qin * c) & 511]) : v[c];
-    __syncthreads();
-    const int c2 = q >> 3, f = q & 7;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = ldsA[(c2 * 64 + 8 * e + f) * kPitch + w];
-    dft8<INV>(v);
-#pragma unroll
-    for (int g = 0; g < 8; ++g) ldsB[(c2 * 64 + 8 * g + f) * kPitch + w] = cmulw<INV>(v[g], tw[(8 * f * g) & 511]);
-    __syncthreads();
-#pragma unroll
-    for (int ff = 0; ff < 8; ++ff) v[ff] = ldsB[(c2 * 64 + 8 * f + ff) * kPitch + w];
-    dft8<INV>(v);
-}
-
-template <bool INV>
-__global__ __launch_bounds__(kT512) void k_colfft512(const float2 *__restrict__ in, float2 *__restrict__ out,
-                                                     int nin, int nout, int64_t J, int64_t in_bs, int64_t out_bs,
-                                                     const float2 *__restrict__ tw512) {
-    __shared__ float2 lds[512 * kPitch];
-    const int t = threadIdx.x;
-    const int w = t & (kW512 - 1), q = t >> kW512Log;  // column in the tile, thread of the column
-    // Rows of J complex values are not 128-byte multiples, so a block's row
-    // segments straddle lines it shares with the next column group: blocks
-    // are renumbered so that each XCD takes one contiguous range of them
-    // (workgroups are dealt to the 8 XCDs in turn) and shared lines meet in
-    // one L2.
-    int64_t bx, b;
-    {
-        const int64_t T = (int64_t)gridDim.x * gridDim.y, id = blockIdx.x + (int64_t)gridDim.x * blockIdx.y;
-        const int64_t qn = T / 8, rn = T % 8, k = id % 8;
-        const int64_t v = k * qn + (k < rn ? k : rn) + id / 8;
-        bx = v % gridDim.x;
-        b = v / gridDim.x;
+        for (int k = 0; k < 4; ++k) {
+            const float2 a = v[k], b = v[k + 4];
+            v[k] = make_float2(a.x + b.x, a.y + b.y);
+            v[k + 4] = make_float2(a.x - b.x, a.y - b.y);
+        }
     }
-    const int64_t j = bx * kW512 + w;
+}
+
+// How an FFT's threads wait for each other's LDS accesses.
+enum { SYNC_WAVE = 0, SYNC_BLOCK = 1 };
+template <int SYNC>
+__device__ __forceinline__ void fft_sync() {
+    if constexpr (SYNC == SYNC_WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+// One exchange and the pass after it: the results of the pass of radix RP
+// (product NSP before it) are put in order in LDS (buf[fft_pos(p) W], buf at
+// the column's slot) and thread t's rows of the next pass read back,
+// multiplied by their twiddles and transformed.  TWO: consecutive exchanges
+// take two buffers in turn, and one barrier each suffices, since a buffer is
+// written again only after the barrier that followed its last read; with one
+// buffer a second barrier precedes the write.
+template <int N, int NSP, int RP, bool INV, int SYNC, bool TWO, int W>
+__device__ __forceinline__ void fft_pass(float2 v[8], float2 *buf, int t, const float2 *__restrict__ tw) {
+    constexpr int Ns = NSP * RP, R = N / Ns < 8 ? N / Ns : 8;
+    static_assert(RP == 8, "only the last pass has a smaller radix");
+    if (!TWO) fft_sync<SYNC>();
+    const int o = fft_pos((t / NSP) * Ns + t % NSP);
+#pragma unroll
+    for (int r = 0; r < RP; ++r) buf[(o + r * NSP / 8 * 9 + (NSP < 8 ? r : 0)) * W] = v[r];  // fft_pos of + r NSP
+    fft_sync<SYNC>();
+#pragma unroll
+    for (int m = 0; m < 8; ++m) v[m] = buf[(fft_pos(t) + m * (N / 64 * 9)) * W];
+#pragma unroll
+    for (int k = 0; k < 8 / R; ++k) {
+        const int a = (t + k * (N / 8)) % Ns * (N / (Ns * R));
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[k + (8 / R) * r] = cmulw<INV>(v[k + (8 / R) * r], tw[a * r]);
+    }
+    dft_sets<R, INV, INV && Ns * R == N>(v);
+}
+
+// N-point FFT of a column: v[m] = row t + (N / 8) m on entry and exit.  A
+// padded extent is at least twice the lattice's, so the forward transform's
+// rows from N / 2 on (v[4..7]) are zero and not read, and the inverse leaves
+// v[4..7] undefined: those rows are cropped.  X: exchanges done so far in the
+// two buffers A and B (which one comes next).
+template <int N, bool INV, int SYNC, bool TWO, int W, int X = 0>
+__device__ __forceinline__ void fft_col(float2 v[8], float2 *A, float2 *B, int t, const float2 *__restrict__ tw) {
+    float2 *const b0 = (X & 1) ? B : A, *const b1 = (X & 1) ? A : B;
+    dft8<INV, !INV>(v);
+    fft_pass<N, 1, 8, INV, SYNC, TWO, W>(v, b0, t, tw);
+    if constexpr (N > 64) fft_pass<N, 8, 8, INV, SYNC, TWO, W>(v, b1, t, tw);
+    if constexpr (N > 512) fft_pass<N, 64, 8, INV, SYNC, TWO, W>(v, b0, t, tw);
+}
+constexpr int fft_exchanges(int N) { return N > 512 ? 3 : N > 64 ? 2 : 1; }
+
+// Blocks renumbered so that each XCD takes one contiguous range of them
+// (workgroups are dealt to the 8 XCDs in turn): lines that straddle
+// neighbouring column groups then meet in one L2.
+__device__ __forceinline__ int64_t xcd_range(int64_t id, int64_t T) {
+    const int64_t q = T / 8, r = T % 8, k = id % 8;
+    return k * q + (k < r ? k : r) + id / 8;
+}
+
+template <int N, bool INV>
+__global__ __launch_bounds__(N / 8 * fft_w(N)) void k_colfft_reg(const float2 *__restrict__ in,
+                                                                 float2 *__restrict__ out, int nin, int nout,
+                                                                 int64_t J, int64_t in_bs, int64_t out_bs,
+                                                                 const float2 *__restrict__ tw) {
+    constexpr int W = fft_w(N), T = N / 8;
+    __shared__ float2 lds[fft_lds(N, W)];
+    const int w = threadIdx.x % W, t = threadIdx.x / W;  // column in the tile, thread of the column
+    const int64_t vb = xcd_range(blockIdx.x + (int64_t)gridDim.x * blockIdx.y, (int64_t)gridDim.x * gridDim.y);
+    const int64_t bx = vb % gridDim.x, b = vb / gridDim.x;
+    const int64_t j = bx * W + w;
     const bool col = j < J;
     const float2 *src = in + b * in_bs + j;
     float2 *dst = out + b * out_bs + j;
     float2 v[8];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        const int r = 64 * a + q;
-        v[a] = (col && r < nin) ? src[(int64_t)r * J] : make_float2(0.0f, 0.0f);
+    for (int m = 0; m < (INV ? 8 : 4); ++m) {
+        const int r = t + m * T;
+        v[m] = (col && r < nin) ? src[(int64_t)r * J] : make_float2(0.0f, 0.0f);
     }
-    fft512<INV>(v, lds, q, q, w, tw512);
+    fft_col<N, INV, SYNC_BLOCK, false, W>(v, lds + w, lds + w, t, tw);
     if (col) {
-        const int base = (q >> 3) + 8 * (q & 7);
 #pragma unroll
-        for (int h = 0; h < 8; ++h) {
-            const int r = base + 64 * h;
-            if (r < nout) dst[(int64_t)r * J] = v[h];
+        for (int m = 0; m < (INV ? 4 : 8); ++m) {
+            const int r = t + m * T;
+            if (r < nout) dst[(int64_t)r * J] = v[m];
         }
     }
 }
 
-// x rows for Px = 512: two real rows (A, B) of one pair transformed as one
-// complex 512-point FFT z = a + i b, whose spectrum Z gives both halves,
-// A[k] = (Z[k] + conj Z[512 - k]) / 2 and B[k] = (Z[k] - conj Z[512 - k]) / 2i
-// for k <= 256.  Global reads and writes run along the rows (consecutive
-// lanes, consecutive x or k: thread t serves pair t / 64, position t % 64);
-// the values pass to and from fft512's column-slot layout through LDS.
-// Row r = (c, line) of the pair index holds spins S[r Lx + x] (x < Lx, zero
-// to 512) and spectrum X[r H + k] (H = 257).
-__global__ __launch_bounds__(kT512) void k_xfft512_fwd(const double *__restrict__ S, float2 *__restrict__ X, int Lx,
-                                                       int64_t nrows, const float2 *__restrict__ tw512) {
-    __shared__ float2 lds[512 * kPitch];
-    const int t = threadIdx.x;
-    const int64_t pair0 = (int64_t)blockIdx.x * kW512;
-    {
-        const int wp = t >> 6, n0 = t & 63;
-        const int64_t ra = 2 * (pair0 + wp), rb = ra + 1;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const int n = 64 * a + n0;
-            const float re = (n < Lx && ra < nrows) ? (float)S[ra * Lx + n] : 0.0f;
-            const float im = (n < Lx && rb < nrows) ? (float)S[rb * Lx + n] : 0.0f;
-            lds[n * kPitch + wp] = make_float2(re, im);
-        }
-    }
-    __syncthreads();
-    const int w = t & (kW512 - 1), q = t >> kW512Log;
+// x rows: two real rows (A, B) of one pair transformed as one complex N-point
+// FFT z = a + i b, whose spectrum Z gives both halves, A[k] = (Z[k] + conj
+// Z[N - k]) / 2 and B[k] = (Z[k] - conj Z[N - k]) / 2i for k <= N / 2.  A pair's
+// threads are consecutive lanes and its rows contiguous, so they load and
+// store directly.  Row r = (c, line) of the pair index holds spins S[r Lx + x]
+// (x < Lx, zero to N) and spectrum X[r H + k] (H = N / 2 + 1).
+template <int N>
+__global__ __launch_bounds__(N / 8 * fft_xw(N)) void k_xfft_fwd(const double *__restrict__ S, float2 *__restrict__ X,
+                                                             int Lx, int64_t nrows, const float2 *__restrict__ tw) {
+    constexpr int W = fft_xw(N), T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
+    constexpr int SYNC = N <= 512 ? SYNC_WAVE : SYNC_BLOCK;
+    __shared__ float2 lds[W * RUN];
+    const int t = threadIdx.x % T;
+    float2 *const run = lds + threadIdx.x / T * RUN;
+    const int64_t ra = 2 * ((int64_t)blockIdx.x * W + threadIdx.x / T), rb = ra + 1;
     float2 v[8];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) v[a] = lds[(64 * a + q) * kPitch + w];
-    fft512<false>(v, lds, q, q, w, tw512);
-    __syncthreads();
-    const int qq = (q >> 3) + 8 * (q & 7);
+    for (int m = 0; m < 4; ++m) {
+        const int n = t + m * T;
+        v[m] = make_float2((n < Lx && ra < nrows) ? (float)S[ra * Lx + n] : 0.0f,
+                           (n < Lx && rb < nrows) ? (float)S[rb * Lx + n] : 0.0f);
+    }
+    fft_col<N, false, SYNC, false, 1>(v, run, run, t, tw);
+    fft_sync<SYNC>();
 #pragma unroll
-    for (int h = 0; h < 8; ++h) lds[(qq + 64 * h) * kPitch + w] = v[h];
-    __syncthreads();
-    {
-        const int wp = t >> 6, k0 = t & 63;
-        const int64_t ra = 2 * (pair0 + wp), rb = ra + 1;
+    for (int m = 0; m < 8; ++m) run[t + m * T] = v[m];
+    fft_sync<SYNC>();
 #pragma unroll
-        for (int m = 0; m < 5; ++m) {
-            const int k = k0 + 64 * m;
-            if (k > 256) break;
-            const float2 zk = lds[k * kPitch + wp], zm = lds[((512 - k) & 511) * kPitch + wp];
-            if (ra < nrows) X[ra * 257 + k] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
-            if (rb < nrows) X[rb * 257 + k] = make_float2(0.5f * (zk.y + zm.y), 0.5f * (zm.x - zk.x));
-        }
+    for (int m = 0; m < 5; ++m) {
+        const int k = t + T * m;
+        if (k > N / 2) break;
+        const float2 zk = m < 4 ? v[m] : run[k], zm = run[(N - k) & (N - 1)];
+        if (ra < nrows) X[ra * H + k] = make_float2(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y));
+        if (rb < nrows) X[rb * H + k] = make_float2(0.5f * (zk.y + zm.y), 0.5f * (zm.x - zk.x));
     }
 }
 
-// The inverse: Z[n] = A[n] + i B[n] over all 512 bins from the stored half
-// (A[512 - k] = conj A[k]; the imaginary parts of bins 0 and 256 dropped, as
+// The inverse: Z[n] = A[n] + i B[n] over all N bins from the stored half
+// (A[N - k] = conj A[k]; the imaginary parts of bins 0 and N / 2 dropped, as
 // for a real inverse transform), one unnormalised inverse FFT, and rows
 // x < Lx of z = a + i b written to the field.
-__global__ __launch_bounds__(kT512) void k_xfft512_inv(const float2 *__restrict__ X, float *__restrict__ b, int Lx,
-                                                       int64_t nrows, const float2 *__restrict__ tw512) {
-    __shared__ float2 lds[512 * kPitch];
-    const int t = threadIdx.x;
-    const int64_t pair0 = (int64_t)blockIdx.x * kW512;
-    {
-        const int wp = t >> 6, n0 = t & 63;
-        const int64_t ra = 2 * (pair0 + wp), rb = ra + 1;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const int n = 64 * a + n0;
-            const int k = n <= 256 ? n : 512 - n;
-            float2 A = ra < nrows ? X[ra * 257 + k] : make_float2(0.0f, 0.0f);
-            float2 B = rb < nrows ? X[rb * 257 + k] : make_float2(0.0f, 0.0f);
-            if (k == 0 || k == 256) {
-                A.y = 0.0f;
-                B.y = 0.0f;
-            } else if (n > 256) {
-                A.y = -A.y;
-                B.y = -B.y;
-            }
-            lds[n * kPitch + wp] = make_float2(A.x - B.y, A.y + B.x);
-        }
-    }
-    __syncthreads();
-    const int w = t & (kW512 - 1), q = t >> kW512Log;
+template <int N>
+__global__ __launch_bounds__(N / 8 * fft_xw(N)) void k_xfft_inv(const float2 *__restrict__ X, float *__restrict__ b,
+                                                             int Lx, int64_t nrows, const float2 *__restrict__ tw) {
+    constexpr int W = fft_xw(N), T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
+    constexpr int SYNC = N <= 512 ? SYNC_WAVE : SYNC_BLOCK;
+    __shared__ float2 lds[W * RUN];
+    const int t = threadIdx.x % T;
+    const int64_t ra = 2 * ((int64_t)blockIdx.x * W + threadIdx.x / T), rb = ra + 1;
     float2 v[8];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) v[a] = lds[(64 * a + q) * kPitch + w];
-    fft512<true>(v, lds, q, q, w, tw512);
-    __syncthreads();
-    const int qq = (q >> 3) + 8 * (q & 7);
-#pragma unroll
-    for (int h = 0; h < 8; ++h) lds[(qq + 64 * h) * kPitch + w] = v[h];
-    __syncthreads();
-    {
-        const int wp = t >> 6, n0 = t & 63;
-        const int64_t ra = 2 * (pair0 + wp), rb = ra + 1;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const int n = 64 * a + n0;
-            if (n >= Lx) break;
-            const float2 z = lds[n * kPitch + wp];
-            if (ra < nrows) b[ra * Lx + n] = z.x;
-            if (rb < nrows) b[rb * Lx + n] = z.y;
+    for (int m = 0; m < 8; ++m) {
+        const int n = t + m * T;
+        const int k = n <= N / 2 ? n : N - n;
+        float2 A = ra < nrows ? X[ra * H + k] : make_float2(0.0f, 0.0f);
+        float2 B = rb < nrows ? X[rb * H + k] : make_float2(0.0f, 0.0f);
+        if (k == 0 || k == N / 2) {
+            A.y = 0.0f;
+            B.y = 0.0f;
+        } else if (n > N / 2) {
+            A.y = -A.y;
+            B.y = -B.y;
         }
+        v[m] = make_float2(A.x - B.y, A.y + B.x);
+    }
+    float2 *const run = lds + threadIdx.x / T * RUN;
+    fft_col<N, true, SYNC, false, 1>(v, run, run, t, tw);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int n = t + m * T;
+        if (n >= Lx) break;
+        if (ra < nrows) b[ra * Lx + n] = v[m].x;
+        if (rb < nrows) b[rb * Lx + n] = v[m].y;
     }
 }
 
-// The dipole spectrum reordered for the fused z pass: block g of 16 columns
-// reads kernb[g][kz][c][0..15] for its kz, one contiguous run per kz.
+// The dipole spectrum reordered for the fused z pass: block g of W columns
+// reads kernb[g][kz][c][0..W-1] for its kz, one contiguous run per kz.
 __global__ void k_kern_block(const float *__restrict__ kern, float *__restrict__ kernb, int64_t J, int64_t n_cplx,
-                             int nkz, int64_t total) {
+                             int nkz, int W, int64_t total) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= total) return;
-    const int w = (int)(q % kW512);
-    int64_t r = q / kW512;
+    const int w = (int)(q % W);
+    int64_t r = q / W;
     const int c = (int)(r % 6);
     r /= 6;
     const int kz = (int)(r % nkz);
     const int64_t g = r / nkz;
-    const int64_t j = g * kW512 + w;
+    const int64_t j = g * W + w;
     kernb[q] = j < J ? kern[c * n_cplx + (int64_t)kz * J + j] : 0.0f;
 }
 
-// z transform, spectral product and inverse z transform fused for Pz = 512:
-// each block takes 8 (y, kx) columns of the three components (rows z < Lz of
-// Y, zero above), transforms them forward, multiplies by the dipole spectrum
-// at its 512 kz and transforms back, writing rows z < Lz in place.  The
-// forward result sits in the thread that needs it for the inverse's first
-// pass (row c + 8 g + 64 h = 64 h + qin with qin = c + 8 g).
-__global__ __launch_bounds__(kT512) void k_zconv512(float2 *__restrict__ Y, const float *__restrict__ kernb, int Lz,
-                                                    int64_t J, int nkz, const float2 *__restrict__ tw512,
-                                                    int zsym) {
-    __shared__ float2 ldsA[512 * kPitch], ldsB[512 * kPitch];
-    const int t = threadIdx.x;
-    const int w = t & (kW512 - 1), q = t >> kW512Log;
-    const int64_t j = (int64_t)blockIdx.x * kW512 + w;
+// z transform, spectral product and inverse z transform fused: each block
+// takes W (y, kx) columns of the three components (rows z < Lz of Y, zero
+// above), transforms them forward, multiplies by the dipole spectrum at its N
+// kz and transforms back, writing rows z < Lz in place.  HBM (2.42 GB at sc
+// 256^3, 510 us at the rate of a copy), the vector ALU (390 us) and LDS (200
+// us) are of a size and overlap in part.
+template <int N>
+__global__ __launch_bounds__(N / 8 * fft_zw(N)) void k_zconv(float2 *__restrict__ Y, const float *__restrict__ kernb,
+                                                             int Lz, int64_t J, int nkz,
+                                                             const float2 *__restrict__ tw, int zsym) {
+    constexpr int W = fft_zw(N), T = N / 8, E = fft_exchanges(N);
+    constexpr bool TWO = N <= 512;  // two buffers fit the CU's LDS
+    __shared__ float2 lds[(TWO ? 2 : 1) * fft_lds(N, W)];
+    const int w = threadIdx.x % W, t = threadIdx.x / W;
+    float2 *const A = lds + w, *const B = A + (TWO ? fft_lds(N, W) : 0);
+    const int64_t blk = xcd_range(blockIdx.x, gridDim.x);
+    const int64_t j = blk * W + w;
     const bool col = j < J;
     const int64_t cs = (int64_t)Lz * J;
     // all three components' loads in flight before the first transform
@@ -491,40 +531,63 @@ __global__ __launch_bounds__(kT512) void k_zconv512(float2 *__restrict__ Y, cons
 #pragma unroll
     for (int c = 0; c < 3; ++c)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const int r = 64 * a + q;
-            v[c][a] = (col && r < Lz) ? Y[c * cs + (int64_t)r * J + j] : make_float2(0.0f, 0.0f);
+        for (int m = 0; m < 4; ++m) {
+            const int r = t + m * T;
+            v[c][m] = (col && r < Lz) ? Y[c * cs + (int64_t)r * J + j] : make_float2(0.0f, 0.0f);
         }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) fft512_2buf<false>(v[c], ldsA, ldsB, q, q, w, tw512);
-    const int qq = (q >> 3) + 8 * (q & 7);
+    // the thread's index hidden from each transform: their twiddles and
+    // addresses are equal, and held over all six they spill
+    auto hid = [](int x) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(x));
+        return x;
+    };
+    fft_col<N, false, SYNC_BLOCK, TWO, W, 0>(v[0], A, B, hid(t), tw);
+    fft_col<N, false, SYNC_BLOCK, TWO, W, E>(v[1], A, B, hid(t), tw);
+    fft_col<N, false, SYNC_BLOCK, TWO, W, 2 * E>(v[2], A, B, hid(t), tw);
     if (col) {
 #pragma unroll
-        for (int h = 0; h < 8; ++h) {
-            // kz and 512 - kz read the same stored entries (sign flip for xz, yz)
-            const int kz = qq + 64 * h;
-            const bool mirror = zsym && kz > 256;
+        for (int m = 0; m < 8; ++m) {
+            // kz and N - kz read the same stored entries (sign flip for xz, yz)
+            const int kz = t + m * T;
+            const bool mirror = zsym && kz > N / 2;
             const float sgn = mirror ? -1.0f : 1.0f;
-            const float *kb = kernb + (((int64_t)blockIdx.x * nkz + (mirror ? 512 - kz : kz)) * 6) * kW512 + w;
-            const float txx = kb[0], txy = kb[kW512], txz = sgn * kb[2 * kW512];
-            const float tyy = kb[3 * kW512], tyz = sgn * kb[4 * kW512], tzz = kb[5 * kW512];
-            const float2 sx = v[0][h], sy = v[1][h], sz = v[2][h];
-            v[0][h] = make_float2(txx * sx.x + txy * sy.x + txz * sz.x, txx * sx.y + txy * sy.y + txz * sz.y);
-            v[1][h] = make_float2(txy * sx.x + tyy * sy.x + tyz * sz.x, txy * sx.y + tyy * sy.y + tyz * sz.y);
-            v[2][h] = make_float2(txz * sx.x + tyz * sy.x + tzz * sz.x, txz * sx.y + tyz * sy.y + tzz * sz.y);
+            const float *kb = kernb + ((blk * nkz + (mirror ? N - kz : kz)) * 6) * W + w;
+            const float txx = kb[0], txy = kb[W], txz = sgn * kb[2 * W];
+            const float tyy = kb[3 * W], tyz = sgn * kb[4 * W], tzz = kb[5 * W];
+            const float2 sx = v[0][m], sy = v[1][m], sz = v[2][m];
+            v[0][m] = make_float2(txx * sx.x + txy * sy.x + txz * sz.x, txx * sx.y + txy * sy.y + txz * sz.y);
+            v[1][m] = make_float2(txy * sx.x + tyy * sy.x + tyz * sz.x, txy * sx.y + tyy * sy.y + tyz * sz.y);
+            v[2][m] = make_float2(txz * sx.x + tyz * sy.x + tzz * sz.x, txz * sx.y + tyz * sy.y + tzz * sz.y);
         }
     }
+    auto store = [&](int c) __attribute__((always_inline)) {
+        if (!col) return;
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        fft512_2buf<true>(v[c], ldsA, ldsB, qq, q, w, tw512);
-        if (col) {
-#pragma unroll
-            for (int h = 0; h < 8; ++h) {
-                const int r = qq + 64 * h;
-                if (r < Lz) Y[c * cs + (int64_t)r * J + j] = v[c][h];
-            }
+        for (int m = 0; m < 4; ++m) {
+            const int r = t + m * T;
+            if (r < Lz) Y[c * cs + (int64_t)r * J + j] = v[c][m];
         }
+    };
+    fft_col<N, true, SYNC_BLOCK, TWO, W, 3 * E>(v[0], A, B, hid(t), tw);
+    store(0);
+    fft_col<N, true, SYNC_BLOCK, TWO, W, 4 * E>(v[1], A, B, hid(t), tw);
+    store(1);
+    fft_col<N, true, SYNC_BLOCK, TWO, W, 5 * E>(v[2], A, B, hid(t), tw);
+    store(2);
+}
+
+// f(std::integral_constant<int, P>) for a padded extent with own transforms
+template <typename F>
+hipError_t with_points(int P, F &&f) {
+    switch (P) {
+    case 64: f(std::integral_constant<int, 64>{}); break;
+    case 128: f(std::integral_constant<int, 128>{}); break;
+    case 256: f(std::integral_constant<int, 256>{}); break;
+    case 512: f(std::integral_constant<int, 512>{}); break;
+    case 1024: f(std::integral_constant<int, 1024>{}); break;
+    default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
 }
 
 unsigned nblocks(int64_t n) { return (unsigned)((n + kB - 1) / kB); }
@@ -536,11 +599,12 @@ spx_status fft_fail(hipfftResult r, const char *where) {
 template <bool INV>
 hipError_t colfft(const float2 *in, float2 *out, int P, int nin, int nout, int64_t J, int64_t nbatch, int64_t in_bs,
                   int64_t out_bs, const float2 *tw, hipStream_t st) {
-    if (P == 512) {
-        dim3 grid((unsigned)((J + kW512 - 1) / kW512), (unsigned)nbatch);
-        k_colfft512<INV><<<grid, kT512, 0, st>>>(in, out, nin, nout, J, in_bs, out_bs, tw);
-        return hipGetLastError();
-    }
+    if (fft_own(P))
+        return with_points(P, [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            dim3 grid((unsigned)((J + fft_w(N) - 1) / fft_w(N)), (unsigned)nbatch);
+            k_colfft_reg<N, INV><<<grid, N / 8 * fft_w(N), 0, st>>>(in, out, nin, nout, J, in_bs, out_bs, tw);
+        });
     const int W = col_width(P);  // P >= 2 (padded extents are at least 2)
     const size_t smem = ((size_t)P * W + P / 2) * sizeof(float2);
     dim3 grid((unsigned)((J + W - 1) / W), (unsigned)nbatch);
@@ -585,11 +649,11 @@ spx_status create_dipolar(const int32_t dims[3], const double cell[9], double mu
         return SPX_OK;
     };
     spx_status s;
-    if ((Px != 512 && (s = alloc((void **)&p->R, sizeof(float) * 3 * rows * Px, "dipolar rows")) != SPX_OK) ||
-        (Px == 512 && (s = alloc((void **)&p->tw_x, sizeof(float2) * 512, "dipolar twiddles")) != SPX_OK) ||
+    if ((!fft_own(Px) && (s = alloc((void **)&p->R, sizeof(float) * 3 * rows * Px, "dipolar rows")) != SPX_OK) ||
+        (fft_own(Px) && (s = alloc((void **)&p->tw_x, sizeof(float2) * Px, "dipolar twiddles")) != SPX_OK) ||
         (s = alloc((void **)&p->X, sizeof(float2) * 3 * rows * p->H, "dipolar x spectra")) != SPX_OK ||
         (s = alloc((void **)&p->Y, sizeof(float2) * 3 * (int64_t)Lz * Py * p->H, "dipolar xy spectra")) != SPX_OK ||
-        (Pz != 512 && (s = alloc((void **)&p->Z, sizeof(float2) * 3 * p->n_cplx, "dipolar spectra")) != SPX_OK) ||
+        (!fft_own(Pz) && (s = alloc((void **)&p->Z, sizeof(float2) * 3 * p->n_cplx, "dipolar spectra")) != SPX_OK) ||
         (s = alloc((void **)&p->kern, sizeof(float) * 6 * p->n_cplx, "dipole spectrum")) != SPX_OK ||
         (s = alloc((void **)&p->tw_y, sizeof(float2) * Py, "dipolar twiddles")) != SPX_OK ||
         (s = alloc((void **)&p->tw_z, sizeof(float2) * Pz, "dipolar twiddles")) != SPX_OK) {
@@ -605,10 +669,10 @@ spx_status create_dipolar(const int32_t dims[3], const double cell[9], double mu
     hipError_t e = hipMemcpyAsync(p->tw_y, ty.data(), sizeof(float2) * ty.size(), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(p->tw_z, tz.data(), sizeof(float2) * tz.size(), hipMemcpyHostToDevice, st);
-    std::vector<float2> tx(Px == 512 ? 512 : 0);
+    std::vector<float2> tx(fft_own(Px) ? Px : 0);
     for (size_t k = 0; k < tx.size(); ++k)
-        tx[k] = make_float2((float)std::cos(2.0 * M_PI * k / 512), (float)(-std::sin(2.0 * M_PI * k / 512)));
-    if (e == hipSuccess && Px == 512)
+        tx[k] = make_float2((float)std::cos(2.0 * M_PI * k / Px), (float)(-std::sin(2.0 * M_PI * k / Px)));
+    if (e == hipSuccess && !tx.empty())
         e = hipMemcpyAsync(p->tw_x, tx.data(), sizeof(float2) * tx.size(), hipMemcpyHostToDevice, st);
     // kernel spectrum, one tensor component at a time in FP64
     const int64_t n_real = (int64_t)Px * Py * Pz;
@@ -655,17 +719,18 @@ spx_status create_dipolar(const int32_t dims[3], const double cell[9], double mu
         destroy_dipolar(p);
         return s;
     }
-    if (Pz == 512) {
+    if (fft_own(Pz)) {
         // the fused z pass's order; the [6][Pz][Py][H] spectrum is then no
         // longer needed
-        const int64_t plane = (int64_t)Py * p->H, ngroup = (plane + kW512 - 1) / kW512;
-        p->nkz = p->zsym ? 257 : 512;
-        const int64_t total = ngroup * p->nkz * 6 * kW512;
+        const int W = fft_zw(Pz);
+        const int64_t plane = (int64_t)Py * p->H, ngroup = (plane + W - 1) / W;
+        p->nkz = p->zsym ? Pz / 2 + 1 : Pz;
+        const int64_t total = ngroup * p->nkz * 6 * W;
         if ((s = alloc((void **)&p->kernb, sizeof(float) * total, "dipole spectrum (z pass order)")) != SPX_OK) {
             destroy_dipolar(p);
             return s;
         }
-        k_kern_block<<<nblocks(total), kB, 0, st>>>(p->kern, p->kernb, plane, p->n_cplx, p->nkz, total);
+        k_kern_block<<<nblocks(total), kB, 0, st>>>(p->kern, p->kernb, plane, p->n_cplx, p->nkz, W, total);
         e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
@@ -676,7 +741,7 @@ spx_status create_dipolar(const int32_t dims[3], const double cell[9], double mu
         p->kern = nullptr;
         *ws_bytes -= (int64_t)(sizeof(float) * 6 * p->n_cplx);
     }
-    if (Px == 512) {  // the x rows run in k_xfft512_fwd / k_xfft512_inv
+    if (fft_own(Px)) {  // the x rows run in k_xfft_fwd / k_xfft_inv
         *out = p;
         return SPX_OK;
     }
@@ -704,12 +769,14 @@ spx_status eval_dipolar(DipolarPlan *p, const double *S, float *bdip, hipStream_
     if (!p) return set_error(SPX_ERR_INVALID_ARG, "dipolar path not set up");
     const int Lx = p->L[0], Ly = p->L[1], Lz = p->L[2], Px = p->P[0], Py = p->P[1], Pz = p->P[2], H = p->H;
     const int64_t rows = (int64_t)Ly * Lz;
-    // x rows: pairs of rows, 16 pairs per block
-    const unsigned xgrid = (unsigned)(((3 * rows + 1) / 2 + kW512 - 1) / kW512);
     hipError_t e;
-    if (Px == 512) {
-        k_xfft512_fwd<<<xgrid, kT512, 0, st>>>(S, p->X, Lx, 3 * rows, p->tw_x);
-        e = hipGetLastError();
+    // x rows in pairs, one pair per column slot
+    auto xgrid = [&](int W) { return (unsigned)(((3 * rows + 1) / 2 + W - 1) / W); };
+    if (fft_own(Px)) {
+        e = with_points(Px, [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            k_xfft_fwd<N><<<xgrid(fft_xw(N)), N / 8 * fft_xw(N), 0, st>>>(S, p->X, Lx, 3 * rows, p->tw_x);
+        });
         if (e != hipSuccess) return set_hip_error(e, "dipolar x rows");
     } else {
         k_pad_rows<<<(unsigned)(3 * rows), kB, 0, st>>>(S, Lx, Px, rows, p->N, p->R);
@@ -722,13 +789,14 @@ spx_status eval_dipolar(DipolarPlan *p, const double *S, float *bdip, hipStream_
     const int64_t plane = (int64_t)Py * H;
     // y: X [3 Lz][Ly rows][H] -> Y [3 Lz][Py][H]
     e = colfft<false>(p->X, p->Y, Py, Ly, Py, H, 3 * (int64_t)Lz, (int64_t)Ly * H, plane, p->tw_y, st);
-    if (Pz == 512) {
+    if (fft_own(Pz)) {
         // z transform, product and inverse z transform in one pass over Y
-        if (e == hipSuccess) {
-            k_zconv512<<<(unsigned)((plane + kW512 - 1) / kW512), kT512, 0, st>>>(p->Y, p->kernb, Lz, plane, p->nkz,
-                                                                                p->tw_z, p->zsym ? 1 : 0);
-            e = hipGetLastError();
-        }
+        if (e == hipSuccess)
+            e = with_points(Pz, [&](auto n) {
+                constexpr int N = decltype(n)::value;
+                k_zconv<N><<<(unsigned)((plane + fft_zw(N) - 1) / fft_zw(N)), N / 8 * fft_zw(N), 0, st>>>(
+                    p->Y, p->kernb, Lz, plane, p->nkz, p->tw_z, p->zsym ? 1 : 0);
+            });
     } else {
         // z: Y [3][Lz planes][Py H] -> Z [3][Pz][Py H]
         if (e == hipSuccess)
@@ -745,9 +813,11 @@ spx_status eval_dipolar(DipolarPlan *p, const double *S, float *bdip, hipStream_
     if (e == hipSuccess)
         e = colfft<true>(p->Y, p->X, Py, Py, Ly, H, 3 * (int64_t)Lz, plane, (int64_t)Ly * H, p->tw_y, st);
     if (e != hipSuccess) return set_hip_error(e, "dipolar column transforms");
-    if (Px == 512) {
-        k_xfft512_inv<<<xgrid, kT512, 0, st>>>(p->X, bdip, Lx, 3 * rows, p->tw_x);
-        e = hipGetLastError();
+    if (fft_own(Px)) {
+        e = with_points(Px, [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            k_xfft_inv<N><<<xgrid(fft_xw(N)), N / 8 * fft_xw(N), 0, st>>>(p->X, bdip, Lx, 3 * rows, p->tw_x);
+        });
         if (e != hipSuccess) return set_hip_error(e, "dipolar x rows");
         return SPX_OK;
     }

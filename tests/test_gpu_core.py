@@ -494,3 +494,22 @@ def test_default_chunk_equals_a_given_one(L, shells, prec):
     assert torch.equal(out[0][0], out[1][0])
     assert torch.equal(out[0][1], out[1][1])
     assert float((out[0][2] - out[1][2]).abs().max()) <= 1e-13 * float(out[0][2].abs().max()) * max(1.0, w.N ** 0.5)
+
+
+@pytest.mark.parametrize("L", [(33, 9, 5), (5, 33, 9), (9, 5, 33), (65, 64, 17), (31, 129, 100), (129, 32, 65),
+                               (300, 18, 7), (7, 300, 18), (18, 7, 300), (600, 3, 2), (2, 3, 600), (1, 40, 130)],
+                         ids=lambda L: "x".join(map(str, L)))
+@pytest.mark.parametrize("cell", [((0.4, 0.0, 0.0), (0.0, 0.4, 0.0), (0.0, 0.0, 0.5)),
+                                  ((0.4, 0.0, 0.0), (0.1, 0.4, 0.0), (0.05, 0.08, 0.4))],
+                         ids=["orthorhombic", "triclinic"])
+def test_dipolar_field_at_every_padded_extent(L, cell):
+    # 64, 128, 256, 512 and 1024 points (own register transforms) and shorter
+    # and longer ones (hipFFT x rows, LDS columns, z in three passes) on each
+    # axis, column groups and row pairs cut short, against the FP64 FFT of the
+    # same convolution (FP32 transforms: 1e-5 of the largest field)
+    import dataclasses
+    from oracle.dipolar_fft import dipolar_field_fft
+    w = dataclasses.replace(dip_workload(L), cell=cell, J_shell=(0.0,), D_shell=None, B=(0.0, 0.0, 0.0))
+    S = random_sphere(w.N, 63)
+    ref = dipolar_field_fft(L, cell, 2.0, S)
+    assert max_rel(gpu_field(w, S, "fp32"), ref) <= 1e-5
