@@ -69,6 +69,7 @@ struct ZPlan {
     int zch = 8;    // z planes per block
     int zauto = 0;  // 1: each launch takes its chunk from zchunk_rule instead
     int txw = 64;   // tile width in x (GNEB passes: 64, 32 or 16; others 64)
+    int film = 0;   // GNEB passes of a film: images per block (0: march through z)
     int frows = 0;  // rows (wavefronts) per block of the fused Heun step, 0: 16 for FP32 NN, else 8
     double wd[9 * kMaxShapeBonds];
     float wf[9 * kMaxShapeBonds];
@@ -123,6 +124,11 @@ int zmarch_gneb_width(const ZPlan &zp, const Grid &g);
 // max_tiles tiles per image, if any split has so few).
 int64_t zmarch_gneb_columns(const ZPlan &zp, const Grid &g);
 int zmarch_gneb_chunk(const ZPlan &zp, const Grid &g, int64_t batch_columns, int64_t max_tiles);
+// Whether the passes of a lattice can march through the images (one plane,
+// open in z), and the images per block of such an instance in a batch whose
+// tiles per image add up to batch_columns.
+bool zmarch_gneb_film(const ZPlan &zp, const Grid &g);
+int zmarch_gneb_film_chunk(int64_t batch_columns, int n_img);
 // The two passes of a GNEB iteration that stores no force (see spx_stencil.hip
 // ZM_GNEB_A2 / ZM_GNEB_C2), over the images of one instance.  pass 0: every
 // image, eleven partials per tile into partial[(item0 + n items_per_img +
@@ -144,7 +150,8 @@ struct GnebPassArgs {
     int string;
     double *partial;
 };
-// Instances whose plans agree in shape, isotropy and tile width share a launch:
+// Instances whose plans agree in shape, isotropy and tile width (films: in
+// shape and isotropy) share a launch:
 // zmarch_gneb_entry fills one instance's entry of the pass (false: the plan
 // has no such pass) and says how many blocks it takes from block0 on (a
 // multiple of 8); zmarch_gneb_batch launches n entries (device memory and the

@@ -19,7 +19,9 @@
 //                             exp-map step into the other buffer
 //   reduce + scalars          max |F_gneb|, CI switch, convergence, buffer flip
 // which moves 96 + 120 = 216 bytes per spin-image-iteration (pass A2 reads
-// S_n, S_n-1, S_n+1 and v; pass C2 reads S_n, S_n-1, S_n+1 and writes v, S').
+// S_n, S_n-1, S_n+1 and v; pass C2 reads S_n, S_n-1, S_n+1 and writes v, S');
+// films (one plane, open in z) march through the images instead of the planes
+// and read each image once a pass, 48 + 72 bytes.
 // Other instances (any bond table) use items: every (instance, image,
 // 256-site tile) is one item of a flat list and each per-site pass is one
 // grid-stride launch over the items of all instances:
@@ -453,7 +455,10 @@ __global__ __launch_bounds__(kGB) void k_gneb_scalars2(const GInst *__restrict__
 }
 
 // Per-image sums of the projection pass, then both scalar steps, of a batch
-// of small two-pass instances: one block per instance, a wavefront per image.
+// of small two-pass instances: one block per instance, each of its threads one
+// strand of one sum, so that the lane steps are few (a wavefront per image
+// adding eleven values by lane steps took 14 of the launch's 19 us, all of it
+// on the LDS unit that carries them).
 // One launch instead of three where the tiles are few (kFoldTiles): between
 // the passes of a batch of films the launches themselves were the time.
 constexpr int kFoldB = 1024;
@@ -462,20 +467,20 @@ __global__ __launch_bounds__(kFoldB) void k_gneb_mid(const GInst *__restrict__ i
                                                      const double *__restrict__ partial) {
     const GInst &G = inst[blockIdx.x];
     if (G.st[ST_DONE] != 0.0) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int n = wave; n < G.n_img; n += kFoldB / 64) {
-        const double *p = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS;
-        double v[kPassA2Values];
-#pragma unroll
-        for (int q = 0; q < kPassA2Values; ++q) v[q] = 0.0;
-        for (int k = lane; k < G.zt_per_img; k += 64)
-#pragma unroll
-            for (int q = 0; q < kPassA2Values; ++q) v[q] += p[(size_t)k * kPS + q];
-#pragma unroll
-        for (int q = 0; q < kPassA2Values; ++q) {
-            const double t = wave_sum(v[q]);
-            if (lane == 0) G.img[n * IS_N + IS_E + q] = t;
+    // L lanes per (image, value), as many as the block has for all of them
+    const int nsum = G.n_img * kPassA2Values;
+    int L = 64;
+    while (L > 1 && nsum * L > kFoldB) L >>= 1;
+    for (int b = 0; b < nsum; b += kFoldB / L) {
+        const int p = b + threadIdx.x / L, n = p / kPassA2Values, q = p - n * kPassA2Values;
+        double t = 0.0;
+        if (p < nsum) {
+            const double *src = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS + q;
+#pragma unroll 4
+            for (int k = threadIdx.x & (L - 1); k < G.zt_per_img; k += L) t += src[(size_t)k * kPS];
         }
+        for (int off = L >> 1; off > 0; off >>= 1) t += __shfl_down(t, off, L);
+        if (p < nsum && (threadIdx.x & (L - 1)) == 0) G.img[n * IS_N + IS_E + q] = t;
     }
     __threadfence_block();
     __syncthreads();
@@ -1033,12 +1038,14 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
     g->n_imgs = (int)imgs.size();
     spx_status s = SPX_OK;
     // widths first: an instance's chunk follows from the whole batch's tiles
-    int64_t columns = 0;
+    int64_t columns = 0, film_columns = 0;
     for (int k = 0; k < n_inst; ++k) {
         ZPlan &zp = g->zplan[k];
         if (!zp.valid || zp.prec != 0) continue;
         zp.txw = zmarch_gneb_width(zp, g->hinst[k].g);
-        columns += zmarch_gneb_columns(zp, g->hinst[k].g) * g->hinst[k].n_img;
+        const int64_t c = zmarch_gneb_columns(zp, g->hinst[k].g);
+        if (zmarch_gneb_film(zp, g->hinst[k].g)) film_columns += c;
+        else columns += c * g->hinst[k].n_img;
     }
     Onsite *d_os = nullptr;
     s = gneb_alloc(g, (void **)&d_os, sizeof(Onsite) * n_inst, "GNEB on-site tables");
@@ -1059,13 +1066,19 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         gi.zt_per_img = 0;
         gi.F = nullptr;
         if (zp.valid && zp.prec == 0) {
-            g->zplan[k].zch = zmarch_gneb_chunk(zp, gi.g, columns, gi.items_per_img);
+            if (zmarch_gneb_film(zp, gi.g)) {
+                g->zplan[k].film = zmarch_gneb_film_chunk(film_columns, gi.n_img);
+                g->zplan[k].zch = 1;
+            } else {
+                g->zplan[k].zch = zmarch_gneb_chunk(zp, gi.g, columns, gi.items_per_img);
+            }
             g->zplan[k].zauto = 0;
         }
         if (zp.valid && zp.prec == 0 && zmarch_gneb_tiles(zp, gi.g) <= gi.items_per_img) {
             gi.zt_per_img = zmarch_gneb_tiles(zp, gi.g);  // the two z-march passes; no stored force
         } else {
             g->zplan[k].txw = 64;
+            g->zplan[k].film = 0;
             if ((s = gneb_alloc(g, (void **)&gi.F, n3 * sizeof(double), "GNEB forces")) != SPX_OK) break;
             if (zp.valid &&
                 (s = gneb_alloc(g, (void **)&gi.Bbil, n3 * sizeof(double), "GNEB bilinear field")) != SPX_OK)
@@ -1083,7 +1096,8 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         const ZPlan &zp = g->zplan[k];
         size_t q = 0;
         while (q < g->groups.size() && (g->groups[q].zp.kind != zp.kind || g->groups[q].zp.iso != zp.iso ||
-                                        g->groups[q].zp.txw != zp.txw))
+                                        (g->groups[q].zp.film > 0) != (zp.film > 0) ||
+                                        (zp.film == 0 && g->groups[q].zp.txw != zp.txw)))
             ++q;
         if (q == g->groups.size()) {
             g->groups.emplace_back();

@@ -96,6 +96,22 @@ int zm_tiles(const Grid &g, int zch, int block, int txw) {
     return ((g.Lx + txw - 1) / txw) * ((g.Ly + rows - 1) / rows) * ((g.Lz + zch - 1) / zch);
 }
 
+// Staged elements of a film tile with its halo, at most over the tile widths
+// 16, 32 and 64 of a block.
+constexpr int zm_film_plane(int block, int rx, int ry) {
+    int most = 0;
+    for (int w = 16; w <= 64; w *= 2) {
+        const int n = (w + 2 * rx) * (block / w + 2 * ry);
+        most = n > most ? n : most;
+    }
+    return most;
+}
+
+// Wavefronts per SIMD of the film passes: a fourth spills 4 to 24 registers
+// (25 iterations of the twelve films below: 3182 us with it, 3139 without);
+// wider shapes stage more per thread.
+constexpr int film_waves(int kind) { return kind == SHAPE_SC_NN ? 3 : 1; }
+
 constexpr int kMaxTensorBonds = 6;  // tensor couplings exist on the nearest-neighbour shape only
 
 template <typename T, int NW>
@@ -154,6 +170,7 @@ struct ZArgs {
     GnebSlots gis;
     double gdt, gmass;
     int gstring;
+    int ltx;  // film passes: log2 of the tile width
 };
 
 // Shape table as a static constant, so that every bond read in an unrolled
@@ -190,6 +207,171 @@ __device__ __forceinline__ int zwrap(int c, int L, int per, bool &ok) {
 template <int KIND, bool ISO>
 constexpr int zm_weights() {
     return ISO ? make_shape(KIND).nshell : 9 * make_shape(KIND).nb;
+}
+
+// What ZM_GNEB_C2 needs of an image: its tangent weights w+-, c_n / |tau| (the
+// spring or climbing-image coefficient over the tangent norm) and the velocity
+// factor (VP projection + dt / m).
+struct GnebScalars {
+    double wp, wm, cn, vf;
+};
+__device__ __forceinline__ GnebScalars gneb_scalars(const ZArgs &g, int gimg) {
+    const double *im = g.gims + (int64_t)gimg * g.gis.n;
+    const double tn = im[g.gis.tn];
+    return {im[g.gis.wp], im[g.gis.wm], tn > 0.0 ? im[g.gis.coef] / tn : 0.0, g.gst[g.gis.proj] + g.gdt / g.gmass};
+}
+
+// Element of an array: by index, or by a byte offset of 32 bits, which with a
+// uniform base takes no address arithmetic and one register instead of two.
+struct ByteOffset {
+    unsigned v;
+};
+template <typename T>
+__device__ __forceinline__ T *elem(T *base, int64_t i) {
+    return base + i;
+}
+template <typename T>
+__device__ __forceinline__ T *elem(T *base, ByteOffset i) {
+    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T *>(reinterpret_cast<Byte *>(base) + i.v);
+}
+
+// GNEB epilogue of one site (sublattice a, index i) of image gimg with spin sp
+// and bilinear field v.  e: the site's spin in the next image (e[0..2]) and the
+// previous one (e[3..5]), zero where there is none; for A2 its velocity
+// (e[6..8], zero for the string method).  A2 adds energy, squared distance
+// and the nine image sums by add(k, value), C2 passes |F_gneb|^2 to add(0, .).
+template <int MODE, typename Index, typename Add>
+__device__ __forceinline__ void gneb_site(const ZArgs &g, const Onsite &os, int a, int gimg, Index i,
+                                          const double *sp, const double *v, const double *e, const GnebScalars &gs,
+                                          Add &&add) {
+    const int64_t N = g.N;
+    const bool interior = gimg > 0 && gimg < g.gntot - 1, has_next = gimg < g.gntot - 1;
+    double ba[3];
+    aniso_field(os, a, sp, ba);
+    double b[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) b[c] = v[c] + ba[c] + os.bz[a][c];
+    if constexpr (MODE == ZM_GNEB_A2) {
+        double sb = 0.0, sz = 0.0, sa = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            sb += sp[c] * v[c];
+            sz += sp[c] * os.bz[a][c];
+            sa += sp[c] * ba[c];
+        }
+        add(0, -0.5 * sb - sz - 0.5 * sa);
+        if (has_next) {
+            const double *q = e;
+            const double c0 = sp[1] * q[2] - sp[2] * q[1], c1 = sp[2] * q[0] - sp[0] * q[2],
+                         c2 = sp[0] * q[1] - sp[1] * q[0];
+            const double cc = c0 * c0 + c1 * c1 + c2 * c2;
+            const double th = atan2_nonneg(cc > 0.0 ? sqrt_pos(cc) : 0.0, sp[0] * q[0] + sp[1] * q[1] + sp[2] * q[2]);
+            add(1, th * th);
+        }
+    }
+    if (!interior) return;
+    const double bs = b[0] * sp[0] + b[1] * sp[1] + b[2] * sp[2];
+    double F[3], ap[3], bp[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        F[c] = b[c] - bs * sp[c];
+        ap[c] = e[c] - sp[c];
+        bp[c] = sp[c] - e[3 + c];
+    }
+    const double as = ap[0] * sp[0] + ap[1] * sp[1] + ap[2] * sp[2];
+    const double bss = bp[0] * sp[0] + bp[1] * sp[1] + bp[2] * sp[2];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        ap[c] -= as * sp[c];
+        bp[c] -= bss * sp[c];
+    }
+    if constexpr (MODE == ZM_GNEB_A2) {
+        const double vv[3] = {e[6], e[7], e[8]};
+        double d9[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            d9[0] += ap[c] * ap[c];
+            d9[1] += ap[c] * bp[c];
+            d9[2] += bp[c] * bp[c];
+            d9[3] += F[c] * ap[c];
+            d9[4] += F[c] * bp[c];
+            d9[5] += vv[c] * ap[c];
+            d9[6] += vv[c] * bp[c];
+            d9[7] += vv[c] * F[c];
+            d9[8] += F[c] * F[c];
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) add(2 + k, d9[k]);
+    } else {
+        // F_gneb = F + c_n tau / |tau|, VP step, exponential map
+        double u[3], vn[3], f2 = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double tau = gs.wp * ap[c] + gs.wm * bp[c];
+            const double ft = F[c] + gs.cn * tau;
+            f2 += ft * ft;
+            vn[c] = g.gstring ? 0.0 : gs.vf * ft;
+            u[c] = g.gstring ? g.gdt * F[c] : g.gdt * vn[c];
+        }
+        // max |F_gneb|^2 here, its square root once per tile
+        add(0, f2);
+        if (!g.gstring) {
+            double *V = g.gV + (int64_t)gimg * g.bstride;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) *elem(V + c * N, i) = vn[c];
+            const double us = u[0] * sp[0] + u[1] * sp[1] + u[2] * sp[2];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) u[c] -= us * sp[c];
+        }
+        // exp_S(u) = cos|u| S + (sin|u| / |u|) u, renormalised;
+        // u = 0 leaves S as it is
+        const double uz = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        double cs, sc;
+        expmap_cs(uz, cs, sc);
+        double o[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = cs * sp[c] + sc * u[c];
+        normalise3(o);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) o[c] = uz == 0.0 ? sp[c] : o[c];
+        double *On = ((g.sel && *g.sel != 0.0) ? g.O1 : g.O0) + (int64_t)gimg * g.bstride;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) *elem(On + c * N, i) = o[c];
+    }
+}
+
+// Fixed-order tile sums of the threads' LDS columns gacc[11][NT]: NT / 16
+// threads sum sixteen entries of a value each, then four or five lane steps
+// (eleven whole-wavefront sums by lane steps cost a block of one plane as much
+// as its sites).
+template <int NT>
+__device__ __forceinline__ void gneb_tile_sums(const double *gacc, double *set) {
+    constexpr int R = NT / 16;
+    const int k = threadIdx.x / R, sub = threadIdx.x % R;
+    double t = 0.0;
+    if (k < 11)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) t += gacc[k * NT + j * R + sub];
+#pragma unroll
+    for (int off = R / 2; off > 0; off >>= 1) t += __shfl_down(t, off, R);
+    if (k < 11 && sub == 0) set[k] = t;
+}
+
+// The tile's max |F_gneb| from the threads' |F_gneb|^2: wavefronts first
+// (gred[wavefront]), then, after a barrier, the tile.
+__device__ __forceinline__ void gneb_wave_max(double f2, double *gred) {
+    double v = sqrt(f2);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
+    if ((threadIdx.x & 63) == 0) gred[threadIdx.x >> 6] = v;
+}
+template <int NT>
+__device__ __forceinline__ void gneb_tile_max(const double *gred, double *set) {
+    if (threadIdx.x != 0) return;
+    double t = 0.0;
+    for (int w = 0; w < NT / 64; ++w) t = fmax(t, gred[w]);
+    set[0] = t;
 }
 
 // The march of one block: block `tile` of the launch's ntile tiles.
@@ -273,18 +455,9 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
                        : MODE == ZM_PREDICT ? 3 : 1;
     // image of the launch in its instance (GNEB two-pass modes)
     const int gimg = img + g.gimg0;
-    // ZM_GNEB_C2: the image's tangent weights w+-, c_n / |tau| (the spring or
-    // climbing-image coefficient over the tangent norm) and the velocity
-    // factor (VP projection + dt / m), uniform over the block
-    double gwp = 0.0, gwm = 0.0, gcn = 0.0, gvf = 0.0;
-    if constexpr (MODE == ZM_GNEB_C2) {
-        const double *im = g.gims + (int64_t)gimg * g.gis.n;
-        gwp = im[g.gis.wp];
-        gwm = im[g.gis.wm];
-        const double tn = im[g.gis.tn];
-        gcn = tn > 0.0 ? im[g.gis.coef] / tn : 0.0;
-        gvf = g.gst[g.gis.proj] + g.gdt / g.gmass;
-    }
+    // ZM_GNEB_C2: uniform over the block
+    GnebScalars gs{};
+    if constexpr (MODE == ZM_GNEB_C2) gs = gneb_scalars(g, gimg);
     // kDeep: the staged plane and the epilogue inputs are fetched two march
     // iterations ahead into two register sets, whose names stay static
     // because the march loop is unrolled by two (passes whose iterations wait
@@ -643,108 +816,15 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
             }
             return;
         }
-        if constexpr (MODE == ZM_GNEB_A2 || MODE == ZM_GNEB_C2) {
+        if constexpr (zm_gneb(MODE)) {
             if (!valid) return;
-            const bool interior = gimg > 0 && gimg < g.gntot - 1, has_next = gimg < g.gntot - 1;
 #pragma unroll
-            for (int a = 0; a < NSUB; ++a) {
-                const double *sp = so[a];
-                double ba[3];
-                aniso_field(os, a, sp, ba);
-                double b[3];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) b[c] = (double)v[a][0][c] + ba[c] + os.bz[a][c];
-                if constexpr (MODE == ZM_GNEB_A2) {
-                    double sb = 0.0, sz = 0.0, sa = 0.0;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        sb += sp[c] * (double)v[a][0][c];
-                        sz += sp[c] * os.bz[a][c];
-                        sa += sp[c] * ba[c];
-                    }
-                    gacc[threadIdx.x] += -0.5 * sb - sz - 0.5 * sa;
-                    if (has_next) {
-                        const double *q = e[a];
-                        const double c0 = sp[1] * q[2] - sp[2] * q[1], c1 = sp[2] * q[0] - sp[0] * q[2],
-                                     c2 = sp[0] * q[1] - sp[1] * q[0];
-                        const double cc = c0 * c0 + c1 * c1 + c2 * c2;
-                        const double th =
-                            atan2_nonneg(cc > 0.0 ? sqrt_pos(cc) : 0.0, sp[0] * q[0] + sp[1] * q[1] + sp[2] * q[2]);
-                        gacc[kThreads + threadIdx.x] += th * th;
-                    }
-                }
-                if (!interior) continue;
-                const double bs = b[0] * sp[0] + b[1] * sp[1] + b[2] * sp[2];
-                double F[3], ap[3], bp[3];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    F[c] = b[c] - bs * sp[c];
-                    ap[c] = e[a][c] - sp[c];
-                    bp[c] = sp[c] - e[a][3 + c];
-                }
-                const double as = ap[0] * sp[0] + ap[1] * sp[1] + ap[2] * sp[2];
-                const double bss = bp[0] * sp[0] + bp[1] * sp[1] + bp[2] * sp[2];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    ap[c] -= as * sp[c];
-                    bp[c] -= bss * sp[c];
-                }
-                if constexpr (MODE == ZM_GNEB_A2) {
-                    // the velocity, fetched a plane ahead (zero for the
-                    // string method)
-                    const double vv[3] = {e[a][6], e[a][7], e[a][8]};
-                    double d9[9] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        d9[0] += ap[c] * ap[c];
-                        d9[1] += ap[c] * bp[c];
-                        d9[2] += bp[c] * bp[c];
-                        d9[3] += F[c] * ap[c];
-                        d9[4] += F[c] * bp[c];
-                        d9[5] += vv[c] * ap[c];
-                        d9[6] += vv[c] * bp[c];
-                        d9[7] += vv[c] * F[c];
-                        d9[8] += F[c] * F[c];
-                    }
-#pragma unroll
-                    for (int k = 0; k < 9; ++k) gacc[(2 + k) * kThreads + threadIdx.x] += d9[k];
-                } else {
-                    // F_gneb = F + c_n tau / |tau|, VP step, exponential map
-                    double u[3], vn[3], f2 = 0.0;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const double tau = gwp * ap[c] + gwm * bp[c];
-                        const double ft = F[c] + gcn * tau;
-                        f2 += ft * ft;
-                        vn[c] = g.gstring ? 0.0 : gvf * ft;
-                        u[c] = g.gstring ? g.gdt * F[c] : g.gdt * vn[c];
-                    }
-                    // max |F_gneb|^2 here, its square root once per tile
-                    gX[0] = fmax(gX[0], f2);
-                    if (!g.gstring) {
-                        double *V = g.gV + (int64_t)gimg * g.bstride;
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) V[c * N + i[a]] = vn[c];
-                        const double us = u[0] * sp[0] + u[1] * sp[1] + u[2] * sp[2];
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) u[c] -= us * sp[c];
-                    }
-                    // exp_S(u) = cos|u| S + (sin|u| / |u|) u, renormalised;
-                    // u = 0 leaves S as it is
-                    const double uz = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-                    double cs, sc;
-                    expmap_cs(uz, cs, sc);
-                    double o[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) o[c] = cs * sp[c] + sc * u[c];
-                    normalise3(o);
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) o[c] = uz == 0.0 ? sp[c] : o[c];
-                    double *On = ((g.sel && *g.sel != 0.0) ? g.O1 : g.O0) + (int64_t)gimg * g.bstride;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) On[c * N + i[a]] = o[c];
-                }
-            }
+            for (int a = 0; a < NSUB; ++a)
+                gneb_site<MODE>(g, os, a, gimg, i[a], so[a], v[a][0], e[a], gs, [&](int k, double t)
+                                    __attribute__((always_inline)) {
+                                        if constexpr (MODE == ZM_GNEB_A2) gacc[k * kThreads + threadIdx.x] += t;
+                                        else gX[0] = fmax(gX[0], t);
+                                    });
             return;
         }
         if constexpr (MODE == ZM_ENERGY) {
@@ -1128,36 +1208,18 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
             g.gpart[(size_t)tile * 6 + k] = t;
         }
     }
-    if constexpr (MODE == ZM_GNEB_A2 || MODE == ZM_GNEB_C2) {
-        // fixed-order block sums (A2: energy, squared distance and the nine
-        // image sums) or maximum (C2: max |F_gneb|), one set per tile
+    if constexpr (zm_gneb(MODE)) {
+        // A2: energy, squared distance and the nine image sums, C2: max
+        // |F_gneb|, one set per tile
         double *const set = g.gpart + ((size_t)g.gitem0 + (size_t)gimg * g.gipi + stile) * 11;
         if constexpr (MODE == ZM_GNEB_A2) {
-            // kThreads / 16 threads sum sixteen LDS entries of a value each,
-            // then four or five lane steps: eleven whole-wavefront sums by
-            // lane steps cost a block of one plane as much as its sites
-            constexpr int R = kThreads / 16;
             __syncthreads();  // every thread's column is final
-            const int k = threadIdx.x / R, sub = threadIdx.x % R;
-            double t = 0.0;
-            if (k < 11)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) t += gacc[k * kThreads + j * R + sub];
-#pragma unroll
-            for (int off = R / 2; off > 0; off >>= 1) t += __shfl_down(t, off, R);
-            if (k < 11 && sub == 0) set[k] = t;
+            gneb_tile_sums<kThreads>(gacc, set);
         } else {
             __shared__ double gred[kThreads / 64];
-            double v = sqrt(gX[0]);
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_down(v, off, 64));
-            if ((threadIdx.x & 63) == 0) gred[threadIdx.x >> 6] = v;
+            gneb_wave_max(gX[0], gred);
             __syncthreads();
-            if (threadIdx.x == 0) {
-                double t = 0.0;
-                for (int w = 0; w < kThreads / 64; ++w) t = fmax(t, gred[w]);
-                set[0] = t;
-            }
+            gneb_tile_max<kThreads>(gred, set);
         }
     }
     if constexpr (MODE == ZM_ENERGY) {
@@ -1200,18 +1262,186 @@ struct ZBatchEntry {
 // are scalar loads where they are used.  Those loads stay behind the march's
 // branches, where kernel arguments are read ahead of them (96^3 x 32 images
 // alone: 821 against 799 us), so an instance alone takes k_zmarch.
-template <int KIND, bool ISO, int MODE, int TXW>
-__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch_batch(const ZBatchEntry *tab, int n) {
+__device__ __forceinline__ const ZBatchEntry &batch_entry(const ZBatchEntry *tab, int n) {
     using CEntry = const __attribute__((address_space(4))) ZBatchEntry;
     CEntry *t = (CEntry *)(uintptr_t)tab;
     int e = 0;
     while (e + 1 < n && t[e + 1].block0 <= blockIdx.x) ++e;
-    const ZBatchEntry &en = *(const ZBatchEntry *)(t + e);
+    return *(const ZBatchEntry *)(t + e);
+}
+
+template <int KIND, bool ISO, int MODE, int TXW>
+__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch_batch(const ZBatchEntry *tab, int n) {
+    const ZBatchEntry &en = batch_entry(tab, n);
     const unsigned b = blockIdx.x - en.block0, ntile = en.ntile;
     if (b >= ntile) return;  // padding between instances
     const HeunConst hc{};
     zmarch_block<KIND, double, ISO, MODE, TXW>(
         en.a, en.os, hc, *reinterpret_cast<const ZWeights<double, zm_weights<KIND, ISO>()> *>(en.w), b, ntile);
+}
+
+// The GNEB passes of films (one plane, open in z): a block keeps its (x, y)
+// tile and marches through g.zch images instead of planes.  An image's plane
+// is staged in LDS while the next one's loads are in flight; a site's spins in
+// the previous and the next image, which the z march reads beside each plane
+// (three reads of every image), are those the thread holds for the march.
+// Only the bonds within the plane are summed.  The tile width is a run-time
+// value (2^g.ltx), so that films of different sizes share one launch.  Twelve
+// skyrmion films of 48^2 .. 96^2 x 32 images: 43 + 45 us a pass, where the z
+// march (three launches side by side, a third of each block's planes empty)
+// took 190 us for both; bound by the chain of an image's FP64 epilogue and two
+// barriers on three blocks per CU (a read of the images alone takes 20 us).
+template <int KIND, bool ISO, int MODE>
+__global__ __launch_bounds__(zm_block(MODE, KIND), film_waves(KIND)) void k_gneb_film(
+    const ZBatchEntry *tab, int n) {
+    constexpr int NT = zm_block(MODE, KIND);
+    constexpr int NB = ShapeC<KIND>::t.nb, RX = ShapeC<KIND>::t.rx, RY = ShapeC<KIND>::t.ry;
+    static_assert(ShapeC<KIND>::t.nsub == 1 && kYB == 1, "one site per thread");
+    constexpr int PLANE = zm_film_plane(NT, RX, RY), NH = (PLANE - NT + NT - 1) / NT, NLD = 1 + NH;
+    __shared__ double plane[3][PLANE];
+    __shared__ double red[MODE == ZM_GNEB_A2 ? 11 * NT : NT / 64];
+
+    const ZBatchEntry &en = batch_entry(tab, n);
+    const ZArgs &g = en.a;
+    unsigned tile = blockIdx.x - en.block0;
+    const unsigned ntile = en.ntile;
+    if (tile >= ntile) return;  // padding between instances
+    if (*g.skip != 0.0) return;
+    if ((ntile & 7u) == 0) tile = (tile & 7u) * (ntile >> 3) + (tile >> 3);
+    const int TXW = 1 << g.ltx, TY = NT >> g.ltx, PW = TXW + 2 * RX, halo = PW * (TY + 2 * RY) - NT;
+    const unsigned nbx = (unsigned)((g.Lx + TXW - 1) / TXW), nby = (unsigned)((g.Ly + TY - 1) / TY);
+    const unsigned stile = tile % (nbx * nby);
+    const int x0 = (int)(stile % nbx) * TXW, y0 = (int)(stile / nbx) * TY;
+    // images m0 .. m1 - 1 of the instance
+    const int m0 = g.gimg0 + (int)(tile / (nbx * nby)) * g.zch, m1 = min(m0 + g.zch, g.gimg0 + g.nimg);
+    const int64_t N = g.N;
+    const double *const S = *g.sel != 0.0 ? g.S0alt : g.S0;
+
+    // staged elements: slot 0 is the thread's own site, the others the halo
+    const int tx = threadIdx.x & (TXW - 1), ty = threadIdx.x >> g.ltx;
+    const bool valid = x0 + tx < g.Lx && y0 + ty < g.Ly;
+    ByteOffset src[NLD];
+    int dst[NLD];
+    bool ok[NLD], have[NLD];
+#pragma unroll
+    for (int t = 0; t < NLD; ++t) {
+        int cx = tx + RX, cy = ty + RY;
+        have[t] = true;
+        if (t > 0) {
+            const int h = threadIdx.x + (t - 1) * NT;
+            have[t] = h < halo;
+            int m = h;
+            if (m < RY * PW) {  // rows above the tile
+                cy = m / PW;
+                cx = m - cy * PW;
+            } else if ((m -= RY * PW) < TY * 2 * RX) {  // left / right columns
+                cy = RY + m / (2 * RX);
+                const int k = m % (2 * RX);
+                cx = k < RX ? k : TXW + k;
+            } else {  // rows below the tile
+                m -= TY * 2 * RX;
+                cy = RY + TY + m / PW;
+                cx = m % PW;
+            }
+        }
+        bool in = have[t];
+        const int gx = zwrap(x0 - RX + cx, g.Lx, g.per[0], in), gy = zwrap(y0 - RY + cy, g.Ly, g.per[1], in);
+        ok[t] = in;
+        src[t].v = in ? (unsigned)(gx + g.Lx * gy) * (unsigned)sizeof(double) : 0u;
+        dst[t] = cy * PW + cx;
+    }
+    const int own = (ty + RY) * PW + tx + RX;
+
+    // the plane (and velocities) of image m + 1 arrive while image m is
+    // summed; images that are not staged here (m1, and m0 - 1 below) are read
+    // at the thread's own site only.  A second register set ahead costs the
+    // fourth wavefront per SIMD.
+    double pre[NLD][3], vnx[3], prv[3], cur[3], vel[3];
+    auto fetch = [&](int m) __attribute__((always_inline)) {
+        const bool exists = m < g.gntot, staged = m < m1;
+        const double *Sm = S + (exists ? m : 0) * g.bstride;
+#pragma unroll
+        for (int t = 0; t < NLD; ++t)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                pre[t][c] = (ok[t] && exists && (t == 0 || staged)) ? *elem(Sm + c * N, src[t]) : 0.0;
+        if constexpr (MODE == ZM_GNEB_A2) {
+            const bool v = ok[0] && staged && m > 0 && m < g.gntot - 1 && !g.gstring;
+            const double *Vm = g.gV + (exists ? m : 0) * g.bstride;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vnx[c] = v ? *elem(Vm + c * N, src[0]) : 0.0;
+        }
+    };
+    auto commit = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < NLD; ++t)
+            if (have[t])
+#pragma unroll
+                for (int c = 0; c < 3; ++c) plane[c][dst[t]] = pre[t][c];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            prv[c] = cur[c];
+            cur[c] = pre[0][c];
+            if constexpr (MODE == ZM_GNEB_A2) vel[c] = vnx[c];
+        }
+    };
+    fetch(m0);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) cur[c] = (ok[0] && m0 > 0) ? *elem(S + (m0 - 1) * g.bstride + c * N, src[0]) : 0.0;
+    commit();
+    fetch(m0 + 1);
+    __syncthreads();
+#pragma unroll 1
+    for (int m = m0; m < m1; ++m) {
+        GnebScalars gs{};
+        if constexpr (MODE == ZM_GNEB_C2) gs = gneb_scalars(g, m);
+        double b[3] = {0.0, 0.0, 0.0};
+        static_for<NB>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int kb = decltype(kc)::value;
+            constexpr ZBond bd = ShapeC<KIND>::t.bonds[kb];
+            if constexpr (bd.dz == 0) {
+                const int off = bd.dy * PW + bd.dx;
+                const double s0 = plane[0][own + off], s1 = plane[1][own + off], s2 = plane[2][own + off];
+                if constexpr (ISO) {
+                    const double J = en.w[bd.shell];
+                    b[0] += J * s0;
+                    b[1] += J * s1;
+                    b[2] += J * s2;
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        b[c] += en.w[9 * kb + 3 * c] * s0 + en.w[9 * kb + 3 * c + 1] * s1 + en.w[9 * kb + 3 * c + 2] * s2;
+                }
+            }
+        });
+        double e[9];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            e[c] = pre[0][c];
+            e[3 + c] = prv[c];
+            if constexpr (MODE == ZM_GNEB_A2) e[6 + c] = vel[c];
+        }
+        double f2 = 0.0;
+        if constexpr (MODE == ZM_GNEB_A2)
+            if (!valid || m == 0 || m == g.gntot - 1)  // sums that the site below does not write
+#pragma unroll
+                for (int k = 0; k < 11; ++k) red[k * NT + threadIdx.x] = 0.0;
+        if (valid)
+            gneb_site<MODE>(g, en.os, 0, m, src[0], cur, b, e, gs, [&](int k, double t) __attribute__((always_inline)) {
+                if constexpr (MODE == ZM_GNEB_A2) red[k * NT + threadIdx.x] = t;
+                else f2 = t;
+            });
+        double *const set = g.gpart + ((size_t)g.gitem0 + (size_t)m * g.gipi + stile) * 11;
+        if constexpr (MODE == ZM_GNEB_C2) gneb_wave_max(f2, red);
+        __syncthreads();  // the plane has been read, the sums are written
+        if (m + 1 < m1) {
+            commit();
+            fetch(m + 2);
+        }
+        if constexpr (MODE == ZM_GNEB_A2) gneb_tile_sums<NT>(red, set);
+        else gneb_tile_max<NT>(red, set);
+        __syncthreads();
+    }
 }
 
 // Thermal noise of one Heun step for every site (Heun mode 4: generated by
@@ -1398,11 +1628,15 @@ struct ZBatchLaunch {
     const ZBatchEntry *only;
     int n;
     unsigned blocks;
+    bool film;
     hipStream_t st;
     template <int KIND, typename T, bool ISO, int MODE, int TXW>
     hipError_t run(const ZPlan &, const Grid &) const {
         static_assert(zm_weights<KIND, ISO>() <= 9 * kMaxTensorBonds, "entry weights");
-        if (n == 1) {
+        if (film) {
+            if constexpr (TXW == kTX) k_gneb_film<KIND, ISO, MODE><<<blocks, zm_block(MODE, KIND), 0, st>>>(tab, n);
+            else return hipErrorInvalidValue;
+        } else if (n == 1) {
             ZWeights<double, zm_weights<KIND, ISO>()> W;
             for (int k = 0; k < zm_weights<KIND, ISO>(); ++k) W.w[k] = only->w[k];
             k_zmarch<KIND, double, ISO, MODE, TXW>
@@ -1647,6 +1881,15 @@ int zmarch_gneb_chunk(const ZPlan &zp, const Grid &g, int64_t batch_columns, int
                        std::max<int64_t>(max_tiles / own, 1) * batch_columns);
 }
 
+bool zmarch_gneb_film(const ZPlan &zp, const Grid &g) {
+    return zp.valid && zp.prec == 0 && g.Lz == 1 && !g.per[2] && (int64_t)g.Lx * g.Ly <= INT32_MAX / 8;  // 32-bit byte offsets
+}
+
+int zmarch_gneb_film_chunk(int64_t batch_columns, int n_img) {
+    // three blocks per CU; two images' reads before the first sum
+    return zchunk_rule(batch_columns, n_img, 3 * device_cus(), 2, 32, INT64_MAX);
+}
+
 size_t zmarch_gneb_entry_bytes() { return sizeof(ZBatchEntry); }
 
 bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
@@ -1683,7 +1926,12 @@ bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &o
     a.xcd = 1;
     en.os = os;
     for (int k = 0; k < zp.nw && k < 9 * kMaxTensorBonds; ++k) en.w[k] = zp.wd[k];
-    const int64_t ntile = (int64_t)zmarch_gneb_tiles(zp, g) * a.nimg;
+    if (zp.film > 0) {
+        a.zch = zp.film;
+        a.ltx = zp.txw == 64 ? 6 : zp.txw == 32 ? 5 : 4;
+    }
+    const int64_t ntile =
+        (int64_t)zmarch_gneb_tiles(zp, g) * (zp.film > 0 ? (a.nimg + zp.film - 1) / zp.film : a.nimg);
     if (ntile > 0x7fffffff || ntile + block0 > 0x7fffffff) return false;
     en.block0 = block0;
     en.ntile = (unsigned)ntile;
@@ -1694,14 +1942,16 @@ bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &o
 
 hipError_t zmarch_gneb_batch(int pass, const ZPlan &zp, const void *entries, const void *host, int n, unsigned blocks,
                              hipStream_t st) {
-    const ZBatchLaunch l{(const ZBatchEntry *)entries, (const ZBatchEntry *)host, n, blocks, st};
+    const ZBatchLaunch l{(const ZBatchEntry *)entries, (const ZBatchEntry *)host, n, blocks, zp.film > 0, st};
     const Grid g{};
+    ZPlan zq = zp;
+    if (zp.film > 0) zq.txw = kTX;  // one kernel for every width
     if (pass == 0) {
-        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zp, g, l);
-        return launch_mode<double, false, ZM_GNEB_A2>(zp, g, l);
+        if (zp.iso) return launch_mode<double, true, ZM_GNEB_A2>(zq, g, l);
+        return launch_mode<double, false, ZM_GNEB_A2>(zq, g, l);
     }
-    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zp, g, l);
-    return launch_mode<double, false, ZM_GNEB_C2>(zp, g, l);
+    if (zp.iso) return launch_mode<double, true, ZM_GNEB_C2>(zq, g, l);
+    return launch_mode<double, false, ZM_GNEB_C2>(zq, g, l);
 }
 
 hipError_t zmarch_bil_images(const ZPlan &zp, const Grid &g, int n_img, const double *S0, const double *S0alt,

@@ -245,3 +245,44 @@ def test_gneb_two_pass_tile_widths_match_oracle():
             np.testing.assert_allclose(s["E"], E, rtol=1e-10, atol=1e-12)
             np.testing.assert_allclose(s["dist"], dist, rtol=1e-10, atol=1e-12)
             assert s["ci_index"] == ci and s["iterations"] == it + 1
+
+
+FILMS = [("nn", dict(J_shell=(1.0,))), ("chiral", dict(J_shell=(1.0,), D_shell=(0.3,))),
+         ("three", dict(J_shell=(1.0, -0.164, -0.082))), ("four", dict(J_shell=(1.0, 0.188, -0.274, -0.161)))]
+
+
+@pytest.mark.parametrize("ci_mode", [1, 4], ids=["climbing", "string"])
+@pytest.mark.parametrize("couplings", [f[1] for f in FILMS], ids=[f[0] for f in FILMS])
+def test_gneb_films_match_oracle(couplings, ci_mode):
+    # one plane, open in z: the passes march through the images.  One batch of
+    # every tile width (16, 64 and 32) with ragged x and y tiles, image counts
+    # that leave a short last run of images per block, wrapped and open edges,
+    # an edge shorter than the couplings' reach, the least number of images,
+    # and a film periodic in z (which marches through planes)
+    import torch
+    from paper_2605_26016_amd import spx
+    cases = [((100, 97, 1), (1, 1, 0), 21), ((14, 30, 1), (0, 0, 0), 8), ((70, 4, 1), (1, 0, 0), 3),
+             ((33, 9, 1), (0, 1, 0), 5), ((1, 2, 1), (0, 0, 0), 4), ((9, 12, 1), (1, 1, 1), 5)]
+    hams, bufs, refs = [], [], []
+    kw = dict(k_spring=1.0, dt=0.05, mass=1.0, ci_mode=ci_mode, ci_on_below=3.0)
+    for k, (L, periodic, n_img) in enumerate(cases):
+        w = Workload(name="t", L=L, periodic=periodic, K=0.05, B=(0.0, 0.0, 0.3), field_prec="fp64", **couplings)
+        A, B = random_sphere(w.N, 41 + k), random_sphere(w.N, 141 + k)
+        Y0 = oracle.geodesic_path(A, B, n_img)
+        hams.append(gpu_hamiltonian(w))
+        bufs.append(to_dev(Y0))
+        refs.append((oracle_model(w), oracle.GnebState(Y0, **kw)))
+    g = spx.gneb_create(hams, bufs, spring_k=1.0, vp_dt=0.05, vp_mass=1.0, ci_mode=ci_mode, ci_on_below=3.0)
+    for it in range(4):
+        spx.gneb_step(g, 1)
+        torch.cuda.synchronize()
+        for k, (m, st) in enumerate(refs):
+            E, dist, fmax, ci = oracle.gneb_iterate(m, st)
+            got = bufs[k].cpu().numpy()
+            err = float(np.max(np.abs(got - st.Y)))
+            assert err <= 1e-9, (it, k, err)
+            s = spx.gneb_get_stats(g, k)
+            np.testing.assert_allclose(s["E"], E, rtol=1e-10, atol=1e-10)
+            np.testing.assert_allclose(s["dist"], dist, rtol=1e-10, atol=1e-10)
+            np.testing.assert_allclose(s["max_force"], fmax, rtol=1e-9)
+            assert s["ci_index"] == ci and s["iterations"] == it + 1
