@@ -3,6 +3,8 @@
 // the LLG right-hand side and the Philox4x32-10 thermal noise.
 #pragma once
 
+#include <type_traits>
+
 #include "spx_internal.hpp"
 #include "spx_math.hpp"
 
@@ -127,6 +129,21 @@ __device__ __forceinline__ void normalise3(double v[3]) {
 // truth table of a ^ b ^ c).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// Element of an array: by index, or by a byte offset of 32 bits, which with a
+// uniform base takes no address arithmetic and one register instead of two.
+struct ByteOffset {
+    unsigned v;
+};
+template <typename T>
+__device__ __forceinline__ T *elem(T *base, int64_t i) {
+    return base + i;
+}
+template <typename T>
+__device__ __forceinline__ T *elem(T *base, ByteOffset i) {
+    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
+    return reinterpret_cast<T *>(reinterpret_cast<Byte *>(base) + i.v);
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two

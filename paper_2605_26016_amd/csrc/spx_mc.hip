@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
     const int64_t total = n_rows * J;
     const int64_t N = g.N;
     unsigned int accepted = 0;
-    for (int64_t t = xcd_block() * kMcB + threadIdx.x; t < total; t += (int64_t)gridDim.x * kMcB) {
+    auto site = [&](int64_t t) __attribute__((always_inline)) {
         // slot -> (j, y, z, a); 32-bit division when the slot count fits
         // (every lattice below 2^32 slots), which is far cheaper than the
         // 64-bit routine
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
         int x0 = (c - col.ky * y - col.kz * z - col.o[a]) % C;
         if (x0 < 0) x0 += C;
         const int x = x0 + C * j;
-        if (x >= g.Lx) continue;
+        if (x >= g.Lx) return;
         const int64_t i = (int64_t)a * g.M + x + (int64_t)g.Lx * (y + (int64_t)g.Ly * z);
         double bl[1][3];
         const bool interior = x >= rad.x && x < g.Lx - rad.x && y >= rad.y && y < g.Ly - rad.y && z >= rad.z &&
@@ -281,7 +281,9 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
         S[i] = sn[0];
         S[N + i] = sn[1];
         S[2 * N + i] = sn[2];
-    }
+    };
+    const int64_t t = xcd_block() * kMcB + threadIdx.x;
+    if (t < total) site(t);
     if (acc) add_accepted(acc, accepted);
 }
 
@@ -292,12 +294,32 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
 // [-rz, Lz + rz) (rx, ry, rz: the bonds' largest offsets).  A virtual site
 // outside the lattice is a ghost: on a periodic axis a copy of its wrapped
 // site, across an open face zero (it adds nothing to a field).
+struct FastDiv {
+    uint32_t m, s, one;  // n / d = (n m >> 32) >> s, or n for d = 1 (one)
+};
+// Division of n < 2^31 by an invariant d >= 1: m = floor(2^(32+s) / d) + 1 with
+// 2^s < d <= 2^(s+1) exceeds the true ratio by less than 2^(s+1) / d / 2^(32+s),
+// too little to reach the next whole number below 2^31 (Granlund and
+// Montgomery, 1994).
+inline FastDiv fast_div(uint32_t d) {
+    if (d <= 1) return {0u, 0u, 1u};
+    uint32_t s = 0;
+    while ((2ull << s) < d) ++s;
+    return {(uint32_t)((1ull << (32 + s)) / d + 1), s, 0u};
+}
+__device__ __forceinline__ uint32_t div_by(uint32_t n, const FastDiv &f) {
+    return f.one ? n : __umulhi(n, f.m) >> f.s;
+}
+
 struct CmDims {
     int C, J, Jp, ex;       // colours, real and padded slots per class block, ghost slots per end
     int lxq, lxm;           // Lx div C, Lx mod C
     int ry, rz, Lyp, Lzp;   // ghost rows and padded row extents
     int64_t n_rows, NP;     // real rows (y, z, a) and padded doubles per component
     int64_t pitch;          // C Jp
+    FastDiv by_J, by_Ly, by_Lz, by_C;
+    // slots, byte offsets and the colour form fit 32 bits (cm_narrow)
+    bool narrow;
 };
 
 // padded slot of virtual site (xv, yv, zv, a)
@@ -351,13 +373,21 @@ __global__ __launch_bounds__(kMcB) void k_mc_from_cm(const double *__restrict__ 
 }
 
 // One colour of one sweep on the padded colour-major copy P: the natural
-// kernel's site loop, draw and update, every neighbour at the tabulated
-// offset of its bond and class, and the new spin also written to the
-// site's ghost copies.  The register allocator is left free: asking it for
-// four waves per SIMD (at most 128 registers) kept the count of resident
-// waves where it was but made the code slower, Metropolis with 2-5 shells
-// by a third (sc 200^3).
-template <bool ISO, int METHOD, int UNR>
+// kernel's draw and update, every neighbour at the tabulated offset of its
+// bond and class, and the new spin also written to the site's ghost copies.
+//
+// Bound by the vector ALU (sc 200^3, one shell, heat-bath: 764 instructions a
+// site, 118 us a launch).  Two things were most of what is not the draw:
+//   - a thread takes one slot, not a grid-stride loop: ahead of a loop the
+//     draw's FP64 coefficients are moved into 80 registers per lane, for the
+//     single turn that nearly every launch makes of it (107 -> 86 us, 119 ->
+//     38 registers)
+//   - NARROW (every lattice whose padded component is below 4 GiB, so that a
+//     byte offset fits 32 bits): one offset a neighbour against the three
+//     components' uniform bases, and the slot's coordinates by multiplication
+//     with reciprocals from the host, instead of 64-bit addresses and run-time
+//     divisions (118 -> 107 us)
+template <bool ISO, int METHOD, int UNR, bool NARROW>
 __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, BondTable tb, Grid g, Onsite os,
                                                       McColour col, int c, double beta, uint64_t seed,
                                                       uint64_t sweep, unsigned long long *__restrict__ acc,
@@ -367,10 +397,35 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
     const int64_t total = d.n_rows * J;
     const int64_t NP = d.NP;
     unsigned int accepted = 0;
+    using Slot = std::conditional_t<NARROW, ByteOffset, int64_t>;
+    auto slot = [&](int yv, int zv, int a, int in_row) __attribute__((always_inline)) -> Slot {
+        if constexpr (NARROW) {
+            const unsigned pr = (unsigned)(yv + d.ry) + (unsigned)d.Lyp * ((unsigned)(zv + d.rz) + (unsigned)d.Lzp * (unsigned)a);
+            return {(pr * (unsigned)d.pitch + (unsigned)in_row) * (unsigned)sizeof(double)};
+        } else {
+            return ((yv + d.ry) + (int64_t)d.Lyp * ((zv + d.rz) + (int64_t)d.Lzp * a)) * d.pitch + in_row;
+        }
+    };
+    auto shifted = [&](Slot q, int64_t by) __attribute__((always_inline)) -> Slot {
+        if constexpr (NARROW) return {q.v + (unsigned)by * (unsigned)sizeof(double)};
+        else return q + by;
+    };
     // slot t -> (j, y, z, a) of row t / J, and the site's class x0
     auto decode = [&](int64_t t, int &j, int &y, int &z, int &a, int64_t &row, int &x0)
                       __attribute__((always_inline)) {
-        if (total <= (int64_t)0xffffffffll) {
+        if constexpr (NARROW) {
+            const uint32_t tt = (uint32_t)t;
+            const uint32_t rw = div_by(tt, d.by_J), yz = div_by(rw, d.by_Ly);
+            j = (int)(tt - rw * (uint32_t)J);
+            y = (int)(rw - yz * (uint32_t)g.Ly);
+            a = (int)div_by(yz, d.by_Lz);
+            z = (int)(yz - (uint32_t)a * (uint32_t)g.Lz);
+            row = rw;
+            const uint32_t h = (uint32_t)(col.ky * y + col.kz * z + col.o[a]);
+            x0 = c - (int)(h - div_by(h, d.by_C) * (uint32_t)C);
+            if (x0 < 0) x0 += C;
+            return;
+        } else if (total <= (int64_t)0xffffffffll) {
             const uint32_t tt = (uint32_t)t, uJ = (uint32_t)J, uLy = (uint32_t)g.Ly, uLz = (uint32_t)g.Lz;
             const uint32_t rw = tt / uJ;
             const uint32_t yz = rw / uLy;
@@ -402,12 +457,12 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
         if (kp >= C) { kp -= C; ++jp; }
         if (jp + d.ex < d.Jp) sp = kp * d.Jp + jp + d.ex;
     };
-    for (int64_t t = xcd_block() * kMcB + threadIdx.x; t < total; t += (int64_t)gridDim.x * kMcB) {
+    auto site = [&](int64_t t) __attribute__((always_inline)) {
         int j, y, z, a, x0;
         int64_t row;
         decode(t, j, y, z, a, row, x0);
         const int x = x0 + C * j;
-        if (x >= g.Lx) continue;
+        if (x >= g.Lx) return;
         // which ghost images the site has (bits: x - Lx, x + Lx, y - Ly,
         // y + Ly, z - Lz, z + Lz); their slots are worked out again after
         // the draw, only by the sites that have some
@@ -419,15 +474,20 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
                      (g.per[1] && y < d.ry ? 8 : 0) | (g.per[2] && z - g.Lz >= -d.rz ? 16 : 0) |
                      (g.per[2] && z < d.rz ? 32 : 0);
         }
-        const int64_t i = x + (int64_t)g.Lx * row;  // natural index (the Philox counter)
-        const int64_t own = ((y + d.ry) + (int64_t)d.Lyp * ((z + d.rz) + (int64_t)d.Lzp * a)) * d.pitch +
-                            (int64_t)x0 * d.Jp + j + d.ex;
+        const int64_t i = NARROW ? (int64_t)(unsigned)(x + g.Lx * (int)row) : x + (int64_t)g.Lx * row;  // natural index (the Philox counter)
+        const Slot own = slot(y, z, a, x0 * d.Jp + j + d.ex);
+        double si[3] = {0.0, 0.0, 0.0};
+        if (METHOD == 1) {
+            si[0] = *elem(P, own);
+            si[1] = *elem(P + NP, own);
+            si[2] = *elem(P + 2 * NP, own);
+        }
         double bl[3] = {0.0, 0.0, 0.0};
         const int p0 = tb.start[a], p1 = tb.start[a + 1];
 #pragma unroll UNR
         for (int p = p0; p < p1; ++p) {
-            const int64_t q = own + coff[p * C + x0];
-            const double s0 = P[q], s1 = P[NP + q], s2 = P[2 * NP + q];
+            const Slot q = shifted(own, coff[p * C + x0]);
+            const double s0 = *elem(P, q), s1 = *elem(P + NP, q), s2 = *elem(P + 2 * NP, q);
             if constexpr (ISO) {
                 const double Jp = tb.Jd[p];
                 bl[0] += Jp * s0;
@@ -441,17 +501,11 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
             }
         }
         const double b[3] = {bl[0] + os.bz[a][0], bl[1] + os.bz[a][1], bl[2] + os.bz[a][2]};
-        double si[3] = {0.0, 0.0, 0.0};
-        if (METHOD == 1) {
-            si[0] = P[own];
-            si[1] = P[NP + own];
-            si[2] = P[2 * NP + own];
-        }
         double sn[3];
         accepted += mc_move<METHOD>(os, a, b, si, beta, seed, sweep, i, sn);
-        P[own] = sn[0];
-        P[NP + own] = sn[1];
-        P[2 * NP + own] = sn[2];
+        *elem(P, own) = sn[0];
+        *elem(P + NP, own) = sn[1];
+        *elem(P + 2 * NP, own) = sn[2];
         // ghost copies: every combination of the real and the other virtual
         // coordinates of each axis except the real site itself
         if (ghosts) {
@@ -468,19 +522,20 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
                 for (int iy = 0; iy < 3; ++iy) {
                     const int yv = iy == 0 ? y : (iy == 1 ? ym : yp);
                     if (yv == INT_MIN) continue;
-                    const int64_t rb = ((yv + d.ry) + (int64_t)d.Lyp * ((zv + d.rz) + (int64_t)d.Lzp * a)) * d.pitch;
 #pragma unroll
                     for (int ix = 0; ix < 3; ++ix) {
                         if ((ix | iy | iz) == 0 || xs[ix] < 0) continue;
-                        const int64_t qg = rb + xs[ix];
-                        P[qg] = sn[0];
-                        P[NP + qg] = sn[1];
-                        P[2 * NP + qg] = sn[2];
+                        const Slot qg = slot(yv, zv, a, xs[ix]);
+                        *elem(P, qg) = sn[0];
+                        *elem(P + NP, qg) = sn[1];
+                        *elem(P + 2 * NP, qg) = sn[2];
                     }
                 }
             }
         }
-    }
+    };
+    const int64_t t = xcd_block() * kMcB + threadIdx.x;
+    if (t < total) site(t);
     if (acc) add_accepted(acc, accepted);
 }
 
@@ -745,6 +800,12 @@ bool mc_cm_buffer(const Grid &g, MCState *m, CmDims &d) {
     d.pitch = (int64_t)d.C * d.Jp;
     d.n_rows = (int64_t)g.Ly * g.Lz * g.n_sub;
     d.NP = (int64_t)d.Lyp * d.Lzp * g.n_sub * d.pitch;
+    d.by_J = fast_div((uint32_t)d.J);
+    d.by_Ly = fast_div((uint32_t)g.Ly);
+    d.by_Lz = fast_div((uint32_t)g.Lz);
+    d.by_C = fast_div((uint32_t)d.C);
+    d.narrow = d.NP <= (int64_t)(UINT32_MAX / sizeof(double)) &&
+               (int64_t)d.C * ((int64_t)g.Ly + g.Lz + 1) <= INT32_MAX;
     if (g.per[0] && ((int64_t)d.C * d.ex > g.Lx || (int64_t)d.C * (d.J + d.ex) > 2 * (int64_t)g.Lx)) return false;
     if ((g.per[1] && d.ry > g.Ly) || (g.per[2] && d.rz > g.Lz)) return false;
     const size_t need = 3 * (size_t)d.NP;
@@ -845,21 +906,17 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
     unsigned long long *acc = accepted && p->method == 1 ? m->d_acc : nullptr;
     if (acc) k_mc_zero<<<1, kMcB, 0, st>>>(acc);
     const int64_t total = (int64_t)((v.grid.Lx + col.C - 1) / col.C) * v.grid.Ly * v.grid.Lz * v.grid.n_sub;
-    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((total + kMcB - 1) / kMcB, 65536));
+    const unsigned grid = (unsigned)std::min<int64_t>((total + kMcB - 1) / kMcB, INT32_MAX);  // total <= the state's sites x 2
     const bool iso = v.tab.iso != 0;
     const int3 rad = make_int3(m->rad[0], m->rad[1], m->rad[2]);
-    // in place, heat-bath runs its neighbour loop two-deep (the FP64 draw
-    // then keeps more waves resident: sc 200^3 one shell 21.3 against
-    // 18.9e9 updates/s; one sweep with two shells 0.87 against 1.01 ms, with
-    // five 11.4 against 15.1 ms); Metropolis is faster four-deep
     int max_bonds = 0;
     for (int a = 0; a < v.grid.n_sub; ++a) max_bonds = std::max(max_bonds, v.tab.start[a + 1] - v.tab.start[a]);
     const bool short_list = max_bonds <= 8;
     // The colour-major copy costs two copies of the state per call; in place,
     // every colour launch moves the whole lattice's cache lines.  A single
-    // sweep of two colours runs faster in place (sc 200^3 one shell: 280
-    // against 403 us); two sweeps or more colours run on the copy (five
-    // shells, 20 colours, one sweep: 1.96 against 15.0 ms).
+    // sweep of two colours runs faster in place (sc 200^3 one shell: 221
+    // against 310 us); two sweeps or more colours run on the copy (five
+    // shells, 20 colours, one sweep: 1.88 against 15.0 ms).
     CmDims cd{};
     const bool cm = p->layout == 0 && (p->n_sweeps >= 2 || (p->n_sweeps == 1 && col.C > 2)) &&
                     mc_cm_buffer(v.grid, m, cd);
@@ -872,27 +929,37 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
             if (cm) {
                 double *P = m->d_cm;
                 const int64_t *co = m->d_coff;
-                // neighbour-loop unroll depths as timed on sc 200^3 with 1-5
-                // shells: heat-bath 2 throughout (a third faster than 4 with
-                // 2-5 shells; with exchange + DMI tensors 342 against 365 us
-                // per sweep at one shell), Metropolis 2 for one scalar shell
-                // and 4 otherwise
-                if (p->method == 0) {
-                    if (iso) k_mc_colour_cm<true, 0, 2><<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, co, cd);
-                    else k_mc_colour_cm<false, 0, 2><<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, co, cd);
-                } else {
-                    if (iso && short_list) k_mc_colour_cm<true, 1, 2><<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, co, cd);
-                    else if (iso) k_mc_colour_cm<true, 1, 4><<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, co, cd);
-                    else k_mc_colour_cm<false, 1, 4><<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, co, cd);
-                }
+                // neighbour-loop unroll depths as timed on sc 200^3 (heat-bath
+                // us per sweep with 5 shells: 2049 two deep, 1690 four, 1763
+                // eight; with 3 shells 625, 590, 601); one shell has too few
+                // neighbours for a difference, and tensors are faster two
+                // deep (Metropolis 270 against 295)
+                auto run = [&](auto narrow) {
+                    constexpr bool NW = decltype(narrow)::value;
+                    auto go = [&](auto kernel) {
+                        kernel<<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc,
+                                                      co, cd);
+                    };
+                    if (p->method == 0) {
+                        if (iso && short_list) go(k_mc_colour_cm<true, 0, 2, NW>);
+                        else if (iso) go(k_mc_colour_cm<true, 0, 4, NW>);
+                        else go(k_mc_colour_cm<false, 0, 2, NW>);
+                    } else {
+                        if (iso && short_list) go(k_mc_colour_cm<true, 1, 2, NW>);
+                        else if (iso) go(k_mc_colour_cm<true, 1, 4, NW>);
+                        else go(k_mc_colour_cm<false, 1, 2, NW>);
+                    }
+                };
+                if (cd.narrow) run(std::true_type{});
+                else run(std::false_type{});
                 continue;
             }
             if (p->method == 0) {
                 if (iso) k_mc_colour<true, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
-                else k_mc_colour<false, 0, 4><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
+                else k_mc_colour<false, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
             } else {
                 if (iso) k_mc_colour<true, 1, 4><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
-                else k_mc_colour<false, 1, 4><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
+                else k_mc_colour<false, 1, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
             }
         }
     }

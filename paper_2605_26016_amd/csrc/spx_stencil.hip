@@ -24,7 +24,6 @@
 // fetched one plane ahead.
 #include <algorithm>
 #include <cstring>
-#include <type_traits>
 #include <vector>
 
 #include "spx_device.hpp"
@@ -219,21 +218,6 @@ __device__ __forceinline__ GnebScalars gneb_scalars(const ZArgs &g, int gimg) {
     const double *im = g.gims + (int64_t)gimg * g.gis.n;
     const double tn = im[g.gis.tn];
     return {im[g.gis.wp], im[g.gis.wm], tn > 0.0 ? im[g.gis.coef] / tn : 0.0, g.gst[g.gis.proj] + g.gdt / g.gmass};
-}
-
-// Element of an array: by index, or by a byte offset of 32 bits, which with a
-// uniform base takes no address arithmetic and one register instead of two.
-struct ByteOffset {
-    unsigned v;
-};
-template <typename T>
-__device__ __forceinline__ T *elem(T *base, int64_t i) {
-    return base + i;
-}
-template <typename T>
-__device__ __forceinline__ T *elem(T *base, ByteOffset i) {
-    using Byte = std::conditional_t<std::is_const_v<T>, const char, char>;
-    return reinterpret_cast<T *>(reinterpret_cast<Byte *>(base) + i.v);
 }
 
 // GNEB epilogue of one site (sublattice a, index i) of image gimg with spin sp

@@ -260,3 +260,25 @@ def test_accepted_count_equals_changed_spins(L, method):
     assert int(acc.item()) == int((S != old).any(0).sum().item())
     spx.mc_sweep(h, S, 12.0, seed=8, sweep0=1, n_sweeps=0, method=method, accepted=acc)
     assert int(acc.item()) == 0
+
+
+@pytest.mark.parametrize("method", [0, 1])
+@pytest.mark.parametrize("L", [(7, 1, 4099), (1, 4096, 3), (64, 2, 33), (129, 31, 5), (100003, 1, 1)],
+                         ids=lambda L: "x".join(map(str, L)))
+def test_reciprocal_slot_coordinates_match_the_natural_layout(L, method):
+    # extents of 1, powers of two and their neighbours, primes: the colour-major
+    # sweep's coordinates come from multiplications by reciprocals, the natural
+    # layout's from divisions; one wrong coordinate changes a draw altogether
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="t", L=L, periodic=(0, 0, 0), J_shell=(1.0,), B=(0.0, 0.3, 1.0), field_prec="fp64")
+    h = gpu_hamiltonian(w)
+    S0 = random_sphere(w.N, 5)
+    out = []
+    for in_place in (False, True):
+        S = to_dev(S0)
+        acc = torch.zeros(1, dtype=torch.int64, device=S.device)
+        spx.mc_sweep(h, S, 60.0, seed=7, sweep0=3, n_sweeps=3, method=method, accepted=acc, in_place=in_place)
+        out.append((S.cpu().numpy(), int(acc.item())))
+    assert np.max(np.abs(out[0][0] - out[1][0])) <= 1e-11
+    assert out[0][1] == out[1][1]
