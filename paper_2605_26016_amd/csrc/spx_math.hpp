@@ -34,8 +34,24 @@
 
 #include <cmath>
 
+// SPX_K(c): polynomial coefficient c.  On the device it is forced into a
+// scalar register pair, the one scalar operand an FMA may have: left to the
+// compiler, loops around these functions hold the coefficients in vector
+// registers (a pair per lane each) and copy one for every term.  GNEB passes
+// 219 -> 161 registers, so that a third wavefront per SIMD fits.  The thermal
+// noise's functions go without: the Heun kernels hold theirs in scalar
+// registers by themselves, and were 0.5 - 1% slower with it.
 #ifndef SPX_MATH_FN
 #define SPX_MATH_FN __device__ __forceinline__
+namespace spx {
+__device__ __forceinline__ double scalar_constant(double c) {
+    asm("" : "+s"(c));
+    return c;
+}
+}  // namespace spx
+#define SPX_K(c) scalar_constant(c)
+#else
+#define SPX_K(c) (c)
 #endif
 #ifndef SPX_EST_RSQ
 #define SPX_EST_RSQ(x) __builtin_amdgcn_rsq(x)
@@ -115,7 +131,8 @@ SPX_MATH_FN double div_pos(double a, double b) {
     return std::fma(std::fma(-q, b, a), r, q);
 }
 
-// sin(pi t) and cos(pi t), |t| < 2^30.
+// sin(pi t) and cos(pi t), |t| < 2^30 (SCALAR: coefficients through SPX_K).
+template <bool SCALAR = false>
 SPX_MATH_FN void sincospi_d(double t, double &sn, double &cs) {
     // Taylor coefficients (-1)^k pi^(2k+1)/(2k+1)! and (-1)^k pi^(2k)/(2k)!
     constexpr double kPiHi = 0x1.921fb54442d18p+1, kPiLo = 0x1.1a62633145c07p-53;
@@ -129,23 +146,23 @@ SPX_MATH_FN void sincospi_d(double t, double &sn, double &cs) {
     const double r = std::fma(-0.5, n, t);  // exact, |r| <= 1/4
     const double z = r * r;
     double ps = S8;
-    ps = std::fma(ps, z, S7);
-    ps = std::fma(ps, z, S6);
-    ps = std::fma(ps, z, S5);
-    ps = std::fma(ps, z, S4);
-    ps = std::fma(ps, z, S3);
-    ps = std::fma(ps, z, S2);
-    ps = std::fma(ps, z, S1);
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S7) : S7));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S6) : S6));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S5) : S5));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S4) : S4));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S3) : S3));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S2) : S2));
+    ps = std::fma(ps, z, (SCALAR ? SPX_K(S1) : S1));
     const double sr = std::fma(r, kPiHi, r * std::fma(z, ps, kPiLo));
     double pc = C9;
-    pc = std::fma(pc, z, C8);
-    pc = std::fma(pc, z, C7);
-    pc = std::fma(pc, z, C6);
-    pc = std::fma(pc, z, C5);
-    pc = std::fma(pc, z, C4);
-    pc = std::fma(pc, z, C3);
-    pc = std::fma(pc, z, C2);
-    pc = std::fma(pc, z, C1);
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C8) : C8));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C7) : C7));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C6) : C6));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C5) : C5));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C4) : C4));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C3) : C3));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C2) : C2));
+    pc = std::fma(pc, z, (SCALAR ? SPX_K(C1) : C1));
     const double cr = std::fma(z, pc, 1.0);
     // pi t = pi r + q pi/2, q = n mod 4
     const int q = (int)n & 3;
@@ -168,24 +185,24 @@ SPX_MATH_FN double atan2_nonneg(double y, double x) {
     const double z = t * t;
     // atan t = t + t z sum_{k>=1} (-1)^k z^(k-1) / (2k + 1), k up to 19
     double p = -1.0 / 39.0;
-    p = std::fma(p, z, 1.0 / 37.0);
-    p = std::fma(p, z, -1.0 / 35.0);
-    p = std::fma(p, z, 1.0 / 33.0);
-    p = std::fma(p, z, -1.0 / 31.0);
-    p = std::fma(p, z, 1.0 / 29.0);
-    p = std::fma(p, z, -1.0 / 27.0);
-    p = std::fma(p, z, 1.0 / 25.0);
-    p = std::fma(p, z, -1.0 / 23.0);
-    p = std::fma(p, z, 1.0 / 21.0);
-    p = std::fma(p, z, -1.0 / 19.0);
-    p = std::fma(p, z, 1.0 / 17.0);
-    p = std::fma(p, z, -1.0 / 15.0);
-    p = std::fma(p, z, 1.0 / 13.0);
-    p = std::fma(p, z, -1.0 / 11.0);
-    p = std::fma(p, z, 1.0 / 9.0);
-    p = std::fma(p, z, -1.0 / 7.0);
-    p = std::fma(p, z, 1.0 / 5.0);
-    p = std::fma(p, z, -1.0 / 3.0);
+    p = std::fma(p, z, SPX_K(1.0 / 37.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 35.0));
+    p = std::fma(p, z, SPX_K(1.0 / 33.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 31.0));
+    p = std::fma(p, z, SPX_K(1.0 / 29.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 27.0));
+    p = std::fma(p, z, SPX_K(1.0 / 25.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 23.0));
+    p = std::fma(p, z, SPX_K(1.0 / 21.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 19.0));
+    p = std::fma(p, z, SPX_K(1.0 / 17.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 15.0));
+    p = std::fma(p, z, SPX_K(1.0 / 13.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 11.0));
+    p = std::fma(p, z, SPX_K(1.0 / 9.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 7.0));
+    p = std::fma(p, z, SPX_K(1.0 / 5.0));
+    p = std::fma(p, z, SPX_K(-1.0 / 3.0));
     const double at = std::fma(t * z, p, t);
     // angle of (mx, mn) in [0, pi/4]
     double th = big ? kPi4Hi + (at + kPi4Lo) : at;
@@ -201,30 +218,30 @@ SPX_MATH_FN void expmap_cs(double z, double &cs, double &sc) {
     if (z <= 1.0) {
         // cos r = sum_k (-1)^k z^k / (2k)!, sin(r)/r = sum_k (-1)^k z^k / (2k+1)!, k <= 9
         double c = 1.0 / 6402373705728000.0;  // 1/18!
-        c = std::fma(c, z, -1.0 / 20922789888000.0);
-        c = std::fma(c, z, 1.0 / 87178291200.0);
-        c = std::fma(c, z, -1.0 / 479001600.0);
-        c = std::fma(c, z, 1.0 / 3628800.0);
-        c = std::fma(c, z, -1.0 / 40320.0);
-        c = std::fma(c, z, 1.0 / 720.0);
-        c = std::fma(c, z, -1.0 / 24.0);
-        c = std::fma(c, z, 0.5);
+        c = std::fma(c, z, SPX_K(-1.0 / 20922789888000.0));
+        c = std::fma(c, z, SPX_K(1.0 / 87178291200.0));
+        c = std::fma(c, z, SPX_K(-1.0 / 479001600.0));
+        c = std::fma(c, z, SPX_K(1.0 / 3628800.0));
+        c = std::fma(c, z, SPX_K(-1.0 / 40320.0));
+        c = std::fma(c, z, SPX_K(1.0 / 720.0));
+        c = std::fma(c, z, SPX_K(-1.0 / 24.0));
+        c = std::fma(c, z, SPX_K(0.5));
         cs = std::fma(-c, z, 1.0);
         double q = 1.0 / 121645100408832000.0;  // 1/19!
-        q = std::fma(q, z, -1.0 / 355687428096000.0);
-        q = std::fma(q, z, 1.0 / 1307674368000.0);
-        q = std::fma(q, z, -1.0 / 6227020800.0);
-        q = std::fma(q, z, 1.0 / 39916800.0);
-        q = std::fma(q, z, -1.0 / 362880.0);
-        q = std::fma(q, z, 1.0 / 5040.0);
-        q = std::fma(q, z, -1.0 / 120.0);
-        q = std::fma(q, z, 1.0 / 6.0);
+        q = std::fma(q, z, SPX_K(-1.0 / 355687428096000.0));
+        q = std::fma(q, z, SPX_K(1.0 / 1307674368000.0));
+        q = std::fma(q, z, SPX_K(-1.0 / 6227020800.0));
+        q = std::fma(q, z, SPX_K(1.0 / 39916800.0));
+        q = std::fma(q, z, SPX_K(-1.0 / 362880.0));
+        q = std::fma(q, z, SPX_K(1.0 / 5040.0));
+        q = std::fma(q, z, SPX_K(-1.0 / 120.0));
+        q = std::fma(q, z, SPX_K(1.0 / 6.0));
         sc = std::fma(-q, z, 1.0);
     } else {
         constexpr double kInvPi = 0x1.45f306dc9c883p-2;
         const double r = sqrt_pos(z);
         double sn;
-        sincospi_d(r * kInvPi, sn, cs);
+        sincospi_d<true>(r * kInvPi, sn, cs);
         sc = div_pos(sn, r);
     }
 }

@@ -30,17 +30,17 @@ namespace spx {
 // e^r - 1 for |r| <= ln 2 / 2 (plus rounding slack)
 SPX_MATH_FN double expm1_reduced(double r) {
     double q = 1.0 / 6227020800.0;     // 1/13!
-    q = std::fma(q, r, 1.0 / 479001600.0);
-    q = std::fma(q, r, 1.0 / 39916800.0);
-    q = std::fma(q, r, 1.0 / 3628800.0);
-    q = std::fma(q, r, 1.0 / 362880.0);
-    q = std::fma(q, r, 1.0 / 40320.0);
-    q = std::fma(q, r, 1.0 / 5040.0);
-    q = std::fma(q, r, 1.0 / 720.0);
-    q = std::fma(q, r, 1.0 / 120.0);
-    q = std::fma(q, r, 1.0 / 24.0);
-    q = std::fma(q, r, 1.0 / 6.0);
-    q = std::fma(q, r, 0.5);
+    q = std::fma(q, r, SPX_K(1.0 / 479001600.0));
+    q = std::fma(q, r, SPX_K(1.0 / 39916800.0));
+    q = std::fma(q, r, SPX_K(1.0 / 3628800.0));
+    q = std::fma(q, r, SPX_K(1.0 / 362880.0));
+    q = std::fma(q, r, SPX_K(1.0 / 40320.0));
+    q = std::fma(q, r, SPX_K(1.0 / 5040.0));
+    q = std::fma(q, r, SPX_K(1.0 / 720.0));
+    q = std::fma(q, r, SPX_K(1.0 / 120.0));
+    q = std::fma(q, r, SPX_K(1.0 / 24.0));
+    q = std::fma(q, r, SPX_K(1.0 / 6.0));
+    q = std::fma(q, r, SPX_K(0.5));
     return std::fma(r, r * q, r);
 }
 

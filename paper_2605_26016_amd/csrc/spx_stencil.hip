@@ -106,10 +106,11 @@ constexpr int zm_film_plane(int block, int rx, int ry) {
     return most;
 }
 
-// Wavefronts per SIMD of the film passes: a fourth spills 4 to 24 registers
-// (25 iterations of the twelve films below: 3182 us with it, 3139 without);
-// wider shapes stage more per thread.
-constexpr int film_waves(int kind) { return kind == SHAPE_SC_NN ? 3 : 1; }
+// Wavefronts per SIMD that the GNEB passes ask for: with the polynomials'
+// coefficients in scalar registers (spx_math.hpp) they fit three (161 registers
+// a lane, 219 before; 48^3 + 64^3 + 96^3 x 32 images, five iterations: 8510 us
+// with two, 7660 with three, 8150 with four, which spill).
+constexpr int zm_waves(int mode, int kind) { return zm_gneb(mode) && kind != SHAPE_SC_4SH ? 3 : 1; }
 
 constexpr int kMaxTensorBonds = 6;  // tensor couplings exist on the nearest-neighbour shape only
 
@@ -444,11 +445,11 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
     if constexpr (MODE == ZM_GNEB_C2) gs = gneb_scalars(g, gimg);
     // kDeep: the staged plane and the epilogue inputs are fetched two march
     // iterations ahead into two register sets, whose names stay static
-    // because the march loop is unrolled by two (passes whose iterations wait
-    // on memory longer than they compute; about 30 more registers, which the
-    // two-cell 4-shell shape does not have)
-    constexpr bool kDeep =
-        kPrefetch && NIN == 1 && (MODE == ZM_GNEB_A2 || MODE == ZM_GNEB_C2) && KIND != SHAPE_SC_4SH;
+    // because the march loop is unrolled by two (the pass whose iterations
+    // wait on memory longer than they compute; about 30 more registers, which
+    // the two-cell 4-shell shape does not have, and which would cost pass A2
+    // its third wavefront per SIMD)
+    constexpr bool kDeep = kPrefetch && NIN == 1 && MODE == ZM_GNEB_C2 && KIND != SHAPE_SC_4SH;
     constexpr int NSET = kDeep ? 2 : 1;
     double epi[NSET][kYB][NSUB][NE];
     auto fetch_epi = [&](int o, auto es) __attribute__((always_inline)) {
@@ -1224,8 +1225,8 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
 }
 
 template <int KIND, typename T, bool ISO, int MODE, int TXW>
-__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch(ZArgs g, Onsite os, HeunConst hc,
-                                                                 ZWeights<T, zm_weights<KIND, ISO>()> W) {
+__global__ __launch_bounds__(zm_block(MODE, KIND), zm_waves(MODE, KIND)) void k_zmarch(
+    ZArgs g, Onsite os, HeunConst hc, ZWeights<T, zm_weights<KIND, ISO>()> W) {
     zmarch_block<KIND, T, ISO, MODE, TXW>(g, os, hc, W, blockIdx.x, gridDim.x);
 }
 
@@ -1255,7 +1256,7 @@ __device__ __forceinline__ const ZBatchEntry &batch_entry(const ZBatchEntry *tab
 }
 
 template <int KIND, bool ISO, int MODE, int TXW>
-__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch_batch(const ZBatchEntry *tab, int n) {
+__global__ __launch_bounds__(zm_block(MODE, KIND), zm_waves(MODE, KIND)) void k_zmarch_batch(const ZBatchEntry *tab, int n) {
     const ZBatchEntry &en = batch_entry(tab, n);
     const unsigned b = blockIdx.x - en.block0, ntile = en.ntile;
     if (b >= ntile) return;  // padding between instances
@@ -1271,12 +1272,12 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_zmarch_batch(const ZBa
 // (three reads of every image), are those the thread holds for the march.
 // Only the bonds within the plane are summed.  The tile width is a run-time
 // value (2^g.ltx), so that films of different sizes share one launch.  Twelve
-// skyrmion films of 48^2 .. 96^2 x 32 images: 43 + 45 us a pass, where the z
-// march (three launches side by side, a third of each block's planes empty)
+// skyrmion films of 48^2 .. 96^2 x 32 images: 38 + 40 us a pass, where the z
+// march (three launches side by side, two of a block's three planes empty)
 // took 190 us for both; bound by the chain of an image's FP64 epilogue and two
-// barriers on three blocks per CU (a read of the images alone takes 20 us).
+// barriers on four blocks per CU (a read of the images alone takes 20 us).
 template <int KIND, bool ISO, int MODE>
-__global__ __launch_bounds__(zm_block(MODE, KIND), film_waves(KIND)) void k_gneb_film(
+__global__ __launch_bounds__(zm_block(MODE, KIND)) void k_gneb_film(
     const ZBatchEntry *tab, int n) {
     constexpr int NT = zm_block(MODE, KIND);
     constexpr int NB = ShapeC<KIND>::t.nb, RX = ShapeC<KIND>::t.rx, RY = ShapeC<KIND>::t.ry;
@@ -1870,8 +1871,8 @@ bool zmarch_gneb_film(const ZPlan &zp, const Grid &g) {
 }
 
 int zmarch_gneb_film_chunk(int64_t batch_columns, int n_img) {
-    // three blocks per CU; two images' reads before the first sum
-    return zchunk_rule(batch_columns, n_img, 3 * device_cus(), 2, 32, INT64_MAX);
+    // four blocks per CU (LDS); two images' reads before the first sum
+    return zchunk_rule(batch_columns, n_img, 4 * device_cus(), 2, 32, INT64_MAX);
 }
 
 size_t zmarch_gneb_entry_bytes() { return sizeof(ZBatchEntry); }
