@@ -131,17 +131,17 @@ bool zmarch_gneb_film(const ZPlan &zp, const Grid &g);
 int zmarch_gneb_film_chunk(int64_t batch_columns, int n_img);
 // The two passes of a GNEB iteration that stores no force (see spx_stencil.hip
 // ZM_GNEB_A2 / ZM_GNEB_C2), over the images of one instance.  pass 0: every
-// image, eleven partials per tile into partial[(item0 + n items_per_img +
+// image, eleven partials per tile into partial[(part0 + n parts_per_img +
 // tile) * 11 + v] (energy, squared distance to the next image, a.a, a.b, b.b,
 // F.a, F.b, v.a, v.b, v.F, F.F); pass 1: interior images, the update into the
 // other buffer and velocities, one max |F_gneb| per tile into
-// partial[(item0 + n items_per_img + tile) * 11].  Reads the current buffer (Y0, or Y1
+// partial[(part0 + n parts_per_img + tile) * 11].  Reads the current buffer (Y0, or Y1
 // when *cur != 0); no-op when *done != 0.  FP64 plans only.
 struct GnebSlots {
     int n, wp, wm, tn, coef, proj;
 };
 struct GnebPassArgs {
-    int n_img, item0, items_per_img;
+    int n_img, part0, parts_per_img;
     double *Y0, *Y1, *V;
     const double *cur, *done;
     const double *img, *st;

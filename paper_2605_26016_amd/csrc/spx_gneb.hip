@@ -61,8 +61,9 @@ constexpr int kMaxImages = 4096;  // images per instance (arc-length table in LD
 enum { IS_E = 0, IS_D2, IS_AA, IS_AB, IS_BB, IS_FA, IS_FB, IS_VA, IS_VB, IS_VF, IS_FF, IS_TT, IS_FT, IS_VT, IS_COEF,
        IS_TN, IS_WP, IS_WM, IS_RD2, IS_RK, IS_RF, IS_FM, IS_N };
 constexpr int kPassA2Values = IS_FF - IS_E + 1;
-// Partial values of item or tile k start at partial[k * kPS] for every pass,
-// so passes of different instances that run at the same time never overlap.
+// The values of partial set k (an item's or a tile's) start at partial[k * kPS]
+// for every pass, so passes of different instances that run at the same time
+// never overlap.
 constexpr int kPS = kPassA2Values;
 // per-instance state (ST_RDONE: the reparameterisation has seen ST_DONE)
 enum { ST_PROJ = 0, ST_MAXF, ST_CI, ST_CION, ST_ITER, ST_DONE, ST_CUR, ST_RDONE, ST_N };
@@ -76,6 +77,9 @@ struct GInst {
     int n_img;
     int item0;            // first item (all images) of this instance
     int items_per_img;
+    // partial sets: img n's start at part0 + n parts_per_img, which is the
+    // larger of its items and its tiles
+    int part0, parts_per_img;
     double *Y[2];         // image buffers [n_img][3][N]; Y[0] is the caller's
     double *V;            // velocities
     double *F;            // projected physical force, then nothing else
@@ -88,14 +92,18 @@ struct GInst {
     // ([n_img][3][N], FP64); NULL: pass A gathers the neighbours itself
     const double *Bbil;
     // > 0: the instance runs the two z-march passes, which leave one partial
-    // set per tile (this many per image) in the image's first item slots; the
-    // item passes skip it
+    // set per tile (this many per image); the item passes skip it
     int zt_per_img;
 };
 
 struct GItem {
     int inst, img, site0, pad;
 };
+
+// partial set of an item
+__device__ __forceinline__ size_t item_part(const GInst &G, const GItem &itm) {
+    return (size_t)G.part0 + (size_t)itm.img * G.parts_per_img + itm.site0 / kGB;
+}
 
 // NT: threads of the block
 template <int NT = kGB>
@@ -240,8 +248,8 @@ __global__ __launch_bounds__(kGB) void k_gneb_a(const GInst *__restrict__ inst, 
         const double es = block_sum(e, red);
         const double ds = block_sum(d2, red);
         if (threadIdx.x == 0) {
-            partial[(size_t)it * kPS] = es;
-            partial[(size_t)it * kPS + 1] = ds;
+            partial[item_part(G, itm) * kPS] = es;
+            partial[item_part(G, itm) * kPS + 1] = ds;
         }
     }
 }
@@ -292,7 +300,7 @@ __global__ __launch_bounds__(kGB) void k_gneb_reduce(const GInst *__restrict__ i
     const bool tiles = G.zt_per_img > 0 && !items_only;
     const int nv = tiles ? nv_tiles : nv_items;
     if (nv == 0) return;
-    const int first = G.item0 + ii.y * G.items_per_img;
+    const int first = G.part0 + ii.y * G.parts_per_img;
     const int count = tiles ? G.zt_per_img : G.items_per_img;
     for (int v = 0; v < nv; ++v) {
         double s = 0.0;
@@ -406,7 +414,7 @@ __global__ __launch_bounds__(kGB) void k_gneb_b(const GInst *__restrict__ inst, 
         }
         for (int q = 0; q < 5; ++q) {
             const double r = block_sum(v5[q], red);
-            if (threadIdx.x == 0) partial[(size_t)it * kPS + q] = r;
+            if (threadIdx.x == 0) partial[item_part(G, itm) * kPS + q] = r;
         }
     }
 }
@@ -475,7 +483,7 @@ __global__ __launch_bounds__(kFoldB) void k_gneb_mid(const GInst *__restrict__ i
         const int p = b + threadIdx.x / L, n = p / kPassA2Values, q = p - n * kPassA2Values;
         double t = 0.0;
         if (p < nsum) {
-            const double *src = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS + q;
+            const double *src = partial + (size_t)(G.part0 + n * G.parts_per_img) * kPS + q;
 #pragma unroll 4
             for (int k = threadIdx.x & (L - 1); k < G.zt_per_img; k += L) t += src[(size_t)k * kPS];
         }
@@ -547,7 +555,7 @@ __global__ __launch_bounds__(kGB) void k_gneb_c(const GInst *__restrict__ inst, 
             }
         }
         const double r = block_max(fm, red);
-        if (threadIdx.x == 0) partial[(size_t)it * kPS] = r;
+        if (threadIdx.x == 0) partial[item_part(G, itm) * kPS] = r;
     }
 }
 
@@ -581,7 +589,7 @@ __global__ __launch_bounds__(kFoldB) void k_gneb_end(const GInst *__restrict__ i
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double m = 0.0;
     for (int n = 1 + wave; n + 1 < G.n_img; n += kFoldB / 64) {
-        const double *p = partial + (size_t)(G.item0 + n * G.items_per_img) * kPS;
+        const double *p = partial + (size_t)(G.part0 + n * G.parts_per_img) * kPS;
         double t = 0.0;
         for (int k = lane; k < G.zt_per_img; k += 64) t = fmax(t, p[(size_t)k * kPS]);
         t = wave_max(t);
@@ -665,7 +673,7 @@ __global__ __launch_bounds__(kGB) void k_gneb_rdist(const GInst *__restrict__ in
             }
         }
         const double ds = block_sum(d2, red);
-        if (threadIdx.x == 0) partial[(size_t)it * kPS] = ds;
+        if (threadIdx.x == 0) partial[item_part(G, itm) * kPS] = ds;
     }
 }
 
@@ -836,8 +844,8 @@ GnebPassArgs pass_args(const spx_gneb *g, int k) {
     const GInst &G = g->hinst[k];
     GnebPassArgs a{};
     a.n_img = G.n_img;
-    a.item0 = G.item0;
-    a.items_per_img = G.items_per_img;
+    a.part0 = G.part0;
+    a.parts_per_img = G.parts_per_img;
     a.Y0 = G.Y[0];
     a.Y1 = G.Y[1];
     a.V = G.V;
@@ -1074,7 +1082,15 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
             }
             g->zplan[k].zauto = 0;
         }
-        if (zp.valid && zp.prec == 0 && zmarch_gneb_tiles(zp, gi.g) <= gi.items_per_img) {
+        // The two passes (4 launches an iteration where the item passes take
+        // 11) where the tiles hold at most four times the sites, or are as few
+        // as the items.  Six films of 34 to 95 cells x 15 images, whose tiles
+        // are more than their items: 129 us an iteration by items, 49 by the
+        // passes; a rod of 2 x 2 x 20000 cells, 4 of a tile's 256 lanes: 555 us
+        // by items, 1383 by the passes.
+        if (zp.valid && zp.prec == 0 &&
+            (zmarch_gneb_tiles(zp, gi.g) <= gi.items_per_img ||
+             zmarch_gneb_columns(zp, gi.g) * kGB <= 4 * (int64_t)gi.g.Lx * gi.g.Ly)) {
             gi.zt_per_img = zmarch_gneb_tiles(zp, gi.g);  // the two z-march passes; no stored force
         } else {
             g->zplan[k].txw = 64;
@@ -1085,6 +1101,13 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
                 break;
         }
     }
+    int64_t parts = 0;
+    for (GInst &gi : g->hinst) {
+        gi.parts_per_img = std::max(gi.items_per_img, gi.zt_per_img);
+        gi.part0 = (int)parts;
+        parts += (int64_t)gi.parts_per_img * gi.n_img;
+    }
+    if (s == SPX_OK && parts > INT32_MAX / 8) s = set_error(SPX_ERR_INVALID_ARG, "too many GNEB work items");
     g->fold = true;
     for (int k = 0; k < n_inst && s == SPX_OK; ++k) {
         const GInst &gi = g->hinst[k];
@@ -1112,7 +1135,7 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_items, sizeof(GItem) * items.size(), "GNEB items");
     if (s == SPX_OK) s = gneb_alloc(g, (void **)&g->d_imgs, sizeof(int2) * imgs.size(), "GNEB image list");
     if (s == SPX_OK)
-        s = gneb_alloc(g, (void **)&g->d_partial, sizeof(double) * kPassA2Values * items.size(), "GNEB partials");
+        s = gneb_alloc(g, (void **)&g->d_partial, sizeof(double) * kPassA2Values * parts, "GNEB partials");
     for (int k = 0; k < n_inst; ++k) g->max_img = std::max(g->max_img, n_img[k]);
     if (s == SPX_OK &&
         hipHostMalloc((void **)&g->h_stats, sizeof(double) * (ST_N + IS_N * (size_t)g->max_img), 0) != hipSuccess) {

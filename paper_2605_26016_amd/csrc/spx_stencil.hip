@@ -151,7 +151,7 @@ struct ZArgs {
     // ZM_MIN_FORCE: force [3][N]; partials of the modes that reduce per tile
     double *gF;
     double *gpart;
-    int gitem0, gipi;
+    int gpart0, gppi;
     // ZM_MIN_FORCE (force in gF, partials [tile][6] in gpart): the method's
     // velocity (0) or previous step and force (1, 2), the L-BFGS history
     // rings and the minimiser state (candidate slot)
@@ -1196,7 +1196,7 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
     if constexpr (zm_gneb(MODE)) {
         // A2: energy, squared distance and the nine image sums, C2: max
         // |F_gneb|, one set per tile
-        double *const set = g.gpart + ((size_t)g.gitem0 + (size_t)gimg * g.gipi + stile) * 11;
+        double *const set = g.gpart + ((size_t)g.gpart0 + (size_t)gimg * g.gppi + stile) * 11;
         if constexpr (MODE == ZM_GNEB_A2) {
             __syncthreads();  // every thread's column is final
             gneb_tile_sums<kThreads>(gacc, set);
@@ -1416,7 +1416,7 @@ __global__ __launch_bounds__(zm_block(MODE, KIND)) void k_gneb_film(
                 if constexpr (MODE == ZM_GNEB_A2) red[k * NT + threadIdx.x] = t;
                 else f2 = t;
             });
-        double *const set = g.gpart + ((size_t)g.gitem0 + (size_t)m * g.gipi + stile) * 11;
+        double *const set = g.gpart + ((size_t)g.gpart0 + (size_t)m * g.gppi + stile) * 11;
         if constexpr (MODE == ZM_GNEB_C2) gneb_wave_max(f2, red);
         __syncthreads();  // the plane has been read, the sums are written
         if (m + 1 < m1) {
@@ -1879,7 +1879,7 @@ size_t zmarch_gneb_entry_bytes() { return sizeof(ZBatchEntry); }
 
 bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &os, const GnebPassArgs &ga,
                        unsigned block0, void *entry, unsigned *blocks) {
-    if (zp.prec != 0 || ga.n_img < 3 || zmarch_gneb_tiles(zp, g) > ga.items_per_img) return false;
+    if (zp.prec != 0 || ga.n_img < 3 || zmarch_gneb_tiles(zp, g) > ga.parts_per_img) return false;
     ZBatchEntry en;
     std::memset(&en, 0, sizeof(en));
     ZArgs &a = en.a;
@@ -1905,8 +1905,8 @@ bool zmarch_gneb_entry(int pass, const ZPlan &zp, const Grid &g, const Onsite &o
     a.gmass = ga.mass;
     a.gstring = ga.string;
     a.gpart = ga.partial;
-    a.gitem0 = ga.item0;
-    a.gipi = ga.items_per_img;
+    a.gpart0 = ga.part0;
+    a.gppi = ga.parts_per_img;
     a.imgfast = 1;
     a.xcd = 1;
     en.os = os;
