@@ -781,7 +781,8 @@ struct spx_gneb {
     float *d_tvals = nullptr;   // reaction coordinates for the learned init
     int max_img = 0;
     double *h_stats = nullptr;  // pinned: one instance's state and image statistics
-    hipGraphExec_t graph = nullptr;
+    hipGraphExec_t graph[2] = {nullptr, nullptr};  // one iteration, and kGraphIters of them
+    int64_t iters = 0;  // iterations asked for
     hipStream_t cap_stream = nullptr;  // library-owned capture stream (the caller's may be the null stream)
     int use_graph = 1;
     // Two-pass instances of one kernel (shape, isotropy, tile width) share its
@@ -818,9 +819,22 @@ spx_status gneb_alloc(spx_gneb *g, void **p, size_t bytes, const char *what) {
     return SPX_OK;
 }
 
+// Iterations in the longer of the two captured graphs.  Between two graph
+// launches the device waits 8 us, between two kernels of one graph not at all
+// (films of 100 us an iteration).
+// Capturing the long one costs about 0.6 ms, so it waits until the handle has
+// been asked for kLongAfter iterations.
+constexpr int kGraphIters = 8;
+constexpr int kLongAfter = 128;
+void gneb_drop_graphs(spx_gneb *g) {
+    for (hipGraphExec_t &x : g->graph) {
+        if (x) (void)hipGraphExecDestroy(x);
+        x = nullptr;
+    }
+}
+
 void gneb_free(spx_gneb *g) {
-    if (g->graph) (void)hipGraphExecDestroy(g->graph);
-    g->graph = nullptr;
+    gneb_drop_graphs(g);
     if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
     g->cap_stream = nullptr;
     for (hipStream_t s : g->side)
@@ -1238,10 +1252,13 @@ spx_status spx_gneb_step(spx_gneb *g, int32_t n_iter, void *stream) {
     if (n_iter < 0) return set_error(SPX_ERR_INVALID_ARG, "n_iter < 0");
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    if (g->use_graph && n_iter > 1 && !g->graph) {
-        // One iteration captured once on a private stream; the graph is then
-        // launched on whatever stream the caller passes.  Capture failure
-        // (graphs unsupported) leaves direct launches in place.
+    const bool want[2] = {n_iter > 1 && !g->graph[0], n_iter >= kGraphIters && !g->graph[1] && g->iters + n_iter >= kLongAfter};
+    g->iters += n_iter;
+    if (g->use_graph && (want[0] || want[1])) {
+        // One iteration, and a run of kGraphIters once kLongAfter are reached,
+        // captured once on a private stream; the graphs are then launched on
+        // whatever stream the caller passes.  Capture failure (graphs unsupported) leaves direct
+        // launches in place.
         if (!g->cap_stream) e = hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking);
         // two to kMaxBranches units of a pass become parallel branches
         // (streams and events of default priority, made once)
@@ -1258,29 +1275,35 @@ spx_status spx_gneb_step(spx_gneb *g, int32_t n_iter, void *stream) {
             for (int p = 0; p < 2 && e == hipSuccess; ++p)
                 e = hipEventCreateWithFlags(&g->fork_ev[p], hipEventDisableTiming);
         }
-        hipGraph_t graph;
-        if (e == hipSuccess) e = hipStreamBeginCapture(g->cap_stream, hipStreamCaptureModeThreadLocal);
-        if (e == hipSuccess) {
+        for (int q = 0; q < 2 && e == hipSuccess; ++q) {
+            if (!want[q]) continue;
+            hipGraph_t graph;
+            e = hipStreamBeginCapture(g->cap_stream, hipStreamCaptureModeThreadLocal);
+            if (e != hipSuccess) break;
             g->branch = branches;
-            hipError_t e2 = enqueue_iteration(g, g->cap_stream);
+            hipError_t e2 = hipSuccess;
+            for (int it = 0; it < (q ? kGraphIters : 1) && e2 == hipSuccess; ++it)
+                e2 = enqueue_iteration(g, g->cap_stream);
             g->branch = false;
             e = hipStreamEndCapture(g->cap_stream, &graph);
             if (e == hipSuccess) e = e2;
             if (e == hipSuccess) {
-                e = hipGraphInstantiate(&g->graph, graph, nullptr, nullptr, 0);
+                e = hipGraphInstantiate(&g->graph[q], graph, nullptr, nullptr, 0);
                 (void)hipGraphDestroy(graph);
             }
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
-            g->graph = nullptr;
+            gneb_drop_graphs(g);
             g->use_graph = 0;
             e = hipSuccess;
         }
     }
-    for (int it = 0; it < n_iter && e == hipSuccess; ++it) {
-        if (g->graph) e = hipGraphLaunch(g->graph, st);
+    for (int it = 0; it < n_iter && e == hipSuccess;) {
+        const bool run = g->graph[1] && n_iter - it >= kGraphIters;
+        if (g->graph[0]) e = hipGraphLaunch(g->graph[run ? 1 : 0], st);
         else e = enqueue_iteration(g, st);
+        it += run ? kGraphIters : 1;
     }
     if (e == hipSuccess) {
         k_gneb_copyback<<<grid_for(g->n_items), kGB, 0, st>>>(g->d_inst, g->d_items, g->n_items);
@@ -1360,9 +1383,8 @@ spx_status spx_gneb_set_params(spx_gneb *g, const spx_gneb_params *p, void *stre
         gi.ci_on_below = p->ci_on_below;
         gi.tol = p->tol_force;
     }
-    // the iteration graph depends on whether any instance runs the string method
-    if (g->graph) (void)hipGraphExecDestroy(g->graph);
-    g->graph = nullptr;
+    // the iteration graphs depend on whether any instance runs the string method
+    gneb_drop_graphs(g);
     hipError_t e = hipMemcpyAsync(g->d_inst, g->hinst.data(), sizeof(GInst) * g->n_inst, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) {
         k_gneb_reset<<<(g->n_inst + 63) / 64, 64, 0, st>>>(g->d_inst, g->n_inst);
@@ -1381,10 +1403,7 @@ spx_status spx_gneb_set_params(spx_gneb *g, const spx_gneb_params *p, void *stre
 spx_status spx_gneb_set_graph(spx_gneb *g, int32_t enable) {
     if (!handle_alive(g)) return set_error(SPX_ERR_BAD_HANDLE, "invalid spx_gneb handle");
     g->use_graph = enable ? 1 : 0;
-    if (!enable && g->graph) {
-        (void)hipGraphExecDestroy(g->graph);
-        g->graph = nullptr;
-    }
+    if (!enable) gneb_drop_graphs(g);
     return SPX_OK;
 }
 

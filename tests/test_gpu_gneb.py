@@ -286,3 +286,31 @@ def test_gneb_films_match_oracle(couplings, ci_mode):
             np.testing.assert_allclose(s["dist"], dist, rtol=1e-10, atol=1e-10)
             np.testing.assert_allclose(s["max_force"], fmax, rtol=1e-9)
             assert s["ci_index"] == ci and s["iterations"] == it + 1
+
+
+@pytest.mark.parametrize("ci_mode", [1, 4], ids=["climbing", "string"])
+def test_gneb_long_graph_equals_single_steps(ci_mode):
+    # from 128 iterations of a handle on, calls of eight or more replay a graph
+    # of eight and single ones for the rest: bit for bit the direct launches,
+    # with the program's own work between the replays
+    import torch
+    from paper_2605_26016_amd import spx
+    cases = [(frustrated((17, 9, 1), periodic=(1, 1, 0)), 5, 31), (frustrated((6, 6, 4)), 4, 32),
+             (frustrated((2, 2, 40)), 4, 33)]
+    bufs, handles = ([], []), []
+    for b in bufs:
+        for w, n_img, seed in cases:
+            b.append(to_dev(oracle.geodesic_path(random_sphere(w.N, seed), random_sphere(w.N, seed + 100), n_img)))
+        handles.append(spx.gneb_create([gpu_hamiltonian(w) for w, _, _ in cases], b, ci_mode=ci_mode,
+                                       ci_on_below=3.0, vp_dt=0.02))
+    done = 0
+    for n in (120, 8, 7, 21, 40, 1, 17):
+        spx.gneb_step(handles[0], n)
+        for _ in range(n):
+            spx.gneb_step(handles[1], 1)
+        done += n
+        torch.cuda.synchronize()
+        for k, (x, y) in enumerate(zip(*bufs)):
+            assert torch.equal(x, y), (done, k)
+            assert float(x.square().sum(1).sub(1.0).abs().max()) < 1e-12
+            assert spx.gneb_get_stats(handles[0], k)["iterations"] == done
