@@ -40,6 +40,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kDX = 10;   // output x per tile
 constexpr int kDY = 32;   // output y per tile (MFMA rows)
@@ -75,7 +77,8 @@ __device__ __forceinline__ short to16(float v) {
 //   j = 0..7, and accumulator r of lane l is D[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 __device__ __forceinline__ int d_row(int lane, int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
-template <bool BF16>
+// NARROW: a component is below 4 GiB, so that byte offsets fit 32 bits.
+template <bool BF16, bool NARROW>
 __global__ __launch_bounds__(kThreadsD) void k_dense_mfma(const double *__restrict__ S, float *__restrict__ b,
                                                     const s16x8 *__restrict__ wfrag, float kscale, float in_scale,
                                                     Grid g, Onsite os) {
@@ -96,12 +99,19 @@ __global__ __launch_bounds__(kThreadsD) void k_dense_mfma(const double *__restri
     const int64_t N = g.N;
     // Stage the input tile (zero outside open faces, wrapped on periodic
     // axes).  The wrapped coordinate of each of the kIX + kIY + kIZ input
-    // lines is computed once (-1 outside an open face).  16 consecutive
-    // lanes then read the 16 x of one input line (one cache-line run per line
-    // and component), kU elements per thread at a time, with every global
-    // load of a batch issued before the first is consumed (masked sites load
-    // site 0 and store zero), so a block waits for memory a few times rather
-    // than once per element.
+    // lines is computed once (-1 outside an open face).  8 consecutive lanes
+    // take the 16 x of one input line, two neighbours each, and go from line
+    // to line, so a thread's x stay the same and one address serves six
+    // values; kU lines at a time, with every global load of a batch issued
+    // before the first is consumed (masked sites load site 0 and store zero),
+    // so a block waits for memory a few times rather than once per line.  What
+    // bounds the kernel is the cache's line rate for these loads and for the
+    // stores, between matrix phases (102 us of them in all) that only a second
+    // block per CU overlaps: a thread's two x in one 16-byte load, and the
+    // stores at uniform steps from one address, took 256^3 in BF16 from 401
+    // to 347 us (two 8-byte loads 404, and 376 before the stores).  Weights
+    // shared less (2 planes a wave) 420, more with half the waves (8 planes)
+    // 552.
     __shared__ int lines[kIX + kIY + kIZ];
     if (threadIdx.x < kIX + kIY + kIZ) {
         const int t = threadIdx.x;
@@ -114,35 +124,65 @@ __global__ __launch_bounds__(kThreadsD) void k_dense_mfma(const double *__restri
     }
     __syncthreads();
     {
-        constexpr int kElems = kIZ * kIY * kIX;
-        constexpr int kU = 16;
-        const int *cx = lines, *cy = lines + kIX, *cz = lines + kIX + kIY;
+        using Index = std::conditional_t<NARROW, ByteOffset, int64_t>;
+        constexpr int kLines = kIZ * kIY, kStep = kThreadsD / (kIX / 2), kU = 7;
+        const int *cy = lines + kIX, *cz = lines + kIX + kIY;
+        const int xx = 2 * (threadIdx.x % (kIX / 2));
+        const int gx[2] = {lines[xx], lines[xx + 1]};
+        auto stage = [&](auto pair) __attribute__((always_inline)) {
+            constexpr bool PAIR = decltype(pair)::value;
 #pragma unroll 1
-        for (int e0 = threadIdx.x; e0 < kElems; e0 += kU * kThreadsD) {
-            double v[kU][3];
+        for (int l0 = threadIdx.x / (kIX / 2); l0 < kLines; l0 += kU * kStep) {
+            double v[kU][2][3];
             unsigned okm = 0;
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                const int q = min(e0 + u * kThreadsD, kElems - 1);
-                const int xx = q & (kIX - 1), yz = q / kIX;
-                const int gx = cx[xx], gy = cy[yz % kIY], gz = cz[yz / kIY];
-                const bool ok = (gx | gy | gz) >= 0;
-                okm |= (ok ? 1u : 0u) << u;
-                const int64_t j = ok ? gx + (int64_t)g.Lx * (gy + (int64_t)g.Ly * gz) : 0;
+                const int l = min(l0 + u * kStep, kLines - 1);
+                const int gy = cy[l % kIY], gz = cz[l / kIY];
+                const bool oky = (gy | gz) >= 0;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) v[u][c] = S[c * N + j];
+                for (int h = 0; h < 2; ++h) {
+                    const bool ok = oky && gx[h] >= 0;
+                    okm |= (ok ? 1u : 0u) << (2 * u + h);
+                    Index j;
+                    if constexpr (NARROW)
+                        j = {ok ? ((unsigned)gx[h] + (unsigned)g.Lx * ((unsigned)gy + (unsigned)g.Ly * (unsigned)gz)) *
+                                      (unsigned)sizeof(double)
+                                : 0u};
+                    else
+                        j = ok ? gx[h] + (int64_t)g.Lx * (gy + (int64_t)g.Ly * gz) : 0;
+                    if constexpr (PAIR) {
+                        if (h == 0)
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) {
+                                const f64x2 t = *reinterpret_cast<const f64x2 *>(elem(S + c * N, j));
+                                v[u][0][c] = t[0];
+                                v[u][1][c] = t[1];
+                            }
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) v[u][h][c] = *elem(S + c * N, j);
+                    }
+                }
             }
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                const int q = e0 + u * kThreadsD;
-                if (q >= kElems) break;
-                const int xx = q & (kIX - 1), yz = q / kIX;
-                const int yy = yz % kIY, zz = yz / kIY;
+                const int l = l0 + u * kStep;
+                if (l >= kLines) break;
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    tile[c][zz][yy][xx] = to16<BF16>((okm >> u) & 1u ? (float)v[u][c] * in_scale : 0.0f);
+                for (int c = 0; c < 3; ++c) {
+                    s16x2 t;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        t[h] = to16<BF16>((okm >> (2 * u + h)) & 1u ? (float)v[u][h][c] * in_scale : 0.0f);
+                    *reinterpret_cast<s16x2 *>(&tile[c][0][0][0] + l * kIX + xx) = t;
+                }
             }
         }
+        };
+        // away from the x faces a thread's two x are neighbours in memory
+        if (x0 >= kR && x0 + kDX + kR <= g.Lx) stage(std::true_type{});
+        else stage(std::false_type{});
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -194,22 +234,26 @@ __global__ __launch_bounds__(kThreadsD) void k_dense_mfma(const double *__restri
     if (col >= 3 * kDX) return;
     const int alpha = col / kDX, x = x0 + col % kDX;
     if (x >= g.Lx) return;
+    // element of the lane's first row; the others are uniform steps away
+    const int yl = y0 + d_row(lane, 0);
+    const int64_t i0 = x + (int64_t)g.Lx * (yl + (int64_t)g.Ly * (z0 + zl0));
+    float *const out = b + alpha * N;
+    const double bz = os.bz[0][alpha];
 #pragma unroll
     for (int p = 0; p < kPW; ++p) {
-        const int z = z0 + zl0 + p;
-        if (z >= g.Lz) continue;
+        if (z0 + zl0 + p >= g.Lz) continue;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int y = y0 + d_row(lane, r);
-            if (y >= g.Ly) continue;
-            const int64_t i = x + (int64_t)g.Lx * (y + (int64_t)g.Ly * z);
+            const int dy = d_row(0, r);
+            if (yl + dy >= g.Ly) continue;
+            const int64_t i = i0 + (int64_t)g.Lx * (dy + (int64_t)g.Ly * p);
             const float v = acc[p][r] * kscale;
             double ba[3] = {0.0, 0.0, 0.0};
             if (os.n_aniso > 0) {  // the spin is read only when an anisotropy needs it
                 const double s[3] = {S[i], S[N + i], S[2 * N + i]};
                 aniso_field(os, 0, s, ba);
             }
-            b[alpha * N + i] = (float)((double)v + ba[alpha] + os.bz[0][alpha]);
+            out[i] = (float)((double)v + ba[alpha] + bz);
         }
     }
 }
@@ -478,10 +522,12 @@ hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, cons
     }
     const unsigned grid =
         (unsigned)((g.Lx + kDX - 1) / kDX) * (unsigned)((g.Ly + kDY - 1) / kDY) * (unsigned)((g.Lz + kDZ - 1) / kDZ);
-    if (p->bf16)
-        k_dense_mfma<true><<<grid, kThreadsD, 0, st>>>(S, b, (const s16x8 *)p->d_frag, p->kscale, p->in_scale, g, os);
-    else
-        k_dense_mfma<false><<<grid, kThreadsD, 0, st>>>(S, b, (const s16x8 *)p->d_frag, p->kscale, p->in_scale, g, os);
+    auto go = [&](auto kernel) {
+        kernel<<<grid, kThreadsD, 0, st>>>(S, b, (const s16x8 *)p->d_frag, p->kscale, p->in_scale, g, os);
+    };
+    const bool narrow = g.N <= (int64_t)(UINT32_MAX / sizeof(double));
+    if (p->bf16) narrow ? go(k_dense_mfma<true, true>) : go(k_dense_mfma<true, false>);
+    else narrow ? go(k_dense_mfma<false, true>) : go(k_dense_mfma<false, false>);
     return hipGetLastError();
 }
 

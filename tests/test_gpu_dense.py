@@ -135,3 +135,16 @@ def test_dense_mfma_256_slabs(prec, rnd):
         err = max_rel(got, ref)
         print(f"{prec} 256^3 planes {z0}..{z0 + nz - 1}: max-rel vs emulated oracle {err:.2e}", flush=True)
         assert err <= 1e-5
+
+
+@pytest.mark.parametrize("prec,rnd", [("bf16", round_bf16), ("fp16", round_fp16)])
+@pytest.mark.parametrize("per", [(0, 0, 0), (1, 0, 1)], ids=["open", "mixed"])
+@pytest.mark.parametrize("L", [(12, 31, 5), (22, 33, 17), (24, 7, 15), (33, 32, 1)], ids=lambda L: "x".join(map(str, L)))
+def test_dense_mfma_at_paired_load_edges(L, per, prec, rnd):
+    # a tile of 10 x that reaches 3 to each side loads neighbouring x in pairs
+    # where all 16 lie in the lattice (23 x or more): one x short of it, one
+    # beyond, no such tile, several; the tolerance of the tests above
+    got, S, lat, (ab, dl, J) = dense_case(L, per, prec)
+    Je, Se = emulated(prec, rnd, J, S)
+    ref = oracle.field(oracle.Model(lat, bonds=(ab[:, 0], ab[:, 1], dl, Je), B=(0, 0, 0.5)), Se)
+    assert max_rel(got, ref) <= 1e-5, max_rel(got, ref)
