@@ -15,6 +15,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "spx_device.hpp"
@@ -86,32 +87,56 @@ __device__ __forceinline__ void pl_bil(const PlView &v, const double *__restrict
     const int64_t N = v.N;
     AccT acc[3] = {AccT(0), AccT(0), AccT(0)};
     const int64_t p0 = v.row[i], p1 = v.row[i + 1];
-    // unrolled so that several entries' index loads, and then their spin
-    // loads, are in flight together instead of one dependent pair per entry;
-    // six deep (timed on sc 200^3 nearest-neighbour rows of six: FP32 field
-    // 220 -> 208 us and FP64 294 -> 248 us against four deep; eight deep
-    // was slower than four), other row lengths finish in the remainder loop
-#pragma unroll 6
-    for (int64_t p = p0; p < p1; ++p) {
-        const int64_t j = v.col[p];
-        const AccT s0 = (AccT)S[j], s1 = (AccT)S[N + j], s2 = (AccT)S[2 * N + j];
-        if constexpr (TENSOR) {
-            AccT J[9];
+    // Entries go in chunks whose index loads, and then their spin loads, are
+    // in flight together instead of one dependent pair per entry: six deep
+    // (timed on sc 200^3 nearest-neighbour rows of six: FP32 field 220 -> 208
+    // us and FP64 294 -> 248 us against four deep; eight deep was slower than
+    // four).  The last one to five of a row are one chunk too, with the index
+    // clamped to the row and the sum kept where there is no entry: a serial
+    // remainder loop, one dependent pair of loads after another, is what
+    // irregular rows spent their time in (800,000 sites with 4.8 entries on
+    // average, FP32: 41 -> 33 us a Heun stage with one site per thread).
+    constexpr int kDeep = 6;
+    auto chunk = [&](int64_t p, auto nc, auto masked) __attribute__((always_inline)) {
+        constexpr int n = decltype(nc)::value;
+        constexpr bool M = decltype(masked)::value;
+        int64_t q[n];
+        AccT s[n][3], Js[n];
 #pragma unroll
-            for (int e = 0; e < 9; ++e) {
-                if constexpr (sizeof(AccT) == 4) J[e] = v.Jf[9 * p + e]; else J[e] = v.Jd[9 * p + e];
+        for (int u = 0; u < n; ++u) q[u] = M ? (p + u < p1 ? p + u : p1 - 1) : p + u;
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            const int64_t j = v.col[q[u]];
+            if constexpr (!TENSOR) {
+                if constexpr (sizeof(AccT) == 4) Js[u] = v.Jf[q[u]]; else Js[u] = v.Jd[q[u]];
             }
-            acc[0] += J[0] * s0 + J[1] * s1 + J[2] * s2;
-            acc[1] += J[3] * s0 + J[4] * s1 + J[5] * s2;
-            acc[2] += J[6] * s0 + J[7] * s1 + J[8] * s2;
-        } else {
-            AccT J;
-            if constexpr (sizeof(AccT) == 4) J = v.Jf[p]; else J = v.Jd[p];
-            acc[0] += J * s0;
-            acc[1] += J * s1;
-            acc[2] += J * s2;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) s[u][c] = (AccT)S[c * N + j];
         }
-    }
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            AccT t[3];
+            if constexpr (TENSOR) {
+                AccT J[9];
+#pragma unroll
+                for (int e = 0; e < 9; ++e) {
+                    if constexpr (sizeof(AccT) == 4) J[e] = v.Jf[9 * q[u] + e]; else J[e] = v.Jd[9 * q[u] + e];
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    t[c] = acc[c] + (J[3 * c] * s[u][0] + J[3 * c + 1] * s[u][1] + J[3 * c + 2] * s[u][2]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) t[c] = acc[c] + Js[u] * s[u][c];
+            }
+            const bool ok = !M || p + u < p1;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc[c] = ok ? t[c] : acc[c];
+        }
+    };
+    int64_t p = p0;
+    for (; p + kDeep <= p1; p += kDeep) chunk(p, std::integral_constant<int, kDeep>{}, std::false_type{});
+    if (p < p1) chunk(p, std::integral_constant<int, kDeep - 1>{}, std::true_type{});
     for (int c = 0; c < 3; ++c) out[c] = (double)acc[c];
 }
 
@@ -148,39 +173,41 @@ struct PlHeun {
 };
 
 // stage 0: S~ = N[S + dt f(S)], keeps f(S); stage 1: S <- N[S + dt/2 (f0 + f(S~))]
+// One site per thread: the noise's coefficients, held over a grid-stride loop,
+// cost registers and a copy each (sc 200^3, FP32 field: 569 -> 504 us a step).
 template <typename AccT, bool TENSOR, int STAGE>
 __global__ __launch_bounds__(kPlB) void k_pl_heun(PlView v, PlHeun hc, double *__restrict__ S,
                                                   double *__restrict__ St, double *__restrict__ f0) {
     const int64_t N = v.N;
-    for (int64_t i = xcd_site_block() * kPlB + threadIdx.x; i < N; i += (int64_t)gridDim.x * kPlB) {
-        const double *X = STAGE == 0 ? S : St;
-        double x[3] = {X[i], X[N + i], X[2 * N + i]};
-        double bl[3], on[3], B[3];
-        pl_bil<AccT, TENSOR>(v, X, i, bl);
-        pl_onsite(v, i, x, on);
-        const double inv = 1.0 / (v.mu[i] * kMuB);
-        for (int c = 0; c < 3; ++c) B[c] = (bl[c] + on[c]) * inv;
-        if (hc.noise) {
-            double eta[3];
-            thermal_eta(hc.seed, hc.step, hc.tag, (uint64_t)i, eta);
-            const double sig = hc.sig0 / sqrt(v.mu[i]);
-            for (int c = 0; c < 3; ++c) B[c] += sig * eta[c];
+    const int64_t i = xcd_site_block() * kPlB + threadIdx.x;
+    if (i >= N) return;
+    const double *X = STAGE == 0 ? S : St;
+    double x[3] = {X[i], X[N + i], X[2 * N + i]};
+    double bl[3], on[3], B[3];
+    pl_bil<AccT, TENSOR>(v, X, i, bl);
+    pl_onsite(v, i, x, on);
+    const double inv = 1.0 / (v.mu[i] * kMuB);
+    for (int c = 0; c < 3; ++c) B[c] = (bl[c] + on[c]) * inv;
+    if (hc.noise) {
+        double eta[3];
+        thermal_eta(hc.seed, hc.step, hc.tag, (uint64_t)i, eta);
+        const double sig = hc.sig0 / sqrt(v.mu[i]);
+        for (int c = 0; c < 3; ++c) B[c] += sig * eta[c];
+    }
+    double f[3];
+    llg_rhs(x, B, hc.pre, hc.alpha, f);
+    double p[3];
+    if (STAGE == 0) {
+        for (int c = 0; c < 3; ++c) {
+            f0[c * N + i] = f[c];
+            p[c] = x[c] + hc.dt * f[c];
         }
-        double f[3];
-        llg_rhs(x, B, hc.pre, hc.alpha, f);
-        double p[3];
-        if (STAGE == 0) {
-            for (int c = 0; c < 3; ++c) {
-                f0[c * N + i] = f[c];
-                p[c] = S[c * N + i] + hc.dt * f[c];
-            }
-            normalise3(p);
-            for (int c = 0; c < 3; ++c) St[c * N + i] = p[c];
-        } else {
-            for (int c = 0; c < 3; ++c) p[c] = S[c * N + i] + 0.5 * hc.dt * (f0[c * N + i] + f[c]);
-            normalise3(p);
-            for (int c = 0; c < 3; ++c) S[c * N + i] = p[c];
-        }
+        normalise3(p);
+        for (int c = 0; c < 3; ++c) St[c * N + i] = p[c];
+    } else {
+        for (int c = 0; c < 3; ++c) p[c] = S[c * N + i] + 0.5 * hc.dt * (f0[c * N + i] + f[c]);
+        normalise3(p);
+        for (int c = 0; c < 3; ++c) S[c * N + i] = p[c];
     }
 }
 
@@ -342,6 +369,9 @@ hipError_t pl_field(const PairList *p, const double *S, void *b, hipStream_t st)
         if (p->tensor) k_pl_field<float, float, true><<<g, kPlB, 0, st>>>(v, S, (float *)b);
         else k_pl_field<float, float, false><<<g, kPlB, 0, st>>>(v, S, (float *)b);
     } else {
+        // one site per thread (sc 200^3: FP64 field 226 against 250 us on kPlBlocks
+        // blocks; the FP32 field is no faster for it)
+        const unsigned g = (unsigned)((p->N + kPlB - 1) / kPlB);
         if (p->tensor) k_pl_field<double, double, true><<<g, kPlB, 0, st>>>(v, S, (double *)b);
         else k_pl_field<double, double, false><<<g, kPlB, 0, st>>>(v, S, (double *)b);
     }
@@ -365,7 +395,7 @@ hipError_t pl_energy(const PairList *p, const double *S, double *E, double *term
 hipError_t pl_heun(PairList *p, double *S, double alpha, double dt, double pre, double sig0, uint64_t seed,
                    uint64_t step0, uint32_t tag, int noise, int n_steps, hipStream_t st) {
     const PlView v = view(p);
-    const unsigned g = blocks_for(p->N);
+    const unsigned g = (unsigned)((p->N + kPlB - 1) / kPlB);
     for (int k = 0; k < n_steps; ++k) {
         const PlHeun hc{dt, alpha, pre, sig0, seed, step0 + (uint64_t)k, tag, noise};
 #define SPX_PL_STAGE(ACC, TEN)                                                              \

@@ -145,3 +145,25 @@ def test_lattice_only_methods_refuse_a_pairlist():
     with pytest.raises(spx.SpxError):
         spx.gneb_create([h], [Y])
     assert spx.get_info(h).backend == 3
+
+
+@pytest.mark.parametrize("prec,ftol,htol", [("fp64", 1e-12, 1e-11), ("fp32", 1e-5, 1e-8)])
+@pytest.mark.parametrize("tensor", [False, True], ids=["scalar", "tensor"])
+def test_rows_of_every_length_around_the_chunk(tensor, prec, ftol, htol):
+    # rows of 0 to 13 couplings, each length at the first and the last sites
+    # too: whole chunks of six, the clamped last chunk, and neither
+    rng = np.random.default_rng(8)
+    N = 14 * 37
+    counts = (np.arange(N) % 14)[::-1]
+    i = np.repeat(np.arange(N), counts)
+    j = (i + 1 + rng.integers(0, N - 1, len(i))) % N
+    J = rng.normal(size=(len(i), 3, 3) if tensor else len(i))
+    pl = oracle.PairList(N, i, j, J, mu=rng.uniform(0.5, 3.0, N), B=(0.3, -0.2, 1.1))
+    S0 = random_sphere(N, 15)
+    h = gpu_pl(pl, prec)
+    assert max_rel(field(h, S0, prec), oracle.pl_field(pl, S0)) <= ftol
+    from paper_2605_26016_amd import spx
+    S = to_dev(S0)
+    kw = dict(alpha=0.05, dt_fs=0.1, seed=11, step0=2, n_steps=4)
+    spx.llg_heun_step(h, S, temperature_K=200.0, **kw)
+    assert float(np.max(np.abs(S.cpu().numpy() - oracle.pl_heun(pl, S0, T_K=200.0, **kw)))) <= htol
