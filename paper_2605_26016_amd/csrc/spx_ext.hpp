@@ -105,13 +105,13 @@ hipError_t zmarch_bil(const ZPlan &zp, const Grid &g, const double *S, float *bi
 // nothing is done when *skip != 0 (skip may be NULL).
 // Force pass of the static minimisers fused into the FP64 z-march field
 // evaluation of S (no-op when state[done_idx] != 0): writes F = b - (b.s) s
-// and one set of six partials per tile (max |F|, v.F, F.F, s.s, s.y, y.y of
+// to F[state[iter_idx] mod 2] (the other buffer holds the force of the
+// iteration before) and one set of six partials per tile (max |F|, v.F, F.F, s.s, s.y, y.y of
 // the method) into partial[tile][6]; method 2 also writes the projected pair
 // into history slot state[cand_idx] of Sh / Yh.
-hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, double *F,
-                            const double *V, const double *Up, const double *Fp, double *Sh, double *Yh,
-                            const double *state, int done_idx, int cand_idx, int method, double *partial,
-                            hipStream_t st);
+hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, double *const F[2],
+                            const double *Up, double *Sh, double *Yh, const double *state, int iter_idx, int done_idx,
+                            int cand_idx, int method, double *partial, hipStream_t st);
 // Tiles (x tiles x y tiles x z chunks) of the energy and minimiser passes.
 int zmarch_energy_tiles(const ZPlan &zp, const Grid &g);
 int zmarch_min_tiles(const ZPlan &zp, const Grid &g);

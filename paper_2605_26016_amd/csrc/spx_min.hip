@@ -19,7 +19,7 @@
 //            newest to oldest then back, one fused pass (axpy of the previous
 //            step + dot of the next) per stored pair
 //   update   step u (per method), tangent projection, length cap, retraction;
-//            keeps u (F stays where it is) for the next iteration
+//            keeps u for the next iteration (F stays in its buffer)
 //   finish   iteration count, convergence flag (max |F| < tol_force)
 #include <algorithm>
 #include <cmath>
@@ -42,14 +42,16 @@ constexpr int kNP = 6;  // partials per block: max|F|, v.F, F.F, s.s, s.y, y.y
 // device scalars
 enum { MS_ITER = 0, MS_NP, MS_NEWEST, MS_DONE, MS_MAXF, MS_PROJ, MS_ALPHA, MS_GAMMA, MS_CAND, MS_RED, MS_VC, MS_N = 16 };
 
-// F and Fp change places every iteration, so the previous force needs no copy.
-// Velocity projection keeps no velocity either: v = MS_VC F of the iteration
-// before, so v.F is MS_VC Fp.F.
+// The force of an iteration goes to the two buffers Fb in turn, by the parity
+// of the device's iteration count, so the previous force needs no copy and a
+// captured iteration can be replayed any number of times.  Velocity projection
+// keeps no velocity either: v = MS_VC F of the iteration before, so v.F is
+// MS_VC times the product of the two forces.
 struct MinArgs {
     int64_t N;
     int method, retraction, hist;
     double dt, mass, b1, b2, eps, max_step, tol;
-    double *F, *V, *W, *Fp, *Up, *Sh, *Yh, *q;
+    double *Fb[2], *V, *W, *Up, *Sh, *Yh, *q;
     double *part;    // [kMinBlocks][kNP]
     double *st;      // [MS_N]
     double *rho;     // [hist + 1]
@@ -93,6 +95,13 @@ __device__ __forceinline__ void proj3(const double s[3], double v[3]) {
     for (int c = 0; c < 3; ++c) v[c] -= d * s[c];
 }
 
+// this iteration's force buffer and that of the iteration before
+__device__ __forceinline__ bool odd_iteration(const MinArgs &a) { return ((int64_t)a.st[MS_ITER] & 1) != 0; }
+__device__ __forceinline__ double *force_now(const MinArgs &a) { return odd_iteration(a) ? a.Fb[1] : a.Fb[0]; }
+__device__ __forceinline__ const double *force_before(const MinArgs &a) {
+    return odd_iteration(a) ? a.Fb[0] : a.Fb[1];
+}
+
 // history slot of the t-th newest pair (ring of hist + 1 slots)
 __device__ __forceinline__ int slot_of(const MinArgs &a, int t) {
     const int R = a.hist + 1;
@@ -106,6 +115,8 @@ __global__ __launch_bounds__(kMinB) void k_min_force(MinArgs a, const double *__
     if (a.st[MS_DONE] != 0.0) return;
     const int64_t N = a.N;
     const bool pair = a.method == 1 || a.method == 2;
+    double *const F = force_now(a);
+    const double *const Fp = force_before(a);
     const int cand = (int)a.st[MS_CAND];
     double mf = 0.0, vf = 0.0, ff = 0.0, ss = 0.0, sy = 0.0, yy = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kMinB + threadIdx.x; i < N; i += (int64_t)gridDim.x * kMinB) {
@@ -117,18 +128,18 @@ __global__ __launch_bounds__(kMinB) void k_min_force(MinArgs a, const double *__
         for (int c = 0; c < 3; ++c) {
             f[c] = bb[c] - bs * s[c];
             f2 += f[c] * f[c];
-            a.F[c * N + i] = f[c];
+            F[c * N + i] = f[c];
         }
         mf = fmax(mf, sqrt(f2));
         ff += f2;
         if (a.method == 0) {
             double v[3];
-            ld3(a.Fp, N, i, v);
+            ld3(Fp, N, i, v);
             vf += v[0] * f[0] + v[1] * f[1] + v[2] * f[2];
         } else if (pair) {
             double sv[3], yv[3];
             ld3(a.Up, N, i, sv);
-            ld3(a.Fp, N, i, yv);
+            ld3(Fp, N, i, yv);
             proj3(s, sv);
             proj3(s, yv);
             for (int c = 0; c < 3; ++c) yv[c] -= f[c];
@@ -213,6 +224,7 @@ __global__ __launch_bounds__(kMinB) void k_lb_gram(MinArgs a, const double *__re
     const int np = (int)a.st[MS_NP];
     if (a.st[MS_DONE] != 0.0 || np == 0) return;
     const int64_t N = a.N;
+    const double *const F = force_now(a);
     int64_t off[M];
 #pragma unroll
     for (int t = 0; t < M; ++t) off[t] = t < np ? (int64_t)slot_of(a, t) * 3 * N : 0;
@@ -222,7 +234,7 @@ __global__ __launch_bounds__(kMinB) void k_lb_gram(MinArgs a, const double *__re
     for (int64_t i = (int64_t)blockIdx.x * kMinB + threadIdx.x; i < N; i += (int64_t)gridDim.x * kMinB) {
         double s[3], f[3], sv[M][3], yv[M][3];
         ld3(S, N, i, s);
-        ld3(a.F, N, i, f);
+        ld3(F, N, i, f);
         // pairs not yet there read slot 0 and add nothing
 #pragma unroll
         for (int t = 0; t < M; ++t) {
@@ -320,6 +332,7 @@ __global__ __launch_bounds__(kMinB) void k_lb_loop1(MinArgs a, const double *__r
     const int np = (int)a.st[MS_NP];
     if (t > np) return;
     const int64_t N = a.N;
+    const double *const F = force_now(a);
     const int jp = t > 0 ? slot_of(a, t - 1) : 0;
     const int j = t < np ? slot_of(a, t) : 0;
     const double alp = t > 0 ? a.al[t - 1] : 0.0;
@@ -328,7 +341,7 @@ __global__ __launch_bounds__(kMinB) void k_lb_loop1(MinArgs a, const double *__r
         double s[3], qv[3];
         ld3(S, N, i, s);
         if (t == 0) {
-            for (int c = 0; c < 3; ++c) qv[c] = -a.F[c * N + i];
+            for (int c = 0; c < 3; ++c) qv[c] = -F[c * N + i];
         } else {
             double yv[3];
             ld3(a.q, N, i, qv);
@@ -441,6 +454,7 @@ template <int M>
 __global__ __launch_bounds__(kMinB) void k_min_update(MinArgs a, double *__restrict__ S) {
     if (a.st[MS_DONE] != 0.0) return;
     const int64_t N = a.N;
+    const double *const F = force_now(a);
     constexpr int MM = M > 0 ? M : 1;
     int64_t off[MM];
     double cs_[MM], cy[MM], cf = 0.0;
@@ -461,7 +475,7 @@ __global__ __launch_bounds__(kMinB) void k_min_update(MinArgs a, double *__restr
     for (int64_t i = (int64_t)blockIdx.x * kMinB + threadIdx.x; i < N; i += (int64_t)gridDim.x * kMinB) {
         double s[3], f[3], u[3];
         ld3(S, N, i, s);
-        ld3(a.F, N, i, f);
+        ld3(F, N, i, f);
         if constexpr (M > 0) {
             // the projection below takes that of every term
             for (int c = 0; c < 3; ++c) u[c] = cf * f[c];
@@ -552,7 +566,6 @@ struct spx_min {
     Grid g{};
     Onsite os{};
     int ntile = 0;
-    bool flip = false;  // F and Fp have changed places
 };
 
 namespace {
@@ -565,7 +578,7 @@ void min_free(spx_min *m) {
 hipError_t min_zero_state(spx_min *m, hipStream_t st) {
     const MinArgs &a = m->a;
     const int64_t n3 = 3 * a.N;
-    double *blocks[] = {a.V, a.W, a.F, a.Fp, a.Up, a.q};
+    double *blocks[] = {a.V, a.W, a.Fb[0], a.Fb[1], a.Up, a.q};
     for (double *p : blocks) k_min_zero<<<1024, 256, 0, st>>>(p, n3);
     k_min_zero<<<1024, 256, 0, st>>>(a.Sh, n3 * (a.hist + 1));
     k_min_zero<<<1024, 256, 0, st>>>(a.Yh, n3 * (a.hist + 1));
@@ -636,9 +649,9 @@ spx_status spx_min_create(spx_ham *h, const spx_min_params *p, void *stream, spx
         m->owned.push_back(*ptr);
         return true;
     };
-    bool ok = alloc(&m->b, n3) && alloc(&a.F, n3) && alloc(&a.V, n3) && alloc(&a.W, n3) && alloc(&a.Fp, n3) &&
+    bool ok = alloc(&m->b, n3) && alloc(&a.Fb[0], n3) && alloc(&a.V, n3) && alloc(&a.W, n3) && alloc(&a.Fb[1], n3) &&
               alloc(&a.Up, n3) && alloc(&a.q, n3) && alloc(&a.Sh, n3 * (a.hist + 1)) &&
-              alloc(&a.Yh, n3 * (a.hist + 1)) && 
+              alloc(&a.Yh, n3 * (a.hist + 1)) &&
               alloc(&a.part, std::max((size_t)std::max(kMinBlocks, m->ntile) * kNP, (size_t)kGramBlocks * gram_n(kGramHist))) &&
               alloc(&a.coef, 1 + 2 * kGramHist) && alloc(&a.st, MS_N) &&
               alloc(&a.rho, a.hist + 1) && alloc(&a.al, a.hist);
@@ -664,13 +677,11 @@ spx_status spx_min_step(spx_min *m, double *S, int32_t n_iter, void *stream) {
     if (!handle_alive(m)) return set_error(SPX_ERR_BAD_HANDLE, "invalid spx_min handle");
     if (!S || n_iter < 0) return set_error(SPX_ERR_INVALID_ARG, "S is NULL or n_iter < 0");
     hipStream_t st = (hipStream_t)stream;
+    const MinArgs &a = m->a;
+    const unsigned nb = (unsigned)a.nb;
     for (int it = 0; it < n_iter; ++it) {
-        MinArgs a = m->a;
-        if (m->flip) std::swap(a.F, a.Fp);
-        m->flip = !m->flip;
-        const unsigned nb = (unsigned)a.nb;
         if (m->fused) {
-            hipError_t e = zmarch_min_force(m->zp, m->g, m->os, S, a.F, a.Fp, a.Up, a.Fp, a.Sh, a.Yh, a.st, MS_DONE,
+            hipError_t e = zmarch_min_force(m->zp, m->g, m->os, S, a.Fb, a.Up, a.Sh, a.Yh, a.st, MS_ITER, MS_DONE,
                                             MS_CAND, a.method, a.part, st);
             if (e != hipSuccess) return set_hip_error(e, "spx_min_step: force pass");
             MinArgs af = a;

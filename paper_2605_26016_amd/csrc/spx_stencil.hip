@@ -148,17 +148,18 @@ struct ZArgs {
     int imgfast;
     const double *S0alt;
     const double *sel, *skip;
-    // ZM_MIN_FORCE: force [3][N]; partials of the modes that reduce per tile
-    double *gF;
+    // partials of the modes that reduce per tile
     double *gpart;
     int gpart0, gppi;
-    // ZM_MIN_FORCE (force in gF, partials [tile][6] in gpart): the method's
-    // velocity (0) or previous step and force (1, 2), the L-BFGS history
-    // rings and the minimiser state (candidate slot)
-    const double *mV, *mUp, *mFp;
+    // ZM_MIN_FORCE (partials [tile][6] in gpart): the force buffers [3][N],
+    // this iteration's by the parity of the iteration count and that of the
+    // one before, the previous step (methods 1, 2), the L-BFGS history rings
+    // and the minimiser state (iteration count, candidate slot)
+    double *mF[2];
+    const double *mUp;
     double *mSh, *mYh;
     const double *mst;
-    int mmethod, mcand_idx;
+    int mmethod, miter_idx, mcand_idx;
     // ZM_GNEB_A2 / C2: launch image k is image gimg0 + k of gntot; velocities
     // gV [gntot][3][N]; C2 writes to O0, or O1 when *sel != 0; per-image
     // scalars gims[n * gis.n + {wp, wm, tn, coef}], the VP projection at
@@ -440,6 +441,13 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
                        : MODE == ZM_PREDICT ? 3 : 1;
     // image of the launch in its instance (GNEB two-pass modes)
     const int gimg = img + g.gimg0;
+    double *mF = nullptr;
+    const double *mFp = nullptr;
+    if constexpr (MODE == ZM_MIN_FORCE) {
+        const bool odd = ((int64_t)g.mst[g.miter_idx] & 1) != 0;
+        mF = odd ? g.mF[1] : g.mF[0];
+        mFp = odd ? g.mF[0] : g.mF[1];
+    }
     // ZM_GNEB_C2: uniform over the block
     GnebScalars gs{};
     if constexpr (MODE == ZM_GNEB_C2) gs = gneb_scalars(g, gimg);
@@ -492,12 +500,12 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
                 } else if constexpr (MODE == ZM_MIN_FORCE) {
                     if (g.mmethod == 0) {
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) e[c] = g.mV[c * N + i];
+                        for (int c = 0; c < 3; ++c) e[c] = mFp[c * N + i];
                     } else {
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
                             e[c] = g.mUp[c * N + i];
-                            e[3 + c] = g.mFp[c * N + i];
+                            e[3 + c] = mFp[c * N + i];
                         }
                     }
                 }
@@ -764,7 +772,7 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
                 for (int c = 0; c < 3; ++c) {
                     f[c] = b[c] - bs * sp[c];
                     f2 += f[c] * f[c];
-                    g.gF[c * N + i[a]] = f[c];
+                    mF[c * N + i[a]] = f[c];
                 }
                 mred[0] = fmax(mred[0], sqrt(f2));
                 mred[2] += f2;
@@ -1796,23 +1804,22 @@ hipError_t zmarch_bil(const ZPlan &zp, const Grid &g, const double *S, float *bi
     return launch_any<ZM_BIL>(zp, g, ZLaunch{a, os, hc, st});
 }
 
-hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S, double *F,
-                            const double *V, const double *Up, const double *Fp, double *Sh, double *Yh,
-                            const double *state, int done_idx, int cand_idx, int method, double *partial,
-                            hipStream_t st) {
+hipError_t zmarch_min_force(const ZPlan &zp, const Grid &g, const Onsite &os, const double *S,
+                            double *const F[2], const double *Up, double *Sh, double *Yh, const double *state,
+                            int iter_idx, int done_idx, int cand_idx, int method, double *partial, hipStream_t st) {
     if (zp.prec != 0) return hipErrorInvalidValue;
     ZArgs a = make_args(zp, g);
     a.S0 = S;
     a.skip = state + done_idx;  // the minimiser has converged: no-op
-    a.gF = F;
     a.gpart = partial;
-    a.mV = V;
+    a.mF[0] = F[0];
+    a.mF[1] = F[1];
     a.mUp = Up;
-    a.mFp = Fp;
     a.mSh = Sh;
     a.mYh = Yh;
     a.mst = state;
     a.mmethod = method;
+    a.miter_idx = iter_idx;
     a.mcand_idx = cand_idx;
     HeunConst hc{};
     if (zp.iso) return launch_mode<double, true, ZM_MIN_FORCE>(zp, g, ZLaunch{a, os, hc, st});

@@ -117,3 +117,38 @@ def test_lbfgs_histories_match_the_oracle(history):
         spx.min_step(mn, S, 1)
         err = float(np.max(np.abs(S.cpu().numpy() - ref)))
         assert err <= 1e-9, (it, err)
+
+
+@pytest.mark.parametrize("engine", [0, 1], ids=["z_march", "gather"])
+@pytest.mark.parametrize("method,history", [("vp", 1), ("bb", 1), ("lbfgs", 3), ("lbfgs", 9), ("adam", 1)])
+@pytest.mark.parametrize("per_graph", [1, 3])
+def test_captured_iterations_can_be_replayed(method, history, engine, per_graph):
+    # a program may capture spx_min_step itself: an odd number of iterations a
+    # graph, replayed several times with direct iterations in between, gives
+    # the states of as many direct iterations, bit for bit
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="c", L=(13, 6, 5), J_shell=(1.0, 0.2), K=0.3, B=(0.5, 0.0, 1.0), field_prec="fp64")
+    S0 = to_dev(random_sphere(w.N, 23))
+    h = gpu_hamiltonian(w, stencil_engine=engine)
+    kw = dict(method=method, dt=0.05, history=history, max_step=0.3)
+    ma, mb = spx.min_create(h, **kw), spx.min_create(h, **kw)
+    Sa, Sb = S0.clone(), S0.clone()
+    spx.min_step(mb, Sb, 1)  # the kernels are loaded before the capture
+    spx.min_reset(mb)
+    Sb.copy_(S0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        spx.min_step(mb, Sb, per_graph)
+    done = 0
+    for rep in range(5):
+        graph.replay()
+        done += per_graph
+        if rep in (1, 2):
+            spx.min_step(mb, Sb, 1)
+            done += 1
+        spx.min_step(ma, Sa, done - spx.min_get_stats(ma)["iterations"])
+        torch.cuda.synchronize()
+        assert spx.min_get_stats(mb)["iterations"] == done
+        assert torch.equal(Sa, Sb), rep
