@@ -44,6 +44,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "spx_device.hpp"
@@ -781,6 +782,7 @@ struct spx_gneb {
     float *d_tvals = nullptr;   // reaction coordinates for the learned init
     int max_img = 0;
     double *h_stats = nullptr;  // pinned: one instance's state and image statistics
+    std::mutex stats_mutex;     // h_stats: held by the call that copies into it
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // one iteration, and kGraphIters of them
     int64_t iters = 0;  // iterations asked for
     hipStream_t cap_stream = nullptr;  // library-owned capture stream (the caller's may be the null stream)
@@ -1321,10 +1323,14 @@ spx_status spx_gneb_get_stats(spx_gneb *g, int32_t inst, double *E, double *dist
     if (inst < 0 || inst >= g->n_inst) return set_error(SPX_ERR_INVALID_ARG, "instance out of range");
     hipStream_t st = (hipStream_t)stream;
     const GInst &gi = g->hinst[inst];
-    // one copy into pinned memory (two into pageable vectors took 80 us a call)
-    const double *s = g->h_stats, *im = g->h_stats + ST_N;
-    hipError_t e = hipMemcpyAsync(g->h_stats, gi.st, sizeof(double) * (ST_N + IS_N * (size_t)gi.n_img),
-                                  hipMemcpyDeviceToHost, st);
+    // one copy into pinned memory (two into pageable vectors took 80 us a
+    // call); a call that finds another thread's in there takes memory of its
+    // own, so neither waits for the other's stream
+    const size_t count = ST_N + IS_N * (size_t)gi.n_img;
+    std::unique_lock<std::mutex> pinned(g->stats_mutex, std::try_to_lock);
+    std::vector<double> own(pinned.owns_lock() ? 0 : count);
+    double *const s = pinned.owns_lock() ? g->h_stats : own.data(), *const im = s + ST_N;
+    hipError_t e = hipMemcpyAsync(s, gi.st, sizeof(double) * count, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return set_hip_error(e, "spx_gneb_get_stats");
     for (int n = 0; n < gi.n_img; ++n) {

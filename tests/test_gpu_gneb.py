@@ -314,3 +314,37 @@ def test_gneb_long_graph_equals_single_steps(ci_mode):
             assert torch.equal(x, y), (done, k)
             assert float(x.square().sum(1).sub(1.0).abs().max()) < 1e-12
             assert spx.gneb_get_stats(handles[0], k)["iterations"] == done
+
+
+def test_statistics_from_several_threads():
+    # threads that read the statistics of one handle's instances at the same
+    # time, each on a stream of its own, each get their own instance's
+    import threading
+
+    import torch
+    from paper_2605_26016_amd import spx
+    cases = [(frustrated((4, 4, 4)), 3, 51), (frustrated((5, 4, 3)), 40, 52), (frustrated((3, 3, 3)), 17, 53),
+             (frustrated((6, 5, 2)), 9, 54)]
+    g = spx.gneb_create([gpu_hamiltonian(w) for w, _, _ in cases],
+                        [to_dev(oracle.geodesic_path(random_sphere(w.N, s), random_sphere(w.N, s + 100), n))
+                         for w, n, s in cases])
+    spx.gneb_step(g, 3)
+    torch.cuda.synchronize()
+    want = [spx.gneb_get_stats(g, k) for k in range(len(cases))]
+    streams = [torch.cuda.Stream() for _ in cases]
+    wrong = []
+
+    def read(k):
+        for _ in range(500):
+            s = spx.gneb_get_stats(g, k, stream=streams[k])
+            if not (np.array_equal(s["E"], want[k]["E"]) and np.array_equal(s["dist"], want[k]["dist"])
+                    and s["max_force"] == want[k]["max_force"]):
+                wrong.append(k)
+                return
+
+    threads = [threading.Thread(target=read, args=(k,)) for k in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
