@@ -49,6 +49,7 @@
 
 #include "spx_device.hpp"
 #include "spx_ext.hpp"
+#include "spx_gneb_graphs.hpp"
 
 namespace spx {
 namespace {
@@ -784,9 +785,8 @@ struct spx_gneb {
     double *h_stats = nullptr;  // pinned: one instance's state and image statistics
     std::mutex stats_mutex;     // h_stats: held by the call that copies into it
     hipGraphExec_t graph[2] = {nullptr, nullptr};  // one iteration, and kGraphIters of them
-    int64_t iters = 0;  // iterations asked for
+    GnebGraphs use;  // which of them are made
     hipStream_t cap_stream = nullptr;  // library-owned capture stream (the caller's may be the null stream)
-    int use_graph = 1;
     // Two-pass instances of one kernel (shape, isotropy, tile width) share its
     // launches: entry tables of the two passes on the device.
     struct Group {
@@ -821,13 +821,6 @@ spx_status gneb_alloc(spx_gneb *g, void **p, size_t bytes, const char *what) {
     return SPX_OK;
 }
 
-// Iterations in the longer of the two captured graphs.  Between two graph
-// launches the device waits 8 us, between two kernels of one graph not at all
-// (films of 100 us an iteration).
-// Capturing the long one costs about 0.6 ms, so it waits until the handle has
-// been asked for kLongAfter iterations.
-constexpr int kGraphIters = 8;
-constexpr int kLongAfter = 128;
 void gneb_drop_graphs(spx_gneb *g) {
     for (hipGraphExec_t &x : g->graph) {
         if (x) (void)hipGraphExecDestroy(x);
@@ -835,10 +828,7 @@ void gneb_drop_graphs(spx_gneb *g) {
     }
 }
 
-void gneb_free(spx_gneb *g) {
-    gneb_drop_graphs(g);
-    if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
-    g->cap_stream = nullptr;
+void gneb_free_branches(spx_gneb *g) {
     for (hipStream_t s : g->side)
         if (s) (void)hipStreamDestroy(s);
     g->side.clear();
@@ -849,6 +839,13 @@ void gneb_free(spx_gneb *g) {
             if (e) (void)hipEventDestroy(e);
         g->join_ev[p].clear();
     }
+}
+
+void gneb_free(spx_gneb *g) {
+    gneb_drop_graphs(g);
+    if (g->cap_stream) (void)hipStreamDestroy(g->cap_stream);
+    g->cap_stream = nullptr;
+    gneb_free_branches(g);
     for (void *p : g->owned) (void)hipFree(p);
     g->owned.clear();
     if (g->h_stats) (void)hipHostFree(g->h_stats);
@@ -989,6 +986,42 @@ hipError_t enqueue_iteration(spx_gneb *g, hipStream_t st) {
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();
+}
+
+// Captures graph q of the handle (0: one iteration, 1: kGraphIters of them)
+// on its private stream.
+hipError_t gneb_capture(spx_gneb *g, int q) {
+    hipError_t e = hipSuccess;
+    if (!g->cap_stream) e = hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking);
+    // two to kMaxBranches units of a pass become parallel branches
+    // (streams and events of default priority, made once)
+    const int units = pass_units(g, 0);
+    const bool branches = units > 1 && units <= kMaxBranches;
+    if (e == hipSuccess && branches && g->side.empty()) {
+        g->side.assign(units, nullptr);
+        for (int p = 0; p < 2; ++p) g->join_ev[p].assign(units, nullptr);
+        for (int k = 0; k < units && e == hipSuccess; ++k) {
+            e = hipStreamCreateWithFlags(&g->side[k], hipStreamNonBlocking);
+            for (int p = 0; p < 2 && e == hipSuccess; ++p)
+                e = hipEventCreateWithFlags(&g->join_ev[p][k], hipEventDisableTiming);
+        }
+        for (int p = 0; p < 2 && e == hipSuccess; ++p)
+            e = hipEventCreateWithFlags(&g->fork_ev[p], hipEventDisableTiming);
+        if (e != hipSuccess) gneb_free_branches(g);
+    }
+    if (e == hipSuccess) e = hipStreamBeginCapture(g->cap_stream, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return e;
+    g->branch = branches;
+    hipError_t e2 = hipSuccess;
+    for (int it = 0; it < (q ? kGraphIters : 1) && e2 == hipSuccess; ++it) e2 = enqueue_iteration(g, g->cap_stream);
+    g->branch = false;
+    hipGraph_t graph = nullptr;
+    e = hipStreamEndCapture(g->cap_stream, &graph);
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess) e = hipGraphInstantiate(&g->graph[q], graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) g->graph[q] = nullptr;
+    if (graph) (void)hipGraphDestroy(graph);
+    return e;
 }
 
 }  // namespace
@@ -1254,53 +1287,13 @@ spx_status spx_gneb_step(spx_gneb *g, int32_t n_iter, void *stream) {
     if (n_iter < 0) return set_error(SPX_ERR_INVALID_ARG, "n_iter < 0");
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    const bool want[2] = {n_iter > 1 && !g->graph[0], n_iter >= kGraphIters && !g->graph[1] && g->iters + n_iter >= kLongAfter};
-    g->iters += n_iter;
-    if (g->use_graph && (want[0] || want[1])) {
-        // One iteration, and a run of kGraphIters once kLongAfter are reached,
-        // captured once on a private stream; the graphs are then launched on
-        // whatever stream the caller passes.  Capture failure (graphs unsupported) leaves direct
-        // launches in place.
-        if (!g->cap_stream) e = hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking);
-        // two to kMaxBranches units of a pass become parallel branches
-        // (streams and events of default priority, made once)
-        const int units = pass_units(g, 0);
-        const bool branches = units > 1 && units <= kMaxBranches;
-        if (e == hipSuccess && branches && g->side.empty()) {
-            g->side.assign(units, nullptr);
-            for (int p = 0; p < 2; ++p) g->join_ev[p].assign(units, nullptr);
-            for (int k = 0; k < units && e == hipSuccess; ++k) {
-                e = hipStreamCreateWithFlags(&g->side[k], hipStreamNonBlocking);
-                for (int p = 0; p < 2 && e == hipSuccess; ++p)
-                    e = hipEventCreateWithFlags(&g->join_ev[p][k], hipEventDisableTiming);
-            }
-            for (int p = 0; p < 2 && e == hipSuccess; ++p)
-                e = hipEventCreateWithFlags(&g->fork_ev[p], hipEventDisableTiming);
-        }
-        for (int q = 0; q < 2 && e == hipSuccess; ++q) {
-            if (!want[q]) continue;
-            hipGraph_t graph;
-            e = hipStreamBeginCapture(g->cap_stream, hipStreamCaptureModeThreadLocal);
-            if (e != hipSuccess) break;
-            g->branch = branches;
-            hipError_t e2 = hipSuccess;
-            for (int it = 0; it < (q ? kGraphIters : 1) && e2 == hipSuccess; ++it)
-                e2 = enqueue_iteration(g, g->cap_stream);
-            g->branch = false;
-            e = hipStreamEndCapture(g->cap_stream, &graph);
-            if (e == hipSuccess) e = e2;
-            if (e == hipSuccess) {
-                e = hipGraphInstantiate(&g->graph[q], graph, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(graph);
-            }
-        }
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            gneb_drop_graphs(g);
-            g->use_graph = 0;
-            e = hipSuccess;
-        }
-    }
+    // captured once on a private stream and then launched on whatever stream
+    // the caller passes
+    make_gneb_graphs(g->use, g->graph[0] != nullptr, g->graph[1] != nullptr, n_iter, [&](int q) {
+        const hipError_t c = gneb_capture(g, q);
+        if (c != hipSuccess) (void)hipGetLastError();
+        return c == hipSuccess;
+    });
     for (int it = 0; it < n_iter && e == hipSuccess;) {
         const bool run = g->graph[1] && n_iter - it >= kGraphIters;
         if (g->graph[0]) e = hipGraphLaunch(g->graph[run ? 1 : 0], st);
@@ -1408,7 +1401,7 @@ spx_status spx_gneb_set_params(spx_gneb *g, const spx_gneb_params *p, void *stre
 
 spx_status spx_gneb_set_graph(spx_gneb *g, int32_t enable) {
     if (!handle_alive(g)) return set_error(SPX_ERR_BAD_HANDLE, "invalid spx_gneb handle");
-    g->use_graph = enable ? 1 : 0;
+    g->use.on = g->use.run_on = enable != 0;
     if (!enable) gneb_drop_graphs(g);
     return SPX_OK;
 }
