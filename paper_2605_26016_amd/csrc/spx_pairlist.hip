@@ -87,56 +87,75 @@ __device__ __forceinline__ void pl_bil(const PlView &v, const double *__restrict
     const int64_t N = v.N;
     AccT acc[3] = {AccT(0), AccT(0), AccT(0)};
     const int64_t p0 = v.row[i], p1 = v.row[i + 1];
-    // Entries go in chunks whose index loads, and then their spin loads, are
-    // in flight together instead of one dependent pair per entry: six deep
-    // (timed on sc 200^3 nearest-neighbour rows of six: FP32 field 220 -> 208
-    // us and FP64 294 -> 248 us against four deep; eight deep was slower than
-    // four).  The last one to five of a row are one chunk too, with the index
-    // clamped to the row and the sum kept where there is no entry: a serial
-    // remainder loop, one dependent pair of loads after another, is what
-    // irregular rows spent their time in (800,000 sites with 4.8 entries on
-    // average, FP32: 41 -> 33 us a Heun stage with one site per thread).
-    constexpr int kDeep = 6;
-    auto chunk = [&](int64_t p, auto nc, auto masked) __attribute__((always_inline)) {
-        constexpr int n = decltype(nc)::value;
-        constexpr bool M = decltype(masked)::value;
-        int64_t q[n];
-        AccT s[n][3], Js[n];
+    if constexpr (TENSOR) {
+        // unrolled six deep, as the scalar chunks below; a coupling is nine
+        // values, and clamped entries for the rest of a row cost more than
+        // they save (1,000,000 sites with one entry each, FP64 field: 21 us
+        // against 42; 100,000 sites with seven: 19 against 27)
+#pragma unroll 6
+        for (int64_t p = p0; p < p1; ++p) {
+            const int64_t j = v.col[p];
+            const AccT s0 = (AccT)S[j], s1 = (AccT)S[N + j], s2 = (AccT)S[2 * N + j];
+            AccT J[9];
 #pragma unroll
-        for (int u = 0; u < n; ++u) q[u] = M ? (p + u < p1 ? p + u : p1 - 1) : p + u;
+            for (int e = 0; e < 9; ++e) {
+                if constexpr (sizeof(AccT) == 4) J[e] = v.Jf[9 * p + e]; else J[e] = v.Jd[9 * p + e];
+            }
+            acc[0] += J[0] * s0 + J[1] * s1 + J[2] * s2;
+            acc[1] += J[3] * s0 + J[4] * s1 + J[5] * s2;
+            acc[2] += J[6] * s0 + J[7] * s1 + J[8] * s2;
+        }
+    } else {
+        // Entries go in chunks whose index loads, and then their spin loads,
+        // are in flight together instead of one dependent pair per entry: six
+        // deep (timed on sc 200^3 nearest-neighbour rows of six: FP32 field
+        // 220 -> 208 us and FP64 294 -> 248 us against four deep; eight deep
+        // was slower than four).  The last one to five of a row are one chunk
+        // too, as long as the longest remainder in the wavefront, with the
+        // index clamped to the row and the sum kept where there is no entry: a
+        // serial remainder loop, one dependent pair of loads after another, is
+        // what irregular rows spent their time in (800,000 sites with 4.8
+        // entries on average, FP32: 41 -> 33 us a Heun stage with one site per
+        // thread).
+        constexpr int kDeep = 6;
+        auto chunk = [&](int64_t p, auto nc, auto masked) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value;
+            constexpr bool M = decltype(masked)::value;
+            int64_t q[n];
+            AccT s[n][3], J[n];
 #pragma unroll
-        for (int u = 0; u < n; ++u) {
-            const int64_t j = v.col[q[u]];
-            if constexpr (!TENSOR) {
-                if constexpr (sizeof(AccT) == 4) Js[u] = v.Jf[q[u]]; else Js[u] = v.Jd[q[u]];
+            for (int u = 0; u < n; ++u) q[u] = M && u > 0 ? (p + u < p1 ? p + u : p1 - 1) : p + u;
+#pragma unroll
+            for (int u = 0; u < n; ++u) {
+                const int64_t j = v.col[q[u]];
+                if constexpr (sizeof(AccT) == 4) J[u] = v.Jf[q[u]]; else J[u] = v.Jd[q[u]];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s[u][c] = (AccT)S[c * N + j];
             }
 #pragma unroll
-            for (int c = 0; c < 3; ++c) s[u][c] = (AccT)S[c * N + j];
-        }
+            for (int u = 0; u < n; ++u) {
+                const bool ok = !M || u == 0 || p + u < p1;
 #pragma unroll
-        for (int u = 0; u < n; ++u) {
-            AccT t[3];
-            if constexpr (TENSOR) {
-                AccT J[9];
-#pragma unroll
-                for (int e = 0; e < 9; ++e) {
-                    if constexpr (sizeof(AccT) == 4) J[e] = v.Jf[9 * q[u] + e]; else J[e] = v.Jd[9 * q[u] + e];
+                for (int c = 0; c < 3; ++c) {
+                    const AccT t = acc[c] + J[u] * s[u][c];
+                    acc[c] = ok ? t : acc[c];
                 }
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    t[c] = acc[c] + (J[3 * c] * s[u][0] + J[3 * c + 1] * s[u][1] + J[3 * c + 2] * s[u][2]);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) t[c] = acc[c] + Js[u] * s[u][c];
             }
-            const bool ok = !M || p + u < p1;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[c] = ok ? t[c] : acc[c];
+        };
+        int64_t p = p0;
+        for (; p + kDeep <= p1; p += kDeep) chunk(p, std::integral_constant<int, kDeep>{}, std::false_type{});
+        if (p < p1) {
+            // (rows of seven, 1,000,000 sites, FP32 field: 30 us with a chunk
+            // of one, 43 with one of five always)
+            const int rest = (int)(p1 - p);
+            const auto masked = std::true_type{};
+            if (__any(rest > 4)) chunk(p, std::integral_constant<int, 5>{}, masked);
+            else if (__any(rest > 3)) chunk(p, std::integral_constant<int, 4>{}, masked);
+            else if (__any(rest > 2)) chunk(p, std::integral_constant<int, 3>{}, masked);
+            else if (__any(rest > 1)) chunk(p, std::integral_constant<int, 2>{}, masked);
+            else chunk(p, std::integral_constant<int, 1>{}, masked);
         }
-    };
-    int64_t p = p0;
-    for (; p + kDeep <= p1; p += kDeep) chunk(p, std::integral_constant<int, kDeep>{}, std::false_type{});
-    if (p < p1) chunk(p, std::integral_constant<int, kDeep - 1>{}, std::true_type{});
+    }
     for (int c = 0; c < 3; ++c) out[c] = (double)acc[c];
 }
 
@@ -175,39 +194,50 @@ struct PlHeun {
 // stage 0: S~ = N[S + dt f(S)], keeps f(S); stage 1: S <- N[S + dt/2 (f0 + f(S~))]
 // One site per thread: the noise's coefficients, held over a grid-stride loop,
 // cost registers and a copy each (sc 200^3, FP32 field: 569 -> 504 us a step).
-template <typename AccT, bool TENSOR, int STAGE>
+// LOOP keeps the loop, on kPlBlocks blocks, for rows of many tensors: there the
+// registers are what keeps the wavefronts few enough for their couplings'
+// lines to stay in the L1 until all nine values are read (100,000 sites,
+// FP32, eight steps: 319 us with 14 entries a row and 865 with 40, against 402
+// and 1098 with one site per thread; with 3 entries 113 against 106).
+template <typename AccT, bool TENSOR, int STAGE, bool LOOP>
 __global__ __launch_bounds__(kPlB) void k_pl_heun(PlView v, PlHeun hc, double *__restrict__ S,
                                                   double *__restrict__ St, double *__restrict__ f0) {
     const int64_t N = v.N;
-    const int64_t i = xcd_site_block() * kPlB + threadIdx.x;
-    if (i >= N) return;
-    const double *X = STAGE == 0 ? S : St;
-    double x[3] = {X[i], X[N + i], X[2 * N + i]};
-    double bl[3], on[3], B[3];
-    pl_bil<AccT, TENSOR>(v, X, i, bl);
-    pl_onsite(v, i, x, on);
-    const double inv = 1.0 / (v.mu[i] * kMuB);
-    for (int c = 0; c < 3; ++c) B[c] = (bl[c] + on[c]) * inv;
-    if (hc.noise) {
-        double eta[3];
-        thermal_eta(hc.seed, hc.step, hc.tag, (uint64_t)i, eta);
-        const double sig = hc.sig0 / sqrt(v.mu[i]);
-        for (int c = 0; c < 3; ++c) B[c] += sig * eta[c];
-    }
-    double f[3];
-    llg_rhs(x, B, hc.pre, hc.alpha, f);
-    double p[3];
-    if (STAGE == 0) {
-        for (int c = 0; c < 3; ++c) {
-            f0[c * N + i] = f[c];
-            p[c] = x[c] + hc.dt * f[c];
+    auto site = [&](int64_t i) __attribute__((always_inline)) {
+        const double *X = STAGE == 0 ? S : St;
+        double x[3] = {X[i], X[N + i], X[2 * N + i]};
+        double bl[3], on[3], B[3];
+        pl_bil<AccT, TENSOR>(v, X, i, bl);
+        pl_onsite(v, i, x, on);
+        const double inv = 1.0 / (v.mu[i] * kMuB);
+        for (int c = 0; c < 3; ++c) B[c] = (bl[c] + on[c]) * inv;
+        if (hc.noise) {
+            double eta[3];
+            thermal_eta(hc.seed, hc.step, hc.tag, (uint64_t)i, eta);
+            const double sig = hc.sig0 / sqrt(v.mu[i]);
+            for (int c = 0; c < 3; ++c) B[c] += sig * eta[c];
         }
-        normalise3(p);
-        for (int c = 0; c < 3; ++c) St[c * N + i] = p[c];
+        double f[3];
+        llg_rhs(x, B, hc.pre, hc.alpha, f);
+        double p[3];
+        if (STAGE == 0) {
+            for (int c = 0; c < 3; ++c) {
+                f0[c * N + i] = f[c];
+                p[c] = x[c] + hc.dt * f[c];
+            }
+            normalise3(p);
+            for (int c = 0; c < 3; ++c) St[c * N + i] = p[c];
+        } else {
+            for (int c = 0; c < 3; ++c) p[c] = S[c * N + i] + 0.5 * hc.dt * (f0[c * N + i] + f[c]);
+            normalise3(p);
+            for (int c = 0; c < 3; ++c) S[c * N + i] = p[c];
+        }
+    };
+    int64_t i = xcd_site_block() * kPlB + threadIdx.x;
+    if constexpr (LOOP) {
+        for (; i < N; i += (int64_t)gridDim.x * kPlB) site(i);
     } else {
-        for (int c = 0; c < 3; ++c) p[c] = S[c * N + i] + 0.5 * hc.dt * (f0[c * N + i] + f[c]);
-        normalise3(p);
-        for (int c = 0; c < 3; ++c) S[c * N + i] = p[c];
+        if (i < N) site(i);
     }
 }
 
@@ -370,8 +400,10 @@ hipError_t pl_field(const PairList *p, const double *S, void *b, hipStream_t st)
         else k_pl_field<float, float, false><<<g, kPlB, 0, st>>>(v, S, (float *)b);
     } else {
         // one site per thread (sc 200^3: FP64 field 226 against 250 us on kPlBlocks
-        // blocks; the FP32 field is no faster for it)
-        const unsigned g = (unsigned)((p->N + kPlB - 1) / kPlB);
+        // blocks; the FP32 field is no faster for it), except where a row has
+        // one entry or none on average (1,000,000 sites: 13.4 us, 12.6 on
+        // kPlBlocks blocks)
+        const unsigned g = p->P > p->N ? (unsigned)((p->N + kPlB - 1) / kPlB) : blocks_for(p->N);
         if (p->tensor) k_pl_field<double, double, true><<<g, kPlB, 0, st>>>(v, S, (double *)b);
         else k_pl_field<double, double, false><<<g, kPlB, 0, st>>>(v, S, (double *)b);
     }
@@ -395,18 +427,25 @@ hipError_t pl_energy(const PairList *p, const double *S, double *E, double *term
 hipError_t pl_heun(PairList *p, double *S, double alpha, double dt, double pre, double sig0, uint64_t seed,
                    uint64_t step0, uint32_t tag, int noise, int n_steps, hipStream_t st) {
     const PlView v = view(p);
-    const unsigned g = (unsigned)((p->N + kPlB - 1) / kPlB);
+    // tensors: the line lies between rows of 3 entries (one site per thread
+    // faster by 6 - 16%) and of 6 (the loop faster by 5 - 10%)
+    const bool loop = p->tensor && p->P > 4 * p->N;
+    const unsigned g = loop ? blocks_for(p->N) : (unsigned)((p->N + kPlB - 1) / kPlB);
     for (int k = 0; k < n_steps; ++k) {
         const PlHeun hc{dt, alpha, pre, sig0, seed, step0 + (uint64_t)k, tag, noise};
-#define SPX_PL_STAGE(ACC, TEN)                                                              \
-    k_pl_heun<ACC, TEN, 0><<<g, kPlB, 0, st>>>(v, hc, S, p->St, p->f0);                     \
-    k_pl_heun<ACC, TEN, 1><<<g, kPlB, 0, st>>>(v, hc, S, p->St, p->f0);
-        if (p->prec == SPX_FP32) {
-            if (p->tensor) { SPX_PL_STAGE(float, true) } else { SPX_PL_STAGE(float, false) }
-        } else {
-            if (p->tensor) { SPX_PL_STAGE(double, true) } else { SPX_PL_STAGE(double, false) }
-        }
-#undef SPX_PL_STAGE
+        auto stages = [&](auto acc, auto tensor, auto looped) {
+            using AccT = decltype(acc);
+            constexpr bool T = decltype(tensor)::value, L = decltype(looped)::value;
+            k_pl_heun<AccT, T, 0, L><<<g, kPlB, 0, st>>>(v, hc, S, p->St, p->f0);
+            k_pl_heun<AccT, T, 1, L><<<g, kPlB, 0, st>>>(v, hc, S, p->St, p->f0);
+        };
+        auto run = [&](auto acc) {
+            if (!p->tensor) stages(acc, std::false_type{}, std::false_type{});
+            else if (loop) stages(acc, std::true_type{}, std::true_type{});
+            else stages(acc, std::true_type{}, std::false_type{});
+        };
+        if (p->prec == SPX_FP32) run(0.0f);
+        else run(0.0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -167,3 +167,60 @@ def test_rows_of_every_length_around_the_chunk(tensor, prec, ftol, htol):
     kw = dict(alpha=0.05, dt_fs=0.1, seed=11, step0=2, n_steps=4)
     spx.llg_heun_step(h, S, temperature_K=200.0, **kw)
     assert float(np.max(np.abs(S.cpu().numpy() - oracle.pl_heun(pl, S0, T_K=200.0, **kw)))) <= htol
+
+
+@pytest.mark.parametrize("prec,ftol,htol", [("fp64", 1e-12, 1e-11), ("fp32", 1e-5, 1e-8)])
+@pytest.mark.parametrize("tensor", [False, True], ids=["scalar", "tensor"])
+@pytest.mark.parametrize("longest", [13, 5])
+def test_rows_of_one_length_per_wavefront(longest, tensor, prec, ftol, htol):
+    # 64 sites of each row length from the longest down to 0, then a wavefront
+    # of rows of one and one longer row among them: the last chunk of a row is
+    # as long as the longest remainder of its wavefront (scalars); a step with
+    # tensors takes one site per thread or a loop by the mean length
+    rng = np.random.default_rng(9)
+    counts = np.concatenate([np.repeat(np.arange(longest, -1, -1), 64), np.ones(64, int)])
+    counts[-20] = 9
+    N = len(counts)
+    i = np.repeat(np.arange(N), counts)
+    j = (i + 1 + rng.integers(0, N - 1, len(i))) % N
+    J = rng.normal(size=(len(i), 3, 3) if tensor else len(i))
+    pl = oracle.PairList(N, i, j, J, mu=rng.uniform(0.5, 3.0, N), B=(0.3, -0.2, 1.1))
+    S0 = random_sphere(N, 16)
+    h = gpu_pl(pl, prec)
+    assert max_rel(field(h, S0, prec), oracle.pl_field(pl, S0)) <= ftol
+    from paper_2605_26016_amd import spx
+    S = to_dev(S0)
+    kw = dict(alpha=0.05, dt_fs=0.1, seed=11, step0=2, n_steps=4)
+    spx.llg_heun_step(h, S, temperature_K=200.0, **kw)
+    assert float(np.max(np.abs(S.cpu().numpy() - oracle.pl_heun(pl, S0, T_K=200.0, **kw)))) <= htol
+
+
+@pytest.mark.parametrize("tensor,prec", [(False, "fp32"), (False, "fp64"), (True, "fp64")],
+                         ids=["scalar_fp32", "scalar_fp64", "tensor_fp64"])
+def test_a_row_of_seven_costs_about_a_row_of_six(tensor, prec):
+    # one entry more than a chunk costs about what an entry costs (a seventh of
+    # the row; 1.2 times the time with scalars, whose cache lines are shared
+    # less evenly), not another chunk (1.8 times); 1.5 lies between
+    import torch
+    from paper_2605_26016_amd import spx
+    N = 100_000 if tensor else 1_000_000
+    rng = np.random.default_rng(10)
+    S = to_dev(random_sphere(N, 17))
+    b = torch.empty((3, N), dtype=torch.float64 if prec == "fp64" else torch.float32, device="cuda")
+    us = []
+    for d in (6, 7):
+        i = np.repeat(np.arange(N), d)
+        j = (i + rng.integers(1, 300, len(i))) % N
+        h = spx.setup_pairlist(N, i, j, rng.normal(size=(len(i), 3, 3) if tensor else len(i)), field_prec=prec)
+        best = 1e9
+        for _ in range(8):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(20):
+                spx.eval_field(h, S, b)
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * t0.elapsed_time(t1) / 20)
+        us.append(best)
+    print("rows of 6 and 7:", us, flush=True)
+    assert us[1] <= 1.5 * us[0], us
