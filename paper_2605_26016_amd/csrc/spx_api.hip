@@ -193,6 +193,7 @@ struct spx_ham {
     MCState *mc = nullptr;              // Monte Carlo colouring and scratch
     PairList *pl = nullptr;             // pair-list Hamiltonian (backend 3)
     int64_t pl_pairs = 0;
+    Index64 index64;
     int tuned = 0;
     double tune_us = 0.0;
     // kernel timing: recorded (start, stop) event pairs per kind, and a pool
@@ -314,6 +315,7 @@ spx_status get_ham_view(spx_ham *h, HamView &v) {
     v.radius[2] = h->radius[2];
     v.mc = &h->mc;
     v.pl = h->pl;
+    v.index64 = &h->index64;
     return SPX_OK;
 }
 }  // namespace spx
@@ -1010,7 +1012,7 @@ spx_status spx_eval_field(spx_ham *h, const double *S, void *b, void *stream) {
     hipError_t e;
     {
         KernelTimer kt(h, 2, st);
-        if (h->dense) e = dense_field(h->dense, h->grid, h->onsite, S, (float *)b, st);
+        if (h->dense) e = dense_field(h->dense, h->grid, h->onsite, S, (float *)b, h->index64.wide, st);
         else if (h->engine == 2) e = zmarch_field(h->zp, h->grid, h->onsite, S, bdip, b, st);
         else e = launch_field(h->field_prec, h->tab, h->grid, h->onsite, S, bdip, b, st);
     }
@@ -1135,6 +1137,16 @@ spx_status spx_llg_heun_step(spx_ham *h, double *S, const spx_llg_params *p, voi
 spx_status spx_set_heun_graph(spx_ham *h, int32_t enable) {
     if (!reg_has(h)) return fail(SPX_ERR_BAD_HANDLE, "invalid spx_ham handle");
     h->use_graph = enable ? 1 : 0;
+    return SPX_OK;
+}
+
+// Test hook, no part of the interface: the handle's kernels take their 64-bit
+// forms at every size (wide), and a Monte Carlo launch at most mc_slots slots
+// (rounded up to whole blocks; 0: the most that fit).
+spx_status spx_debug_index64(spx_ham *h, int32_t wide, int64_t mc_slots) {
+    if (!reg_has(h)) return fail(SPX_ERR_BAD_HANDLE, "invalid spx_ham handle");
+    if (mc_slots < 0 || mc_slots > INT32_MAX) return fail(SPX_ERR_INVALID_ARG, "mc_slots out of range");
+    h->index64 = {wide != 0, (mc_slots + 255) / 256 * 256};
     return SPX_OK;
 }
 

@@ -513,7 +513,8 @@ void dense_destroy(DensePlan *p) {
     delete p;
 }
 
-hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, const double *S, float *b, hipStream_t st) {
+hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, const double *S, float *b, bool wide,
+                       hipStream_t st) {
     if (p->direct) {
         const unsigned tiles = (unsigned)((g.Lx + kFX - 1) / kFX) * (unsigned)((g.Ly + kFY - 1) / kFY) *
                                (unsigned)((g.Lz + kFZ - 1) / kFZ);
@@ -525,7 +526,7 @@ hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, cons
     auto go = [&](auto kernel) {
         kernel<<<grid, kThreadsD, 0, st>>>(S, b, (const s16x8 *)p->d_frag, p->kscale, p->in_scale, g, os);
     };
-    const bool narrow = g.N <= (int64_t)(UINT32_MAX / sizeof(double));
+    const bool narrow = !wide && g.N <= (int64_t)(UINT32_MAX / sizeof(double));
     if (p->bf16) narrow ? go(k_dense_mfma<true, true>) : go(k_dense_mfma<true, false>);
     else narrow ? go(k_dense_mfma<false, true>) : go(k_dense_mfma<false, false>);
     return hipGetLastError();

@@ -36,6 +36,14 @@ void mc_destroy(MCState *m);
 
 // Read-only view of a Hamiltonian handle for other subsystems.
 struct ZPlan;
+// Kernels chosen by size alone: their 64-bit forms serve lattices of 2^29 sites
+// and more, and a launch holds less than 2^32 threads.  A handle can ask for
+// them at any size, so that tests reach them (spx_debug_index64).
+struct Index64 {
+    bool wide = false;     // 64-bit addresses throughout
+    int64_t mc_slots = 0;  // Monte Carlo slots per launch (0: as many as fit)
+};
+
 struct HamView {
     const ZPlan *zp64;  // FP64 z-march plan of the bond table (NULL if none or engine forced to gather)
     Grid grid;
@@ -47,6 +55,7 @@ struct HamView {
     int radius[3];
     MCState **mc;  // the handle's Monte Carlo state slot (created on first use)
     const PairList *pl;  // non-NULL for a pair-list Hamiltonian
+    const Index64 *index64;
 };
 spx_status get_ham_view(spx_ham *h, HamView &v);
 
@@ -185,7 +194,8 @@ struct DensePlan;
 bool dense_plan(int prec, int n_sub, const int *bond_a, const int *bond_b, const int *bond_d, const double *bond_J,
                 int n_bonds, DensePlan **out, hipStream_t st, std::string &why);
 void dense_destroy(DensePlan *p);
-hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, const double *S, float *b, hipStream_t st);
+hipError_t dense_field(const DensePlan *p, const Grid &g, const Onsite &os, const double *S, float *b, bool wide,
+                       hipStream_t st);
 
 // Learned path corrector (spx_net.hip).
 spx_status net_apply(spx_net *net, const float *params, const int32_t dims[3], int32_t batch, const double *Sg,

@@ -197,8 +197,9 @@ __device__ __forceinline__ void add_accepted(unsigned long long *__restrict__ ac
     }
 }
 
-// One colour of one sweep.  Thread t covers x-slot j = t % J of row (y, z, a)
-// = t / J, J = ceil(Lx / C): the row's sites of colour c are x = x0 + C j.
+// One colour of one sweep, slots from t0 on.  Thread t covers x-slot j = t % J
+// of row (y, z, a) = t / J, J = ceil(Lx / C): the row's sites of colour c are
+// x = x0 + C j.
 // Bilinear field of an interior site (every neighbour inside the lattice):
 // neighbour j = i + off_p, no coordinate wrapping.
 template <bool ISO, int UNR>
@@ -228,7 +229,7 @@ template <bool ISO, int METHOD, int UNR>
 __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, BondTable tb, Grid g, Onsite os,
                                                     McColour col, int c, double beta, uint64_t seed,
                                                     uint64_t sweep, unsigned long long *__restrict__ acc,
-                                                    const int64_t *__restrict__ off, int3 rad) {
+                                                    const int64_t *__restrict__ off, int3 rad, int64_t t0) {
     const int C = col.C;
     const int J = (g.Lx + C - 1) / C;
     const int64_t n_rows = (int64_t)g.Ly * g.Lz * g.n_sub;
@@ -282,10 +283,13 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour(double *__restrict__ S, Bond
         S[N + i] = sn[1];
         S[2 * N + i] = sn[2];
     };
-    const int64_t t = xcd_block() * kMcB + threadIdx.x;
+    const int64_t t = t0 + xcd_block() * kMcB + threadIdx.x;
     if (t < total) site(t);
     if (acc) add_accepted(acc, accepted);
 }
+
+// Slots of one launch, whole blocks: a launch of 2^32 threads or more is refused.
+constexpr int64_t kMaxSlots = ((1ll << 24) - 1) * kMcB;
 
 // The padded colour-major layout.  Row (y, z, a) holds C class blocks of Jp
 // = J + 2 ex slots (J = ceil(Lx / C), ex = ceil(rx / C)); slot ex + jv of
@@ -318,7 +322,7 @@ struct CmDims {
     int64_t n_rows, NP;     // real rows (y, z, a) and padded doubles per component
     int64_t pitch;          // C Jp
     FastDiv by_J, by_Ly, by_Lz, by_C;
-    // slots, byte offsets and the colour form fit 32 bits (cm_narrow)
+    // slots, byte offsets and the colour form fit 32 bits
     bool narrow;
 };
 
@@ -391,7 +395,7 @@ template <bool ISO, int METHOD, int UNR, bool NARROW>
 __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, BondTable tb, Grid g, Onsite os,
                                                       McColour col, int c, double beta, uint64_t seed,
                                                       uint64_t sweep, unsigned long long *__restrict__ acc,
-                                                      const int64_t *__restrict__ coff, CmDims d) {
+                                                      const int64_t *__restrict__ coff, CmDims d, int64_t t0) {
     const int C = col.C;
     const int J = d.J;
     const int64_t total = d.n_rows * J;
@@ -534,7 +538,7 @@ __global__ __launch_bounds__(kMcB) void k_mc_colour_cm(double *__restrict__ P, B
             }
         }
     };
-    const int64_t t = xcd_block() * kMcB + threadIdx.x;
+    const int64_t t = (NARROW ? 0 : t0) + xcd_block() * kMcB + threadIdx.x;
     if (t < total) site(t);
     if (acc) add_accepted(acc, accepted);
 }
@@ -785,7 +789,7 @@ spx_status mc_colouring(spx_ham *h, const HamView &v, MCState *m) {
 // than an extent, when a ghost band of a periodic axis is wider than the
 // extent (a site would need copies two periods away), or when the buffer
 // cannot be allocated.
-bool mc_cm_buffer(const Grid &g, MCState *m, CmDims &d) {
+bool mc_cm_buffer(const Grid &g, MCState *m, bool wide, CmDims &d) {
     if (g.wrap_general) return false;
     d.C = m->C;
     d.J = (g.Lx + m->C - 1) / m->C;
@@ -804,7 +808,7 @@ bool mc_cm_buffer(const Grid &g, MCState *m, CmDims &d) {
     d.by_Ly = fast_div((uint32_t)g.Ly);
     d.by_Lz = fast_div((uint32_t)g.Lz);
     d.by_C = fast_div((uint32_t)d.C);
-    d.narrow = d.NP <= (int64_t)(UINT32_MAX / sizeof(double)) &&
+    d.narrow = !wide && d.NP <= (int64_t)(UINT32_MAX / sizeof(double)) &&
                (int64_t)d.C * ((int64_t)g.Ly + g.Lz + 1) <= INT32_MAX;
     if (g.per[0] && ((int64_t)d.C * d.ex > g.Lx || (int64_t)d.C * (d.J + d.ex) > 2 * (int64_t)g.Lx)) return false;
     if ((g.per[1] && d.ry > g.Ly) || (g.per[2] && d.rz > g.Lz)) return false;
@@ -906,7 +910,6 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
     unsigned long long *acc = accepted && p->method == 1 ? m->d_acc : nullptr;
     if (acc) k_mc_zero<<<1, kMcB, 0, st>>>(acc);
     const int64_t total = (int64_t)((v.grid.Lx + col.C - 1) / col.C) * v.grid.Ly * v.grid.Lz * v.grid.n_sub;
-    const unsigned grid = (unsigned)std::min<int64_t>((total + kMcB - 1) / kMcB, INT32_MAX);  // total <= the state's sites x 2
     const bool iso = v.tab.iso != 0;
     const int3 rad = make_int3(m->rad[0], m->rad[1], m->rad[2]);
     int max_bonds = 0;
@@ -919,13 +922,17 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
     // shells, 20 colours, one sweep: 1.88 against 15.0 ms).
     CmDims cd{};
     const bool cm = p->layout == 0 && (p->n_sweeps >= 2 || (p->n_sweeps == 1 && col.C > 2)) &&
-                    mc_cm_buffer(v.grid, m, cd);
+                    mc_cm_buffer(v.grid, m, v.index64->wide, cd);
+    // a launch holds less than 2^32 threads (the narrow form has fewer slots)
+    const int64_t most = cm && cd.narrow ? total : v.index64->mc_slots > 0 ? v.index64->mc_slots : kMaxSlots;
     const unsigned pgrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((cd.NP + kMcB - 1) / kMcB, 65536));
     const unsigned ngrid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((v.grid.N + kMcB - 1) / kMcB, 65536));
     if (cm) k_mc_to_cm<<<pgrid, kMcB, 0, st>>>(S, m->d_cm, v.grid, cd);
     for (int n = 0; n < p->n_sweeps; ++n) {
         const uint64_t sweep = p->sweep0 + (uint64_t)n;
-        for (int c = 0; c < col.C; ++c) {
+        for (int c = 0; c < col.C; ++c)
+        for (int64_t t0 = 0; t0 < total; t0 += most) {
+            const unsigned grid = (unsigned)((std::min(most, total - t0) + kMcB - 1) / kMcB);
             if (cm) {
                 double *P = m->d_cm;
                 const int64_t *co = m->d_coff;
@@ -938,7 +945,7 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
                     constexpr bool NW = decltype(narrow)::value;
                     auto go = [&](auto kernel) {
                         kernel<<<grid, kMcB, 0, st>>>(P, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc,
-                                                      co, cd);
+                                                      co, cd, t0);
                     };
                     if (p->method == 0) {
                         if (iso && short_list) go(k_mc_colour_cm<true, 0, 2, NW>);
@@ -955,11 +962,11 @@ spx_status spx_mc_sweep(spx_ham *h, double *S, const spx_mc_params *p, unsigned 
                 continue;
             }
             if (p->method == 0) {
-                if (iso) k_mc_colour<true, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
-                else k_mc_colour<false, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
+                if (iso) k_mc_colour<true, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad, t0);
+                else k_mc_colour<false, 0, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad, t0);
             } else {
-                if (iso) k_mc_colour<true, 1, 4><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
-                else k_mc_colour<false, 1, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad);
+                if (iso) k_mc_colour<true, 1, 4><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad, t0);
+                else k_mc_colour<false, 1, 2><<<grid, kMcB, 0, st>>>(S, v.tab, v.grid, v.onsite, col, c, beta, p->seed, sweep, acc, m->d_off, rad, t0);
             }
         }
     }

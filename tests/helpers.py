@@ -38,6 +38,15 @@ def gpu_hamiltonian(w: Workload, field_prec=None, **kw):
                                  dipolar=w.dipolar, field_prec=prec, **kw)
 
 
+def index64(h, wide, mc_slots=0):
+    """Ask a handle for the 64-bit forms of its kernels at any size, and for at
+    most mc_slots slots in a Monte Carlo launch (spx_debug_index64)."""
+    import ctypes as C
+    from paper_2605_26016_amd import spx
+    status = spx.load().spx_debug_index64(C.c_void_p(h.handle), C.c_int32(wide), C.c_int64(mc_slots))
+    assert status == 0, spx.last_error()
+
+
 def to_dev(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()

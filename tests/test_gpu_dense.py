@@ -19,7 +19,7 @@ import numpy as np
 import pytest
 
 import oracle
-from tests.helpers import k7_table, max_rel, require_gpu, round_bf16, round_fp16, to_dev
+from tests.helpers import index64, k7_table, max_rel, require_gpu, round_bf16, round_fp16, to_dev
 from workloads import random_sphere
 
 pytestmark = pytest.mark.gpu
@@ -148,3 +148,22 @@ def test_dense_mfma_at_paired_load_edges(L, per, prec, rnd):
     Je, Se = emulated(prec, rnd, J, S)
     ref = oracle.field(oracle.Model(lat, bonds=(ab[:, 0], ab[:, 1], dl, Je), B=(0, 0, 0.5)), Se)
     assert max_rel(got, ref) <= 1e-5, max_rel(got, ref)
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("per", [(0, 0, 0), (1, 0, 1)], ids=["open", "mixed"])
+@pytest.mark.parametrize("L", [(22, 33, 17), (24, 7, 15), (37, 32, 1)], ids=lambda L: "x".join(map(str, L)))
+def test_dense_mfma_large_lattice_form_equals_the_small_one(L, per, prec):
+    # 64-bit addresses, which only lattices of 2^29 sites take by themselves
+    import torch
+    from paper_2605_26016_amd import spx
+    ab, dl, J = k7_table()
+    h = spx.setup_hamiltonian(L, mu=(2.0,), periodic=per, bonds=(ab, dl, J), B=(0, 0, 0.5), K=0.2, field_prec=prec,
+                              backend=2)
+    S = to_dev(random_sphere(L[0] * L[1] * L[2], 12))
+    out = []
+    for wide in (0, 1):
+        index64(h, wide)
+        out.append(torch.full_like(S, np.nan, dtype=torch.float32))
+        spx.eval_field(h, S, out[-1])
+    assert torch.equal(*out)

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import oracle
-from tests.helpers import gpu_hamiltonian, oracle_model, require_gpu, to_dev
+from tests.helpers import gpu_hamiltonian, index64, oracle_model, require_gpu, to_dev
 from workloads import Workload, bcc_5shell_stochastic, random_sphere
 
 pytestmark = pytest.mark.gpu
@@ -282,3 +282,27 @@ def test_reciprocal_slot_coordinates_match_the_natural_layout(L, method):
         out.append((S.cpu().numpy(), int(acc.item())))
     assert np.max(np.abs(out[0][0] - out[1][0])) <= 1e-11
     assert out[0][1] == out[1][1]
+
+
+@pytest.mark.parametrize("couplings", [dict(J_shell=(1.0,)), dict(J_shell=(1.0, 0.3, -0.2)),
+                                       dict(J_shell=(1.0,), D_shell=(0.3,))], ids=["one_shell", "shells", "dmi"])
+@pytest.mark.parametrize("method", [0, 1], ids=["heat_bath", "metropolis"])
+@pytest.mark.parametrize("L,periodic", [((12, 8, 24), (1, 1, 1)), ((33, 17, 9), (0, 0, 0))], ids=["periodic", "open"])
+@pytest.mark.parametrize("slots", [0, 256, 700])
+def test_large_lattice_forms_equal_the_small_ones(L, periodic, method, couplings, slots):
+    # the 64-bit forms and a colour cut into launches, which only lattices far
+    # beyond a test's size take by themselves, in both layouts
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="t", L=L, periodic=periodic, B=(0.0, 0.3, 1.0), field_prec="fp64", **couplings)
+    S0 = random_sphere(w.N, 6)
+    for in_place in (False, True):
+        out = []
+        for wide in (0, 1):
+            h = gpu_hamiltonian(w)
+            index64(h, wide, slots if wide else 0)
+            S = to_dev(S0)
+            acc = torch.zeros(1, dtype=torch.int64, device=S.device)
+            spx.mc_sweep(h, S, 60.0, seed=7, sweep0=3, n_sweeps=3, method=method, accepted=acc, in_place=in_place)
+            out.append((S, int(acc.item())))
+        assert torch.equal(out[0][0], out[1][0]) and out[0][1] == out[1][1], in_place
