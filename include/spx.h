@@ -112,8 +112,10 @@ typedef struct {
  * backend representations: dense convolution).  autotune: 0 off, 1 time candidate launch shapes at setup and
  * keep the fastest (cached per shape key in tune_cache_path if non-NULL, one
  * JSON object per line: {"key": ..., "zchunk": ..., "heun_mode": ..., "us": ...,
- * "tile_rows": ...}; plain lines "key zchunk heun_mode us [tile_rows]" are
- * read as well; the last entry of a key wins).
+ * "tile_rows": ..., "rule": ...}; rule 1: the Heun step splits z as an untuned
+ * handle does, 0 or absent: it marches zchunk planes; plain lines "key zchunk
+ * heun_mode us [tile_rows]" are read as well; the last entry of a key wins).
+ * The tuned chunk is the Heun step's; field and energy keep the default split.
  * stencil_engine: 0 auto, 1 gather kernel (any bond table), 2 z-marching LDS
  * engine (bond tables that match a built-in shell shape: simple cubic shells
  * 1, 1-3, 1-4; bcc shells 1-5).  zchunk: z planes per block of the z-march

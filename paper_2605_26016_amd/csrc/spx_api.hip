@@ -176,6 +176,7 @@ struct spx_ham {
     DensePlan *dense = nullptr;  // dense-window MFMA backend
     // z-march engine plan (valid when the bond table matches a shell shape)
     ZPlan zp;
+    ZPlan zheun;  // the Heun step's: as zp, with the chunk and rows that the tuner chose
     ZPlan zp64;  // FP64 plan of the same table for batched-image field passes (GNEB)
     int engine = 1;          // 1 gather, 2 z-march
     bool fusable = false;    // the fused Heun step (mode 8) applies
@@ -322,6 +323,7 @@ spx_status get_ham_view(spx_ham *h, HamView &v) {
 
 static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z, bool tune_field, hipStream_t st);
 static spx_status heun_buffers(spx_ham *h, int hf);
+static int nominal_zchunk(int hf);
 // Heun modes of the z-march engine: 1 .. kMaxHeunMode (spx_options.heun_field);
 // mode 8 is the temporally fused single-pass step
 constexpr int kMaxHeunMode = 8;
@@ -562,8 +564,9 @@ spx_status spx_setup_hamiltonian(const spx_lattice_desc *lat, const spx_model_de
         // recomputes.  Default: the fused step where it applies, else mode 3
         if (h->engine == 2) {
             h->heun_field = hfield_req > 0 ? hfield_req : (fusable ? kHeunFused : 3);
-            if (hfield_req == 0 && fusable && zchunk_req == 0) h->zp.zch = 64;
         }
+        h->zheun = h->zp;
+        if (h->engine == 2 && hfield_req == 0 && fusable && zchunk_req == 0) h->zheun.zch = nominal_zchunk(kHeunFused);
         if ((s = heun_buffers(h, h->heun_field)) != SPX_OK) {
             free_all(h);
             delete h;
@@ -644,11 +647,11 @@ spx_status spx_get_info(spx_ham *h, spx_ham_info *info) {
     info->workspace_bytes = h->ws_bytes;
     info->stencil_engine = h->engine;
     info->shape = h->engine == 2 ? h->zp.kind : -1;
-    info->zchunk = h->engine == 2 ? h->zp.zch : 0;
+    info->zchunk = h->engine == 2 ? h->zheun.zch : 0;
     info->heun_field = h->heun_field;
     info->tuned = h->tuned;
     info->tuned_step_us = h->tune_us;
-    info->tile_rows = (h->engine == 2 && h->heun_field == kHeunFused) ? fused_rows(h->zp) : 0;
+    info->tile_rows = (h->engine == 2 && h->heun_field == kHeunFused) ? fused_rows(h->zheun) : 0;
     info->heun_graph = h->heun_graph ? 1 : 0;
     return SPX_OK;
 }
@@ -686,7 +689,7 @@ static spx_status enqueue_heun_step(spx_ham *h, const HeunConst &hc, uint64_t st
     hipError_t e;
     if (h->engine == 2 && h->heun_field == kHeunFused) {
         KernelTimer kt(h, 0, st);
-        e = heun_fused(h->zp, h->grid, h->onsite, hc, step, cur, nxt, st);
+        e = heun_fused(h->zheun, h->grid, h->onsite, hc, step, cur, nxt, st);
         if (e != hipSuccess) return hip_fail(e, "spx_llg_heun_step: fused step");
         return SPX_OK;
     }
@@ -700,7 +703,7 @@ static spx_status enqueue_heun_step(spx_ham *h, const HeunConst &hc, uint64_t st
         // elementwise FP64 stage; corrector split (mode 5) or fused (mode 6)
         {
             KernelTimer kt(h, 0, st);
-            e = zmarch_bil(h->zp, h->grid, cur, h->d_bstore, st);
+            e = zmarch_bil(h->zheun, h->grid, cur, h->d_bstore, st);
             if (e == hipSuccess)
                 e = heun_split_pre(h->grid, h->onsite, hc, step, cur, h->d_bstore, bd0, h->d_St, h->d_P, h->d_eta, st);
         }
@@ -713,11 +716,11 @@ static spx_status enqueue_heun_step(spx_ham *h, const HeunConst &hc, uint64_t st
         {
             KernelTimer kt(h, 1, st);
             if (h->heun_field == 5) {
-                e = zmarch_bil(h->zp, h->grid, h->d_St, h->d_bstore, st);
+                e = zmarch_bil(h->zheun, h->grid, h->d_St, h->d_bstore, st);
                 if (e == hipSuccess)
                     e = heun_split_post(h->grid, h->onsite, hc, h->d_St, h->d_bstore, bd1, h->d_P, h->d_eta, nxt, st);
             } else {
-                e = zmarch_correct(h->zp, h->grid, h->onsite, hc, step, cur, h->d_St, bd0, bd1, nullptr, h->d_P,
+                e = zmarch_correct(h->zheun, h->grid, h->onsite, hc, step, cur, h->d_St, bd0, bd1, nullptr, h->d_P,
                                    hc.noise ? h->d_eta : nullptr, nxt, st);
             }
         }
@@ -730,7 +733,7 @@ static spx_status enqueue_heun_step(spx_ham *h, const HeunConst &hc, uint64_t st
         {
             const int hf = h->heun_field;
             const bool staged = hf >= 3;
-            e = zmarch_predict(h->zp, h->grid, h->onsite, hc, step, cur, bd0, h->d_St,
+            e = zmarch_predict(h->zheun, h->grid, h->onsite, hc, step, cur, bd0, h->d_St,
                                hf == 2 ? h->d_bstore : nullptr, staged ? h->d_P : nullptr,
                                (hf == 3 && hc.noise) ? h->d_eta : nullptr, (hf == 4 && hc.noise) ? h->d_eta : nullptr,
                                st);
@@ -747,7 +750,7 @@ static spx_status enqueue_heun_step(spx_ham *h, const HeunConst &hc, uint64_t st
     {
         KernelTimer kt(h, 1, st);
         if (h->engine == 2)
-            e = zmarch_correct(h->zp, h->grid, h->onsite, hc, step, cur, h->d_St, bd0, bd1,
+            e = zmarch_correct(h->zheun, h->grid, h->onsite, hc, step, cur, h->d_St, bd0, bd1,
                                h->heun_field == 2 ? h->d_bstore : nullptr, h->heun_field >= 3 ? h->d_P : nullptr,
                                (h->heun_field >= 3 && h->heun_field != 7 && hc.noise) ? h->d_eta : nullptr, nxt,
                                st);
@@ -766,6 +769,9 @@ __global__ void k_fill_up(double *S, int64_t N) {
     S[N + i] = 0.0;
     S[2 * N + i] = 1.0;
 }
+
+// What a handle reports as its chunk when the rule makes it.
+static int nominal_zchunk(int hf) { return hf == kHeunFused ? 64 : 8; }
 
 // Buffers that Heun mode hf needs (allocated if missing): 2 the FP32 field
 // store, 3 the stage store P and the noise store.
@@ -798,53 +804,57 @@ static void heun_buffers_trim(spx_ham *h) {
 }
 
 // Autotuner of the z-march engine: times stochastic Heun steps for every
-// candidate (z planes per block, stored or recomputed corrector field, and
-// for the fused step the block rows) on a scratch state and keeps the
-// fastest.  Results are cached per shape key (shell shape, precision,
-// sublattices, extents, boundary flags) in cache_path when it is given, one
-// JSON object per line, {"key": ..., "zchunk": ..., "heun_mode": ...,
-// "us": ..., "tile_rows": ...}; lines of the earlier plain form
-// "key zchunk heun_mode us [tile_rows]" are read as well.
+// candidate (z planes per block: the untuned handle's own rule and fixed ones;
+// stored or recomputed corrector field, and for the fused step the block rows)
+// on a scratch state and keeps the fastest.  The choice is the Heun step's
+// (h->zheun): field and energy keep the rule.  Results are cached per shape key
+// (shell shape, precision, sublattices, extents, boundary flags) in cache_path
+// when it is given, one JSON object per line, {"key": ..., "zchunk": ...,
+// "heun_mode": ..., "us": ..., "tile_rows": ..., "rule": ...}; lines without
+// "rule" hold a fixed chunk, and lines of the earlier plain form "key zchunk
+// heun_mode us [tile_rows]" are read as well.
 static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z, bool tune_field, hipStream_t st) {
     const Grid &g = h->grid;
     char key[160];
     std::snprintf(key, sizeof(key), "shape%d_prec%d_sub%d_%dx%dx%d_per%d%d%d", h->zp.kind, h->field_prec, g.n_sub,
                   g.Lx, g.Ly, g.Lz, g.per[0], g.per[1], g.per[2]);
-    // cache entries: key, z chunk, Heun mode, microseconds per step, and the
-    // fused step's rows per block (0 for the other modes; plain lines
-    // without it read as 0)
-    const bool tune_rows = h->fusable && h->zp.kind == SHAPE_SC_NN && h->zp.prec == 1 && h->zp.frows == 0;
+    // cache entries: key, z chunk (with the rule its nominal value), Heun mode,
+    // microseconds per step, the fused step's rows per block (0 for the other
+    // modes; plain lines without it read as 0) and whether the rule was kept
+    ZPlan &zp = h->zheun;
+    const bool tune_rows = h->fusable && zp.kind == SHAPE_SC_NN && zp.prec == 1 && zp.frows == 0;
+    auto set_chunk = [&](int z, int hf) {  // z = 0: the rule
+        zp.zauto = z == 0 ? 1 : 0;
+        zp.zch = z == 0 ? nominal_zchunk(hf) : z;
+    };
     if (cache_path) {
         if (FILE *f = std::fopen(cache_path, "r")) {
             char line[256], k2[160];
-            int z, hf, rows;
+            int z, hf, rows, rule;
             double us;
             bool hit = false;
-            int cz = 0, chf = 0, crows = 0;
+            int cz = 0, chf = 0, crows = 0, crule = 0;
             double cus = 0.0;
             while (std::fgets(line, sizeof(line), f)) {
-                rows = 0;
+                rows = rule = 0;
                 int n = std::sscanf(line, " {\"key\": \"%159[^\"]\", \"zchunk\": %d, \"heun_mode\": %d, \"us\": %lf, "
-                                          "\"tile_rows\": %d",
-                                    k2, &z, &hf, &us, &rows);
-                if (n != 5) {
-                    rows = 0;
+                                          "\"tile_rows\": %d, \"rule\": %d",
+                                    k2, &z, &hf, &us, &rows, &rule);
+                if (n < 5) {
+                    rows = rule = 0;
                     n = line[0] == '{' ? 0 : std::sscanf(line, "%159s %d %d %lf %d", k2, &z, &hf, &us, &rows);
                 }
                 if (n >= 4 && std::strcmp(k2, key) == 0 && z > 0 && z <= 4096 && hf >= 1 && hf <= kMaxHeunMode &&
                     (rows == 0 || rows == 8 || rows == 16)) {
-                    cz = z; chf = hf; cus = us; crows = rows; hit = true;   // the last matching line wins
+                    cz = z; chf = hf; cus = us; crows = rows; crule = rule; hit = true;   // the last matching line wins
                 }
             }
             std::fclose(f);
             if (hit && !((chf == 2 || chf == 5 || chf == 6) && h->field_prec != SPX_FP32) &&
                 !(chf == kHeunFused && !h->fusable)) {
-                if (tune_z) {
-                    h->zp.zch = cz;
-                    h->zp.zauto = 0;
-                }
+                if (tune_z) set_chunk(crule ? 0 : cz, chf);
                 if (tune_field) h->heun_field = chf;
-                if (tune_rows && h->heun_field == kHeunFused && chf == kHeunFused && crows != 0) h->zp.frows = crows;
+                if (tune_rows && h->heun_field == kHeunFused && chf == kHeunFused && crows != 0) zp.frows = crows;
                 h->tune_us = cus;
                 h->tuned = 1;
                 spx_status s = heun_buffers(h, h->heun_field);
@@ -853,18 +863,16 @@ static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z,
             }
         }
     }
-    // candidate z chunks: the two-sweep modes march short chunks; the fused
-    // step pays a four-plane pipeline fill per chunk, so it tries longer ones
+    // candidate z chunks: the rule first; the two-sweep modes march short
+    // chunks; the fused step pays a four-plane pipeline fill per chunk, so it
+    // tries longer ones
     auto zlist = [&](int hf) {
-        std::vector<int> zs;
-        if (!tune_z) {
-            zs.push_back(h->zp.zch);
-            return zs;
-        }
+        if (!tune_z) return std::vector<int>{zp.zch};
+        std::vector<int> zs = {0};
         const std::vector<int> cand = hf == kHeunFused ? std::vector<int>{16, 32, 64, 128}
                                                        : std::vector<int>{4, 8, 16, 32};
         for (int z : cand)
-            if (z <= g.Lz || zs.empty()) zs.push_back(z);
+            if (z <= g.Lz) zs.push_back(z);
         return zs;
     };
     std::vector<int> hfs = {h->heun_field};
@@ -896,20 +904,21 @@ static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z,
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);
-    double best = 1e300;
-    int bz = h->zp.zch, bh = h->heun_field, brows = h->zp.frows;
+    struct Choice {
+        double us;
+        int z, hf, rows;
+    } best[2] = {{1e300, 0, 0, 0}, {1e300, 0, 0, 0}};  // of the rule, of fixed chunks
     const int reps = 4;
     // block shapes of the fused step: 16 or 8 rows (wavefronts) per block
     auto rowlist = [&](int hf) {
         if (hf == kHeunFused && tune_rows) return std::vector<int>{16, 8};
-        return std::vector<int>{h->zp.frows};
+        return std::vector<int>{zp.frows};
     };
     for (int hf : hfs)
         for (int rows : rowlist(hf))
         for (int z : zlist(hf)) {
-            h->zp.zch = z;
-            h->zp.zauto = 0;
-            h->zp.frows = rows;
+            set_chunk(z, hf);
+            zp.frows = rows;
             h->heun_field = hf;
             spx_status r = SPX_OK;
             for (int k = 0; k < 2 && r == SPX_OK; ++k) r = enqueue_heun_step(h, hc, k, tmp, h->d_Sp, st);
@@ -924,22 +933,26 @@ static spx_status autotune_heun(spx_ham *h, const char *cache_path, bool tune_z,
             float ms = 0.0f;
             (void)hipEventElapsedTime(&ms, e0, e1);
             const double us = 1e3 * ms / reps;
-            if (us < best) { best = us; bz = z; bh = hf; brows = rows; }
+            if (us < best[z > 0].us) best[z > 0] = {us, z, hf, rows};
         }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipFree(tmp);
     if (s != SPX_OK) return s;
-    h->zp.zch = bz;
-    h->zp.frows = brows;
-    h->heun_field = bh;
+    // a fixed chunk has to beat the rule by more than two timings of a short
+    // step differ
+    const Choice &b = best[best[1].us < best[0].us - 0.5];
+    set_chunk(b.z, b.hf);
+    zp.frows = b.rows;
+    h->heun_field = b.hf;
     h->tuned = 1;
-    h->tune_us = best;
+    h->tune_us = b.us;
     heun_buffers_trim(h);
     if (cache_path) {
         if (FILE *f = std::fopen(cache_path, "a")) {
-            std::fprintf(f, "{\"key\": \"%s\", \"zchunk\": %d, \"heun_mode\": %d, \"us\": %.3f, \"tile_rows\": %d}\n",
-                         key, bz, bh, best, bh == kHeunFused ? fused_rows(h->zp) : 0);
+            std::fprintf(f, "{\"key\": \"%s\", \"zchunk\": %d, \"heun_mode\": %d, \"us\": %.3f, \"tile_rows\": %d, "
+                            "\"rule\": %d}\n",
+                         key, zp.zch, b.hf, b.us, b.hf == kHeunFused ? fused_rows(zp) : 0, zp.zauto);
             std::fclose(f);
         }
     }

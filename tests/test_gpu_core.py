@@ -513,3 +513,57 @@ def test_dipolar_field_at_every_padded_extent(L, cell):
     S = random_sphere(w.N, 63)
     ref = dipolar_field_fft(L, cell, 2.0, S)
     assert max_rel(gpu_field(w, S, "fp32"), ref) <= 1e-5
+
+
+def best_step_us(h, S, n=64):
+    import torch
+    from paper_2605_26016_amd import spx
+    best = 1e9
+    for k in range(8):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        spx.llg_heun_step(h, S, alpha=0.1, dt_fs=0.1, temperature_K=10.0, seed=3, step0=n * k, n_steps=n)
+        t1.record()
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * t0.elapsed_time(t1) / n)
+    return best
+
+
+@pytest.mark.parametrize("w", [Workload(name="t", L=(32, 32, 32), J_shell=(1.0,)),
+                               Workload(name="t", L=(100, 100, 100), J_shell=(1.0, 0.188, -0.274)),
+                               bcc_5shell_stochastic((32, 32, 32))], ids=["sc32", "sc100", "bcc32"])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_tuned_steps_are_no_slower_than_untuned_ones(w, prec):
+    # the untuned handle's own split of z is one of the tuner's candidates; 1.2
+    # covers the difference of two timings, where fixed chunks alone took twice
+    # the time on the first of these lattices
+    S = to_dev(random_sphere(w.N, 5))
+    us = [best_step_us(gpu_hamiltonian(w, field_prec=prec, autotune=k), S.clone()) for k in (0, 1)]
+    print("untuned, tuned us a step:", us, flush=True)
+    assert us[1] <= 1.2 * us[0], us
+
+
+@pytest.mark.parametrize("line,zchunk", [
+    ('{"key": "%s", "zchunk": 4, "heun_mode": 3, "us": 1.500, "tile_rows": 0}', 4),
+    ('{"key": "%s", "zchunk": 4, "heun_mode": 3, "us": 1.500, "tile_rows": 0, "rule": 0}', 4),
+    ('{"key": "%s", "zchunk": 8, "heun_mode": 3, "us": 1.500, "tile_rows": 0, "rule": 1}', 8),
+    ('%s 4 3 1.5', 4)], ids=["no_rule_field", "fixed", "rule", "plain"])
+def test_tuned_chunk_is_the_heun_steps_alone(tmp_path, line, zchunk):
+    # whatever a cache line says, field and energy take the untuned handle's
+    # tiles: the energy's fixed-order sums agree bit for bit
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="t", L=(70, 33, 100), J_shell=(1.0, 0.188, -0.274, -0.161), K=0.1, field_prec="fp32")
+    cache = tmp_path / "tune.txt"
+    cache.write_text(line % "shape2_prec1_sub1_70x33x100_per111" + "\n")
+    S = to_dev(random_sphere(w.N, 6))
+    out = []
+    for kw in (dict(), dict(autotune=1, tune_cache_path=str(cache))):
+        h = gpu_hamiltonian(w, **kw)
+        E = torch.zeros(5, dtype=torch.float64, device="cuda")
+        spx.energy(h, S, E[4:], E)
+        out.append(E)
+    info = spx.get_info(h)
+    assert (info.tuned, info.zchunk, info.heun_field, info.tuned_step_us) == (1, zchunk, 3, 1.5)
+    assert cache.read_text().count("\n") == 1
+    assert torch.equal(*out)
