@@ -236,8 +236,8 @@ constexpr bool fft_own(int P) { return P >= 64 && P <= 1024; }
 // Rows (x): consecutive lanes on consecutive points, so up to 512 points a
 // pair of rows is part of one wavefront and needs no barrier (1024 points: two
 // wavefronts, barriers).  The same for the columns, staged through LDS to and
-// from their wavefronts, was slower (sc 256^3: y 390 against 335 us, the z pass
-// 1116 against 835), as were persistent z blocks that load ahead (971).  At sc
+// from their wavefronts, was slower (sc 256^3: y 390 against 335 us then, the z
+// pass 1116 against 835), as were persistent z blocks that load ahead (971).  At sc
 // 100^3 (256 points) the passes take 15 + 25 + 89 + 24 + 13 us.
 constexpr int fft_w(int N) { return N <= 512 ? 16 : 8; }
 constexpr int fft_zw(int N) { return N <= 128 ? 16 : 8; }
@@ -335,17 +335,32 @@ __device__ __forceinline__ void fft_sync() {
     }
 }
 
+// Twiddles of a pass (product Ns of the radices before it) for thread t's rows.
+template <int N, int Ns>
+__device__ __forceinline__ void fft_twiddles(float2 w[8], int t, const float2 *__restrict__ tw) {
+    constexpr int R = N / Ns < 8 ? N / Ns : 8;
+#pragma unroll
+    for (int k = 0; k < 8 / R; ++k) {
+        const int a = (t + k * (N / 8)) % Ns * (N / (Ns * R));
+#pragma unroll
+        for (int r = 1; r < R; ++r) w[k + (8 / R) * r] = tw[a * r];
+    }
+}
+
 // One exchange and the pass after it: the results of the pass of radix RP
 // (product NSP before it) are put in order in LDS (buf[fft_pos(p) W], buf at
 // the column's slot) and thread t's rows of the next pass read back,
 // multiplied by their twiddles and transformed.  TWO: consecutive exchanges
 // take two buffers in turn, and one barrier each suffices, since a buffer is
 // written again only after the barrier that followed its last read; with one
-// buffer a second barrier precedes the write.
-template <int N, int NSP, int RP, bool INV, int SYNC, bool TWO, int W>
+// buffer a second barrier precedes the write.  AHEAD: the twiddles are loaded
+// before the barriers instead of after them.
+template <int N, int NSP, int RP, bool INV, int SYNC, bool TWO, int W, bool AHEAD>
 __device__ __forceinline__ void fft_pass(float2 v[8], float2 *buf, int t, const float2 *__restrict__ tw) {
     constexpr int Ns = NSP * RP, R = N / Ns < 8 ? N / Ns : 8;
     static_assert(RP == 8, "only the last pass has a smaller radix");
+    float2 w[8];
+    if constexpr (AHEAD) fft_twiddles<N, Ns>(w, t, tw);
     if (!TWO) fft_sync<SYNC>();
     const int o = fft_pos((t / NSP) * Ns + t % NSP);
 #pragma unroll
@@ -353,27 +368,26 @@ __device__ __forceinline__ void fft_pass(float2 v[8], float2 *buf, int t, const 
     fft_sync<SYNC>();
 #pragma unroll
     for (int m = 0; m < 8; ++m) v[m] = buf[(fft_pos(t) + m * (N / 64 * 9)) * W];
+    if constexpr (!AHEAD) fft_twiddles<N, Ns>(w, t, tw);
 #pragma unroll
-    for (int k = 0; k < 8 / R; ++k) {
-        const int a = (t + k * (N / 8)) % Ns * (N / (Ns * R));
+    for (int k = 0; k < 8 / R; ++k)
 #pragma unroll
-        for (int r = 1; r < R; ++r) v[k + (8 / R) * r] = cmulw<INV>(v[k + (8 / R) * r], tw[a * r]);
-    }
+        for (int r = 1; r < R; ++r) v[k + (8 / R) * r] = cmulw<INV>(v[k + (8 / R) * r], w[k + (8 / R) * r]);
     dft_sets<R, INV, INV && Ns * R == N>(v);
 }
 
 // N-point FFT of a column: v[m] = row t + (N / 8) m on entry and exit.  A
 // padded extent is at least twice the lattice's, so the forward transform's
-// rows from N / 2 on (v[4..7]) are zero and not read, and the inverse leaves
-// v[4..7] undefined: those rows are cropped.  X: exchanges done so far in the
-// two buffers A and B (which one comes next).
-template <int N, bool INV, int SYNC, bool TWO, int W, int X = 0>
+// rows from N / 2 on (v[4..7]) are zero, and with HIN not read; the inverse
+// leaves v[4..7] undefined: those rows are cropped.  X: exchanges done so far
+// in the two buffers A and B (which one comes next).
+template <int N, bool INV, int SYNC, bool TWO, int W, int X = 0, bool HIN = !INV, bool AHEAD = false>
 __device__ __forceinline__ void fft_col(float2 v[8], float2 *A, float2 *B, int t, const float2 *__restrict__ tw) {
     float2 *const b0 = (X & 1) ? B : A, *const b1 = (X & 1) ? A : B;
-    dft8<INV, !INV>(v);
-    fft_pass<N, 1, 8, INV, SYNC, TWO, W>(v, b0, t, tw);
-    if constexpr (N > 64) fft_pass<N, 8, 8, INV, SYNC, TWO, W>(v, b1, t, tw);
-    if constexpr (N > 512) fft_pass<N, 64, 8, INV, SYNC, TWO, W>(v, b0, t, tw);
+    dft8<INV, HIN>(v);
+    fft_pass<N, 1, 8, INV, SYNC, TWO, W, AHEAD>(v, b0, t, tw);
+    if constexpr (N > 64) fft_pass<N, 8, 8, INV, SYNC, TWO, W, AHEAD>(v, b1, t, tw);
+    if constexpr (N > 512) fft_pass<N, 64, 8, INV, SYNC, TWO, W, AHEAD>(v, b0, t, tw);
 }
 constexpr int fft_exchanges(int N) { return N > 512 ? 3 : N > 64 ? 2 : 1; }
 
@@ -391,6 +405,11 @@ __global__ __launch_bounds__(N / 8 * fft_w(N)) void k_colfft_reg(const float2 *_
                                                                  int64_t J, int64_t in_bs, int64_t out_bs,
                                                                  const float2 *__restrict__ tw) {
     constexpr int W = fft_w(N), T = N / 8;
+    // 512 points: twiddles ahead of the barriers (inverse, sc 256^3: 325 -> 297
+    // us; the fused z pass 809 -> 858) and the forward transform's first
+    // butterflies over all eight rows, zeros included (334 -> 311).  Other
+    // extents are the same or slower with either.
+    constexpr bool HIN = !INV && N != 512, AHEAD = N == 512;
     __shared__ float2 lds[fft_lds(N, W)];
     const int w = threadIdx.x % W, t = threadIdx.x / W;  // column in the tile, thread of the column
     const int64_t vb = xcd_range(blockIdx.x + (int64_t)gridDim.x * blockIdx.y, (int64_t)gridDim.x * gridDim.y);
@@ -401,11 +420,11 @@ __global__ __launch_bounds__(N / 8 * fft_w(N)) void k_colfft_reg(const float2 *_
     float2 *dst = out + b * out_bs + j;
     float2 v[8];
 #pragma unroll
-    for (int m = 0; m < (INV ? 8 : 4); ++m) {
+    for (int m = 0; m < (HIN ? 4 : 8); ++m) {
         const int r = t + m * T;
         v[m] = (col && r < nin) ? src[(int64_t)r * J] : make_float2(0.0f, 0.0f);
     }
-    fft_col<N, INV, SYNC_BLOCK, false, W>(v, lds + w, lds + w, t, tw);
+    fft_col<N, INV, SYNC_BLOCK, false, W, 0, HIN, AHEAD>(v, lds + w, lds + w, t, tw);
     if (col) {
 #pragma unroll
         for (int m = 0; m < (INV ? 4 : 8); ++m) {
