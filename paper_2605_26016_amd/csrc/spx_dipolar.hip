@@ -242,6 +242,10 @@ constexpr bool fft_own(int P) { return P >= 64 && P <= 1024; }
 constexpr int fft_w(int N) { return N <= 512 ? 16 : 8; }
 constexpr int fft_zw(int N) { return N <= 128 ? 16 : 8; }
 constexpr int fft_xw(int N) { return N <= 256 ? 16 : 8; }  // row pairs per block
+// ... where blocks of as many would leave CUs without one: a wavefront's (1024
+// points: two wavefronts).  500 x 200 x 1: 96 us a field evaluation, 107 with 38
+// full blocks for the rows; 300 x 100 x 1 63 against 74.
+constexpr int fft_xfew(int N) { return N <= 512 ? 512 / N : 1; }
 // position p of an exchange: one row (value) skipped after every eight, so
 // that the steps of 1 and of 8 between the rows that half a wavefront touches
 // both fall on different banks
@@ -440,10 +444,10 @@ __global__ __launch_bounds__(N / 8 * fft_w(N)) void k_colfft_reg(const float2 *_
 // threads are consecutive lanes and its rows contiguous, so they load and
 // store directly.  Row r = (c, line) of the pair index holds spins S[r Lx + x]
 // (x < Lx, zero to N) and spectrum X[r H + k] (H = N / 2 + 1).
-template <int N>
-__global__ __launch_bounds__(N / 8 * fft_xw(N)) void k_xfft_fwd(const double *__restrict__ S, float2 *__restrict__ X,
-                                                             int Lx, int64_t nrows, const float2 *__restrict__ tw) {
-    constexpr int W = fft_xw(N), T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
+template <int N, int W>
+__global__ __launch_bounds__(N / 8 * W) void k_xfft_fwd(const double *__restrict__ S, float2 *__restrict__ X, int Lx,
+                                                        int64_t nrows, const float2 *__restrict__ tw) {
+    constexpr int T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
     constexpr int SYNC = N <= 512 ? SYNC_WAVE : SYNC_BLOCK;
     __shared__ float2 lds[W * RUN];
     const int t = threadIdx.x % T;
@@ -475,10 +479,10 @@ __global__ __launch_bounds__(N / 8 * fft_xw(N)) void k_xfft_fwd(const double *__
 // (A[N - k] = conj A[k]; the imaginary parts of bins 0 and N / 2 dropped, as
 // for a real inverse transform), one unnormalised inverse FFT, and rows
 // x < Lx of z = a + i b written to the field.
-template <int N>
-__global__ __launch_bounds__(N / 8 * fft_xw(N)) void k_xfft_inv(const float2 *__restrict__ X, float *__restrict__ b,
-                                                             int Lx, int64_t nrows, const float2 *__restrict__ tw) {
-    constexpr int W = fft_xw(N), T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
+template <int N, int W>
+__global__ __launch_bounds__(N / 8 * W) void k_xfft_inv(const float2 *__restrict__ X, float *__restrict__ b, int Lx,
+                                                        int64_t nrows, const float2 *__restrict__ tw) {
+    constexpr int T = N / 8, H = N / 2 + 1, RUN = fft_lds(N, 1) + 4;
     constexpr int SYNC = N <= 512 ? SYNC_WAVE : SYNC_BLOCK;
     __shared__ float2 lds[W * RUN];
     const int t = threadIdx.x % T;
@@ -790,11 +794,14 @@ spx_status eval_dipolar(DipolarPlan *p, const double *S, float *bdip, hipStream_
     const int64_t rows = (int64_t)Ly * Lz;
     hipError_t e;
     // x rows in pairs, one pair per column slot
+    auto few_rows = [&](int W) { return (3 * rows + 1) / 2 < (int64_t)W * device_cus(); };
     auto xgrid = [&](int W) { return (unsigned)(((3 * rows + 1) / 2 + W - 1) / W); };
     if (fft_own(Px)) {
         e = with_points(Px, [&](auto n) {
             constexpr int N = decltype(n)::value;
-            k_xfft_fwd<N><<<xgrid(fft_xw(N)), N / 8 * fft_xw(N), 0, st>>>(S, p->X, Lx, 3 * rows, p->tw_x);
+            constexpr int W = fft_xw(N), F = fft_xfew(N);
+            if (few_rows(W)) k_xfft_fwd<N, F><<<xgrid(F), N / 8 * F, 0, st>>>(S, p->X, Lx, 3 * rows, p->tw_x);
+            else k_xfft_fwd<N, W><<<xgrid(W), N / 8 * W, 0, st>>>(S, p->X, Lx, 3 * rows, p->tw_x);
         });
         if (e != hipSuccess) return set_hip_error(e, "dipolar x rows");
     } else {
@@ -835,7 +842,9 @@ spx_status eval_dipolar(DipolarPlan *p, const double *S, float *bdip, hipStream_
     if (fft_own(Px)) {
         e = with_points(Px, [&](auto n) {
             constexpr int N = decltype(n)::value;
-            k_xfft_inv<N><<<xgrid(fft_xw(N)), N / 8 * fft_xw(N), 0, st>>>(p->X, bdip, Lx, 3 * rows, p->tw_x);
+            constexpr int W = fft_xw(N), F = fft_xfew(N);
+            if (few_rows(W)) k_xfft_inv<N, F><<<xgrid(F), N / 8 * F, 0, st>>>(p->X, bdip, Lx, 3 * rows, p->tw_x);
+            else k_xfft_inv<N, W><<<xgrid(W), N / 8 * W, 0, st>>>(p->X, bdip, Lx, 3 * rows, p->tw_x);
         });
         if (e != hipSuccess) return set_hip_error(e, "dipolar x rows");
         return SPX_OK;

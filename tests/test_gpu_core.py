@@ -515,6 +515,19 @@ def test_dipolar_field_at_every_padded_extent(L, cell):
     assert max_rel(gpu_field(w, S, "fp32"), ref) <= 1e-5
 
 
+@pytest.mark.parametrize("L", [(20, 9, 5), (20, 60, 50), (40, 9, 5), (40, 61, 50), (70, 9, 5), (70, 61, 50), (140, 9, 5),
+                               (140, 61, 25), (260, 9, 5), (260, 61, 25)], ids=lambda L: "x".join(map(str, L)))
+def test_dipolar_rows_few_and_many(L):
+    # x rows of 64 to 1024 points, few (a wavefront of row pairs a block) and
+    # many (full blocks), an odd number of rows among them
+    import dataclasses
+    from oracle.dipolar_fft import dipolar_field_fft
+    cell = ((0.4, 0.0, 0.0), (0.1, 0.4, 0.0), (0.05, 0.08, 0.4))
+    w = dataclasses.replace(dip_workload(L), cell=cell, J_shell=(0.0,), D_shell=None, B=(0.0, 0.0, 0.0))
+    S = random_sphere(w.N, 64)
+    assert max_rel(gpu_field(w, S, "fp32"), dipolar_field_fft(L, cell, 2.0, S)) <= 1e-5
+
+
 def best_step_us(h, S, n=64):
     import torch
     from paper_2605_26016_amd import spx
