@@ -578,10 +578,10 @@ void min_free(spx_min *m) {
 hipError_t min_zero_state(spx_min *m, hipStream_t st) {
     const MinArgs &a = m->a;
     const int64_t n3 = 3 * a.N;
-    double *blocks[] = {a.V, a.W, a.Fb[0], a.Fb[1], a.Up, a.q};
-    for (double *p : blocks) k_min_zero<<<1024, 256, 0, st>>>(p, n3);
-    k_min_zero<<<1024, 256, 0, st>>>(a.Sh, n3 * (a.hist + 1));
-    k_min_zero<<<1024, 256, 0, st>>>(a.Yh, n3 * (a.hist + 1));
+    for (double *p : {a.V, a.W, a.Fb[0], a.Fb[1], a.Up, a.q})
+        if (p) k_min_zero<<<1024, 256, 0, st>>>(p, n3);
+    for (double *p : {a.Sh, a.Yh})
+        if (p) k_min_zero<<<1024, 256, 0, st>>>(p, n3 * (a.hist + 1));
     k_min_zero<<<1, 64, 0, st>>>(a.st, MS_N);
     k_min_zero<<<1, 64, 0, st>>>(a.rho, a.hist + 1);
     k_min_zero<<<1, 64, 0, st>>>(a.al, a.hist);
@@ -649,12 +649,17 @@ spx_status spx_min_create(spx_ham *h, const spx_min_params *p, void *stream, spx
         m->owned.push_back(*ptr);
         return true;
     };
-    bool ok = alloc(&m->b, n3) && alloc(&a.Fb[0], n3) && alloc(&a.V, n3) && alloc(&a.W, n3) && alloc(&a.Fb[1], n3) &&
-              alloc(&a.Up, n3) && alloc(&a.q, n3) && alloc(&a.Sh, n3 * (a.hist + 1)) &&
-              alloc(&a.Yh, n3 * (a.hist + 1)) &&
-              alloc(&a.part, std::max((size_t)std::max(kMinBlocks, m->ntile) * kNP, (size_t)kGramBlocks * gram_n(kGramHist))) &&
-              alloc(&a.coef, 1 + 2 * kGramHist) && alloc(&a.st, MS_N) &&
-              alloc(&a.rho, a.hist + 1) && alloc(&a.al, a.hist);
+    // the vectors of the state that the method reads, and no others
+    const bool pairs = a.method == 1 || a.method == 2, adam = a.method == 3, lbfgs = a.method == 2;
+    auto vec = [&](double **ptr, bool used, size_t slots = 1) { return !used || alloc(ptr, n3 * slots); };
+    bool ok = vec(&m->b, !m->fused) && vec(&a.Fb[0], true) && vec(&a.Fb[1], !adam) && vec(&a.V, adam) &&
+              vec(&a.W, adam) && vec(&a.Up, pairs) && vec(&a.q, lbfgs && a.hist > kGramHist) &&
+              vec(&a.Sh, lbfgs, a.hist + 1) && vec(&a.Yh, lbfgs, a.hist + 1) &&
+              alloc(&a.part, std::max((size_t)std::max(kMinBlocks, m->ntile) * kNP,
+                                      (size_t)kGramBlocks * gram_n(kGramHist))) &&
+              alloc(&a.coef, 1 + 2 * kGramHist) && alloc(&a.st, MS_N) && alloc(&a.rho, a.hist + 1) &&
+              alloc(&a.al, a.hist);
+    if (adam) a.Fb[1] = a.Fb[0];  // Adam looks at no earlier force
     if (!ok) {
         min_free(m);
         delete m;

@@ -152,3 +152,25 @@ def test_captured_iterations_can_be_replayed(method, history, engine, per_graph)
         torch.cuda.synchronize()
         assert spx.min_get_stats(mb)["iterations"] == done
         assert torch.equal(Sa, Sb), rep
+
+
+@pytest.mark.parametrize("engine", [0, 1], ids=["z_march", "gather"])
+@pytest.mark.parametrize("method,history,vectors", [("vp", 1, 2), ("bb", 1, 3), ("lbfgs", 5, 15), ("lbfgs", 9, 24),
+                                                    ("adam", 1, 3)])
+def test_state_holds_only_what_the_method_reads(method, history, vectors, engine):
+    # device memory taken by a minimiser in vectors of the state (12.6 MB; the
+    # allocator's granularity and the scalars stay below one): two forces; the
+    # previous step; 2 (history + 1) pairs; q of the vector recursion; Adam's
+    # force and moments; the field where the force is a pass of its own
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="m", L=(128, 64, 64), J_shell=(1.0,), field_prec="fp64")
+    h = gpu_hamiltonian(w, stencil_engine=engine)
+    free = torch.cuda.mem_get_info()[0]
+    mn = spx.min_create(h, method=method, history=history, dt=0.05)
+    used = (free - torch.cuda.mem_get_info()[0]) / (24 * w.N)
+    S = to_dev(random_sphere(w.N, 3))
+    spx.min_step(mn, S, 3)
+    assert spx.min_get_stats(mn)["iterations"] == 3 and float((S * S).sum(0).sub(1.0).abs().max()) < 1e-12
+    print(f"{method} {history}: {used:.2f} vectors", flush=True)
+    assert used < vectors + engine + 1
