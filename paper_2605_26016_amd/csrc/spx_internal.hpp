@@ -79,7 +79,9 @@ hipError_t launch_heun_correct(int field_prec, const BondTable &tb, const Grid &
 int energy_partial_count(const Grid &g);
 // Second-level quadruples of the energy reduction, stored after the first level.
 constexpr int kEnergyL2 = 1024;
-// Doubles of the energy partial buffer (both levels).
+// Doubles of the energy partial buffer (both levels): a quadruple per 256 sites,
+// and at least one for each of the z-march tiles that are resident at once.
+constexpr int kEnergyTiles = 512;
 size_t energy_partial_doubles(const Grid &g);
 // bil: precomputed bilinear field (double for field_prec 0, float otherwise)
 // or NULL to gather the neighbours.

@@ -309,7 +309,9 @@ int energy_partial_count(const Grid &g) {
     return (int)(((g.M + kBlock - 1) / kBlock) * g.n_sub);
 }
 
-size_t energy_partial_doubles(const Grid &g) { return (size_t)4 * ((size_t)energy_partial_count(g) + kEnergyL2); }
+size_t energy_partial_doubles(const Grid &g) {
+    return (size_t)4 * ((size_t)std::max(energy_partial_count(g), kEnergyTiles) + kEnergyL2);
+}
 
 hipError_t launch_energy(int field_prec, const BondTable &tb, const Grid &g, const Onsite &os,
                          const double *S, const float *bdip, const void *bil, double *partial, double *E,

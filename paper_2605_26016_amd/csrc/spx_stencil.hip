@@ -1586,9 +1586,7 @@ int chunk_of(const ZPlan &zp, const Grid &g, int nimg) {
     const int64_t columns = (int64_t)((g.Lx + TXW - 1) / TXW) * ((g.Ly + rows - 1) / rows) * nimg;
     const int occ = std::min(kernel_occupancy<KIND, T, ISO, MODE, TXW>(), 2);
     constexpr int D = make_shape(KIND).dzhi - make_shape(KIND).dzlo + 1;
-    // the energy's tiles fit its partial buffer (one quadruple per 256 sites)
-    const int64_t most = MODE == ZM_ENERGY ? energy_partial_count(g) : INT64_MAX;
-    return zchunk_rule(columns, g.Lz, device_cus() * occ, D, 64, most);
+    return zchunk_rule(columns, g.Lz, device_cus() * occ, D, 64, INT64_MAX);
 }
 
 template <int KIND, typename T, bool ISO, int MODE, int TXW>

@@ -515,6 +515,57 @@ def test_dipolar_field_at_every_padded_extent(L, cell):
     assert max_rel(gpu_field(w, S, "fp32"), ref) <= 1e-5
 
 
+@pytest.mark.parametrize("L", [(1, 1, 3000), (1, 1, 70000), (2, 2, 2000), (3, 700, 2), (70, 1, 500), (65, 33, 257)],
+                         ids=lambda L: "x".join(map(str, L)))
+@pytest.mark.parametrize("shells", [1, 4])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_energy_of_thin_lattices(L, shells, prec):
+    # lattices whose tiles are more than one per 256 sites, also many more (which
+    # gather), and one whose are fewer.  Against the gather energy, and a given chunk against the default:
+    # FP64 sums of at most 100 additions in a row, in two orders, of site
+    # energies of at most 3 |J0| + 6 |J1| + 4 |J2| + 3 |J3| + K + mu_B B each;
+    # the gather adds its FP32 bilinear sums in another order (1e-6 of it)
+    import torch
+    from paper_2605_26016_amd import spx
+    J = (1.0, 0.188, -0.274, -0.161)[:shells]
+    w = Workload(name="e", L=L, periodic=(1, 0, 0), J_shell=J, K=0.1, B=(0.0, 0.0, 1.0), field_prec=prec)
+    S = to_dev(random_sphere(w.N, 73))
+    most = sum(n * abs(j) for n, j in zip((3, 6, 4, 3), J)) + 0.1 + 0.06
+    out = []
+    for kw in (dict(), dict(zchunk=5), dict(stencil_engine=1)):
+        E = torch.zeros(5, dtype=torch.float64, device="cuda")
+        spx.energy(gpu_hamiltonian(w, **kw), S, E[4:], E)
+        out.append(E)
+    eps = 2.0 ** -53
+    assert float((out[0] - out[1]).abs().max()) <= 2 * 100 * eps * w.N * most
+    assert float((out[0] - out[2]).abs().max()) <= (1e-6 if prec == "fp32" else 300 * eps) * w.N * most
+
+
+def test_energy_of_a_rod_costs_little_more_than_its_field():
+    # the energy is the field's pass with a sum at its end; 2 lies between what
+    # it takes that way (1.3) and with tiles as few as one per 256 sites (4.7)
+    import torch
+    from paper_2605_26016_amd import spx
+    w = Workload(name="e", L=(2, 2, 2000), J_shell=(1.0, 0.188, -0.274, -0.161), field_prec="fp64")
+    h = gpu_hamiltonian(w)
+    S = to_dev(random_sphere(w.N, 74))
+    b, E = torch.zeros_like(S), torch.zeros(5, dtype=torch.float64, device="cuda")
+    us = []
+    for f in (lambda: spx.eval_field(h, S, b), lambda: spx.energy(h, S, E[4:], E)):
+        best = 1e9
+        for _ in range(8):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(50):
+                f()
+            t1.record()
+            torch.cuda.synchronize()
+            best = min(best, 1e3 * t0.elapsed_time(t1) / 50)
+        us.append(best)
+    print("field, energy us:", us, flush=True)
+    assert us[1] <= 2.0 * us[0], us
+
+
 @pytest.mark.parametrize("L", [(20, 9, 5), (20, 60, 50), (40, 9, 5), (40, 61, 50), (70, 9, 5), (70, 61, 50), (140, 9, 5),
                                (140, 61, 25), (260, 9, 5), (260, 61, 25)], ids=lambda L: "x".join(map(str, L)))
 def test_dipolar_rows_few_and_many(L):
