@@ -24,7 +24,7 @@
 namespace spx {
 
 struct PairList {
-    int64_t N = 0, P = 0;
+    int64_t N = 0, P = 0, longest = 0;  // sites, entries, entries of the longest row
     int tensor = 0, prec = 0;
     bool has_K = false;
     double B[3] = {0, 0, 0};
@@ -111,49 +111,66 @@ __device__ __forceinline__ void pl_bil(const PlView &v, const double *__restrict
         // deep (timed on sc 200^3 nearest-neighbour rows of six: FP32 field
         // 220 -> 208 us and FP64 294 -> 248 us against four deep; eight deep
         // was slower than four).  The last one to five of a row are one chunk
-        // too, as long as the longest remainder in the wavefront, with the
-        // index clamped to the row and the sum kept where there is no entry: a
-        // serial remainder loop, one dependent pair of loads after another, is
-        // what irregular rows spent their time in (800,000 sites with 4.8
-        // entries on average, FP32: 41 -> 33 us a Heun stage with one site per
-        // thread).
+        // too, as long as the longest remainder in the wavefront: a serial
+        // remainder loop, one dependent pair of loads after another, is what
+        // irregular rows spent their time in (800,000 sites with 4.8 entries
+        // on average, FP32: 41 -> 33 us a Heun stage with one site per
+        // thread).  A lane without an entry keeps its sum, and either loads its
+        // row's last one again or skips the load: where three quarters of the
+        // places hold entries the first is faster (that case, ten steps: 658
+        // us, 669 skipping), where few do the second (200,000 sites with 1.3,
+        // FP64 field: 11.0 us, 14.5 loading).
+        enum { FULL, CLAMP, SKIP };
         constexpr int kDeep = 6;
-        auto chunk = [&](int64_t p, auto nc, auto masked) __attribute__((always_inline)) {
-            constexpr int n = decltype(nc)::value;
-            constexpr bool M = decltype(masked)::value;
-            int64_t q[n];
+        auto chunk = [&](int64_t p, auto nc, auto mode) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value, M = decltype(mode)::value;
             AccT s[n][3], J[n];
-#pragma unroll
-            for (int u = 0; u < n; ++u) q[u] = M && u > 0 ? (p + u < p1 ? p + u : p1 - 1) : p + u;
+            int32_t j[n];
+            auto here = [&](int u) __attribute__((always_inline)) { return M == FULL || u == 0 || p + u < p1; };
 #pragma unroll
             for (int u = 0; u < n; ++u) {
-                const int64_t j = v.col[q[u]];
-                if constexpr (sizeof(AccT) == 4) J[u] = v.Jf[q[u]]; else J[u] = v.Jd[q[u]];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) s[u][c] = (AccT)S[c * N + j];
+                j[u] = 0;
+                J[u] = AccT(0);
+                if (M == CLAMP || here(u)) {
+                    const int64_t q = here(u) ? p + u : p1 - 1;
+                    j[u] = v.col[q];
+                    if constexpr (sizeof(AccT) == 4) J[u] = v.Jf[q]; else J[u] = v.Jd[q];
+                }
             }
 #pragma unroll
             for (int u = 0; u < n; ++u) {
-                const bool ok = !M || u == 0 || p + u < p1;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) s[u][c] = AccT(0);
+                if (M == CLAMP || here(u)) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) s[u][c] = (AccT)S[c * N + j[u]];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < n; ++u)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const AccT t = acc[c] + J[u] * s[u][c];
-                    acc[c] = ok ? t : acc[c];
+                    acc[c] = here(u) ? t : acc[c];
                 }
-            }
         };
         int64_t p = p0;
-        for (; p + kDeep <= p1; p += kDeep) chunk(p, std::integral_constant<int, kDeep>{}, std::false_type{});
+        for (; p + kDeep <= p1; p += kDeep) chunk(p, std::integral_constant<int, kDeep>{}, std::integral_constant<int, FULL>{});
         if (p < p1) {
-            // (rows of seven, 1,000,000 sites, FP32 field: 30 us with a chunk
-            // of one, 43 with one of five always)
+            // lanes with at least k entries left, of the lanes that have any
             const int rest = (int)(p1 - p);
-            const auto masked = std::true_type{};
-            if (__any(rest > 4)) chunk(p, std::integral_constant<int, 5>{}, masked);
-            else if (__any(rest > 3)) chunk(p, std::integral_constant<int, 4>{}, masked);
-            else if (__any(rest > 2)) chunk(p, std::integral_constant<int, 3>{}, masked);
-            else if (__any(rest > 1)) chunk(p, std::integral_constant<int, 2>{}, masked);
-            else chunk(p, std::integral_constant<int, 1>{}, masked);
+            const int c1 = __popcll(__ballot(1)), c2 = __popcll(__ballot(rest > 1)), c3 = __popcll(__ballot(rest > 2)),
+                      c4 = __popcll(__ballot(rest > 3)), c5 = __popcll(__ballot(rest > 4));
+            const int most = c5 ? 5 : c4 ? 4 : c3 ? 3 : c2 ? 2 : 1;
+            auto last = [&](auto mode) __attribute__((always_inline)) {
+                if (most == 5) chunk(p, std::integral_constant<int, 5>{}, mode);
+                else if (most == 4) chunk(p, std::integral_constant<int, 4>{}, mode);
+                else if (most == 3) chunk(p, std::integral_constant<int, 3>{}, mode);
+                else if (most == 2) chunk(p, std::integral_constant<int, 2>{}, mode);
+                else chunk(p, std::integral_constant<int, 1>{}, mode);
+            };
+            if (4 * (c1 + c2 + c3 + c4 + c5) >= 3 * most * c1) last(std::integral_constant<int, CLAMP>{});
+            else last(std::integral_constant<int, SKIP>{});
         }
     }
     for (int c = 0; c < 3; ++c) out[c] = (double)acc[c];
@@ -194,14 +211,15 @@ struct PlHeun {
 // stage 0: S~ = N[S + dt f(S)], keeps f(S); stage 1: S <- N[S + dt/2 (f0 + f(S~))]
 // One site per thread: the noise's coefficients, held over a grid-stride loop,
 // cost registers and a copy each (sc 200^3, FP32 field: 569 -> 504 us a step).
-// LOOP keeps the loop, on kPlBlocks blocks, for rows of many tensors: there the
-// registers are what keeps the wavefronts few enough for their couplings'
-// lines to stay in the L1 until all nine values are read (100,000 sites,
-// FP32, eight steps: 319 us with 14 entries a row and 865 with 40, against 402
-// and 1098 with one site per thread; with 3 entries 113 against 106).
+// Tensors ask for four wavefronts per SIMD: left alone the compiler holds fewer
+// couplings in flight to fit seven (100,000 sites with 14 entries, FP32, eight
+// steps: 402 us, 314 with four, 320 by the loop).  LOOP keeps the loop, on
+// kPlBlocks blocks, for long rows of tensors.
 template <typename AccT, bool TENSOR, int STAGE, bool LOOP>
-__global__ __launch_bounds__(kPlB) void k_pl_heun(PlView v, PlHeun hc, double *__restrict__ S,
-                                                  double *__restrict__ St, double *__restrict__ f0) {
+__global__ __launch_bounds__(kPlB) __attribute__((amdgpu_waves_per_eu(
+    TENSOR && !LOOP ? 4 : 1, TENSOR && !LOOP ? 4 : 8))) void k_pl_heun(PlView v, PlHeun hc, double *__restrict__ S,
+                                                                       double *__restrict__ St,
+                                                                       double *__restrict__ f0) {
     const int64_t N = v.N;
     auto site = [&](int64_t i) __attribute__((always_inline)) {
         const double *X = STAGE == 0 ? S : St;
@@ -327,6 +345,7 @@ spx_status pl_create(const spx_pairlist_desc *d, int prec, hipStream_t st, PairL
             return set_error(SPX_ERR_INVALID_ARG, "pair " + std::to_string(p) + " names a site out of range");
         ++row[d->target[p] + 1];
     }
+    const int64_t longest = *std::max_element(row.begin(), row.end());
     for (int64_t i = 0; i < N; ++i) row[i + 1] += row[i];
     std::vector<int32_t> col(std::max<int64_t>(P, 1));
     std::vector<int64_t> fill(row.begin(), row.end() - 1);
@@ -353,6 +372,7 @@ spx_status pl_create(const spx_pairlist_desc *d, int prec, hipStream_t st, PairL
     PairList *pl = new PairList();
     pl->N = N;
     pl->P = P;
+    pl->longest = longest;
     pl->tensor = tensor;
     pl->prec = prec;
     pl->has_K = d->K != nullptr;
@@ -427,9 +447,11 @@ hipError_t pl_energy(const PairList *p, const double *S, double *E, double *term
 hipError_t pl_heun(PairList *p, double *S, double alpha, double dt, double pre, double sig0, uint64_t seed,
                    uint64_t step0, uint32_t tag, int noise, int n_steps, hipStream_t st) {
     const PlView v = view(p);
-    // tensors: the line lies between rows of 3 entries (one site per thread
-    // faster by 6 - 16%) and of 6 (the loop faster by 5 - 10%)
-    const bool loop = p->tensor && p->P > 4 * p->N;
+    // tensors: the line lies between longest rows of 14 entries (100,000 sites,
+    // FP64, eight steps: 493 us with one site per thread, 530 by the loop) and
+    // of 40 (2020 against 1925; one row of 3000 in 5000 sites: 11.5 ms against
+    // 8.8)
+    const bool loop = p->tensor && p->longest > 16;
     const unsigned g = loop ? blocks_for(p->N) : (unsigned)((p->N + kPlB - 1) / kPlB);
     for (int k = 0; k < n_steps; ++k) {
         const PlHeun hc{dt, alpha, pre, sig0, seed, step0 + (uint64_t)k, tag, noise};
