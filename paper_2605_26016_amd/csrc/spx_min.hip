@@ -55,11 +55,15 @@ struct MinArgs {
     double *part;    // [kMinBlocks][kNP]
     double *st;      // [MS_N]
     double *rho;     // [hist + 1]
-    double *al;      // [hist]
-    double *coef;    // L-BFGS step coefficients of F, the pairs' s and y [1 + 2 kGramHist]
+    // [hist], then the L-BFGS step's coefficients of F and of the pairs' s and y
+    // [1 + 2 kGramHist] (coef_of): no pointer of their own, which would take the
+    // arguments into another cache line (0.2 of 2 us of the smallest kernels)
+    double *al;
     int nb;          // blocks of the elementwise passes
     int npart;       // partial sets the scalar pass reduces (nb, or the z-march tiles of the fused force pass)
 };
+
+__device__ __forceinline__ double *coef_of(const MinArgs &a) { return a.al + a.hist; }
 
 __device__ __forceinline__ double blk_sum(double v, double *red) {
     v = wave_sum(v);
@@ -314,11 +318,12 @@ __global__ __launch_bounds__(1024) void k_lb_coef(MinArgs a, int nb) {
         for (int u = t + 1; u < M; ++u) d += c[u] * g[gram_sy(M, u, t)];
         c[t] = al[t] - rho[t] * d;
     }
-    a.coef[0] = gamma;
+    double *const coef = coef_of(a);
+    coef[0] = gamma;
 #pragma unroll
     for (int t = 0; t < M; ++t) {
-        a.coef[1 + t] = -c[t];
-        a.coef[1 + kGramHist + t] = gamma * al[t];
+        coef[1 + t] = -c[t];
+        coef[1 + kGramHist + t] = gamma * al[t];
     }
 }
 
@@ -460,12 +465,13 @@ __global__ __launch_bounds__(kMinB) void k_min_update(MinArgs a, double *__restr
     double cs_[MM], cy[MM], cf = 0.0;
     if constexpr (M > 0) {
         const int np = (int)a.st[MS_NP];
-        cf = np ? a.coef[0] : a.dt;
+        const double *const coef = coef_of(a);
+        cf = np ? coef[0] : a.dt;
 #pragma unroll
         for (int t = 0; t < M; ++t) {
             off[t] = t < np ? (int64_t)slot_of(a, t) * 3 * N : -1;
-            cs_[t] = t < np ? a.coef[1 + t] : 0.0;
-            cy[t] = t < np ? a.coef[1 + kGramHist + t] : 0.0;
+            cs_[t] = t < np ? coef[1 + t] : 0.0;
+            cy[t] = t < np ? coef[1 + kGramHist + t] : 0.0;
         }
     }
     const double proj = a.st[MS_PROJ], alpha = a.st[MS_ALPHA];
@@ -657,8 +663,7 @@ spx_status spx_min_create(spx_ham *h, const spx_min_params *p, void *stream, spx
               vec(&a.Sh, lbfgs, a.hist + 1) && vec(&a.Yh, lbfgs, a.hist + 1) &&
               alloc(&a.part, std::max((size_t)std::max(kMinBlocks, m->ntile) * kNP,
                                       (size_t)kGramBlocks * gram_n(kGramHist))) &&
-              alloc(&a.coef, 1 + 2 * kGramHist) && alloc(&a.st, MS_N) && alloc(&a.rho, a.hist + 1) &&
-              alloc(&a.al, a.hist);
+              alloc(&a.st, MS_N) && alloc(&a.rho, a.hist + 1) && alloc(&a.al, a.hist + 1 + 2 * kGramHist);
     if (adam) a.Fb[1] = a.Fb[0];  // Adam looks at no earlier force
     if (!ok) {
         min_free(m);
