@@ -1104,6 +1104,47 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         if (zmarch_gneb_film(zp, g->hinst[k].g)) film_columns += c;
         else columns += c * g->hinst[k].n_img;
     }
+    for (int k = 0; k < n_inst; ++k) {
+        ZPlan &zp = g->zplan[k];
+        const GInst &gi = g->hinst[k];
+        if (!zp.valid || zp.prec != 0) continue;
+        if (zmarch_gneb_film(zp, gi.g)) {
+            zp.film = zmarch_gneb_film_chunk(film_columns, gi.n_img);
+            zp.zch = 1;
+        } else {
+            zp.zch = zmarch_gneb_chunk(zp, gi.g, columns, gi.items_per_img);
+        }
+        zp.zauto = 0;
+    }
+    // Ragged instances: their tiles are more than their items, but one tile of
+    // kGB lanes holds a fourth of its lanes in sites at least (four shells, 512
+    // lanes: an eighth).  Six open films of 34 to 95 cells x 15 images: 129 us
+    // an iteration by items, 49 by the passes; a rod of 2 x 2 x 20000 cells, 4
+    // of a tile's lanes: 555 us by items, 1383 by the passes.
+    // Those that march through planes spend more on a lane than the item passes
+    // do on a site.  With four shells, or isotropic and three quarters full,
+    // they still are faster at every size tried (one plane periodic in z, ten
+    // iterations, four shells: 600 x 600 x 16 images 8.4 ms by the passes, 10.1
+    // by items; one shell: 4.1 and 4.5).  Others only save launches, so they
+    // are for batches of few sites x images, fewer where more of a tile is
+    // empty (with tensors 65 x 65 x 50 546 us by the passes, 603 by items; 97 x
+    // 33 x 400 2025 and 1590; 20 x 20 x 400, half empty, 717 and 670).
+    constexpr int64_t kRaggedSites = 512 * 1024;
+    auto two_pass = [&](int k) { return g->zplan[k].valid && g->zplan[k].prec == 0; };
+    auto lanes = [&](int k) { return zmarch_gneb_columns(g->zplan[k], g->hinst[k].g) * kGB; };
+    auto plane = [&](int k) { return (int64_t)g->hinst[k].g.Lx * g->hinst[k].g.Ly; };
+    auto tiles_fit = [&](int k) {
+        return two_pass(k) && zmarch_gneb_tiles(g->zplan[k], g->hinst[k].g) <= g->hinst[k].items_per_img;
+    };
+    auto ragged = [&](int k) { return two_pass(k) && !tiles_fit(k) && lanes(k) <= 4 * plane(k); };
+    auto launch_bound = [&](int k) {  // faster by the passes in a small batch only
+        const ZPlan &zp = g->zplan[k];
+        return zp.film == 0 && zp.kind != SHAPE_SC_4SH && !(zp.iso && 3 * lanes(k) <= 4 * plane(k));
+    };
+    int64_t ragged_sites = 0;
+    for (int k = 0; k < n_inst; ++k)
+        if (ragged(k) && launch_bound(k))
+            ragged_sites += g->hinst[k].g.N * g->hinst[k].n_img * (6 * lanes(k) <= 10 * plane(k) ? 1 : 4);
     Onsite *d_os = nullptr;
     s = gneb_alloc(g, (void **)&d_os, sizeof(Onsite) * n_inst, "GNEB on-site tables");
     for (int k = 0; k < n_inst && s == SPX_OK; ++k) {
@@ -1122,24 +1163,10 @@ spx_status spx_gneb_create(spx_ham *const *H, int32_t n_inst, double *const *ima
         const ZPlan &zp = g->zplan[k];
         gi.zt_per_img = 0;
         gi.F = nullptr;
-        if (zp.valid && zp.prec == 0) {
-            if (zmarch_gneb_film(zp, gi.g)) {
-                g->zplan[k].film = zmarch_gneb_film_chunk(film_columns, gi.n_img);
-                g->zplan[k].zch = 1;
-            } else {
-                g->zplan[k].zch = zmarch_gneb_chunk(zp, gi.g, columns, gi.items_per_img);
-            }
-            g->zplan[k].zauto = 0;
-        }
         // The two passes (4 launches an iteration where the item passes take
-        // 11) where the tiles hold at most four times the sites, or are as few
-        // as the items.  Six films of 34 to 95 cells x 15 images, whose tiles
-        // are more than their items: 129 us an iteration by items, 49 by the
-        // passes; a rod of 2 x 2 x 20000 cells, 4 of a tile's 256 lanes: 555 us
-        // by items, 1383 by the passes.
-        if (zp.valid && zp.prec == 0 &&
-            (zmarch_gneb_tiles(zp, gi.g) <= gi.items_per_img ||
-             zmarch_gneb_columns(zp, gi.g) * kGB <= 4 * (int64_t)gi.g.Lx * gi.g.Ly)) {
+        // 11) where the tiles are as few as the items, or ragged ones (above)
+        // whose batch is small enough for the launches to count.
+        if (tiles_fit(k) || (ragged(k) && (!launch_bound(k) || ragged_sites <= kRaggedSites))) {
             gi.zt_per_img = zmarch_gneb_tiles(zp, gi.g);  // the two z-march passes; no stored force
         } else {
             g->zplan[k].txw = 64;

@@ -348,3 +348,33 @@ def test_statistics_from_several_threads():
     for t in threads:
         t.join()
     assert not wrong
+
+
+@pytest.mark.parametrize("n_img", [20, 130], ids=["passes", "items"])
+@pytest.mark.parametrize("couplings", [f[1] for f in FILMS], ids=[f[0] for f in FILMS])
+def test_ragged_lattices_of_few_and_many_images(couplings, n_img):
+    # films periodic in z, whose tiles are more than their items: the two passes
+    # up to 512 x 1024 sites x images of a batch, the item passes beyond (four
+    # shells: the two passes)
+    import torch
+    from paper_2605_26016_amd import spx
+    cases = [((65, 65, 1), (1, 1, 1)), ((33, 9, 1), (0, 1, 1))]
+    hams, bufs, refs = [], [], []
+    kw = dict(k_spring=1.0, dt=0.05, mass=1.0, ci_mode=1, ci_on_below=3.0)
+    for k, (L, periodic) in enumerate(cases):
+        w = Workload(name="t", L=L, periodic=periodic, K=0.05, B=(0.0, 0.0, 0.3), field_prec="fp64", **couplings)
+        Y0 = oracle.geodesic_path(random_sphere(w.N, 61 + k), random_sphere(w.N, 161 + k), n_img)
+        hams.append(gpu_hamiltonian(w))
+        bufs.append(to_dev(Y0))
+        refs.append((oracle_model(w), oracle.GnebState(Y0, **kw)))
+    g = spx.gneb_create(hams, bufs, spring_k=1.0, vp_dt=0.05, vp_mass=1.0, ci_mode=1, ci_on_below=3.0)
+    for it in range(2):
+        spx.gneb_step(g, 1)
+        torch.cuda.synchronize()
+        for k, (m, st) in enumerate(refs):
+            E, dist, fmax, ci = oracle.gneb_iterate(m, st)
+            assert float(np.max(np.abs(bufs[k].cpu().numpy() - st.Y))) <= 1e-9, (it, k)
+            s = spx.gneb_get_stats(g, k)
+            np.testing.assert_allclose(s["E"], E, rtol=1e-10, atol=1e-10)
+            np.testing.assert_allclose(s["dist"], dist, rtol=1e-10, atol=1e-10)
+            np.testing.assert_allclose(s["max_force"], fmax, rtol=1e-9)
