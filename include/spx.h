@@ -517,7 +517,7 @@ spx_status spx_net_destroy(spx_net *net);
  * SPX_ERR_INVALID_ARG for a value out of range. */
 spx_status spx_net_set_dilation(spx_net *net, const int32_t *dil);
 /* Arithmetic of the forward pass (spx_net_forward and the learned initial
- * path): SPX_FP32 (default, direct convolution on the vector ALUs) or
+ * path): SPX_FP32 (default, direct convolution on the FP32 matrix cores) or
  * SPX_BF16_MFMA (each layer a BF16 implicit GEMM on the matrix cores:
  * activations and weights rounded to BF16 to nearest even, FP32
  * accumulation, bias and output in FP32).  spx_net_backward always runs in

@@ -185,7 +185,7 @@ struct spx_ham {
     void *d_ebil = nullptr;  // energy: bilinear field of the z-march pass (made at the first call)
     double *d_P = nullptr;   // heun_field 3: S^n + dt/2 f(S^n)
     double *d_eta = nullptr; // heun_field 3, 4, 5, 6: the step's thermal noise
-    // Heun graph replay: 2-step graph with a device step counter
+    // Heun graph replay: a graph of 2 or 16 steps with a device step counter
     uint64_t *d_step = nullptr;
     hipGraphExec_t heun_graph = nullptr;
     std::vector<unsigned char> graph_key;

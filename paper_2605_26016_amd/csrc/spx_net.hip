@@ -7,13 +7,14 @@
 // S_hat = exp_{S_g}(P u) (the retraction of the Methods' minimum-energy-path
 // section).  Training loss: mean over images and sites of |S_hat - S*|^2.
 //
-// Activations are [batch][channel][z][y][x] FP32.  Convolutions are direct:
-// a 256-thread block owns an 8 x 8 x 4 output tile, stages the (10 x 10 x 6)
-// input halo tile of every input channel in LDS (SiLU applied on load) and
-// reads the weights through the scalar cache (uniform over the block).  The
-// input gradient is the same convolution with transposed, flipped weights;
-// weight gradients use one (out, in) channel pair per thread over the block's
-// sites, then a fixed-order reduction over blocks (deterministic).
+// Activations are [batch][channel][z][y][x] FP32.  Convolutions are direct
+// sums on the FP32 matrix cores: a 256-thread block takes boxes of at most 256
+// sites in turn (conv_box), stages a box and its one-cell halo for every input
+// channel in LDS (SiLU applied on load) and keeps the layer's weights there
+// over all its boxes.  The input gradient is the same convolution with
+// transposed, flipped weights; weight gradients are sums over the sites on the
+// FP64 matrix cores, one partial per block in registers over its boxes, then a
+// fixed-order reduction over the blocks (deterministic).
 //
 // A layer may be dilated by d (tap k reads offset (k - 1) d per axis, which
 // widens the receptive field of the four layers from 9 to 1 + 2 (d1 + d2 +
@@ -328,7 +329,9 @@ __global__ __launch_bounds__(kNT, 2) void k_conv_wgrad(const float *__restrict__
     double sb[COUT];
 #pragma unroll
     for (int c = 0; c < COUT; ++c) sb[c] = 0.0;
-    const int groups = (bx.vol + 3) / 4;  // at most 64, a multiple of 4 WS
+    // groups of four sites, at most 64 (54 for a box of 6 x 6 x 6); the last turn
+    // below may pass them but stays below 64, where rows are zero and hb valid
+    const int groups = (bx.vol + 3) / 4;
     for (int64_t tl = first_tile(); tl < bx.tiles; tl += gridDim.x) {
         const BoxTile o = box_tile(d, bx, tl);
         const float *csrc = (SWAP ? g : in) + (int64_t)o.image * CC * d.P;

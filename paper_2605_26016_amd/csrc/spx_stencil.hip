@@ -1007,10 +1007,13 @@ __device__ __forceinline__ void zmarch_block(const ZArgs &g, const Onsite &os, c
                 }
             });
         } else if (!zm_gneb(MODE) || plane_inside(q)) {
-        // (an input plane beyond an open face holds zeros and adds nothing: a
-        // film is one plane between two of them, and its tensors are most of
-        // the GNEB passes' arithmetic; the isotropic sums are too few for the
-        // branch, which held back the fetches around it: 96^3 809 against 799 us)
+        // (an input plane beyond an open face holds zeros and adds nothing.
+        // Of a slab of two planes every other input plane is one, and its
+        // tensors are most of the GNEB passes' arithmetic: ten iterations of 64
+        // x 64 x 2 x 24 images 343 us with the branch, 359 without; three
+        // slabs of 48^2 .. 96^2 x 3 1067 and 1111; 96^3 x 12 4350 and 4280.
+        // The isotropic sums are too few for the branch, which held back the
+        // fetches around it: 96^3 809 against 799 us)
         static_for<NB>([&](auto kc) __attribute__((always_inline)) {
             constexpr int kb = decltype(kc)::value;
             constexpr ZBond bd = ShapeC<KIND>::t.bonds[kb];
@@ -1248,9 +1251,10 @@ struct ZBatchEntry {
     unsigned block0, ntile;
 };
 
-// The GNEB passes of several instances in one launch.  The films of a
-// skyrmion batch are a few dozen to a few hundred blocks each; launched one
-// after another (twelve 48^2 .. 96^2 films of 32 images) a pass took 210 us.
+// The GNEB passes of several instances in one launch: the instances of a batch
+// may be a few dozen blocks each (twelve slabs of 5 .. 16 x 9 x 4 cells x 8
+// images: 371 us an iteration with a launch per instance and pass, 39 with one
+// and the scalar steps folded).
 // The entries are read through the constant address space, so their fields
 // are scalar loads where they are used.  Those loads stay behind the march's
 // branches, where kernel arguments are read ahead of them (96^3 x 32 images
