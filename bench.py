@@ -20,6 +20,7 @@ import hashlib
 import json
 import os
 import sys
+import tempfile
 import time
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
@@ -67,7 +68,8 @@ def measured_traffic(kernel: str, workload: str, heun_mode, zchunk, tile_rows=0)
     committed rocprofv3 --pmc summary, if it was taken on the current source
     of the files it lists, on this workload and in this launch configuration
     (else None).  An entry holds one record per launch configuration it was
-    measured in ("configs": z chunk, Heun mode, fused rows, bytes)."""
+    measured in ("configs": z chunk, 0 where the library splits z itself,
+    Heun mode, fused rows, bytes)."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -167,7 +169,7 @@ def gneb_workload(args):
                 "ms_per_step": ms / n_it,
                 "roofline": {"bound": "hbm", "achieved": rate * GNEB_BYTES / 1e9, "peak": HBM_PEAK_GBS,
                              "unit": "GB/s", "frac": rate * GNEB_BYTES / 1e9 / HBM_PEAK_GBS,
-                             "traffic": measured_traffic("gneb_iteration", "sc_frustrated_gneb", None, 16),
+                             "traffic": measured_traffic("gneb_iteration", "sc_frustrated_gneb", None, None),
                              "kernel": "GNEB iteration (two z-march passes + reductions)",
                              "bytes_per_spin_image_iteration": GNEB_BYTES,
                              "bytes_per_spin_image_iteration_of_the_passes": GNEB_PASS_BYTES,
@@ -337,10 +339,10 @@ def mc_workload(args):
     print(json.dumps(out), flush=True)
 
 
-# static minimiser iteration, per spin: field pass (24 B in, 24 B out) +
-# force pass (read S, b, u_prev, F_prev; write F) + update pass (read S, F;
-# write S, u, F_prev): 48 + 120 + 120 B, plus the L-BFGS two-loop passes
-MIN_BYTES = {"vp": 48 + 120 + 144, "bb": 48 + 120 + 120, "lbfgs": 48 + 120 + 120, "adam": 48 + 72 + 192}
+# velocity-projection iteration, per spin: force pass (read S and the force
+# before, write the force) and update (read S and the force, write S); the
+# velocity is a multiple of the force before and is not stored
+VP_BYTES = 72 + 72
 
 
 def min_workload(args):
@@ -385,11 +387,11 @@ def min_workload(args):
            "vs_baseline": None, "dtype": "f64", "data": "synthetic (seeded random spins)",
            "config": {"workload": "sc200_min", "cells": [L, L, L], "spins": N, "K_meV": 0.1, "B_T": [0.0, 0.0, 1.0],
                       "shells": [list(J) for J in MC_SHELLS], "parallelism": "single GPU"},
-           "roofline": {"bound": "hbm", "achieved": rate * MIN_BYTES["vp"] / 1e9, "peak": HBM_PEAK_GBS,
-                        "unit": "GB/s", "frac": rate * MIN_BYTES["vp"] / 1e9 / HBM_PEAK_GBS,
+           "roofline": {"bound": "hbm", "achieved": rate * VP_BYTES / 1e9, "peak": HBM_PEAK_GBS,
+                        "unit": "GB/s", "frac": rate * VP_BYTES / 1e9 / HBM_PEAK_GBS,
                         "traffic": measured_traffic("min_vp_iteration", "sc200_min", None, None),
-                        "kernel": "velocity-projection iteration (field, force, update)",
-                        "bytes_per_spin_iteration": MIN_BYTES["vp"]},
+                        "kernel": "velocity-projection iteration (force pass, update)",
+                        "bytes_per_spin_iteration": VP_BYTES},
            "table": table, "cpu_baseline": None}
     print(json.dumps(out), flush=True)
 
@@ -524,6 +526,24 @@ def learned_experiment(family, args):
                                         damping=damp, log=log)
 
 
+def own_split(w, info, cache) -> bool:
+    """Whether the handle's Heun step splits z by the library's rule: an untuned
+    handle's does; a tuned one's if the last entry of its lattice in the tuning
+    cache says so (lines without "rule" hold a fixed chunk)."""
+    if not info.tuned:
+        return True
+    size = "_sub%d_%dx%dx%d_per%d%d%d" % (info.n_sites // (w.L[0] * w.L[1] * w.L[2]), *w.L,
+                                          *(int(bool(p)) for p in w.periodic))
+    rule = False
+    with open(cache) as f:
+        for line in f:
+            if line.startswith("{"):
+                e = json.loads(line)
+                if e["key"] == f"shape{info.shape}_prec{info.field_prec}" + size:
+                    rule = bool(e.get("rule", 0))
+    return rule
+
+
 def heun_workload(args, w, steps=None, warmup=None, cpu=True):
     """Field + (stochastic) Heun throughput of one lattice workload; returns
     the JSON record.  The timed region replays the library's captured Heun
@@ -540,12 +560,21 @@ def heun_workload(args, w, steps=None, warmup=None, cpu=True):
     warmup = args.warmup if warmup is None else warmup
     log(f"[bench] workload {w.name}: {w.N} spins, {warmup} warmup + {steps} timed Heun steps")
     stream = torch.cuda.current_stream()
+    # what the tuner chose is in its cache file, also whether the library's own
+    # split of z was the fastest (an untuned handle's always)
+    cache = args.tune_cache
+    if cache is None:
+        fd, cache = tempfile.mkstemp(prefix="spx_tune_", suffix=".txt")
+        os.close(fd)
     h = spx.setup_hamiltonian(w.L, cell=w.cell, sub_frac=w.frac, mu=w.mu, periodic=w.periodic,
                               J_shell=w.J_shell, D_shell=w.D_shell, K=(w.K if w.K else None),
                               K_axis=w.K_axis, B=w.B, dipolar=w.dipolar, field_prec=w.field_prec,
-                              autotune=0 if args.no_autotune else 1, tune_cache_path=args.tune_cache)
+                              autotune=0 if args.no_autotune else 1, tune_cache_path=cache)
     info = spx.get_info(h)
-    log(f"[bench] engine {info.stencil_engine} shape {info.shape} zchunk {info.zchunk} "
+    zchunk = 0 if own_split(w, info, cache) else info.zchunk
+    if args.tune_cache is None:
+        os.unlink(cache)
+    log(f"[bench] engine {info.stencil_engine} shape {info.shape} zchunk {zchunk} "
         f"heun_field {info.heun_field} tile_rows {info.tile_rows} tuned {info.tuned} "
         f"({info.tuned_step_us:.1f} us/step while tuning), "
         f"library workspace {info.workspace_bytes / 2**30:.2f} GiB")
@@ -629,7 +658,7 @@ def heun_workload(args, w, steps=None, warmup=None, cpu=True):
         timing = "HIP events around every launch in a separate pass of direct launches after the timed region"
         bpl = BYTES_PER_SPIN[dom]
         step_bytes = sum(BYTES_PER_SPIN.values())
-    traffic = measured_traffic(dom, w.name, info.heun_field, info.zchunk, info.tile_rows)
+    traffic = measured_traffic(dom, w.name, info.heun_field, zchunk, info.tile_rows)
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kname,
             "bytes_per_spin_algorithmic": bpl, "bytes_per_launch_algorithmic": bpl * w.N,
@@ -656,7 +685,7 @@ def heun_workload(args, w, steps=None, warmup=None, cpu=True):
                    "cells": list(w.L), "spins": w.N, "shells": w.n_shells, "T_K": w.T_K,
                    "alpha": w.alpha, "dt_fs": w.dt_fs, "field_prec": w.field_prec,
                    "parallelism": "single GPU", "stencil_engine": info.stencil_engine,
-                   "zchunk": info.zchunk, "heun_mode": info.heun_field, "tile_rows": info.tile_rows},
+                   "zchunk": zchunk, "heun_mode": info.heun_field, "tile_rows": info.tile_rows},
         "roofline": roof,
         "cpu_baseline": cpu_rec,
         "kernels": kernels,
@@ -837,19 +866,19 @@ def dipolar_traffic(L, ms, zsym=True):
     written once per pass: pad, x-row R2C, y columns, fused z pass with the
     dipole spectrum, inverse y, C2R, crop) and the rate they imply.  With a
     cell whose third vector is along z (zsym) the fused pass reads the
-    spectrum only for kz <= Pz / 2.  With Px = 512 the x-row passes read the
-    spins and write the x spectra directly (and back), with no padded real
-    rows in between."""
+    spectrum only for kz <= Pz / 2.  With Px of 64 to 1024 the x-row passes read
+    the spins and write the x spectra directly (and back), with no padded real
+    rows in between; Pz of 64 to 1024 has the fused z pass."""
     Lx, Ly, Lz = L
     P = [1 << (2 * v - 1).bit_length() for v in L]
     H = P[0] // 2 + 1
     rows = 3 * Ly * Lz
     R, X = rows * P[0] * 4, rows * H * 8
     Y = 3 * Lz * P[1] * H * 8
-    kz_read = P[2] // 2 + 1 if (zsym and P[2] == 512) else P[2]
+    kz_read = P[2] // 2 + 1 if (zsym and 64 <= P[2] <= 1024) else P[2]
     kern = 6 * kz_read * P[1] * H * 4
     N = Lx * Ly * Lz
-    if P[0] == 512:
+    if 64 <= P[0] <= 1024:
         total = (3 * N * 8 + X) + (X + Y) + (Y + kern + Y) + (Y + X) + (X + 3 * N * 4)
     else:
         total = (3 * N * 8 + R) + (R + X) + (X + Y) + (Y + kern + Y) + (Y + X) + (X + R) + (3 * N * 4 * 2)
