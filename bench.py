@@ -532,15 +532,15 @@ def own_split(w, info, cache) -> bool:
     cache says so (lines without "rule" hold a fixed chunk)."""
     if not info.tuned:
         return True
-    size = "_sub%d_%dx%dx%d_per%d%d%d" % (info.n_sites // (w.L[0] * w.L[1] * w.L[2]), *w.L,
-                                          *(int(bool(p)) for p in w.periodic))
+    key = "shape%d_prec%d_sub%d_%dx%dx%d_per%d%d%d" % (info.shape, info.field_prec,
+                                                       info.n_sites // (w.L[0] * w.L[1] * w.L[2]), *w.L,
+                                                       *(int(bool(p)) for p in w.periodic))
     rule = False
     with open(cache) as f:
         for line in f:
-            if line.startswith("{"):
-                e = json.loads(line)
-                if e["key"] == f"shape{info.shape}_prec{info.field_prec}" + size:
-                    rule = bool(e.get("rule", 0))
+            e = json.loads(line) if line.startswith("{") else {"key": line.split(" ")[0]}
+            if e["key"] == key:
+                rule = bool(e.get("rule", 0))
     return rule
 
 
